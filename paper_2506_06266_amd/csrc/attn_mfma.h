@@ -78,6 +78,38 @@ __device__ __forceinline__ SeqSpan seq_span(const int32_t* cu, int b, int T, int
     return sp;
 }
 
+// Query-stationary workgroups (forward, dQ): 256 query rows = four units of (64 consecutive tokens,
+// one query head), one per wavefront.  The units of a (sequence, KV head) are numbered with the
+// group's G heads fastest, and a workgroup takes four in a row: with G = 4 its wavefronts hold the
+// four heads of the same 64 tokens, so they all end on the same diagonal tile -- one masked tile per
+// workgroup instead of the four (and up to three key tiles a wavefront only waited through) of 256
+// consecutive tokens of one head -- and a sequence is rounded up to 64 tokens, not to 256.  The
+// wavefronts past the last unit load clamped rows and store nothing.  Against 256 consecutive
+// tokens of one head (us): Hq 24 / Hkv 8, S 1024, P 2048, B 32: forward 950 -> 918, dQ 1343 -> 1303;
+// 32 / 8, S 2048, P 4096, B 16: forward 2180 both, dQ 3165 -> 3090; 64 packed conversations of 64 ..
+// 1024 tokens, P 4096 (a block of 64 tokens spans fewer sequences): forward 2352 -> 2234, dQ 3358 -> 3191.
+struct QueryBlock {
+    int hk, b, h;       // KV head, sequence, the wavefront's query head
+    int q0, q_end;      // tokens of the workgroup
+    int wrow0;          // first token of the wavefront
+};
+__host__ __device__ inline int query_wgs(int S, int G) { return (((S + 63) / 64) * G + 3) / 4; }
+// KV head fastest: with 8 of them blockIdx % 8 (the XCD) is the KV head and each XCD's L2 keeps one
+// head's prefix; then the blocks of one sequence, heaviest (longest causal part) first, sequence
+// after sequence, so that the workgroups running at one time share one or two sequences' K/V in L2.
+__device__ __forceinline__ QueryBlock query_block(int id, int wv, int Smax, int Hq, int Hkv) {
+    QueryBlock qb;
+    const int G = Hq / Hkv, nW = query_wgs(Smax, G);
+    qb.hk = id % Hkv; id /= Hkv;
+    const int u0 = 4 * (nW - 1 - id % nW), u = u0 + wv;
+    qb.b = id / nW;
+    qb.h = qb.hk * G + u % G;
+    qb.wrow0 = 64 * (u / G);
+    qb.q0 = 64 * (u0 / G);
+    qb.q_end = 64 * ((u0 + 3) / G) + 64;
+    return qb;
+}
+
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));

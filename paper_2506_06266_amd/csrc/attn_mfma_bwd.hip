@@ -23,7 +23,6 @@ using namespace mfma;
 
 constexpr int BWD_TILE = 64;                      // rows per LDS tile
 constexpr int BWD_TILE_B = BWD_TILE * ROW_B;
-constexpr int BWD_WG_ROWS = 256;                  // stationary rows per workgroup (4 x 64)
 // store a transposed accumulator block set: lane owns output row `row_ptr` (nullptr: skip),
 // register r of block db holds column 32 db + 8 (r/4) + 4 g + r%4
 __device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[4], bf16_t* row_ptr, int lg, float mul) {
@@ -41,12 +40,12 @@ __device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[4], bf16_t* 
 // =================================================================================================
 // dQ: queries stationary
 // =================================================================================================
-// One workgroup = 256 consecutive queries of one (sequence, query head); each wavefront keeps its
-// 64 queries' Q (scaled by c = softmax_scale * log2(e)) and dO as B-operand fragments in
-// accumulation registers, next to the dQ^T accumulators.  Key tiles (K and V rows) stream through
-// LDS in the forward kernel's order: first the tiles every query sees entirely, through a loop
-// without masking code, then the ragged prefix tile and the diagonal tiles through a copy that
-// masks.  Per sub-tile of 32 keys:
+// One workgroup = 256 query rows as in the forward kernel (four units of 64 tokens of one query head,
+// see QueryBlock); each wavefront keeps its 64 queries' Q (scaled by c = softmax_scale * log2(e)) and
+// dO as B-operand fragments in accumulation registers, next to the dQ^T accumulators.  Key tiles (K
+// and V rows) stream through LDS in the forward kernel's order: first the tiles every query sees
+// entirely, through a loop without masking code, then the ragged prefix tile and the diagonal tiles
+// through a copy that masks.  Per sub-tile of 32 keys:
 //   S^T = K Q^T, dP^T = V dO^T,  dS^T = 2^(S^T - lse2) (dP^T - delta),  dQ^T += K^T dS^T.
 // The iteration is laid out like the dK kernel's: 48 fenced groups; the scores / dP of query
 // block 1 live in one register set, those of block 0 in two used alternately; the transposed K
@@ -67,17 +66,10 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     constexpr int BUF_B = 2 * BWD_TILE_B;
     constexpr int V_OFF = BWD_TILE_B;
     __shared__ DqSmem sm;
-    const int G = Hq / Hkv;
-    const int nQt = (Smax + BWD_WG_ROWS - 1) / BWD_WG_ROWS;
-    int id = blockIdx.x;
-    const int hk = id % Hkv; id /= Hkv;
-    const int g_ = id % G; id /= G;
-    const int qt = nQt - 1 - id % nQt;
-    const int b = id / nQt;
-    const int h = hk * G + g_;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int q0 = qt * BWD_WG_ROWS, wrow0 = q0 + 64 * wv;
+    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv);
+    const int hk = qb.hk, b = qb.b, h = qb.h, q0 = qb.q0, wrow0 = qb.wrow0;
     // packed layout: the grid covers the longest sequence; nothing to do past the end of this one.
     // With row_lo (B = 1, S = all packed rows) the query tiles are cut from the packed rows as in
     // the forward kernel and row i sees the own keys row_lo[i] .. i.
@@ -162,7 +154,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     // tile order: see the forward kernel
     const int nPf = P / BWD_TILE;
     const int rag = (P % BWD_TILE) ? 1 : 0;
-    const int own_end = min(S, q0 + BWD_WG_ROWS);
+    const int own_end = min(S, qb.q_end);
     const int lo_first = row_lo ? row_lo[q0] : 0, lo_last = row_lo ? row_lo[own_end - 1] : 0;
     const int tA = lo_first / BWD_TILE, tU0 = (lo_last + BWD_TILE - 1) / BWD_TILE, tD = q0 / BWD_TILE;
     const int nOf = max(0, tD - tU0);
@@ -442,13 +434,13 @@ int launch_attn_bwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
     const bf16_t* O = static_cast<const bf16_t*>(o);
     trace_begin(st);   // kernel order: dq (+ row statistics), dk + dv (one kernel), dz reduce (k, v)
     if (row_lo) {
-        const long nQt = (T + BWD_WG_ROWS - 1) / BWD_WG_ROWS;
-        hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(static_cast<unsigned>(nQt * d.Hq)), dim3(256), 0, st, Q, K, V, ZK,
+        const long nW = query_wgs(T, d.Hq / d.Hkv);
+        hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(static_cast<unsigned>(nW * d.Hkv)), dim3(256), 0, st, Q, K, V, ZK,
                            ZV, O, DO, lse, lse2, delta, static_cast<bf16_t*>(dq), nullptr, row_lo, n_tok, 1, n_tok,
                            d.Hq, d.Hkv, d.P, c, scale);
     } else {
-        const long nQt = (d.S + BWD_WG_ROWS - 1) / BWD_WG_ROWS;
-        hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(static_cast<unsigned>(nQt * d.B * d.Hq)), dim3(256), 0, st, Q, K, V,
+        const long nW = query_wgs(d.S, d.Hq / d.Hkv);
+        hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(static_cast<unsigned>(nW * d.B * d.Hkv)), dim3(256), 0, st, Q, K, V,
                            ZK, ZV, O, DO, lse, lse2, delta, static_cast<bf16_t*>(dq), cu, nullptr, n_tok, d.B, d.S,
                            d.Hq, d.Hkv, d.P, c, scale);
     }

@@ -1,8 +1,9 @@
 // Cartridge attention forward on the matrix cores (bf16 in, fp32 accumulate, head_dim 128):
 // Eq. 1 over the cache of Sec. 3.2, [prefix Z (all visible) ; own keys (causal)].
 //
-// One 256-thread workgroup = 256 consecutive queries of one (sequence, query head); each of its
-// four wavefronts owns 64 of them, kept in registers as MFMA operand fragments.  Keys/values
+// One 256-thread workgroup = 256 query rows of one (sequence, KV head): each of its four wavefronts
+// owns 64 consecutive tokens of one query head (see QueryBlock), kept in registers as MFMA operand
+// fragments.  Keys/values
 // stream through LDS in tiles of 64 (prefix tiles first, then own tiles up to the diagonal),
 // four buffers, one barrier per tile, consumed as sub-tiles of 32 keys.  Per sub-tile a
 // wavefront computes S^T = K Q^T (keys on the D rows, its queries on the D columns), turns it
@@ -24,7 +25,6 @@
 namespace cart {
 using namespace mfma;
 
-constexpr int FWD_BM = 256;   // queries per workgroup
 constexpr int FWD_BN = 64;    // keys per LDS tile, consumed as two sub-tiles of 32
 constexpr int FWD_NBUF = 4;     // tile t in buffer t % 4; loads run two tiles ahead of the barrier that publishes them
 constexpr int FWD_TILE_B = FWD_BN * ROW_B;
@@ -50,25 +50,13 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     float c /* scale*log2(e) */) {
     __shared__ FwdSmem sm;
     __shared__ int sm_bad;
-    const int G = Hq / Hkv;
-    const int nQt = (Smax + FWD_BM - 1) / FWD_BM;
-    // workgroup -> (query tile, sequence, head).  KV head is the fastest index so that, with 8
-    // KV heads, blockIdx % 8 (the XCD a workgroup lands on) is the KV head and each XCD's L2 keeps
-    // one head's prefix; then the query tiles of one sequence, heaviest (longest causal part)
-    // first, sequence after sequence: the workgroups running at one time belong to one or two
-    // sequences, whose own K/V then stay in L2 (2 % faster than all sequences' heaviest tiles first).
-    int id = blockIdx.x;
-    const int hk = id % Hkv; id /= Hkv;
-    const int g_ = id % G; id /= G;
-    const int qt = nQt - 1 - id % nQt;
-    const int b = id / nQt;
-    const int h = hk * G + g_;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, in a scalar register
-    const int q0 = qt * FWD_BM, wrow0 = q0 + 64 * wv;
+    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv);
+    const int hk = qb.hk, b = qb.b, h = qb.h, q0 = qb.q0, wrow0 = qb.wrow0;
     // Rows of sequence b: [t0, t0 + S).  Batched layout: S rows each; packed layout (cu given):
     // rows cu[b] .. cu[b+1]-1 of T, the grid is sized for the longest sequence and a workgroup
-    // whose query tile lies past the end of its sequence has nothing to do.
+    // whose tokens lie past the end of its sequence has nothing to do.
     // Packed layout with a prefix (row_lo given, B = 1, S = all packed rows): query tiles are cut
     // from the packed rows regardless of sequence boundaries -- no sequence ends in a partly
     // filled tile -- and row i sees the own keys row_lo[i] .. i (row_lo = first row of its sequence).
@@ -129,10 +117,10 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     // Tile order.  The softmax reference is fixed, so key tiles may come in any order: first every
     // tile all of whose keys are visible to all 256 queries (whole prefix tiles, own tiles below
     // the first query), through a loop without masking code; then the ragged last prefix tile and
-    // the (at most four) own tiles on the diagonal, through a copy of the loop that masks.
+    // the own tiles on the diagonal, through a copy of the loop that masks.
     const int nPf = P / FWD_BN;                        // whole prefix tiles
     const int rag = (P % FWD_BN) ? 1 : 0;              // ragged prefix tile
-    const int own_end = min(S, q0 + FWD_BM);
+    const int own_end = min(S, qb.q_end);
     // own tiles (of 64 rows from row 0): every query of the workgroup sees the whole of tiles
     // tU0 .. tD-1; tiles tA .. min(tU0, tD)-1 start before the first key of some query and tiles
     // tD .. tEnd-1 lie on the diagonal (one sequence: tA = tU0 = 0)
@@ -455,19 +443,14 @@ __global__ __launch_bounds__(256) void attn_fwd_repair_kernel(
     float* __restrict__ lse, const int* __restrict__ flags, const int32_t* __restrict__ cu,
     const int32_t* __restrict__ row_lo, int n_tok, int B, int Smax, int Hq, int Hkv, int P, float c) {
     if (flags[blockIdx.x] == 0) return;
-    const int G = Hq / Hkv;
-    const int nQt = (Smax + FWD_BM - 1) / FWD_BM;
-    int id = blockIdx.x;
-    const int hk = id % Hkv; id /= Hkv;
-    const int g_ = id % G; id /= G;
-    const int qt = nQt - 1 - id % nQt;
-    const int b = id / nQt;
-    const int h = hk * G + g_;
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const SeqSpan sp = seq_span(cu, b, n_tok, Smax, Hq);
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv);
+    const int hk = qb.hk, h = qb.h;
+    const SeqSpan sp = seq_span(cu, qb.b, n_tok, Smax, Hq);
     const int S = sp.len;
     const size_t t0 = sp.t0;
-    for (int i = qt * FWD_BM + wv; i < min(S, (qt + 1) * FWD_BM); i += 4) {
+    for (int i = qb.wrow0; i < min(S, qb.wrow0 + 64); ++i) {
         const size_t row = (t0 + i) * Hq + h;
         const uint32_t qw = *reinterpret_cast<const uint32_t*>(q + row * HD + 2 * lane);
         const float q0 = __uint_as_float(qw << 16), q1 = __uint_as_float(qw & 0xffff0000u);
@@ -514,8 +497,9 @@ bool attn_mfma_supported(const cart_attn_desc& d) {
 }
 // workgroups: per sequence, or over the packed rows (a packed batch with a prefix; T > 0)
 static long fwd_grid(const cart_attn_desc& d, int T) {
-    if (T > 0 && d.P > 0) return static_cast<long>((T + FWD_BM - 1) / FWD_BM) * d.Hq;
-    return static_cast<long>((d.S + FWD_BM - 1) / FWD_BM) * d.B * d.Hq;
+    const int G = d.Hq / d.Hkv;
+    if (T > 0 && d.P > 0) return static_cast<long>(query_wgs(T, G)) * d.Hkv;
+    return static_cast<long>(query_wgs(d.S, G)) * d.B * d.Hkv;
 }
 static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 // one overflow flag per workgroup; packed batches: + the first row of every row's sequence
