@@ -1,43 +1,31 @@
 // Context-distillation loss (Eq. 3, Sec. 4.2, over the teacher's recorded top entries of
-// App. A.2) fused with its gradient: one streaming pass over the student's logits.  Two
-// readings of the truncated teacher (recorded terms only / plus a rest bucket) share the pass:
-// they differ in one per-row coefficient and in the k fix-ups; next-token cross-entropy is the
-// case of one recorded token of probability 1.
+// App. A.2) fused with its gradient.  Two readings of the truncated teacher (recorded terms only /
+// plus a rest bucket) share the kernels: they differ in one per-row coefficient and in the k
+// fix-ups; next-token cross-entropy is the case of one recorded token of probability 1.
 //
-// kl_row_resident: one 1024-thread workgroup per position holds the whole bf16 row
-// (<= 131072 logits) in registers, so HBM sees each logit read once and each gradient written
-// once.  Three sweeps over the registers: max, sum of exponentials, gradient.
-// kl_row_stream: any vocabulary size / fp32 logits; reads the row twice.
-#include "cart_common.h"
+// A row is cut into an aligned body of 16-byte vectors and up to 2 x (vector - 1) single elements
+// around it (rows of a vocabulary that is not a multiple of the vector start anywhere); body and
+// singles take the same arithmetic, so every vocabulary size and both data types run the same code.
+//
+// kl_row_resident: one workgroup per row, the row held in registers (fp32 rows of more than 65536
+// logits: also in LDS), so HBM sees each logit read once and each gradient written once; what
+// exceeds both is read twice.
+#include "attn_mfma.h"
 
 namespace cart {
 
-constexpr int KL_MAXK = 1024;
-
-struct KlTeacher {      // per-row teacher records staged in LDS
-    int idx[KL_MAXK];
-    float t[KL_MAXK];   // exp(logp), 0 for ignored entries
-    float lp[KL_MAXK];
-    float x[KL_MAXK];   // student logit at idx (read before anything is overwritten)
+// A row's K teacher records staged in LDS (4 arrays of K words, dynamic: at K = 20 they must not
+// limit how many workgroups share a CU)
+struct KlTeacher {
+    int* idx;           // token, -1 for ignored entries
+    float* t;           // exp(logp), 0 for ignored entries
+    float* lp;
+    float* x;           // student logit at idx (read before anything is overwritten)
 };
-
-template <typename T, int THREADS>
-__device__ __forceinline__ float kl_stage_teacher(KlTeacher& tc, const T* logits_row,
-                                                  const int32_t* idx, const float* logp, int V,
-                                                  int K) {
-    float m_part = 0.f;
-    for (int j = threadIdx.x; j < K; j += THREADS) {
-        int id = idx[j];
-        float lp = logp ? logp[j] : 0.f;
-        bool ok = id >= 0 && id < V;
-        float t = ok ? __expf(lp) : 0.f;
-        tc.idx[j] = ok ? id : -1;
-        tc.t[j] = t;
-        tc.lp[j] = ok ? lp : 0.f;
-        tc.x[j] = ok ? elem<T>::load(logits_row + id) : 0.f;
-        m_part += t;
-    }
-    return m_part;
+extern __shared__ int kl_records[];
+__device__ __forceinline__ KlTeacher kl_teacher(int K) {
+    float* f = reinterpret_cast<float*>(kl_records);
+    return KlTeacher{kl_records, f + K, f + 2 * K, f + 3 * K};
 }
 
 // KL_n = sum_j t_j (logp_j - x_j + lse) (+ extra, the rest-bucket term), by the first wavefront
@@ -76,92 +64,266 @@ __device__ __forceinline__ float max3_raw(float a, uint32_t b, uint32_t c) {
     asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
 }
+
+// One 16-byte vector of logits: its elements widened to fp32, and the gradient packed back.
+template <typename T> struct KlVec;
+template <> struct KlVec<bf16_t> {
+    static constexpr int N = 8;
+    static constexpr uint32_t FILL = 0xff7fff7fu;      // two bf16 of the most negative finite value
+    static __device__ __forceinline__ uint32_t bits(const u32x4& w, int e) {
+        return (e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16);
+    }
+};
+template <> struct KlVec<float> {
+    static constexpr int N = 4;
+    static constexpr uint32_t FILL = 0xff7fffffu;
+    static __device__ __forceinline__ uint32_t bits(const u32x4& w, int e) { return w[e]; }
+};
+template <typename T> __device__ __forceinline__ u32x4 kl_fill() {
+    constexpr uint32_t f = KlVec<T>::FILL;
+    return u32x4{f, f, f, f};
+}
+template <typename T> __device__ __forceinline__ float kl_vec_max(float mx, const u32x4& w) {
+#pragma unroll
+    for (int e = 0; e < KlVec<T>::N; e += 2) mx = max3_raw(mx, KlVec<T>::bits(w, e), KlVec<T>::bits(w, e + 1));
+    return mx;
+}
+// s0 + s1 += sum of 2^(x log2e + c0)
+template <typename T> __device__ __forceinline__ void kl_vec_sum(float& s0, float& s1, const u32x4& w, float c0) {
+#pragma unroll
+    for (int e = 0; e < KlVec<T>::N; e += 2) {
+        s0 += fast_exp2(fmaf(__uint_as_float(KlVec<T>::bits(w, e)), CART_LOG2E, c0));
+        s1 += fast_exp2(fmaf(__uint_as_float(KlVec<T>::bits(w, e + 1)), CART_LOG2E, c0));
+    }
+}
+// Gradient off the recorded tokens: g = c 2^(x log2e - lse2), c = scale * M (rest-bucket mode: scale *
+// (M - S) / (1 - S)).  bf16: |c| rides in the exponent (c == 0 gives 2^-inf = 0).
+struct KlGrad {
+    float c, off;
+    uint32_t sgn;
+};
+template <typename T> __device__ __forceinline__ KlGrad kl_grad_coef(float c, float lse2) {
+    if (sizeof(T) == 2) return KlGrad{c, -(lse2 - fast_log2(fabsf(c))), c < 0.f ? 0x80008000u : 0u};
+    return KlGrad{c, -lse2, 0u};
+}
+template <typename T> __device__ __forceinline__ u32x4 kl_vec_grad(const u32x4& w, const KlGrad& g) {
+    u32x4 r;
+    if constexpr (sizeof(T) == 2) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float lo = fast_exp2(fmaf(__uint_as_float(w[e] << 16), CART_LOG2E, g.off));
+            const float hi = fast_exp2(fmaf(__uint_as_float(w[e] & 0xffff0000u), CART_LOG2E, g.off));
+            r[e] = pack_bf16x2(lo, hi) ^ g.sgn;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            r[e] = __float_as_uint(g.c * fast_exp2(fmaf(__uint_as_float(w[e]), CART_LOG2E, g.off)));
+    }
+    return r;
+}
+
+// Row n of [N][V]: `head` single elements, nvec whole vectors, `tail` single elements.  The base of
+// the tensor is 16-byte aligned.  Single element s (of head + tail <= 14) belongs to thread s of the
+// workgroup, vector v to thread v % THREADS.
+struct KlRow {
+    size_t row;
+    int head, nvec, tail;
+};
+template <typename T> __device__ __forceinline__ KlRow kl_row(int n, int V) {
+    constexpr int VE = KlVec<T>::N;
+    KlRow r;
+    r.row = static_cast<size_t>(n) * V;
+    r.head = min(static_cast<int>((VE - (r.row & (VE - 1))) & (VE - 1)), V);
+    r.nvec = (V - r.head) / VE;
+    r.tail = V - r.head - r.nvec * VE;
+    return r;
+}
+// element index of single s
+template <typename T> __device__ __forceinline__ int kl_single(const KlRow& r, int s) {
+    return s < r.head ? s : s + r.nvec * KlVec<T>::N;
+}
+// the thread (of THREADS) that stores element id
+template <typename T, int THREADS> __device__ __forceinline__ int kl_owner(const KlRow& r, int id) {
+    const int e = id - r.head, v = e / KlVec<T>::N;
+    return e < 0 ? id : v < r.nvec ? v & (THREADS - 1) : id - r.nvec * KlVec<T>::N;
+}
+
+// The body of a row as a buffer resource: a load past its end returns 0 and a store past it is
+// dropped, and an access takes one 32-bit offset instead of a 64-bit address and a predicate.
+struct KlBuf {
+    __amdgpu_buffer_rsrc_t r;
+};
+template <typename T> __device__ __forceinline__ KlBuf kl_buf(const T* base, const KlRow& r) {
+    return KlBuf{__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base + r.row + r.head), 0,
+                                                   static_cast<int>(static_cast<uint32_t>(r.nvec) * 16u), 0x00027000)};
+}
+constexpr int KL_NT = 2;             // cache policy: non-temporal
+template <int AUX> __device__ __forceinline__ u32x4 kl_ld(const KlBuf& b, int off) {
+    return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b.r, off, 0, AUX));
+}
+__device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
+    __builtin_amdgcn_raw_buffer_store_b128(w, b.r, off, 0, KL_NT);
+}
+
 // Makes the register-resident row opaque to the optimiser between sweeps; otherwise the
 // unpacked fp32 copies of one sweep are kept alive for the next one and spill.
 #define KL_FORGET(x)                                                                      \
-    _Pragma("unroll") for (int i_ = 0; i_ < NV; ++i_)                                      \
-        asm volatile("" : "+v"(x[i_].x), "+v"(x[i_].y), "+v"(x[i_].z), "+v"(x[i_].w))
+    _Pragma("unroll") for (int i_ = 0; i_ < NV; ++i_)                                   \
+        asm volatile("" : "+v"(x[i_]))
 
-#ifndef KL_RESIDENT_WGS
-#define KL_RESIDENT_WGS 256      // workgroups of the register-resident kernel: one per CU of an MI355X
-#endif
-
-template <int NV>
-__global__ __launch_bounds__(1024) void kl_row_resident(const bf16_t* logits, const int32_t* idx,
-                                                        const float* logp, bf16_t* dlogits,
-                                                        float* row_kl, int N, int V, int K, float scale,
-                                                        int rest) {
-    constexpr int THREADS = 1024, NW = THREADS / CART_WAVE;
-    __shared__ KlTeacher tc;
-    __shared__ float red_max[NW], red_m[NW], red_sum[NW], rest_terms[2];
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int nvec = V >> 3;
-    const uint32_t FILL = 0xff7fff7fu;   // two bf16 of the most negative finite value
-
-    // One workgroup fills a CU, so nothing else would cover the latency of a row's load: the
-    // workgroup walks rows n, n + gridDim.x, ... and fetches the next row into the registers of
-    // the current one as the last sweep releases them.
+// One row per workgroup at a time: THREADS x (16 vectors in registers + NL in LDS) are resident,
+// the rest of a longer row is read twice.  A CU holds 1024 such threads (128 registers each), so the
+// launcher takes the smallest THREADS whose registers hold the row: 256 (four workgroups per CU
+// cover each other's loads and reductions), 512, or 1024.  At 1024 nothing else runs on the CU:
+// the workgroup walks rows n, n + gridDim.x, ... and fetches the next row's vectors and teacher
+// records into the registers (LDS slots) of the current row as its last sweep releases them.
+// Bound by HBM, one read and one write of the tensor.  Kernel time in us against one-workgroup-per-
+// row kernels that took whole-vector bf16 rows at 1024 threads whatever their length and read every
+// other row twice, element by element (rows x vocabulary):
+//   16384 x 128256 bf16  1649 -> 1593 (5.28 TB/s)     4096 x 32000 bf16  153 -> 100
+//    1024 x  50257 bf16   146 ->   47                16384 x  1000 fp32   54 ->  47
+//    2048 x 128256 fp32   785 ->  412 (423 without the LDS part)
+template <typename T, int THREADS, int NV, int NL>
+__global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const T* logits, const int32_t* idx,
+                                                              const float* logp, T* dlogits, float* row_kl,
+                                                              int N, int V, int K, float scale, int rest) {
+    constexpr int GRP = NV < 8 ? NV : 8;
+    constexpr int NW = THREADS / CART_WAVE, VE = KlVec<T>::N;
+    const KlTeacher tc = kl_teacher(K);
+    __shared__ float red_c[NW], red_m[NW], red_sum[NW], rest_terms[2];
+    __shared__ __attribute__((aligned(16))) u32x4 lds_x[NL > 0 ? NL * THREADS : 1];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     int n = blockIdx.x;
     if (n >= N) return;
+    KlRow R = kl_row<T>(n, V);
+
+    // vector i of the next row's LDS part, straight into the thread's own slot (clamped to the row)
+    auto lds_fetch = [&](const T* base, const KlRow& r, int i) __attribute__((always_inline)) {
+        const int v = min((NV + i) * THREADS + tid, max(r.nvec - 1, 0));
+        mfma::dma16(reinterpret_cast<const char*>(base + r.row + r.head), static_cast<uint32_t>(v) * 16u,
+                    mfma::lds_addr(lds_x + i * THREADS + wv * CART_WAVE));
+    };
     u32x4 x[NV];
-    {
-        const u32x4* src = reinterpret_cast<const u32x4*>(logits + static_cast<size_t>(n) * V);
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            int v = i * THREADS + tid;
-            x[i] = u32x4{FILL, FILL, FILL, FILL};
-            if (v < nvec) x[i] = __builtin_nontemporal_load(src + v);
+    const int voff = tid * 16;
+    constexpr int STEP = THREADS * 16;
+    float xs = -3.0e38f;          // the thread's single element
+    int my_id = -1;               // the thread's teacher record (record tid; more of them by a loop)
+    float my_lp = 0.f, my_x = 0.f;
+    // The records of row m are two dependent round trips: tokens and log-probabilities first ...
+    auto fetch_record = [&](int m) __attribute__((always_inline)) {
+        if (tid < K) {
+            my_id = idx[static_cast<size_t>(m) * K + tid];
+            if (logp) my_lp = logp[static_cast<size_t>(m) * K + tid];
         }
+    };
+    // ... then the logits of the tokens
+    auto fetch_logit = [&](const KlRow& r) __attribute__((always_inline)) {
+        if (my_id >= V) my_id = -1;
+        if (my_id >= 0) my_x = elem<T>::load(logits + r.row + my_id);
+    };
+    {
+        const KlBuf src = kl_buf(logits, R);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) x[i] = kl_ld<KL_NT>(src, voff + i * STEP);
+        if constexpr (NL > 0) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) lds_fetch(logits, R, i);
+        }
+        if (tid < R.head + R.tail) xs = elem<T>::load(logits + R.row + kl_single<T>(R, tid));
+        fetch_record(n);
+        fetch_logit(R);
     }
     for (;;) {
-        const size_t row = static_cast<size_t>(n) * V;
-        float m_part = kl_stage_teacher<bf16_t, THREADS>(tc, logits + row, idx + static_cast<size_t>(n) * K,
-                                                        logp ? logp + static_cast<size_t>(n) * K : nullptr, V, K);
-
-        // sweep 1: the row maximum; both elements of a packed word widened to fp32 (a word of two
-        // -inf logits read whole would be a NaN) and a three-way maximum
-        float mx = -3.0e38f;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const uint32_t w[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) mx = max3_raw(mx, w[e] & 0xffff0000u, w[e] << 16);
-        }
-        KL_FORGET(x);
-        mx = wave_max(mx);
-        m_part = wave_sum(m_part);
-        if (lane == 0) { red_max[wv] = mx; red_m[wv] = m_part; }
-        __syncthreads();
-        float M = 0.f;
-        mx = red_max[0];
-#pragma unroll
-        for (int w = 0; w < NW; ++w) { mx = fmaxf(mx, red_max[w]); M += red_m[w]; }
-
-        // sweep 2: sum of exp(x - max), in base 2
-        const float c0 = -mx * CART_LOG2E;
-        float s0 = 0.f, s1 = 0.f;
-#pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            const uint32_t w[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                s0 += fast_exp2(fmaf(__uint_as_float(w[e] << 16), CART_LOG2E, c0));
-                s1 += fast_exp2(fmaf(__uint_as_float(w[e] & 0xffff0000u), CART_LOG2E, c0));
+        // teacher records into LDS
+        float m_part = 0.f;
+        for (int j = tid; j < K; j += THREADS) {
+            int id = my_id;
+            float lp = my_lp, xj = my_x;
+            if (j >= THREADS) {        // (more records than threads)
+                id = idx[static_cast<size_t>(n) * K + j];
+                lp = logp ? logp[static_cast<size_t>(n) * K + j] : 0.f;
+                if (id < 0 || id >= V) id = -1;
+                xj = id >= 0 ? elem<T>::load(logits + R.row + id) : 0.f;
             }
-            __builtin_amdgcn_sched_barrier(0);   // keep the sweeps' temporaries from piling up
+            const float t = id >= 0 ? __expf(lp) : 0.f;
+            tc.idx[j] = id >= 0 ? id : -1;
+            tc.t[j] = t;
+            tc.lp[j] = id >= 0 ? lp : 0.f;
+            tc.x[j] = id >= 0 ? xj : 0.f;
+            m_part += t;
+        }
+        const int n_next = n + static_cast<int>(gridDim.x);
+        const bool more = n_next < N;
+        if (more) fetch_record(n_next);
+
+        // sweep 1, the thread's maximum.  It is the thread's own reference for the exponentials (no
+        // barrier between the sweeps); kept above -2e38 so that c0 stays finite.
+        float mx = fmaxf(xs, -2.0e38f);
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if ((i + 1) * THREADS > R.nvec && i * THREADS + tid >= R.nvec) x[i] = kl_fill<T>();
+            mx = kl_vec_max<T>(mx, x[i]);
+        }
+        if constexpr (NL > 0) {
+            mfma::dma_wait();            // the LDS part (each thread reads only what its own lane fetched)
+#pragma unroll
+            for (int i = 0; i < NL; ++i)
+                if ((NV + i) * THREADS + tid < R.nvec) mx = kl_vec_max<T>(mx, lds_x[i * THREADS + tid]);
         }
         KL_FORGET(x);
-        float sum = wave_sum(s0 + s1);
-        if (lane == 0) red_sum[wv] = sum;
+        // sweep 2: sum of 2^((x - reference) log2e)
+        float c0 = -mx * CART_LOG2E;
+        float s0 = fast_exp2(fmaf(xs, CART_LOG2E, c0)), s1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (i * THREADS < R.nvec) kl_vec_sum<T>(s0, s1, x[i], c0);
+            asm volatile("" : "+v"(s0), "+v"(s1));   // summed here: the compiler would sink the adds behind all the exponentials
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if constexpr (NL > 0) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                if ((NV + i) * THREADS + tid < R.nvec) kl_vec_sum<T>(s0, s1, lds_x[i * THREADS + tid], c0);
+                asm volatile("" : "+v"(s0), "+v"(s1));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        KL_FORGET(x);
+        float sum = s0 + s1;
+        const KlBuf src = kl_buf(logits, R), dst = kl_buf(dlogits, R);
+        for (int v = (NV + NL) * THREADS + tid; v < R.nvec; v += THREADS) {   // what is not resident
+            const u32x4 w = kl_ld<0>(src, v * 16);
+            const float m1 = kl_vec_max<T>(mx, w);
+            if (m1 > mx) {
+                const float c1 = -m1 * CART_LOG2E;
+                sum *= fast_exp2(c1 - c0);
+                mx = m1;
+                c0 = c1;
+            }
+            s0 = s1 = 0.f;
+            kl_vec_sum<T>(s0, s1, w, c0);
+            sum += s0 + s1;
+        }
+        // the row's sum, relative to the largest reference
+        const float wc = -wave_max(-c0);
+        sum = wave_sum(sum * fast_exp2(wc - c0));
+        m_part = wave_sum(m_part);
+        if (lane == 0) { red_c[wv] = wc; red_sum[wv] = sum; red_m[wv] = m_part; }
         __syncthreads();
+        float M = 0.f, gc = red_c[0];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) { gc = fminf(gc, red_c[w]); M += red_m[w]; }
         sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) sum += red_sum[w];
-        const float lse2 = fast_log2(sum) - c0;          // log2 of the softmax denominator
+        for (int w = 0; w < NW; ++w) sum += red_sum[w] * fast_exp2(gc - red_c[w]);
+        const float lse2 = fast_log2(sum) - gc;          // log2 of the softmax denominator
 
-        // sweep 3: g = c * exp(x - lse) with c = scale * M (rest-bucket mode: the off-support
-        // coefficient scale * (M - S) / (1 - S)); |c| rides in the exponent.  Each vector's
-        // registers take the same vector of the next row as soon as its gradient is stored.
+        // sweep 3: the gradient, eight vectors at a time: their stores, then the loads of the same
+        // vectors of the next row into their registers.  One store and one load in turn turns the
+        // memory bus around too often (16384 rows of 128256 bf16 logits, us: groups of 1 / 2 / 4 / 8 /
+        // 16 vectors -> 1674 / 1672 / 1627 / 1605 / 1603; 2048 fp32 rows: 434 / 433 / 426 / 419 / 415).
         float coef = M, extra = 0.f;
         if (rest) {
             kl_rest_terms(tc, K, lse2, M, rest_terms);
@@ -169,144 +331,105 @@ __global__ __launch_bounds__(1024) void kl_row_resident(const bf16_t* logits, co
             coef = rest_terms[0];
             extra = rest_terms[1];
         }
-        const float c = scale * coef;
-        const float off = -(lse2 - fast_log2(fabsf(c)));  // c == 0 gives -inf, hence g == 0
-        const uint32_t sgn = c < 0.f ? 0x80008000u : 0u;
-        u32x4* dst = reinterpret_cast<u32x4*>(dlogits + row);
-        const int n_next = n + static_cast<int>(gridDim.x);
-        const bool more = n_next < N;
-        const u32x4* src_next = reinterpret_cast<const u32x4*>(logits + static_cast<size_t>(more ? n_next : n) * V);
+        const KlGrad g = kl_grad_coef<T>(scale * coef, lse2);
+        const KlRow Rn = kl_row<T>(more ? n_next : n, V);
+        if (more) fetch_logit(Rn);
+        if (tid < R.head + R.tail)
+            elem<T>::store(dlogits + R.row + kl_single<T>(R, tid), g.c * fast_exp2(fmaf(xs, CART_LOG2E, -lse2)));
+        xs = -3.0e38f;
+        if (more && tid < Rn.head + Rn.tail) xs = elem<T>::load(logits + Rn.row + kl_single<T>(Rn, tid));
+        for (int v = (NV + NL) * THREADS + tid; v < R.nvec; v += THREADS)
+            kl_st(dst, kl_vec_grad<T>(kl_ld<KL_NT>(src, v * 16), g), v * 16);
+        const KlBuf src_next = kl_buf(logits, Rn);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            int v = i * THREADS + tid;
-            const uint32_t w[4] = {x[i].x, x[i].y, x[i].z, x[i].w};
-            uint32_t r[4];
+        for (int i0 = 0; i0 < NV; i0 += GRP) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float lo = fast_exp2(fmaf(__uint_as_float(w[e] << 16), CART_LOG2E, off));
-                float hi = fast_exp2(fmaf(__uint_as_float(w[e] & 0xffff0000u), CART_LOG2E, off));
-                r[e] = pack_bf16x2(lo, hi) ^ sgn;
+            for (int i = i0; i < i0 + GRP; ++i) {
+                if (i * THREADS < R.nvec) kl_st(dst, kl_vec_grad<T>(x[i], g), voff + i * STEP);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (v < nvec) __builtin_nontemporal_store(u32x4{r[0], r[1], r[2], r[3]}, dst + v);
-            x[i] = u32x4{FILL, FILL, FILL, FILL};
-            if (more && v < nvec) x[i] = __builtin_nontemporal_load(src_next + v);
+            if (more) {
+#pragma unroll
+                for (int i = i0; i < i0 + GRP; ++i) x[i] = kl_ld<KL_NT>(src_next, voff + i * STEP);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
-        // recorded tokens: the thread that stored the vector holding idx_j rewrites that element,
-        // so the two stores to one address are in program order
+        if constexpr (NL > 0) {
+#pragma unroll
+            for (int i = 0; i < NL; ++i) {
+                kl_st(dst, kl_vec_grad<T>(lds_x[i * THREADS + tid], g), voff + (NV + i) * STEP);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the slots have been read
+            if (more) {
+#pragma unroll
+                for (int i = 0; i < NL; ++i) lds_fetch(logits, Rn, i);
+            }
+        }
+        // recorded tokens: the thread that stored the element's vector rewrites that element, so
+        // the two stores to one address are in program order
         for (int j = 0; j < K; ++j) {
-            int id = tc.idx[j];
-            if (id >= 0 && ((id >> 3) & (THREADS - 1)) == tid) {
-                float s = fast_exp2(fmaf(tc.x[j], CART_LOG2E, -lse2));
-                dlogits[row + id] = f32_to_bf16(scale * ((rest ? 1.f : M) * s - tc.t[j]));
+            const int id = tc.idx[j];
+            if (id >= 0 && kl_owner<T, THREADS>(R, id) == tid) {
+                const float s = fast_exp2(fmaf(tc.x[j], CART_LOG2E, -lse2));
+                elem<T>::store(dlogits + R.row + id, scale * ((rest ? 1.f : M) * s - tc.t[j]));
             }
         }
         kl_row_value(tc, K, lse2 * CART_LN2, extra, row_kl + n);
         if (!more) break;
         n = n_next;
+        R = Rn;
         __syncthreads();    // the teacher staging area and the reduction arrays are reused
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void kl_row_stream(const T* logits, const int32_t* idx,
-                                                     const float* logp, T* dlogits, float* row_kl,
-                                                     int V, int K, float scale, int rest) {
-    constexpr int THREADS = 256, NW = THREADS / CART_WAVE;
-    __shared__ KlTeacher tc;
-    __shared__ float red_max[NW], red_m[NW], red_sum[NW], rest_terms[2];
-    const int n = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const size_t row = static_cast<size_t>(n) * V;
-    const T* src = logits + row;
-
-    float m_part = kl_stage_teacher<T, THREADS>(tc, src, idx + static_cast<size_t>(n) * K,
-                                               logp ? logp + static_cast<size_t>(n) * K : nullptr, V, K);
-    // pass 1: running (max, sum) per thread in base 2
-    float mx = -3.0e38f, sum = 0.f;
-    for (int v = tid; v < V; v += THREADS) {
-        float y = elem<T>::load(src + v) * CART_LOG2E;
-        float nm = fmaxf(mx, y);
-        sum = sum * fast_exp2(mx - nm) + fast_exp2(y - nm);
-        mx = nm;
-    }
-    float wmx = wave_max(mx);
-    sum = wave_sum(sum * fast_exp2(mx - wmx));
-    m_part = wave_sum(m_part);
-    if (lane == 0) { red_max[wv] = wmx; red_sum[wv] = sum; red_m[wv] = m_part; }
-    __syncthreads();
-    float M = 0.f, gmx = red_max[0];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) { gmx = fmaxf(gmx, red_max[w]); M += red_m[w]; }
-    sum = 0.f;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) sum += red_sum[w] * fast_exp2(red_max[w] - gmx);
-    const float lse2 = gmx + fast_log2(sum);
-
-    // pass 2: gradient; each thread rewrites the recorded tokens it owns after its own stores
-    float coef = M, extra = 0.f;
-    if (rest) {
-        kl_rest_terms(tc, K, lse2, M, rest_terms);
-        __syncthreads();
-        coef = rest_terms[0];
-        extra = rest_terms[1];
-    }
-    const float c = scale * coef;
-    T* dst = dlogits + row;
-    for (int v = tid; v < V; v += THREADS) {
-        float y = elem<T>::load(src + v);
-        elem<T>::store(dst + v, c * fast_exp2(fmaf(y, CART_LOG2E, -lse2)));
-    }
-    for (int j = 0; j < K; ++j) {
-        int id = tc.idx[j];
-        if (id >= 0 && (id & (THREADS - 1)) == tid) {
-            float s = fast_exp2(fmaf(tc.x[j], CART_LOG2E, -lse2));
-            elem<T>::store(dst + id, scale * ((rest ? 1.f : M) * s - tc.t[j]));
-        }
-    }
-    kl_row_value(tc, K, lse2 * CART_LN2, extra, row_kl + n);
-}
-
-// loss = scale * sum_n row_kl[n]: one workgroup, fixed summation order, fp64 accumulation
+// loss = scale * sum_n row_kl[n]: one workgroup, fixed summation order, fp64 accumulation.  A launch and a few
+// round trips: 16384 rows 5.8 -> 4.0 us with two barriers' worth of tree instead of eleven.
 __global__ __launch_bounds__(1024) void kl_reduce_rows(const float* row_kl, int N, float scale,
                                                        float* loss) {
-    __shared__ double red[1024];
+    __shared__ double red[1024 / CART_WAVE];
     double a = 0.0;
+#pragma unroll 8
     for (int i = threadIdx.x; i < N; i += 1024) a += static_cast<double>(row_kl[i]);
-    red[threadIdx.x] = a;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, CART_WAVE);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
-    for (int s = 512; s > 0; s >>= 1) {
-        if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        a = red[0];
+#pragma unroll
+        for (int w = 1; w < 1024 / CART_WAVE; ++w) a += red[w];
+        *loss = static_cast<float>(static_cast<double>(scale) * a);
     }
-    if (threadIdx.x == 0) *loss = static_cast<float>(static_cast<double>(scale) * red[0]);
+}
+
+template <typename T, int THREADS, int NV, int NL>
+static void resident(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
+                     float* rows, hipStream_t st) {
+    const int slots = 256 * ((NV > 4 ? 1024 : 2048) / THREADS);      // workgroups an MI355X keeps resident
+    hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
+                       dim3(THREADS), static_cast<unsigned>(d.K) * 16u, st, static_cast<const T*>(logits), idx, logp,
+                       static_cast<T*>(d_logits), rows, d.N, d.V, d.K, d.scale, d.mode == CART_KL_REST ? 1 : 0);
+}
+template <typename T, int NL>
+static void launch_rows(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
+                        float* rows, hipStream_t st) {
+    const long nvec = d.V / KlVec<T>::N;
+    if (nvec <= 128 * 4) resident<T, 128, 4, 0>(d, logits, idx, logp, d_logits, rows, st);
+    else if (nvec <= 256 * 4) resident<T, 256, 4, 0>(d, logits, idx, logp, d_logits, rows, st);
+    else if (nvec <= 256 * 16) resident<T, 256, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
+    else if (nvec <= 512 * 16) resident<T, 512, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
+    else if (nvec <= 1024 * 16) resident<T, 1024, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
+    else resident<T, 1024, 16, NL>(d, logits, idx, logp, d_logits, rows, st);
 }
 
 int launch_kl(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp,
               float* loss, void* d_logits, float* row_kl, void* ws, hipStream_t st) {
     float* rows = row_kl ? row_kl : static_cast<float*>(ws);
-    const int rest = d.mode == CART_KL_REST ? 1 : 0;
     trace_begin(st);   // kernel order: row kernel, loss reduce
-    const bool resident = d.logits_dtype == CART_BF16 && (d.V % 8) == 0 && d.V <= 1024 * 16 * 8;
-    if (resident) {
-        const bf16_t* x = static_cast<const bf16_t*>(logits);
-        bf16_t* g = static_cast<bf16_t*>(d_logits);
-        const int nvec = d.V / 8;
-        const dim3 grid(static_cast<unsigned>(d.N < KL_RESIDENT_WGS ? d.N : KL_RESIDENT_WGS));
-        if (nvec <= 1024 * 4)
-            hipLaunchKernelGGL(kl_row_resident<4>, grid, dim3(1024), 0, st, x, idx, logp, g, rows, d.N, d.V, d.K, d.scale, rest);
-        else if (nvec <= 1024 * 8)
-            hipLaunchKernelGGL(kl_row_resident<8>, grid, dim3(1024), 0, st, x, idx, logp, g, rows, d.N, d.V, d.K, d.scale, rest);
-        else
-            hipLaunchKernelGGL(kl_row_resident<16>, grid, dim3(1024), 0, st, x, idx, logp, g, rows, d.N, d.V, d.K, d.scale, rest);
-    } else if (d.logits_dtype == CART_BF16) {
-        hipLaunchKernelGGL(kl_row_stream<bf16_t>, dim3(d.N), dim3(256), 0, st,
-                           static_cast<const bf16_t*>(logits), idx, logp,
-                           static_cast<bf16_t*>(d_logits), rows, d.V, d.K, d.scale, rest);
-    } else {
-        hipLaunchKernelGGL(kl_row_stream<float>, dim3(d.N), dim3(256), 0, st,
-                           static_cast<const float*>(logits), idx, logp,
-                           static_cast<float*>(d_logits), rows, d.V, d.K, d.scale, rest);
-    }
+    // (a bf16 row too long for the registers alone is rare: no LDS part for it)
+    if (d.logits_dtype == CART_BF16) launch_rows<bf16_t, 0>(d, logits, idx, logp, d_logits, rows, st);
+    else launch_rows<float, 8>(d, logits, idx, logp, d_logits, rows, st);
     trace_mark(st);
     hipLaunchKernelGGL(kl_reduce_rows, dim3(1), dim3(1024), 0, st, rows, d.N, d.scale, loss);
     trace_mark(st);

@@ -60,3 +60,47 @@ def check_attn(q, k, v, zk, zv, do, impl=cb.IMPL_AUTO, n_frozen=0):
                                           (1, 193, 12, 2, 130), (1, 320, 1, 1, 5), (3, 1, 4, 1, 3)])
 def test_attention_query_blocks(B, S, Hq, Hkv, P):
     check_attn(*attn_case((B, S), Hq, Hkv, 128, P, torch.bfloat16, 31 * S + Hq), impl=cb.IMPL_MFMA)
+
+
+# Loss: every width of the row kernel at its last size and just past it, rows that start at every
+# offset from a 16-byte boundary (odd vocabularies), more records than threads, more rows than the
+# launch has workgroups.  (data type, rows, vocabulary, records)
+LOSS_CASES = [
+    (torch.bfloat16, 9, 5, 3), (torch.bfloat16, 5, 4096, 20), (torch.bfloat16, 9, 4107, 200), (torch.bfloat16, 3, 8199, 20),
+    (torch.bfloat16, 3, 32768, 20), (torch.bfloat16, 9, 32777, 300), (torch.bfloat16, 5, 65543, 20),
+    (torch.bfloat16, 2, 131079, 20), (torch.bfloat16, 3, 140003, 20), (torch.bfloat16, 4100, 131, 4),
+    (torch.float32, 7, 3, 2), (torch.float32, 5, 2048, 140), (torch.float32, 5, 2055, 20), (torch.float32, 5, 4099, 20),
+    (torch.float32, 3, 16385, 20), (torch.float32, 3, 32771, 20), (torch.float32, 2, 65536, 20), (torch.float32, 5, 65541, 1024),
+    (torch.float32, 300, 65541, 5), (torch.float32, 3, 98307, 20), (torch.float32, 3, 120001, 20), (torch.float32, 2050, 2060, 4),
+]
+
+
+@pytest.mark.parametrize("dtype,N,V,K", LOSS_CASES, ids=lambda v: str(v).replace("torch.", ""))
+def test_loss_rows(dtype, N, V, K):
+    g = torch.Generator().manual_seed(V + K)
+    x = (3.0 * torch.randn(N, V, generator=g)).to(dtype)
+    if V > 1000:
+        x[0, V // 2:] = float("-inf")              # a masked tail
+        x[-1] = x[-1] + 60.0                        # far from 0
+    idx = torch.stack([torch.randperm(V // 2 if n == 0 and V > 1000 else V, generator=g)[:K] for n in range(N)]).to(torch.int32)
+    lp = torch.log_softmax(2.0 * torch.randn(N, K, generator=g), 1) - 0.1
+    idx[-1, 0] = -1
+    scale = 1.0 / N
+    xs, fin = f64(x), torch.isfinite(x).numpy()
+    for mode, ref in ((cb.KL_TOPK, orc.distill_kl), (cb.KL_REST, orc.distill_kl_rest_bucket)):
+        loss_ref, dl_ref, kl_ref = ref(np.where(fin, xs, -1e4), idx.numpy(), f64(lp), scale)
+        d = x.to(DEV)
+        row = torch.empty(N, device=DEV)
+        loss, dl = cb.cart_distill_kl_fwd_bwd(d, idx.to(DEV), lp.to(DEV), scale, mode=mode, row_kl=row)
+        loss2, dl2 = cb.cart_distill_kl_fwd_bwd(d, idx.to(DEV), lp.to(DEV), scale, mode=mode, d_logits=d)   # in place
+        torch.cuda.synchronize()
+        assert torch.equal(dl, dl2) and torch.equal(loss, loss2)
+        # rest bucket: the student's mass off the records is 1 - S in fp32, an error of a few 2^-24
+        # in a difference of order min(1 - S) (small only where nearly every token is recorded)
+        p = np.exp(xs - xs.max(1, keepdims=True))
+        rec = idx.numpy() >= 0
+        off = 1.0 - (np.take_along_axis(p, np.maximum(idx.numpy(), 0), 1) * rec).sum(1) / p.sum(1)
+        ill = 2.0 ** -22 / off.min() if mode == cb.KL_REST else 0.0
+        assert rel_err(dl, dl_ref) <= TOL[dtype] + ill
+        assert abs(loss.item() - loss_ref) <= (1e-4 + ill) * max(abs(loss_ref), 1e-3)
+        assert rel_err(row, kl_ref) <= 1e-4 + ill
