@@ -11,6 +11,7 @@
 // logits: also in LDS), so HBM sees each logit read once and each gradient written once; what
 // exceeds both is read twice.
 #include "attn_mfma.h"
+#include "logit_rows.h"
 
 namespace cart {
 
@@ -57,43 +58,21 @@ __device__ __forceinline__ void kl_rest_terms(const KlTeacher& tc, int K, float 
     }
 }
 
-// max of a float and two raw fp32 bit patterns in one instruction, without the NaN-quieting
-// moves the compiler would add around fmaxf for values it cannot prove canonical
-__device__ __forceinline__ float max3_raw(float a, uint32_t b, uint32_t c) {
-    float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-    return r;
-}
-
-// One 16-byte vector of logits: its elements widened to fp32, and the gradient packed back.
-template <typename T> struct KlVec;
-template <> struct KlVec<bf16_t> {
-    static constexpr int N = 8;
-    static constexpr uint32_t FILL = 0xff7fff7fu;      // two bf16 of the most negative finite value
-    static __device__ __forceinline__ uint32_t bits(const u32x4& w, int e) {
-        return (e & 1) ? (w[e >> 1] & 0xffff0000u) : (w[e >> 1] << 16);
-    }
-};
-template <> struct KlVec<float> {
-    static constexpr int N = 4;
-    static constexpr uint32_t FILL = 0xff7fffffu;
-    static __device__ __forceinline__ uint32_t bits(const u32x4& w, int e) { return w[e]; }
-};
 template <typename T> __device__ __forceinline__ u32x4 kl_fill() {
-    constexpr uint32_t f = KlVec<T>::FILL;
+    constexpr uint32_t f = LogitVec<T>::FILL;
     return u32x4{f, f, f, f};
 }
 template <typename T> __device__ __forceinline__ float kl_vec_max(float mx, const u32x4& w) {
 #pragma unroll
-    for (int e = 0; e < KlVec<T>::N; e += 2) mx = max3_raw(mx, KlVec<T>::bits(w, e), KlVec<T>::bits(w, e + 1));
+    for (int e = 0; e < LogitVec<T>::N; e += 2) mx = max3_raw(mx, LogitVec<T>::bits(w, e), LogitVec<T>::bits(w, e + 1));
     return mx;
 }
 // s0 + s1 += sum of 2^(x log2e + c0)
 template <typename T> __device__ __forceinline__ void kl_vec_sum(float& s0, float& s1, const u32x4& w, float c0) {
 #pragma unroll
-    for (int e = 0; e < KlVec<T>::N; e += 2) {
-        s0 += fast_exp2(fmaf(__uint_as_float(KlVec<T>::bits(w, e)), CART_LOG2E, c0));
-        s1 += fast_exp2(fmaf(__uint_as_float(KlVec<T>::bits(w, e + 1)), CART_LOG2E, c0));
+    for (int e = 0; e < LogitVec<T>::N; e += 2) {
+        s0 += fast_exp2(fmaf(__uint_as_float(LogitVec<T>::bits(w, e)), CART_LOG2E, c0));
+        s1 += fast_exp2(fmaf(__uint_as_float(LogitVec<T>::bits(w, e + 1)), CART_LOG2E, c0));
     }
 }
 // Gradient off the recorded tokens: g = c 2^(x log2e - lse2), c = scale * M (rest-bucket mode: scale *
@@ -123,30 +102,10 @@ template <typename T> __device__ __forceinline__ u32x4 kl_vec_grad(const u32x4& 
     return r;
 }
 
-// Row n of [N][V]: `head` single elements, nvec whole vectors, `tail` single elements.  The base of
-// the tensor is 16-byte aligned.  Single element s (of head + tail <= 14) belongs to thread s of the
-// workgroup, vector v to thread v % THREADS.
-struct KlRow {
-    size_t row;
-    int head, nvec, tail;
-};
-template <typename T> __device__ __forceinline__ KlRow kl_row(int n, int V) {
-    constexpr int VE = KlVec<T>::N;
-    KlRow r;
-    r.row = static_cast<size_t>(n) * V;
-    r.head = min(static_cast<int>((VE - (r.row & (VE - 1))) & (VE - 1)), V);
-    r.nvec = (V - r.head) / VE;
-    r.tail = V - r.head - r.nvec * VE;
-    return r;
-}
-// element index of single s
-template <typename T> __device__ __forceinline__ int kl_single(const KlRow& r, int s) {
-    return s < r.head ? s : s + r.nvec * KlVec<T>::N;
-}
 // the thread (of THREADS) that stores element id
-template <typename T, int THREADS> __device__ __forceinline__ int kl_owner(const KlRow& r, int id) {
-    const int e = id - r.head, v = e / KlVec<T>::N;
-    return e < 0 ? id : v < r.nvec ? v & (THREADS - 1) : id - r.nvec * KlVec<T>::N;
+template <typename T, int THREADS> __device__ __forceinline__ int kl_owner(const LogitRow& r, int id) {
+    const int e = id - r.head, v = e / LogitVec<T>::N;
+    return e < 0 ? id : v < r.nvec ? v & (THREADS - 1) : id - r.nvec * LogitVec<T>::N;
 }
 
 // The body of a row as a buffer resource: a load past its end returns 0 and a store past it is
@@ -154,7 +113,7 @@ template <typename T, int THREADS> __device__ __forceinline__ int kl_owner(const
 struct KlBuf {
     __amdgpu_buffer_rsrc_t r;
 };
-template <typename T> __device__ __forceinline__ KlBuf kl_buf(const T* base, const KlRow& r) {
+template <typename T> __device__ __forceinline__ KlBuf kl_buf(const T* base, const LogitRow& r) {
     return KlBuf{__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base + r.row + r.head), 0,
                                                    static_cast<int>(static_cast<uint32_t>(r.nvec) * 16u), 0x00027000)};
 }
@@ -189,7 +148,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
                                                               const float* logp, T* dlogits, float* row_kl,
                                                               int N, int V, int K, float scale, int rest) {
     constexpr int GRP = NV < 8 ? NV : 8;
-    constexpr int NW = THREADS / CART_WAVE, VE = KlVec<T>::N;
+    constexpr int NW = THREADS / CART_WAVE, VE = LogitVec<T>::N;
     const KlTeacher tc = kl_teacher(K);
     __shared__ float red_c[NW], red_m[NW], red_sum[NW], rest_terms[2];
     __shared__ __attribute__((aligned(16))) u32x4 lds_x[NL > 0 ? NL * THREADS : 1];
@@ -197,10 +156,10 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     int n = blockIdx.x;
     if (n >= N) return;
-    KlRow R = kl_row<T>(n, V);
+    LogitRow R = logit_row<T>(n, V);
 
     // vector i of the next row's LDS part, straight into the thread's own slot (clamped to the row)
-    auto lds_fetch = [&](const T* base, const KlRow& r, int i) __attribute__((always_inline)) {
+    auto lds_fetch = [&](const T* base, const LogitRow& r, int i) __attribute__((always_inline)) {
         const int v = min((NV + i) * THREADS + tid, max(r.nvec - 1, 0));
         mfma::dma16(reinterpret_cast<const char*>(base + r.row + r.head), static_cast<uint32_t>(v) * 16u,
                     mfma::lds_addr(lds_x + i * THREADS + wv * CART_WAVE));
@@ -219,7 +178,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         }
     };
     // ... then the logits of the tokens
-    auto fetch_logit = [&](const KlRow& r) __attribute__((always_inline)) {
+    auto fetch_logit = [&](const LogitRow& r) __attribute__((always_inline)) {
         if (my_id >= V) my_id = -1;
         if (my_id >= 0) my_x = elem<T>::load(logits + r.row + my_id);
     };
@@ -231,7 +190,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
 #pragma unroll
             for (int i = 0; i < NL; ++i) lds_fetch(logits, R, i);
         }
-        if (tid < R.head + R.tail) xs = elem<T>::load(logits + R.row + kl_single<T>(R, tid));
+        if (tid < R.head + R.tail) xs = elem<T>::load(logits + R.row + logit_single<T>(R, tid));
         fetch_record(n);
         fetch_logit(R);
     }
@@ -332,12 +291,12 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             extra = rest_terms[1];
         }
         const KlGrad g = kl_grad_coef<T>(scale * coef, lse2);
-        const KlRow Rn = kl_row<T>(more ? n_next : n, V);
+        const LogitRow Rn = logit_row<T>(more ? n_next : n, V);
         if (more) fetch_logit(Rn);
         if (tid < R.head + R.tail)
-            elem<T>::store(dlogits + R.row + kl_single<T>(R, tid), g.c * fast_exp2(fmaf(xs, CART_LOG2E, -lse2)));
+            elem<T>::store(dlogits + R.row + logit_single<T>(R, tid), g.c * fast_exp2(fmaf(xs, CART_LOG2E, -lse2)));
         xs = -3.0e38f;
-        if (more && tid < Rn.head + Rn.tail) xs = elem<T>::load(logits + Rn.row + kl_single<T>(Rn, tid));
+        if (more && tid < Rn.head + Rn.tail) xs = elem<T>::load(logits + Rn.row + logit_single<T>(Rn, tid));
         for (int v = (NV + NL) * THREADS + tid; v < R.nvec; v += THREADS)
             kl_st(dst, kl_vec_grad<T>(kl_ld<KL_NT>(src, v * 16), g), v * 16);
         const KlBuf src_next = kl_buf(logits, Rn);
@@ -414,7 +373,7 @@ static void resident(const cart_kl_desc& d, const void* logits, const int32_t* i
 template <typename T, int NL>
 static void launch_rows(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
                         float* rows, hipStream_t st) {
-    const long nvec = d.V / KlVec<T>::N;
+    const long nvec = d.V / LogitVec<T>::N;
     if (nvec <= 128 * 4) resident<T, 128, 4, 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec <= 256 * 4) resident<T, 256, 4, 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec <= 256 * 16) resident<T, 256, 16, 0>(d, logits, idx, logp, d_logits, rows, st);

@@ -104,3 +104,29 @@ def test_loss_rows(dtype, N, V, K):
         assert rel_err(dl, dl_ref) <= TOL[dtype] + ill
         assert abs(loss.item() - loss_ref) <= (1e-4 + ill) * max(abs(loss_ref), 1e-3)
         assert rel_err(row, kl_ref) <= 1e-4 + ill
+
+
+# Teacher records: the three widths of the row kernel at and past their last size, rows starting at
+# every offset, K at the edges of the widths and beyond the finite logits of a row, rows made of ties.
+TOPK_CASES = [
+    (torch.bfloat16, 9, 33, 20), (torch.bfloat16, 9, 4099, 128), (torch.bfloat16, 5, 32771, 129), (torch.bfloat16, 3, 32775, 20),
+    (torch.bfloat16, 3, 98311, 256), (torch.bfloat16, 3, 98320, 64), (torch.bfloat16, 9, 131, 131), (torch.bfloat16, 3, 20003, 512),
+    (torch.float32, 9, 7, 7), (torch.float32, 5, 16387, 128), (torch.float32, 5, 16389, 20), (torch.float32, 3, 49155, 257),
+    (torch.float32, 3, 49161, 20), (torch.float32, 2, 130001, 64),
+]
+
+
+@pytest.mark.parametrize("dtype,N,V,K", TOPK_CASES, ids=lambda v: str(v).replace("torch.", ""))
+def test_topk_rows(dtype, N, V, K):
+    g = torch.Generator().manual_seed(V + K)
+    x = 3.0 * torch.randn(N, V, generator=g)
+    x[1] = torch.round(x[1])                                   # thousands of ties at every level
+    if V > 100:
+        x[-1] = -1.0e4                                         # few logits above the rest, at both ends of the row
+        x[-1, :3], x[-1, -3:] = 1.0, 1.0
+    x = x.to(dtype)
+    idx_ref, lp_ref = orc.teacher_topk(f64(x), K)
+    idx, lp = cb.cart_teacher_topk(x.to(DEV), K)
+    torch.cuda.synchronize()
+    assert np.array_equal(idx.cpu().numpy().astype(np.int64), idx_ref)
+    assert np.abs(f64(lp) - lp_ref).max() <= 2e-6 * max(1.0, np.abs(lp_ref).max())
