@@ -184,6 +184,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
     };
     {
         const KlBuf src = kl_buf(logits, R);
+        fetch_record(n);          // (ahead of the row: what depends on it need not wait for the row)
 #pragma unroll
         for (int i = 0; i < NV; ++i) x[i] = kl_ld<KL_NT>(src, voff + i * STEP);
         if constexpr (NL > 0) {
@@ -191,7 +192,6 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             for (int i = 0; i < NL; ++i) lds_fetch(logits, R, i);
         }
         if (tid < R.head + R.tail) xs = elem<T>::load(logits + R.row + logit_single<T>(R, tid));
-        fetch_record(n);
         fetch_logit(R);
     }
     for (;;) {
