@@ -9,6 +9,17 @@ Trace& trace() {
     static Trace t;
     return t;
 }
+int device_cus() {
+    static int cached[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    if (!cached[dev]) {
+        int cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
+        cached[dev] = cus;
+    }
+    return cached[dev];
+}
 }  // namespace cart
 
 namespace {

@@ -92,23 +92,90 @@ struct QueryBlock {
     int hk, b, h;       // KV head, sequence, the wavefront's query head
     int q0, q_end;      // tokens of the workgroup
     int wrow0;          // first token of the wavefront
+    int part, n_parts;  // which part of the block's key tiles, of how many
+    int slot;           // where the part's partial result goes (n_parts > 1)
 };
 __host__ __device__ inline int query_wgs(int S, int G) { return (((S + 63) / 64) * G + 3) / 4; }
+
+// One workgroup fills a CU, so a launch runs in rounds of one block per CU, and what is left over
+// after the whole rounds -- everything, for a small problem -- leaves CUs idle for a block's whole
+// length.  Those last blocks may be split along their key tiles into parts of about equal length;
+// each part leaves a partial result (128 KB) and the finishing kernel of the call combines them.  All blocks of one KV head are numbered b * nW + (nW-1-w) (heaviest first
+// within a sequence); the first e_full of them run whole, the parts of the others are listed (a
+// search over the blocks in the kernels took longer than the parts' own set-up).
+constexpr int MAX_SPLIT = 256;          // parts per KV head, at most one per CU
+struct QuerySplit {
+    int e_full;                         // blocks per KV head that run whole
+    int n_blocks, n_parts;              // split blocks and their parts, per KV head
+    uint32_t part[MAX_SPLIT];           // part i: block (from e_full) | part of the block << 8 | parts of the block << 16
+    uint32_t first[MAX_SPLIT];          // split block -> its first part
+};
 // KV head fastest: with 8 of them blockIdx % 8 (the XCD) is the KV head and each XCD's L2 keeps one
 // head's prefix; then the blocks of one sequence, heaviest (longest causal part) first, sequence
 // after sequence, so that the workgroups running at one time share one or two sequences' K/V in L2.
-__device__ __forceinline__ QueryBlock query_block(int id, int wv, int Smax, int Hq, int Hkv) {
+__device__ __forceinline__ QueryBlock query_block_of(int hk, int e, int wv, int nW, int G) {
     QueryBlock qb;
-    const int G = Hq / Hkv, nW = query_wgs(Smax, G);
-    qb.hk = id % Hkv; id /= Hkv;
-    const int u0 = 4 * (nW - 1 - id % nW), u = u0 + wv;
-    qb.b = id / nW;
-    qb.h = qb.hk * G + u % G;
+    const int u0 = 4 * (nW - 1 - e % nW), u = u0 + wv;
+    qb.hk = hk;
+    qb.b = e / nW;
+    qb.h = hk * G + u % G;
     qb.wrow0 = 64 * (u / G);
     qb.q0 = 64 * (u0 / G);
     qb.q_end = 64 * ((u0 + 3) / G) + 64;
+    qb.part = 0;
+    qb.n_parts = 1;
+    qb.slot = 0;
     return qb;
 }
+__device__ __forceinline__ QueryBlock query_block(int id, int wv, int Smax, int Hq, int Hkv, const QuerySplit& sp) {
+    const int G = Hq / Hkv, hk = id % Hkv, x = id / Hkv;
+    const uint32_t it = x < sp.e_full ? 0x10000u : sp.part[x - sp.e_full];
+    QueryBlock qb = query_block_of(hk, x < sp.e_full ? x : sp.e_full + (it & 255), wv, query_wgs(Smax, G), G);
+    qb.part = (it >> 8) & 255;
+    qb.n_parts = it >> 16;
+    qb.slot = (x - sp.e_full) * Hkv + hk;
+    return qb;
+}
+// Key tiles of a query block, in the order the kernels take them: the tiles every query of the block
+// sees entirely (whole prefix tiles, then own tiles tU0 .. tD-1), then the ones that need a mask (the
+// ragged last prefix tile, own tiles tA .. that start before the first key of some query, the own
+// tiles from tD on the diagonal).  [lo, hi): the tiles of this part.  A part other than the first
+// starts at a tile of the first kind, so that every query has a visible key in it.
+struct KeyTiles {
+    int nPf, rag, tA, tU0, tD, nLow, nMain, nT, lo, hi;
+    __device__ __forceinline__ bool pre(int t) const { return t < nPf || (rag && t == nMain); }
+    __device__ __forceinline__ int j0(int t) const {
+        const int m = t - nMain - rag;      // among the masked own tiles
+        return (t < nPf ? t : t < nMain ? tU0 + t - nPf : (rag && t == nMain) ? nPf : m < nLow ? tA + m : tD + m - nLow) * 64;
+    }
+};
+__device__ __forceinline__ KeyTiles key_tiles(const QueryBlock& qb, int S, int P, const int32_t* row_lo) {
+    KeyTiles k;
+    const int own_end = min(S, qb.q_end);
+    k.nPf = P / 64;
+    k.rag = (P % 64) ? 1 : 0;
+    const int lo_first = row_lo ? row_lo[qb.q0] : 0, lo_last = row_lo ? row_lo[own_end - 1] : 0;
+    k.tA = lo_first / 64;
+    k.tU0 = (lo_last + 63) / 64;
+    k.tD = qb.q0 / 64;
+    const int nOf = max(0, k.tD - k.tU0);
+    k.nLow = min(k.tU0, k.tD) - k.tA;
+    k.nMain = k.nPf + nOf;
+    k.nT = k.nMain + k.rag + k.nLow + (own_end + 63) / 64 - k.tD;
+    const int step = (k.nT + qb.n_parts - 1) / qb.n_parts, last = max(k.nMain - 1, 0);
+    k.lo = qb.part == 0 ? 0 : min(qb.part * step, last);
+    k.hi = qb.part == qb.n_parts - 1 ? k.nT : min((qb.part + 1) * step, last);
+    return k;
+}
+// (host) the split of a query-stationary launch: B sequences of at most S tokens, blocks of at most
+// own_cap own-key tiles (packed rows: bounded by the longest sequence),
+// and the time of a whole block, a + b per key tile (us).
+void plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, float a, float b);
+// The cut of the key-stationary launch: token rows per dZ partial, the partials, and into how many parts the
+// query heads that read an own key are split
+struct KvPlan { int chunk, n_part, head_parts; };
+// partial results of one part: 256 rows x 128 fp32, then (forward) 256 fp32 LSEs
+constexpr size_t PART_O_BYTES = 256 * 128 * sizeof(float), PART_L_BYTES = 256 * sizeof(float);
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -235,6 +302,79 @@ __device__ __forceinline__ bf16x8 pack_frag(const f32x16& s, int r0) {
     u32x4 w = {pack_bf16x2(s[r0 + 0], s[r0 + 1]), pack_bf16x2(s[r0 + 2], s[r0 + 3]),
                pack_bf16x2(s[r0 + 4], s[r0 + 5]), pack_bf16x2(s[r0 + 6], s[r0 + 7])};
     return __builtin_bit_cast(bf16x8, w);
+}
+
+// ---- storing a wavefront's transposed accumulators ---------------------------------------------
+// acc[db][cb] holds, for row 32 cb + lane % 32 of the wavefront's 64, columns 32 db + 8 (r/4) +
+// 4 (lane/32) + r%4.  Stored from the registers, an instruction touches 32 rows with 16 or 32 bytes
+// each, and the 32 to 64 of them take 4-5 us of a workgroup's life; turned around in LDS (the
+// wavefront's own 16 or 32 KB, free once the key or query tiles are done with) every store
+// instruction writes whole rows.  The 16-byte chunks are swizzled by row so that neither side has
+// bank conflicts: a forward block of 256 rows 4.7 -> 3.4 us from its last product to its end (16 sequences
+// of 256 tokens, 32 heads, 1024 slots: 88.8 -> 85.7 us a forward call).  Rows from n_rows on are not stored; consecutive rows are `pitch` elements apart.
+// Returns, per block of 32 rows, the sum of the lane's scaled values (not finite when one is not).
+struct RowSums { float s[2]; };
+__device__ __forceinline__ RowSums store_rows64(char* lds, const f32x16 (&acc)[4][2], float mul0, float mul1,
+                                                   bf16_t* __restrict__ out, size_t pitch, int n_rows, int lane) {
+    const int lg = lane >> 5, lc = lane & 31;
+    RowSums rs;
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+        const float mul = cb ? mul1 : mul0;
+        float sum = 0.f;
+        char* row = lds + (32 * cb + lc) * ROW_B + ((lg ^ (lc >> 4)) << 3);
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const float v0 = acc[db][cb][4 * r4] * mul, v1 = acc[db][cb][4 * r4 + 1] * mul,
+                            v2 = acc[db][cb][4 * r4 + 2] * mul, v3 = acc[db][cb][4 * r4 + 3] * mul;
+                sum += (v0 + v1) + (v2 + v3);
+                const u32x2 w = {pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
+                *reinterpret_cast<u32x2*>(row + (((4 * db + r4) ^ (lc & 15)) << 4)) = w;
+            }
+        rs.s[cb] = sum;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    const int rl = lane >> 4, ch = lane & 15;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int r = 4 * i + rl;
+        u32x4 w = *reinterpret_cast<const u32x4*>(lds + r * ROW_B + ((ch ^ (r & 15)) << 4));
+        if (i & 4) w = u32x4{w.z, w.w, w.x, w.y};       // (rows 16-31 of a block: halves stored the other way round)
+        if (r < n_rows) *reinterpret_cast<u32x4*>(out + r * pitch + 8 * ch) = w;
+    }
+    return rs;
+}
+__device__ __forceinline__ RowSums store_rows64(char* lds, const f32x16 (&acc)[4][2], float mul0, float mul1,
+                                                float* __restrict__ out, size_t pitch, int n_rows, int lane) {
+    const int lg = lane >> 5, lc = lane & 31;
+    RowSums rs;
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+        const float mul = cb ? mul1 : mul0;
+        float sum = 0.f;
+        char* row = lds + (32 * cb + lc) * 2 * ROW_B;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const f32x4 w = {acc[db][cb][4 * r4] * mul, acc[db][cb][4 * r4 + 1] * mul, acc[db][cb][4 * r4 + 2] * mul,
+                                 acc[db][cb][4 * r4 + 3] * mul};
+                sum += (w[0] + w[1]) + (w[2] + w[3]);
+                *reinterpret_cast<f32x4*>(row + (((8 * db + 2 * r4 + lg) ^ lc) << 4)) = w;
+            }
+        rs.s[cb] = sum;
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    const int rl = lane >> 5, ch = lane & 31;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) {
+        const int r = 2 * i + rl;
+        const f32x4 w = *reinterpret_cast<const f32x4*>(lds + r * 2 * ROW_B + ((ch ^ (r & 31)) << 4));
+        if (r < n_rows) *reinterpret_cast<f32x4*>(out + r * pitch + 4 * ch) = w;
+    }
+    return rs;
 }
 
 // ---- direct-to-LDS loads --------------------------------------------------------------------

@@ -23,20 +23,6 @@ using namespace mfma;
 
 constexpr int BWD_TILE = 64;                      // rows per LDS tile
 constexpr int BWD_TILE_B = BWD_TILE * ROW_B;
-// store a transposed accumulator block set: lane owns output row `row_ptr` (nullptr: skip),
-// register r of block db holds column 32 db + 8 (r/4) + 4 g + r%4
-__device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[4], bf16_t* row_ptr, int lg, float mul) {
-    if (!row_ptr) return;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            u32x2 w = {pack_bf16x2(acc[db][4 * r4] * mul, acc[db][4 * r4 + 1] * mul),
-                       pack_bf16x2(acc[db][4 * r4 + 2] * mul, acc[db][4 * r4 + 3] * mul)};
-            *reinterpret_cast<u32x2*>(row_ptr + 32 * db + 8 * r4 + 4 * lg) = w;
-        }
-}
-
 // =================================================================================================
 // dQ: queries stationary
 // =================================================================================================
@@ -52,6 +38,7 @@ __device__ __forceinline__ void store_rows_bf16(const f32x16 (&acc)[4], bf16_t* 
 // fragments of the previous sub-tile are fetched about ten groups ahead, so a tile is read over
 // three tile iterations: four buffers.
 constexpr int DQ_NBUF = 4;
+constexpr float DQ_BLOCK_US = 11.f, DQ_TILE_US = 1.95f;     // a block's time: set-up and store, each key tile (see plan_query_split)
 struct DqSmem {
     struct { char k[BWD_TILE_B]; char v[BWD_TILE_B]; } t[DQ_NBUF];
 };
@@ -61,14 +48,15 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     const bf16_t* __restrict__ zk, const bf16_t* __restrict__ zv, const bf16_t* __restrict__ o,
     const bf16_t* __restrict__ d_o, const float* __restrict__ lse, float* __restrict__ nlse2,
     float* __restrict__ ndelta, bf16_t* __restrict__ dq, const int32_t* __restrict__ cu,
-    const int32_t* __restrict__ row_lo, int n_tok, int B, int Smax, int Hq, int Hkv, int P, float c, float scale) {
+    const int32_t* __restrict__ row_lo, int n_tok, int Smax, int Hq, int Hkv, int P, float c, float scale,
+    QuerySplit split, float* __restrict__ part_o) {
     constexpr int NBUF = DQ_NBUF;
     constexpr int BUF_B = 2 * BWD_TILE_B;
     constexpr int V_OFF = BWD_TILE_B;
     __shared__ DqSmem sm;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv);
+    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv, split);
     const int hk = qb.hk, b = qb.b, h = qb.h, q0 = qb.q0, wrow0 = qb.wrow0;
     // packed layout: the grid covers the longest sequence; nothing to do past the end of this one.
     // With row_lo (B = 1, S = all packed rows) the query tiles are cut from the packed rows as in
@@ -77,6 +65,12 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     const int S = sp.len;
     const size_t t0 = sp.t0;
     if (q0 >= S) return;
+    const KeyTiles kt = key_tiles(qb, S, P, row_lo);
+    float* const my_part = part_o + (static_cast<size_t>(qb.slot) * 256 + 64 * wv) * HD;
+    if (kt.lo >= kt.hi) {       // (fewer tiles than the launch assumed: this part is empty)
+        for (int i = lane; i < 64 * HD / 4; i += 64) reinterpret_cast<f32x4*>(my_part)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+        return;
+    }
 
     // The row statistics of the backward pass are formed here, where O and dO of every query row
     // pass through registers anyway: -delta = -rowsum(dO * O) and -lse2 = -lse * log2(e)
@@ -116,7 +110,7 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
         ds += partner(ds);
         nl2[cb] = -lse[sp.stat_b + h * sp.stat_h + qi] * CART_LOG2E;
         ndl[cb] = -ds;
-        if (lg == 0 && qi_raw < S) {      // internal layout [Hq][all token rows], both input layouts
+        if (lg == 0 && qi_raw < S && qb.part == qb.n_parts - 1) {      // (the last part is never empty) internal layout [Hq][all token rows], both input layouts
             const size_t st = static_cast<size_t>(h) * n_tok + t0 + qi;
             nlse2[st] = nl2[cb];
             ndelta[st] = ndl[cb];
@@ -151,26 +145,15 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     };
     pin();
 
-    // tile order: see the forward kernel
-    const int nPf = P / BWD_TILE;
-    const int rag = (P % BWD_TILE) ? 1 : 0;
-    const int own_end = min(S, qb.q_end);
-    const int lo_first = row_lo ? row_lo[q0] : 0, lo_last = row_lo ? row_lo[own_end - 1] : 0;
-    const int tA = lo_first / BWD_TILE, tU0 = (lo_last + BWD_TILE - 1) / BWD_TILE, tD = q0 / BWD_TILE;
-    const int nOf = max(0, tD - tU0);
-    const int nLow = min(tU0, tD) - tA;
-    const int nMain = nPf + nOf;
-    const int nT = nMain + rag + nLow + (own_end + BWD_TILE - 1) / BWD_TILE - tD;
+    // tile order: see KeyTiles
+    const int nMain = kt.nMain, nT = kt.hi;
     const char* zk_b = reinterpret_cast<const char*>(zk) + static_cast<size_t>(hk) * P * ROW_B;
     const char* zv_b = reinterpret_cast<const char*>(zv) + static_cast<size_t>(hk) * P * ROW_B;
     const uint32_t own_pitch = static_cast<uint32_t>(Hkv) * ROW_B;
     const char* k_b = reinterpret_cast<const char*>(k) + (t0 * Hkv + hk) * ROW_B;
     const char* v_b = reinterpret_cast<const char*>(v) + (t0 * Hkv + hk) * ROW_B;
-    auto tile_pre = [&](int t) __attribute__((always_inline)) { return t < nPf || (rag && t == nMain); };
-    auto tile_j0 = [&](int t) __attribute__((always_inline)) {
-        const int m = t - nMain - rag;
-        return (t < nPf ? t : t < nMain ? tU0 + t - nPf : (rag && t == nMain) ? nPf : m < nLow ? tA + m : tD + m - nLow) * BWD_TILE;
-    };
+    auto tile_pre = [&](int t) __attribute__((always_inline)) { return kt.pre(t); };
+    auto tile_j0 = [&](int t) __attribute__((always_inline)) { return kt.j0(t); };
     const uint32_t dma_c0 = (lane & 15) ^ (((lane >> 4) & 3) << 2);
     struct TileSrc { const char* kb; const char* vb; int lim; uint32_t pitch; uint32_t lds_k, lds_v; };
     auto tile_src = [&](int t, int buf) __attribute__((always_inline)) {
@@ -300,12 +283,12 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     auto settle = [&]() __attribute__((always_inline)) { asm volatile("s_nop 15\n\ts_nop 7" ::: "memory"); };
 
     {   // prologue: tiles 0 and 1 on their way, scores of sub-tile 0
-        const TileSrc t0 = tile_src(0, 0);
+        const TileSrc t0 = tile_src(kt.lo, 0);
 #pragma unroll
         for (int n = 0; n < 8; ++n) dma_piece(t0, n);
         dma_wait();
         __syncthreads();
-        const TileSrc t1 = tile_src(min(1, nT - 1), 1);
+        const TileSrc t1 = tile_src(min(kt.lo + 1, nT - 1), 1);
 #pragma unroll
         for (int n = 0; n < 8; ++n) dma_piece(t1, n);
 #pragma unroll
@@ -343,8 +326,8 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
         first = false;
         buf = nbuf;
     };
-    for (int T = 0; T < nMain; ++T) tile_iter(T, std::false_type{});
-    for (int T = nMain; T < nT; ++T) tile_iter(T, std::true_type{});
+    for (int T = kt.lo; T < min(nMain, nT); ++T) tile_iter(T, std::false_type{});
+    for (int T = max(kt.lo, nMain); T < nT; ++T) tile_iter(T, std::true_type{});
     {   // drain: dQ^T += K^T dS^T of the last sub-tile (fragments 0-4 are in registers)
         pin();
 #pragma unroll
@@ -357,102 +340,166 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
                 acc[db][1] = mma(ta[4 * ks + db], __builtin_bit_cast(bf16x8, dsf[1][ks]), acc[db][1]);
             }
     }
-#pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-        const int qi = wrow0 + 32 * cb + lc;
-        f32x16 col[4] = {acc[0][cb], acc[1][cb], acc[2][cb], acc[3][cb]};
-        store_rows_bf16(col, qi < S ? dq + ((t0 + qi) * Hq + h) * HD : nullptr, lg, scale);
-    }
+    // turned around in LDS once nobody reads a tile or has a load in flight
+    dma_wait();
+    __syncthreads();
+    char* const turn = reinterpret_cast<char*>(&sm) + wv * BUF_B;
+    if (qb.n_parts == 1)
+        store_rows64(turn, acc, scale, scale, dq + ((t0 + wrow0) * Hq + h) * HD, static_cast<size_t>(Hq) * HD, S - wrow0, lane);
+    else
+        store_rows64(turn, acc, scale, scale, my_part, HD, S - wrow0, lane);
 }
 
-// dZ[hk,slot,:] = sum_b part[b,hk,slot,:] in order of b (+ the previous value when accumulating);
-// rows below n_frozen are 0 / left alone.  One 16-byte vector per thread.
-__global__ __launch_bounds__(256) void dz_reduce_kernel(const float* __restrict__ part,
-                                                        float* __restrict__ dz, int B, long n4,
-                                                        int P, int n_frozen, int accumulate) {
-    const long i = static_cast<long>(blockIdx.x) * 256 + threadIdx.x;
-    if (i >= n4) return;
-    const int slot = (i / (HD / 4)) % P;
-    const f32x4* src = reinterpret_cast<const f32x4*>(part);
+// Everything the backward pass leaves as fp32 partials, summed in a fixed order, in one launch (two
+// launches for dZ_k and dZ_v alone cost 2 x 5 us and a gap); one 16-byte vector per thread.  Workgroups [0, dz_wgs): dZ_k, dZ_v (one partial per chunk of token rows; rows below
+// n_frozen are 0 / left alone; added to the previous value when accumulating); then the split query
+// blocks of dQ, 32 workgroups each; then dK, dV of the own tokens when their heads were split.
+struct BwdReduce {
+    const float *dz_part[2], *dq_part, *own_part[2];
+    float* dz[2];
+    bf16_t *dq, *own[2];
+    long dz_n4, own_n4;                 // vectors per partial
+    int dz_parts, own_parts, dz_wgs, dq_wgs;
+    int P, n_frozen, accumulate;
+    const int32_t* cu;
+    int n_tok, Smax, Hq, Hkv;
+};
+__device__ __forceinline__ f32x4 sum_parts(const f32x4* __restrict__ src, long i, long stride, int n) {
     f32x4 a = {0.f, 0.f, 0.f, 0.f};
-    if (slot >= n_frozen)
-        for (int b = 0; b < B; ++b) a += src[static_cast<long>(b) * n4 + i];
-    f32x4* dst = reinterpret_cast<f32x4*>(dz);
-    if (accumulate) a += dst[i];
-    dst[i] = a;
+#pragma unroll 4
+    for (int p = 0; p < n; ++p) a += src[p * stride + i];
+    return a;
+}
+__device__ __forceinline__ u32x2 pack4(const f32x4& a) { return u32x2{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3])}; }
+
+__global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(BwdReduce r, QuerySplit split) {
+    int id = blockIdx.x;
+    if (id < r.dz_wgs) {
+        const int which = id >= r.dz_wgs / 2;
+        const long i = static_cast<long>(id - which * (r.dz_wgs / 2)) * 256 + threadIdx.x;
+        if (i >= r.dz_n4) return;
+        f32x4 a = {0.f, 0.f, 0.f, 0.f};
+        if ((i / (HD / 4)) % r.P >= r.n_frozen)
+            a = sum_parts(reinterpret_cast<const f32x4*>(r.dz_part[which]), i, r.dz_n4, r.dz_parts);
+        f32x4* dst = reinterpret_cast<f32x4*>(r.dz[which]);
+        if (r.accumulate) a += dst[i];
+        dst[i] = a;
+        return;
+    }
+    id -= r.dz_wgs;
+    if (id < r.dq_wgs) {
+        const int hk = (id >> 5) % r.Hkv, blk = (id >> 5) / r.Hkv, G = r.Hq / r.Hkv;
+        const int row = 8 * (id & 31) + (threadIdx.x >> 5), d4 = threadIdx.x & 31;      // row of the block, vector of the row
+        const int first = split.first[blk], n_parts = split.part[first] >> 16;
+        if (n_parts == 1) return;           // (a short block among the split ones ran whole)
+        const QueryBlock qb = query_block_of(hk, split.e_full + blk, row >> 6, query_wgs(r.Smax, G), G);
+        const SeqSpan sp = seq_span(r.cu, qb.b, r.n_tok, r.Smax, r.Hq);
+        const int i = qb.wrow0 + (row & 63);
+        if (i >= sp.len) return;
+        const f32x4 a = sum_parts(reinterpret_cast<const f32x4*>(r.dq_part) + (static_cast<size_t>(first) * r.Hkv + hk) * (256 * HD / 4),
+                                  row * (HD / 4) + d4, static_cast<long>(r.Hkv) * (256 * HD / 4), n_parts);
+        reinterpret_cast<u32x2*>(r.dq + ((sp.t0 + i) * r.Hq + qb.h) * HD)[d4] = pack4(a);
+        return;
+    }
+    id -= r.dq_wgs;
+    const int half = static_cast<int>((r.own_n4 + 255) / 256), which = id >= half;
+    const long i = static_cast<long>(id - which * half) * 256 + threadIdx.x;
+    if (i >= r.own_n4) return;
+    reinterpret_cast<u32x2*>(r.own[which])[i] =
+        pack4(sum_parts(reinterpret_cast<const f32x4*>(r.own_part[which]), i, r.own_n4, r.own_parts));
 }
 
 bool attn_mfma_bwd_supported(const cart_attn_desc& d) { return d.dtype == CART_BF16 && d.D == 128; }
 
 // the fused dK + dV kernel (attn_mfma_bwd_kv.hip)
-int bwd_kv_chunk(const cart_attn_desc& d, long tokens, int* n_part);
+KvPlan plan_bwd_kv(const cart_attn_desc& d, long tokens);
 void launch_attn_bwd_kv(const cart_attn_desc& d, float scale, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
                         const bf16_t* ZK, const bf16_t* ZV, const bf16_t* DO, const float* lse2, const float* delta,
-                        bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, const int32_t* cu, int n_tok, int chunk,
-                        int n_part, hipStream_t st);
+                        bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, float* own_k, float* own_v, const int32_t* cu,
+                        int n_tok, const KvPlan& plan, hipStream_t st);
+// the split of the query blocks (attn_mfma_fwd.hip)
+void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, float a, float b);
 
 static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 
-// beyond the delta array: lse2 (one value per token and head) and the two dZ partial buffers
-// [n_part,Hkv,P,128]; packed layout (tokens >= 0 = the packed row count): + the row_lo array.
+// The workspace of a backward call: -delta and -lse2 (one value per token and head), the dZ partials
+// [n_part,Hkv,P,128] for keys and values, the partials of split query blocks and of own keys with
+// split heads; packed layout: + the row_lo array.
+struct BwdLayout {
+    KvPlan kv;
+    QuerySplit split;
+    size_t rows, part, dq, own, row_lo;
+    size_t total() const { return 2 * rows + 2 * part + dq + 2 * own + row_lo; }
+};
+static void bwd_layout(BwdLayout& w, const cart_attn_desc& d, int T) {
+    const long tokens = T > 0 ? T : static_cast<long>(d.B) * d.S;
+    w.kv = plan_bwd_kv(d, tokens);
+    attn_query_split(w.split, d, T, DQ_BLOCK_US, DQ_TILE_US);
+    w.rows = r256(static_cast<size_t>(tokens) * d.Hq * sizeof(float));
+    w.part = r256(static_cast<size_t>(w.kv.n_part) * d.Hkv * d.P * HD * sizeof(float));
+    w.dq = static_cast<size_t>(w.split.n_parts) * d.Hkv * PART_O_BYTES;
+    w.own = w.kv.head_parts > 1 ? r256(static_cast<size_t>(w.kv.head_parts) * tokens * d.Hkv * HD * sizeof(float)) : 0;
+    w.row_lo = T > 0 ? r256(static_cast<size_t>(T) * sizeof(int32_t)) : 0;
+}
 size_t attn_mfma_bwd_workspace(const cart_attn_desc& d, long tokens) {
-    const bool packed = tokens >= 0;
-    if (!packed) tokens = static_cast<long>(d.B) * d.S;
-    int n_part;
-    bwd_kv_chunk(d, tokens, &n_part);
-    const size_t rows = r256(static_cast<size_t>(tokens) * d.Hq * sizeof(float));
-    const size_t part = r256(static_cast<size_t>(n_part) * d.Hkv * d.P * HD * sizeof(float));
-    return rows + 2 * part + (packed ? r256(static_cast<size_t>(tokens) * sizeof(int32_t)) : 0);
+    BwdLayout w;
+    bwd_layout(w, d, tokens >= 0 ? static_cast<int>(tokens) : 0);
+    return w.total() - w.rows;      // (beyond the delta array)
 }
 
 int launch_attn_bwd_mfma(const cart_attn_desc& d, float scale, const void* q, const void* k,
                          const void* v, const void* zk, const void* zv, const void* o,
                          const float* lse, const void* d_o, void* dq, void* dk, void* dv,
                          float* dzk, float* dzv, void* ws, hipStream_t st, const int32_t* cu, int T) {
-    const long tokens = cu ? T : static_cast<long>(d.B) * d.S;
-    const size_t rows_b = r256(static_cast<size_t>(tokens) * d.Hq * sizeof(float));
-    int n_part;
-    const int chunk = bwd_kv_chunk(d, tokens, &n_part);
-    const int n_tok = static_cast<int>(tokens);
-    const size_t part_b = r256(static_cast<size_t>(n_part) * d.Hkv * d.P * HD * sizeof(float));
+    if (!cu) T = 0;
+    BwdLayout L;
+    bwd_layout(L, d, T);
+    const int n_tok = T > 0 ? T : d.B * d.S;
     char* w = static_cast<char*>(ws);
-    float* delta = reinterpret_cast<float*>(w);
-    float* lse2 = reinterpret_cast<float*>(w + rows_b);
-    float* part_k = reinterpret_cast<float*>(w + 2 * rows_b);
-    float* part_v = reinterpret_cast<float*>(w + 2 * rows_b + part_b);
-    // packed batch with a prefix: the dQ kernel cuts its query tiles from the packed rows (it sees
+    auto take = [&](size_t bytes) { char* p = w; w += bytes; return p; };
+    float* delta = reinterpret_cast<float*>(take(L.rows));
+    float* lse2 = reinterpret_cast<float*>(take(L.rows));
+    float* part_k = reinterpret_cast<float*>(take(L.part));
+    float* part_v = reinterpret_cast<float*>(take(L.part));
+    float* part_q = reinterpret_cast<float*>(take(L.dq));
+    float* own_k = reinterpret_cast<float*>(take(L.own));
+    float* own_v = reinterpret_cast<float*>(take(L.own));
+    // packed batch with a prefix: the dQ kernel cuts its query blocks from the packed rows (it sees
     // one sequence of T rows and the first row of every row's sequence)
     int32_t* row_lo = nullptr;
     if (cu && d.P > 0) {
-        row_lo = reinterpret_cast<int32_t*>(w + 2 * rows_b + 2 * part_b);
+        row_lo = reinterpret_cast<int32_t*>(take(L.row_lo));
         launch_row_lo(cu, d.B, T, row_lo, st);
     }
+    const int32_t* q_cu = row_lo ? nullptr : cu;
+    const int q_S = row_lo ? n_tok : d.S;
     const bf16_t *Q = static_cast<const bf16_t*>(q), *K = static_cast<const bf16_t*>(k),
                  *V = static_cast<const bf16_t*>(v), *ZK = static_cast<const bf16_t*>(zk),
                  *ZV = static_cast<const bf16_t*>(zv), *DO = static_cast<const bf16_t*>(d_o);
-    const float c = scale * CART_LOG2E;
     const bf16_t* O = static_cast<const bf16_t*>(o);
-    trace_begin(st);   // kernel order: dq (+ row statistics), dk + dv (one kernel), dz reduce (k, v)
-    if (row_lo) {
-        const long nW = query_wgs(T, d.Hq / d.Hkv);
-        hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(static_cast<unsigned>(nW * d.Hkv)), dim3(256), 0, st, Q, K, V, ZK,
-                           ZV, O, DO, lse, lse2, delta, static_cast<bf16_t*>(dq), nullptr, row_lo, n_tok, 1, n_tok,
-                           d.Hq, d.Hkv, d.P, c, scale);
-    } else {
-        const long nW = query_wgs(d.S, d.Hq / d.Hkv);
-        hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(static_cast<unsigned>(nW * d.B * d.Hkv)), dim3(256), 0, st, Q, K, V,
-                           ZK, ZV, O, DO, lse, lse2, delta, static_cast<bf16_t*>(dq), cu, nullptr, n_tok, d.B, d.S,
-                           d.Hq, d.Hkv, d.P, c, scale);
-    }
+    trace_begin(st);   // kernel order: dq (+ row statistics), dk + dv (one kernel), the partials' sums
+    hipLaunchKernelGGL(attn_bwd_dq_kernel, dim3(static_cast<unsigned>(L.split.e_full + L.split.n_parts) * d.Hkv), dim3(256), 0,
+                       st, Q, K, V, ZK, ZV, O, DO, lse, lse2, delta, static_cast<bf16_t*>(dq), q_cu, row_lo, n_tok, q_S,
+                       d.Hq, d.Hkv, d.P, scale * CART_LOG2E, scale, L.split, part_q);
     trace_mark(st);
     launch_attn_bwd_kv(d, scale, Q, K, V, ZK, ZV, DO, lse2, delta, static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv),
-                       part_k, part_v, cu, n_tok, chunk, n_part, st);
+                       part_k, part_v, own_k, own_v, cu, n_tok, L.kv, st);
     trace_mark(st);
-    if (d.P > 0) {
-        const long n4 = static_cast<long>(d.Hkv) * d.P * HD / 4;
-        const unsigned rg = static_cast<unsigned>((n4 + 255) / 256);
-        hipLaunchKernelGGL(dz_reduce_kernel, dim3(rg), dim3(256), 0, st, part_k, dzk, n_part, n4, d.P, d.n_frozen, d.dz_accumulate);
-        hipLaunchKernelGGL(dz_reduce_kernel, dim3(rg), dim3(256), 0, st, part_v, dzv, n_part, n4, d.P, d.n_frozen, d.dz_accumulate);
+    BwdReduce r;
+    r.dz_part[0] = part_k; r.dz_part[1] = part_v; r.dq_part = part_q; r.own_part[0] = own_k; r.own_part[1] = own_v;
+    r.dz[0] = dzk; r.dz[1] = dzv; r.dq = static_cast<bf16_t*>(dq);
+    r.own[0] = static_cast<bf16_t*>(dk); r.own[1] = static_cast<bf16_t*>(dv);
+    r.dz_n4 = static_cast<long>(d.Hkv) * d.P * HD / 4;
+    r.own_n4 = static_cast<long>(n_tok) * d.Hkv * HD / 4;
+    r.dz_parts = L.kv.n_part; r.own_parts = L.kv.head_parts;
+    r.dz_wgs = static_cast<int>((r.dz_n4 + 255) / 256) * 2;
+    r.dq_wgs = L.split.n_blocks * d.Hkv * 32;
+    r.P = d.P; r.n_frozen = d.n_frozen; r.accumulate = d.dz_accumulate;
+    r.cu = q_cu; r.n_tok = n_tok; r.Smax = q_S; r.Hq = d.Hq; r.Hkv = d.Hkv;
+    const long own_wgs = L.kv.head_parts > 1 ? (r.own_n4 + 255) / 256 * 2 : 0;
+    const long wgs = r.dz_wgs + r.dq_wgs + own_wgs;
+    if (wgs > 0) {
+        hipLaunchKernelGGL(attn_bwd_reduce_kernel, dim3(static_cast<unsigned>(wgs)), dim3(256), 0, st, r, L.split);
         trace_mark(st);
     }
     return static_cast<int>(hipGetLastError());

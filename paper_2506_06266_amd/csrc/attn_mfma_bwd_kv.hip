@@ -31,10 +31,7 @@ constexpr int KV_BUF_B = 2 * KV_TILE_B;           // one buffer: Q tile, dO tile
 constexpr int KV_G_OFF = KV_TILE_B;               // dO tile inside a buffer
 constexpr int KV_WG_KEYS = 128;                   // keys per workgroup: two pairs of wavefronts x 64
 constexpr int KV_SLOT_B = 4096;                   // P of one sub-tile for 64 keys: 4 fragments x 64 lanes x 16 B
-#ifndef KV_PREFIX_WGS
-#define KV_PREFIX_WGS 512                         // prefix workgroups aimed at when the token rows are cut into chunks
-#endif
-constexpr int KV_MIN_CHUNK = 2048;
+constexpr int KV_MIN_CHUNK = 128;                 // fewest token rows per dZ partial
 
 struct KvSmem {
     struct { char q[KV_TILE_B]; char g[KV_TILE_B]; } t[KV_NBUF];
@@ -54,28 +51,6 @@ __shared__ KvSmem kv_sm;
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 __device__ __forceinline__ void lds_wait0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ void kv_store_f32(const f32x16 (&acc)[4], float* row_ptr, int lg, float mul) {
-    if (!row_ptr) return;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            f32x4 w = {acc[db][4 * r4] * mul, acc[db][4 * r4 + 1] * mul, acc[db][4 * r4 + 2] * mul, acc[db][4 * r4 + 3] * mul};
-            *reinterpret_cast<f32x4*>(row_ptr + 32 * db + 8 * r4 + 4 * lg) = w;
-        }
-}
-__device__ __forceinline__ void kv_store_bf16(const f32x16 (&acc)[4], bf16_t* row_ptr, int lg, float mul) {
-    if (!row_ptr) return;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4) {
-            u32x2 w = {pack_bf16x2(acc[db][4 * r4] * mul, acc[db][4 * r4 + 1] * mul),
-                       pack_bf16x2(acc[db][4 * r4 + 2] * mul, acc[db][4 * r4 + 3] * mul)};
-            *reinterpret_cast<u32x2*>(row_ptr + 32 * db + 8 * r4 + 4 * lg) = w;
-        }
-}
-
 // The kernel's arguments.  The role functions are real calls, and a call passes its arguments in
 // vector registers; they get one pointer -- the kernel-argument segment, taken in the kernel itself
 // (the builtin that returns it is only meaningful there: inside a called function it yields a null
@@ -85,9 +60,10 @@ struct KvArgs {
     const bf16_t *q, *k, *v, *zk, *zv, *d_o;
     const float *nlse2, *ndelta;
     bf16_t *dk_own, *dv_own;
-    float *part_k, *part_v;
+    float *part_k, *part_v;             // dZ partials, one per chunk of token rows
+    float *own_k, *own_v;               // partials of own keys, one per part of the heads (head_parts > 1)
     const int32_t* cu;
-    int n_tok, chunk, B, Smax, Hq, Hkv, P;
+    int n_tok, chunk, head_parts, Smax, Hq, Hkv, P;
     float c, scale;
 };
 
@@ -113,11 +89,11 @@ __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
     KvSmem& sm = kv_sm;
     const int G = Hq / Hkv;
     const int nPb = (P + KV_WG_KEYS - 1) / KV_WG_KEYS, nOb = (Smax + KV_WG_KEYS - 1) / KV_WG_KEYS;
-    // workgroup -> (KV head, key block, chunk of token rows | sequence): KV head fastest; the
-    // prefix blocks (long streams: every token row of a chunk, all G heads) first
+    // workgroup -> (KV head, key block, chunk of token rows | sequence and part of the heads): KV head
+    // fastest; the prefix blocks (long streams: every token row of a chunk, all G heads) first
     int id = blockIdx.x;
     const int hk = id % Hkv; id /= Hkv;
-    int kb_, b_;
+    int kb_, b_, g0 = 0, g1 = G;
     SeqSpan sp;
     const int nChunk = (n_tok + chunk - 1) / chunk;
     if (id < nPb * nChunk) {
@@ -128,8 +104,10 @@ __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
         sp.stat_b = sp.stat_h = 0;
     } else {
         id -= nPb * nChunk;
-        kb_ = nPb + id % nOb;
-        b_ = id / nOb;
+        kb_ = nPb + id % nOb; id /= nOb;
+        b_ = id / a.head_parts;
+        g0 = (id % a.head_parts) * (G / a.head_parts);
+        g1 = g0 + G / a.head_parts;
         sp = seq_span(cu, b_, n_tok, Smax, Hq);
     }
     const int kb = kb_, b = b_;      // for a prefix block b is the chunk
@@ -182,7 +160,7 @@ __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
     const int nFull = max(0, nFullEnd - qtF0);
     const int nM1 = min(qtF0, nQtAll) - qt0;
     const int nM = nM1 + ((nFullEnd < nQtAll && nFullEnd >= qtF0) ? 1 : 0);
-    const int nMain = G * nFull, nT = G * (nFull + nM);
+    const int nG = g1 - g0, nMain = nG * nFull, nT = nG * (nFull + nM);
     const char* q_c = reinterpret_cast<const char*>(q);
     const char* g_c = reinterpret_cast<const char*>(d_o);
     const uint32_t q_pitch = static_cast<uint32_t>(Hq) * ROW_B;
@@ -191,7 +169,7 @@ __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
     const uint32_t dma_c0 = (lane & 15) ^ (((lane >> 4) & 3) << 2);
     auto next_tile = [&](int buf) __attribute__((always_inline)) {
         const int qt = it_ph == 0 ? qtF0 + it_n : (it_n < nM1 ? qt0 + it_n : nFullEnd);
-        const int h = hk * G + it_g;
+        const int h = hk * G + g0 + it_g;
         TileSrc ts;
         ts.i0 = qt * KV_TILE;
         const size_t base = (t0 * Hq + h) * ROW_B + static_cast<size_t>(ts.i0) * q_pitch;
@@ -207,7 +185,7 @@ __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
             ++it_n;
             if (it_n == (it_ph == 0 ? nFull : nM)) {
                 it_n = 0;
-                if (++it_g == G) { it_g = 0; ++it_ph; }
+                if (++it_g == nG) { it_g = 0; ++it_ph; }
             }
         }
         return ts;
@@ -231,6 +209,24 @@ __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
     const uint32_t fwd = static_cast<uint32_t>(KV_BUF_B), back = static_cast<uint32_t>(-(KV_NBUF - 1) * KV_BUF_B);
     const uint32_t rfwd = static_cast<uint32_t>(KV_TILE * 4), rback = static_cast<uint32_t>(-(KV_NBUF - 1) * KV_TILE * 4);
     const uint32_t slot0 = lds_addr(sm.slot[pair][0]) + lane * 16;     // fragment f of parity s: + s * SLOT_B + f * 1024
+
+    // The wavefront's 64 rows of dV (A) or dK (B), turned around in LDS (32 KB each, the tile buffers)
+    // once every wavefront is done with them; A waits for its direct-to-LDS loads first.
+    auto kv_store = [&]() __attribute__((always_inline)) {
+        __syncthreads();
+        char* const turn = reinterpret_cast<char*>(&sm.t[wv]);
+        const float mul = roleB ? scale : 1.f;
+        float* const part = roleB ? part_k : part_v;
+        float* const own_part = roleB ? a.own_k : a.own_v;
+        bf16_t* const own = roleB ? dk_own : dv_own;
+        if (pre)
+            store_rows64(turn, acc, mul, mul, part + ((static_cast<size_t>(b) * Hkv + hk) * P + wkey0) * HD, HD, P - wkey0, lane);
+        else if (a.head_parts > 1)
+            store_rows64(turn, acc, mul, mul, own_part + ((static_cast<size_t>(g0 / nG) * n_tok + t0 + wkey0) * Hkv + hk) * HD,
+                         static_cast<size_t>(Hkv) * HD, S - wkey0, lane);
+        else
+            store_rows64(turn, acc, mul, mul, own + ((t0 + wkey0) * Hkv + hk) * HD, static_cast<size_t>(Hkv) * HD, S - wkey0, lane);
+    };
 
     if constexpr (!roleB) {
         // =========================================================================================
@@ -415,15 +411,8 @@ __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
                     acc[db][1] = mma(tf, __builtin_bit_cast(bf16x8, xf[1][ks]), acc[db][1]);
                 }
         }
-#pragma unroll
-        for (int kc = 0; kc < 2; ++kc) {
-            const int key = wkey0 + 32 * kc + lc;
-            f32x16 col[4] = {acc[0][kc], acc[1][kc], acc[2][kc], acc[3][kc]};
-            if (pre)
-                kv_store_f32(col, key < P ? part_v + ((static_cast<size_t>(b) * Hkv + hk) * P + key) * HD : nullptr, lg, 1.f);
-            else
-                kv_store_bf16(col, key < S ? dv_own + ((t0 + key) * Hkv + hk) * HD : nullptr, lg, 1.f);
-        }
+        dma_wait();
+        kv_store();
     } else {
         // =========================================================================================
         // B: dP, dS, dK, one sub-tile behind A.  Iteration u: on entry yin = dP(u-1) - delta,
@@ -594,15 +583,7 @@ __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
                     acc[db][1] = mma(ta[4 * ks + db], __builtin_bit_cast(bf16x8, xf[1][ks]), acc[db][1]);
                 }
         }
-#pragma unroll
-        for (int kc = 0; kc < 2; ++kc) {
-            const int key = wkey0 + 32 * kc + lc;
-            f32x16 col[4] = {acc[0][kc], acc[1][kc], acc[2][kc], acc[3][kc]};
-            if (pre)
-                kv_store_f32(col, key < P ? part_k + ((static_cast<size_t>(b) * Hkv + hk) * P + key) * HD : nullptr, lg, scale);
-            else
-                kv_store_bf16(col, key < S ? dk_own + ((t0 + key) * Hkv + hk) * HD : nullptr, lg, scale);
-        }
+        kv_store();
     }
 }
 
@@ -617,27 +598,108 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_kernel(KvArgs args) {
     else                                                      kv_role<false>(ap);
 }
 
-// token rows per prefix-gradient partial, and the number of partials
-int bwd_kv_chunk(const cart_attn_desc& d, long tokens, int* n_part) {
-    const long nPb = (d.P + KV_WG_KEYS - 1) / KV_WG_KEYS;
-    long n = nPb > 0 ? (KV_PREFIX_WGS + nPb * d.Hkv - 1) / (nPb * d.Hkv) : 1;
-    const long most = (tokens + KV_MIN_CHUNK - 1) / KV_MIN_CHUNK;
-    n = n < 1 ? 1 : (n > most ? most : n);
-    const long chunk = (((tokens + n - 1) / n) + KV_TILE - 1) / KV_TILE * KV_TILE;
-    *n_part = static_cast<int>((tokens + chunk - 1) / chunk);
-    return static_cast<int>(chunk);
+// How the key-stationary launch is cut: token rows per dZ partial (prefix blocks stream chunks of the
+// token rows, every head of the group), parts of the heads for own-key blocks (they stream the rows from
+// their first key on).  The cheapest by playing each cut through, one KV head's workgroups on its
+// share of the CUs, in launch order: a workgroup costs KV_BLOCK_US and, per 64 query rows, 1.4 us
+// while most of the chip idles and 1.8 us when it is full (the clock follows the load); partials cost
+// their way through memory.  Measured, a whole backward call (us), chunks n / parts of the heads h:
+//   B 1  S 700  32 / 8 heads P 1000   n1/h1 117  n2/h1 122  n2/h2  96  n3/h2 113
+//   B 4  S 200   8 / 2 heads P 300    n1/h1 107  n4/h1  65  n8/h2  55  n12/h4 53
+//   B 16 S 256  32 / 8 heads P 1024   n1/h1 465  n2/h1 308  n3/h1 281  n4/h1 296
+//   B 2  S 1024 32 / 8 heads P 2048   n1/h1 308  n2/h1 342  n3/h1 327  n1/h2 314
+//   B 1  S 2048 32 / 8 heads P 8192   n1/h1 992  n1/h2 925  n2/h1 1043
+//   B 3  S 1659 32 / 8 heads P 723    n1/h1 616  n2/h1 459  n3/h1 512  n6/h1 473
+constexpr float KV_BLOCK_US = 10.f, KV_LIGHT_US = 1.4f, KV_FULL_US = 1.8f, KV_US_PER_MB = 0.6f;
+constexpr int KV_MAX_CUS = 256;
+
+static KvPlan search_plan(const cart_attn_desc& d, long tokens, int cus) {
+    const int G = d.Hq / d.Hkv, nT = (d.S + KV_TILE - 1) / KV_TILE;
+    const int nPb = (d.P + KV_WG_KEYS - 1) / KV_WG_KEYS, nOb = (d.S + KV_WG_KEYS - 1) / KV_WG_KEYS;
+    int M = cus / d.Hkv;
+    M = M < 1 ? 1 : (M > KV_MAX_CUS ? KV_MAX_CUS : M);
+    KvPlan best = {};
+    float best_t = 0.f;
+    for (int hp = 1; hp <= G; ++hp) {
+        if (G % hp) continue;
+        const long n_own = static_cast<long>(nOb) * d.B * hp;
+        if (hp > 1 && n_own > 4L * M) break;            // (plenty of own-key workgroups as it is)
+        int last = 0;
+        for (int n = 1; n <= 32; n += 1 + n / 8) {
+            KvPlan p;
+            p.chunk = static_cast<int>((((tokens + n - 1) / n) + KV_TILE - 1) / KV_TILE * KV_TILE);
+            p.n_part = static_cast<int>((tokens + p.chunk - 1) / p.chunk);
+            p.head_parts = hp;
+            if (p.n_part == last || (n > 1 && p.chunk < KV_MIN_CHUNK)) break;
+            last = p.n_part;
+            const long n_pre = static_cast<long>(nPb) * p.n_part;
+            const bool full_pre = 4 * n_pre >= 3L * M, full_own = 4 * n_own >= 3L * M;
+            const float bp = full_pre ? KV_FULL_US : (4 * (n_pre + n_own) >= 3L * M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);
+            const float bo = full_own ? KV_FULL_US : (n_pre % M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);
+            const float pre = KV_BLOCK_US + bp * static_cast<float>(p.chunk / KV_TILE * G);
+            auto own = [&](int kb) { return KV_BLOCK_US + bo * static_cast<float>((nT - 2 * kb) * (G / hp)); };
+            const long q = n_pre / M, r = n_pre % M;
+            float end = pre * static_cast<float>(q + (r ? 1 : 0));
+            if (n_own > 512) {
+                float sum = pre * static_cast<float>(n_pre);
+                for (int kb = 0; kb < nOb; ++kb) sum += own(kb) * static_cast<float>(d.B * hp);
+                const float even = sum / static_cast<float>(M) + 0.5f * own(0);
+                end = even > end ? even : end;
+            } else {
+                float cu[KV_MAX_CUS];                   // a heap of the times at which the CUs are free
+                for (int m = 0; m < M; ++m) cu[m] = pre * static_cast<float>(q + (m >= M - static_cast<int>(r) ? 1 : 0));
+                for (long j = 0; j < n_own; ++j) {
+                    const float t = cu[0] + own(static_cast<int>(j % nOb));
+                    end = t > end ? t : end;
+                    int m = 0;
+                    for (;;) {
+                        int c = 2 * m + 1;
+                        if (c >= M) break;
+                        if (c + 1 < M && cu[c + 1] < cu[c]) ++c;
+                        if (cu[c] >= t) break;
+                        cu[m] = cu[c];
+                        m = c;
+                    }
+                    cu[m] = t;
+                }
+            }
+            end += KV_US_PER_MB * 1e-6f * 2.f * HD * 4.f * static_cast<float>(d.Hkv) *
+                   (static_cast<float>(p.n_part) * d.P + (hp > 1 ? static_cast<float>(hp) * tokens : 0.f));
+            if (best.chunk == 0 || end < best_t) {
+                best_t = end;
+                best = p;
+            }
+            if (d.P == 0) break;
+        }
+    }
+    return best;
+}
+
+KvPlan plan_bwd_kv(const cart_attn_desc& d, long tokens) {
+    // (a call asks twice, for the workspace and for the launch: the thread's last plan is kept with the
+    // sizes it depends on)
+    struct Key { long tokens; int B, S, Hq, Hkv, P, cus; };
+    static thread_local Key key;
+    static thread_local KvPlan plan;
+    const Key k = {tokens, d.B, d.S, d.Hq, d.Hkv, d.P, device_cus()};
+    if (plan.chunk == 0 || key.tokens != k.tokens || key.B != k.B || key.S != k.S || key.Hq != k.Hq || key.Hkv != k.Hkv ||
+        key.P != k.P || key.cus != k.cus) {
+        plan = search_plan(d, tokens, k.cus);
+        key = k;
+    }
+    return plan;
 }
 
 void launch_attn_bwd_kv(const cart_attn_desc& d, float scale, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
                         const bf16_t* ZK, const bf16_t* ZV, const bf16_t* DO, const float* lse2, const float* delta,
-                        bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, const int32_t* cu, int n_tok, int chunk,
-                        int n_part, hipStream_t st) {
+                        bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, float* own_k, float* own_v, const int32_t* cu,
+                        int n_tok, const KvPlan& plan, hipStream_t st) {
     const long nPb = (d.P + KV_WG_KEYS - 1) / KV_WG_KEYS, nOb = (d.S + KV_WG_KEYS - 1) / KV_WG_KEYS;
-    const unsigned grid = static_cast<unsigned>((nPb * n_part + nOb * d.B) * d.Hkv);
+    const unsigned grid = static_cast<unsigned>((nPb * plan.n_part + nOb * d.B * plan.head_parts) * d.Hkv);
     KvArgs a;
     a.q = Q; a.k = K; a.v = V; a.zk = ZK; a.zv = ZV; a.d_o = DO; a.nlse2 = lse2; a.ndelta = delta;
-    a.dk_own = dk; a.dv_own = dv; a.part_k = part_k; a.part_v = part_v; a.cu = cu;
-    a.n_tok = n_tok; a.chunk = chunk; a.B = d.B; a.Smax = d.S; a.Hq = d.Hq; a.Hkv = d.Hkv; a.P = d.P;
+    a.dk_own = dk; a.dv_own = dv; a.part_k = part_k; a.part_v = part_v; a.own_k = own_k; a.own_v = own_v; a.cu = cu;
+    a.n_tok = n_tok; a.chunk = plan.chunk; a.head_parts = plan.head_parts; a.Smax = d.S; a.Hq = d.Hq; a.Hkv = d.Hkv; a.P = d.P;
     a.c = scale * CART_LOG2E; a.scale = scale;
     hipLaunchKernelGGL(attn_bwd_kv_kernel, dim3(grid), dim3(256), 0, st, a);
 }

@@ -14,7 +14,7 @@
 // running max and the O accumulators are never rescaled.  exp2 and the fp32 accumulators cover
 // 2^+-126 around that reference, so this is exact unless a later score exceeds the first
 // sub-tile's maximum by more than ~80 in natural-log units; then the row sum overflows to
-// inf/NaN, the workgroup raises a flag, and attn_fwd_repair_kernel recomputes that block of rows
+// inf/NaN, the workgroup raises a flag, and attn_fwd_finish_kernel recomputes that block of rows
 // with a plain running-max loop.  The hot loop is one straight-line block per sub-tile with two
 // independent instruction streams: the matrix cores work on S(u+1) and on O += V P(u-1) while the
 // vector ALU turns S(u) into P(u).
@@ -28,6 +28,7 @@ using namespace mfma;
 constexpr int FWD_BN = 64;    // keys per LDS tile, consumed as two sub-tiles of 32
 constexpr int FWD_NBUF = 4;     // tile t in buffer t % 4; loads run two tiles ahead of the barrier that publishes them
 constexpr int FWD_TILE_B = FWD_BN * ROW_B;
+constexpr float FWD_BLOCK_US = 10.f, FWD_TILE_US = 1.4f;   // a block's time: set-up and store, each key tile
 
 struct FwdSmem {
     char k[FWD_NBUF][FWD_TILE_B];
@@ -46,13 +47,12 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ zk, const bf16_t* __restrict__ zv, bf16_t* __restrict__ o,
     float* __restrict__ lse, int* __restrict__ flags, const int32_t* __restrict__ cu,
-    const int32_t* __restrict__ row_lo, int n_tok, int B, int Smax, int Hq, int Hkv, int P,
-    float c /* scale*log2(e) */) {
+    const int32_t* __restrict__ row_lo, int n_tok, int Smax, int Hq, int Hkv, int P,
+    float c /* scale*log2(e) */, QuerySplit split, float* __restrict__ part_o, float* __restrict__ part_l) {
     __shared__ FwdSmem sm;
-    __shared__ int sm_bad;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, in a scalar register
-    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv);
+    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv, split);
     const int hk = qb.hk, b = qb.b, h = qb.h, q0 = qb.q0, wrow0 = qb.wrow0;
     // Rows of sequence b: [t0, t0 + S).  Batched layout: S rows each; packed layout (cu given):
     // rows cu[b] .. cu[b+1]-1 of T, the grid is sized for the longest sequence and a workgroup
@@ -64,11 +64,16 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     const int S = sp.len;
     const size_t t0 = sp.t0;
     if (q0 >= S) {
-        if (threadIdx.x == 0) flags[blockIdx.x] = 0;
+        if (lane == 0) flags[4 * blockIdx.x + wv] = 0;
         return;
     }
-    if (threadIdx.x == 0) sm_bad = 0;
-
+    const KeyTiles kt = key_tiles(qb, S, P, row_lo);
+    float* const my_l = part_l + static_cast<size_t>(qb.slot) * 256 + 64 * wv;
+    if (kt.lo >= kt.hi) {      // (fewer tiles than the launch assumed: this part is empty)
+        if (lane == 0) flags[4 * blockIdx.x + wv] = 0;
+        my_l[lane] = __uint_as_float(0xff800000u);
+        return;
+    }
     // this wavefront's 64 queries as B-operand fragments: column = query, k = head element
     // They are pinned to accumulation registers (the matrix cores read B operands from there
     // directly), which leaves the ordinary vector registers to the softmax arithmetic.
@@ -114,35 +119,16 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     };
     pin();
 
-    // Tile order.  The softmax reference is fixed, so key tiles may come in any order: first every
-    // tile all of whose keys are visible to all 256 queries (whole prefix tiles, own tiles below
-    // the first query), through a loop without masking code; then the ragged last prefix tile and
-    // the own tiles on the diagonal, through a copy of the loop that masks.
-    const int nPf = P / FWD_BN;                        // whole prefix tiles
-    const int rag = (P % FWD_BN) ? 1 : 0;              // ragged prefix tile
-    const int own_end = min(S, qb.q_end);
-    // own tiles (of 64 rows from row 0): every query of the workgroup sees the whole of tiles
-    // tU0 .. tD-1; tiles tA .. min(tU0, tD)-1 start before the first key of some query and tiles
-    // tD .. tEnd-1 lie on the diagonal (one sequence: tA = tU0 = 0)
-    const int lo_first = row_lo ? row_lo[q0] : 0, lo_last = row_lo ? row_lo[own_end - 1] : 0;
-    const int tA = lo_first / FWD_BN, tU0 = (lo_last + FWD_BN - 1) / FWD_BN, tD = q0 / FWD_BN;
-    const int nOf = max(0, tD - tU0);
-    const int nLow = min(tU0, tD) - tA;
-    const int nMain = nPf + nOf;
-    const int nT = nMain + rag + nLow + (own_end + FWD_BN - 1) / FWD_BN - tD;
+    // The softmax reference is fixed, so key tiles may come in any order: the unmasked ones (see
+    // KeyTiles) run through a loop without masking code, the others through a copy that masks.
+    const int nMain = kt.nMain, nT = kt.hi;
     const char* zk_b = reinterpret_cast<const char*>(zk) + static_cast<size_t>(hk) * P * ROW_B;
     const char* zv_b = reinterpret_cast<const char*>(zv) + static_cast<size_t>(hk) * P * ROW_B;
     const uint32_t own_pitch = static_cast<uint32_t>(Hkv) * ROW_B;
     const char* k_b = reinterpret_cast<const char*>(k) + (t0 * Hkv + hk) * ROW_B;
     const char* v_b = reinterpret_cast<const char*>(v) + (t0 * Hkv + hk) * ROW_B;
-    // tile t of that order: prefix or own, first key (all scalar)
-    auto tile_pre = [&](int t) __attribute__((always_inline)) {
-        return t < nPf || (rag && t == nMain);
-    };
-    auto tile_j0 = [&](int t) __attribute__((always_inline)) {
-        const int m = t - nMain - rag;      // among the masked own tiles
-        return (t < nPf ? t : t < nMain ? tU0 + t - nPf : (rag && t == nMain) ? nPf : m < nLow ? tA + m : tD + m - nLow) * FWD_BN;
-    };
+    auto tile_pre = [&](int t) __attribute__((always_inline)) { return kt.pre(t); };
+    auto tile_j0 = [&](int t) __attribute__((always_inline)) { return kt.j0(t); };
 
     // Direct-to-LDS load of one tile, eight instructions per wavefront (K rows, then V rows),
     // handed out one per matrix-core instruction by the stage below.
@@ -305,13 +291,13 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
 
     {   // tiles 0 and 1 on their way; scores of sub-tile 0 and the softmax reference of every
         // query: its maximum over that sub-tile (which holds a visible key for every query)
-        const TileSrc t0 = tile_src(0, 0);
+        const TileSrc t0 = tile_src(kt.lo, 0);
 #pragma unroll
         for (int n = 0; n < 8; ++n) dma_piece(t0, n);
-        const TileSrc t1 = tile_src(min(1, nT - 1), 1);
+        const TileSrc t1 = tile_src(min(kt.lo + 1, nT - 1), 1);
 #pragma unroll
         for (int n = 0; n < 8; ++n) dma_piece(t1, n);
-        const TileSrc t2 = tile_src(min(2, nT - 1), 2);
+        const TileSrc t2 = tile_src(min(kt.lo + 2, nT - 1), 2);
 #pragma unroll
         for (int n = 0; n < 8; ++n) dma_piece(t2, n);
         dma_wait_but<16>();
@@ -324,7 +310,7 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
             else         { mma_vd(sa[0], ka[t8], qraw[0][t8]);    mma_vd(sa[1], ka[t8], qraw[1][t8]); }
         }
         settle();
-        mask(sa, tile_pre(0), tile_j0(0));
+        mask(sa, tile_pre(kt.lo), tile_j0(kt.lo));
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
             float tm = sa[cb][0];
@@ -383,8 +369,8 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
         for (int db = 0; db < 4; ++db) { vofs[db][0] += dv; vofs[db][1] += dv; }
         buf = nbuf;
     };
-    for (int t = 0; t < nMain; ++t) tile_iter(t, std::false_type{});
-    for (int t = nMain; t < nT; ++t) tile_iter(t, std::true_type{});
+    for (int t = kt.lo; t < min(nMain, nT); ++t) tile_iter(t, std::false_type{});
+    for (int t = max(kt.lo, nMain); t < nT; ++t) tile_iter(t, std::true_type{});
     {   // drain: O^T += V^T P^T of the last sub-tile (its V fragments are already in registers)
         pin();
 #pragma unroll
@@ -403,54 +389,114 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     float m_ref[2] = {-negm[0], -negm[1]};
 #endif
 
-    // normalise and store: lane holds, for its query, head elements 32db + 8(r/4) + 4g + r%4
-    bool bad = false;
+    // normalise and store, turned around in LDS once nobody reads a tile or has a load in flight
+    dma_wait();
+    __syncthreads();
+    float l_tot[2], inv[2];
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
         const int qi = wrow0 + 32 * cb + lc;
-        const float l_tot = l_run[cb] + partner(l_run[cb]);
-        const float inv = 1.f / l_tot;
-        float chk = 0.f;
-        if (qi < S) {
-            bf16_t* op = o + ((t0 + qi) * Hq + h) * HD;
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int r4 = 0; r4 < 4; ++r4) {
-                    const float o0 = acc[db][cb][4 * r4] * inv, o1 = acc[db][cb][4 * r4 + 1] * inv,
-                                o2 = acc[db][cb][4 * r4 + 2] * inv, o3 = acc[db][cb][4 * r4 + 3] * inv;
-                    chk += (o0 + o1) + (o2 + o3);
-                    u32x2 w = {pack_bf16x2(o0, o1), pack_bf16x2(o2, o3)};
-                    *reinterpret_cast<u32x2*>(op + 32 * db + 8 * r4 + 4 * lg) = w;
-                }
-            if (lg == 0)
-                lse[sp.stat_b + h * sp.stat_h + qi] = (m_ref[cb] + fast_log2(l_tot)) * CART_LN2;
-            // overflow of the fixed-reference softmax shows as a non-finite row sum or output
-            bad |= !(l_tot < 3.0e38f) || !(fabsf(chk) < 3.0e38f);
+        l_tot[cb] = l_run[cb] + partner(l_run[cb]);
+        inv[cb] = 1.f / l_tot[cb];
+        const float row_lse = (m_ref[cb] + fast_log2(l_tot[cb])) * CART_LN2;
+        if (qi < S && lg == 0) {
+            if (qb.n_parts == 1) lse[sp.stat_b + h * sp.stat_h + qi] = row_lse;
+            else                 my_l[32 * cb + lc] = row_lse;
         }
     }
-    if (__any(bad) && lane == 0) sm_bad = 1;
-    __syncthreads();
-    if (threadIdx.x == 0) flags[blockIdx.x] = sm_bad;
+    char* const turn = reinterpret_cast<char*>(&sm) + wv * (2 * FWD_TILE_B);
+    RowSums rs;
+    if (qb.n_parts == 1)
+        rs = store_rows64(turn, acc, inv[0], inv[1], o + ((t0 + wrow0) * Hq + h) * HD, static_cast<size_t>(Hq) * HD, S - wrow0, lane);
+    else
+        rs = store_rows64(turn, acc, inv[0], inv[1], part_o + (static_cast<size_t>(qb.slot) * 256 + 64 * wv) * HD, HD, S - wrow0, lane);
+    // overflow of the fixed-reference softmax shows as a non-finite row sum or output
+    bool bad = false;
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb)
+        bad |= wrow0 + 32 * cb + lc < S && (!(l_tot[cb] < 3.0e38f) || !(fabsf(rs.s[cb]) < 3.0e38f));
+    // (a flag per wavefront: a barrier here would wait for the stores of O, 4-5 us of a block)
+    bad = __any(bad);
+    if (lane == 0) flags[4 * blockIdx.x + wv] = bad ? 1 : 0;
 }
 
-// Recomputes the 256 queries of every flagged workgroup with a running-max loop on the vector
-// ALU (one wavefront per query, lane l owns head elements 2l, 2l+1).  Launched after every
-// forward call; a workgroup whose flag is clear returns at once.
-__global__ __launch_bounds__(256) void attn_fwd_repair_kernel(
+// Finishes the forward call.  Blocks that ran whole (one workgroup each): returns at once unless the
+// block raised its overflow flag.  Split blocks (eight workgroups each, 32 rows apiece): combines the
+// parts by their log-sum-exps.  A flagged block's rows are recomputed with a running-max loop on the
+// vector ALU instead.  One wavefront per row at a time, lane l owns head elements 2l, 2l+1.
+__global__ __launch_bounds__(256) void attn_fwd_finish_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ zk, const bf16_t* __restrict__ zv, bf16_t* __restrict__ o,
     float* __restrict__ lse, const int* __restrict__ flags, const int32_t* __restrict__ cu,
-    const int32_t* __restrict__ row_lo, int n_tok, int B, int Smax, int Hq, int Hkv, int P, float c) {
-    if (flags[blockIdx.x] == 0) return;
+    const int32_t* __restrict__ row_lo, int n_tok, int Smax, int Hq, int Hkv, int P, float c, QuerySplit split,
+    const float* __restrict__ part_o, const float* __restrict__ part_l) {
+    const int G = Hq / Hkv, nW = query_wgs(Smax, G);
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv);
-    const int hk = qb.hk, h = qb.h;
+    const int n_whole = split.e_full * Hkv;
+    int id = blockIdx.x, rows = 64, r0 = 0, n_parts = 1, hk, e, x;      // x: the block's first part among the KV head's items
+    if (id < n_whole) {
+        hk = id % Hkv;
+        e = x = id / Hkv;
+    } else {
+        id -= n_whole;
+        rows = 8;
+        r0 = 8 * (id & 7);
+        id >>= 3;
+        hk = id % Hkv;
+        e = split.e_full + id / Hkv;
+        x = split.e_full + split.first[id / Hkv];
+        n_parts = split.part[x - split.e_full] >> 16;
+    }
+    const QueryBlock qb = query_block_of(hk, e, wv, nW, G);
     const SeqSpan sp = seq_span(cu, qb.b, n_tok, Smax, Hq);
-    const int S = sp.len;
+    const int S = sp.len, h = qb.h, i0 = qb.wrow0 + r0, i1 = min(S, i0 + rows);
     const size_t t0 = sp.t0;
-    for (int i = qb.wrow0; i < min(S, qb.wrow0 + 64); ++i) {
+    int bad = 0;         // of this wavefront's rows
+    for (int p = 0; p < n_parts; ++p) bad |= flags[4 * ((x + p) * Hkv + hk) + wv];
+    if (!bad && n_parts > 1) {
+        // half a wavefront per row, four head elements per lane: two rows per load, eight rows in
+        // flight; the loads of a part do not wait for its LSE (an empty part's are not used)
+        constexpr int R = 4;
+        const int half = lane >> 5, d4 = 4 * (lane & 31);
+        const float ninf = __uint_as_float(0xff800000u);
+        float m[R], l[R];
+        f32x4 a[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) { m[r] = -3.0e38f; l[r] = 0.f; a[r] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+        const size_t row0 = (static_cast<size_t>(x - split.e_full) * Hkv + hk) * 256 + 64 * wv + r0 + half;
+#pragma unroll 2
+        for (int p = 0; p < n_parts; ++p) {
+            const size_t row = row0 + static_cast<size_t>(p) * Hkv * 256;
+            float pl[R];
+            f32x4 po[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                pl[r] = part_l[row + 2 * r];
+                po[r] = *reinterpret_cast<const f32x4*>(part_o + (row + 2 * r) * HD + d4);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const float nm = fmaxf(m[r], pl[r]), corr = __expf(m[r] - nm), w = __expf(pl[r] - nm);
+                l[r] = l[r] * corr + w;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) a[r][e] = a[r][e] * corr + (pl[r] > ninf ? w * po[r][e] : 0.f);
+                m[r] = nm;
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = i0 + 2 * r + half;
+            if (i >= i1) continue;
+            const float inv = 1.f / l[r];
+            u32x2 w = {pack_bf16x2(a[r][0] * inv, a[r][1] * inv), pack_bf16x2(a[r][2] * inv, a[r][3] * inv)};
+            *reinterpret_cast<u32x2*>(o + ((t0 + i) * Hq + h) * HD + d4) = w;
+            if ((lane & 31) == 0) lse[sp.stat_b + h * sp.stat_h + i] = m[r] + __logf(l[r]);
+        }
+        return;
+    }
+    if (!bad) return;
+    for (int i = i0; i < i1; ++i) {
         const size_t row = (t0 + i) * Hq + h;
         const uint32_t qw = *reinterpret_cast<const uint32_t*>(q + row * HD + 2 * lane);
         const float q0 = __uint_as_float(qw << 16), q1 = __uint_as_float(qw & 0xffff0000u);
@@ -492,19 +538,99 @@ int launch_row_lo(const int32_t* cu, int B, int T, int32_t* row_lo, hipStream_t 
     return static_cast<int>(hipGetLastError());
 }
 
+// Whether and how far to split is decided by playing the launch through: blocks go to the CU that is
+// free first, in order.  Splitting costs the finishing kernel's second role and the partials' way
+// through memory (SPLIT_FIX, SPLIT_PER us): measured on one sequence of 128 tokens with 1024 prefix
+// slots (16 blocks of 18 tiles), 16 / 64 / 96 / 160 workgroups -> 31.0 / 24.7 / 26.4 / 30.9 us a
+// forward call; 700 tokens, 1000 slots (88 blocks of 17-27 tiles), 88 / 160 / 192 / 248 workgroups -> 44.4
+// / 43.0 / 40.4 / 38.3; 8 sequences of 512, 24 heads, 4096 slots (384 blocks, 1.5 rounds): the last half
+// round in two parts 209 -> 190.  With many rounds there is little to gain, and blocks of very
+// different lengths (long sequences, short prefix) even each other out: not split.
+constexpr float SPLIT_FIX = 4.f, SPLIT_PER = 0.05f;
+
+void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, float a, float b) {
+    const int nW = query_wgs(S, G);
+    const long n_all = static_cast<long>(B) * nW;
+    int slots = device_cus() / Hkv;                         // blocks per KV head the chip runs at one time
+    slots = slots < 1 ? 1 : (slots > MAX_SPLIT ? MAX_SPLIT : slots);
+    sp.e_full = static_cast<int>(n_all);
+    sp.n_blocks = sp.n_parts = 0;
+    if (n_all > 4L * slots || n_all > 2 * MAX_SPLIT) return;
+    const int n = static_cast<int>(n_all), left = n % slots;       // the blocks left over after whole rounds
+    if (left == 0) return;
+    auto tiles = [&](int e) {
+        const int w = nW - 1 - e % nW, q_end = 64 * ((4 * w + 3) / G) + 64;
+        const int own = ((q_end < S ? q_end : S) + 63) / 64;
+        return (P + 63) / 64 + (own < own_cap ? own : own_cap);
+    };
+    float cu[MAX_SPLIT];                                    // when each CU is free
+    auto run = [&](float* c, float t) {
+        int m = 0;
+        for (int i = 1; i < slots; ++i) m = c[i] < c[m] ? i : m;
+        c[m] += t;
+        return c[m];
+    };
+    for (int i = 0; i < slots; ++i) cu[i] = 0.f;
+    float done = 0.f;                                       // when the whole rounds are done
+    for (int e = 0; e < n - left; ++e) {
+        const float t = run(cu, a + b * tiles(e));
+        done = t > done ? t : done;
+    }
+    int tl[MAX_SPLIT], most = 0;
+    for (int i = 0; i < left; ++i) {
+        tl[i] = tiles(n - left + i);
+        most = tl[i] > most ? tl[i] : most;
+    }
+    int best = 0;                                           // tiles per part, 0: whole
+    float best_t = 0.f;
+    for (int parts = 1; parts <= 32 && parts <= most; ++parts) {
+        const int tps = (most + parts - 1) / parts;
+        int items = 0;
+        for (int i = 0; i < left; ++i) items += (tl[i] + tps - 1) / tps;
+        if (items > slots) break;
+        float c[MAX_SPLIT], end = done;
+        for (int i = 0; i < slots; ++i) c[i] = cu[i];
+        for (int i = 0; i < left; ++i) {
+            const int np = (tl[i] + tps - 1) / tps;
+            for (int p = 0; p < np; ++p) {
+                const float t = n == left ? a + b * ((tl[i] + np - 1) / np) : run(c, a + b * ((tl[i] + np - 1) / np));
+                end = t > end ? t : end;
+            }
+        }
+        if (parts > 1) end += SPLIT_FIX + SPLIT_PER * items * Hkv;
+        if (parts == 1 || end < best_t) {
+            best_t = end;
+            best = parts == 1 ? 0 : tps;
+        }
+    }
+    if (best == 0) return;
+    sp.e_full = n - left;
+    sp.n_blocks = left;
+    for (int i = 0; i < left; ++i) {
+        const uint32_t np = static_cast<uint32_t>((tl[i] + best - 1) / best);
+        sp.first[i] = static_cast<uint32_t>(sp.n_parts);
+        for (uint32_t p = 0; p < np; ++p) sp.part[sp.n_parts++] = static_cast<uint32_t>(i) | p << 8 | np << 16;
+    }
+}
+static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
+
 bool attn_mfma_supported(const cart_attn_desc& d) {
     return d.dtype == CART_BF16 && d.D == 128;
 }
-// workgroups: per sequence, or over the packed rows (a packed batch with a prefix; T > 0)
-static long fwd_grid(const cart_attn_desc& d, int T) {
+// blocks per sequence, or over the packed rows (a packed batch with a prefix; T > 0)
+void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, float a, float b) {
     const int G = d.Hq / d.Hkv;
-    if (T > 0 && d.P > 0) return static_cast<long>(query_wgs(T, G)) * d.Hkv;
-    return static_cast<long>(query_wgs(d.S, G)) * d.B * d.Hkv;
+    if (T > 0 && d.P > 0) plan_query_split(sp, 1, T, G, d.Hkv, d.P, (d.S + 255) / 64 + 2, a, b);
+    else                  plan_query_split(sp, d.B, d.S, G, d.Hkv, d.P, 1 << 30, a, b);
 }
-static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
-// one overflow flag per workgroup; packed batches: + the first row of every row's sequence
+// one overflow flag per wavefront; packed batches: + the first row of every row's sequence; + the
+// partial results of the split blocks
 size_t attn_mfma_fwd_workspace(const cart_attn_desc& d, int T) {
-    return r256(static_cast<size_t>(fwd_grid(d, T)) * sizeof(int)) + (T > 0 ? r256(static_cast<size_t>(T) * sizeof(int32_t)) : 0);
+    QuerySplit sp;
+    attn_query_split(sp, d, T, FWD_BLOCK_US, FWD_TILE_US);
+    return r256(static_cast<size_t>(sp.e_full + sp.n_parts) * d.Hkv * 4 * sizeof(int)) +
+           (T > 0 ? r256(static_cast<size_t>(T) * sizeof(int32_t)) : 0) +
+           static_cast<size_t>(sp.n_parts) * d.Hkv * (PART_O_BYTES + PART_L_BYTES);
 }
 
 // cu == nullptr: batched layout [B,S,...].  Otherwise the packed layout: d.S is the longest
@@ -513,26 +639,37 @@ int launch_attn_fwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
                          const void* v, const void* zk, const void* zv, void* o, float* lse,
                          void* ws, hipStream_t st, const int32_t* cu, int T) {
     if (!cu) T = 0;
-    const unsigned grid = static_cast<unsigned>(fwd_grid(d, T));
-    int* flags = static_cast<int*>(ws);
+    QuerySplit sp;
+    attn_query_split(sp, d, T, FWD_BLOCK_US, FWD_TILE_US);
+    const size_t slots = static_cast<size_t>(sp.n_parts) * d.Hkv;
+    const unsigned n_items = static_cast<unsigned>(sp.e_full + sp.n_parts) * d.Hkv;
+    char* w = static_cast<char*>(ws);
+    int* flags = reinterpret_cast<int*>(w);
+    w += r256(static_cast<size_t>(n_items) * 4 * sizeof(int));
     int32_t* row_lo = nullptr;
-    int B = d.B, S = d.S;
+    if (T > 0) {
+        if (d.P > 0) row_lo = reinterpret_cast<int32_t*>(w);
+        w += r256(static_cast<size_t>(T) * sizeof(int32_t));
+    }
+    float* part_l = reinterpret_cast<float*>(w);
+    float* part_o = reinterpret_cast<float*>(w + slots * PART_L_BYTES);
+    int S = d.S;
     const bf16_t *Q = static_cast<const bf16_t*>(q), *K = static_cast<const bf16_t*>(k),
                  *V = static_cast<const bf16_t*>(v), *ZK = static_cast<const bf16_t*>(zk),
                  *ZV = static_cast<const bf16_t*>(zv);
-    if (cu && d.P > 0) {   // tiles over the packed rows: the kernels see one sequence of T rows
-        row_lo = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + r256(static_cast<size_t>(grid) * sizeof(int)));
+    if (row_lo) {          // blocks over the packed rows: the kernels see one sequence of T rows
         launch_row_lo(cu, d.B, T, row_lo, st);
         cu = nullptr;
-        B = 1;
         S = T;
     }
-    trace_begin(st);   // kernel order: forward, repair
-    hipLaunchKernelGGL(attn_fwd_mfma_kernel, dim3(grid), dim3(256), 0, st, Q, K, V, ZK, ZV,
-                       static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T, B, S, d.Hq, d.Hkv, d.P, scale * CART_LOG2E);
+    trace_begin(st);   // kernel order: forward, finish
+    hipLaunchKernelGGL(attn_fwd_mfma_kernel, dim3(n_items), dim3(256), 0, st, Q, K, V, ZK, ZV,
+                       static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T, S, d.Hq, d.Hkv, d.P, scale * CART_LOG2E, sp,
+                       part_o, part_l);
     trace_mark(st);
-    hipLaunchKernelGGL(attn_fwd_repair_kernel, dim3(grid), dim3(256), 0, st, Q, K, V, ZK, ZV,
-                       static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T, B, S, d.Hq, d.Hkv, d.P, scale * CART_LOG2E);
+    hipLaunchKernelGGL(attn_fwd_finish_kernel, dim3(static_cast<unsigned>(sp.e_full + 8 * sp.n_blocks) * d.Hkv), dim3(256), 0, st,
+                       Q, K, V, ZK, ZV, static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T, S, d.Hq, d.Hkv, d.P,
+                       scale * CART_LOG2E, sp, part_o, part_l);
     trace_mark(st);
     return static_cast<int>(hipGetLastError());
 }

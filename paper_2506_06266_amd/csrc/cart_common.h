@@ -79,6 +79,8 @@ inline void trace_mark(hipStream_t st) {
     if (t.events && t.next < t.count) hipEventRecord(static_cast<hipEvent_t>(t.events[t.next++]), st);
 }
 
+int device_cus();      // compute units of the current device (looked up once per device)
+
 // ---- internal launchers (host side), one per kernel family; all return hipError_t as int ----
 int launch_kl(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp,
               float* loss, void* d_logits, float* row_kl, void* ws, hipStream_t st);

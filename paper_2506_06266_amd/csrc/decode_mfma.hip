@@ -63,19 +63,6 @@ struct DecodePlan {
     size_t part_o_bytes, part_l_bytes;
 };
 
-// workgroups of 256 threads the chip holds at two per CU (per device, looked up once)
-static int resident_wgs() {
-    static int cached[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 512;
-    if (!cached[dev]) {
-        int cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-        cached[dev] = 2 * cus;
-    }
-    return cached[dev];
-}
-
 // seg_p[n_seg]: slots per shared segment; pool_p: slots of a private cartridge (0 = none);
 // T: rows of the packed own caches
 static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p) {
@@ -107,7 +94,7 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     // each, one wavefront per (range of token rows, KV head); the ranges cut T evenly, in whole
     // steps of 32 rows.
     const int n_pre_wg = p.n_ps > 0 ? p.tab.blk0[p.tab.n_seg] : 0;
-    long wgs = resident_wgs() - n_pre_wg;
+    long wgs = 2L * device_cus() - n_pre_wg;      // (256 threads, two workgroups per CU)
     if (wgs < 64) wgs = 64;
     long ranges = 4 * wgs / Hkv;
     if (ranges < 1) { ranges = 1; wgs = (Hkv + 3) / 4; }

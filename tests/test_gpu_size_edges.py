@@ -62,6 +62,33 @@ def test_attention_query_blocks(B, S, Hq, Hkv, P):
     check_attn(*attn_case((B, S), Hq, Hkv, 128, P, torch.bfloat16, 31 * S + Hq), impl=cb.IMPL_MFMA)
 
 
+
+# Small launches: query blocks split along their key tiles (forward, dQ), the key-stationary kernel cut
+# into chunks of token rows and parts of the heads.  Many short parts, parts with a ragged prefix tile
+# or nothing but masked tiles, blocks of one part among split ones, no prefix, one token block, a
+# split last round after a whole one (the last shape: 36 blocks of one KV head's 32).
+@pytest.mark.parametrize("B,S,Hq,Hkv,P", [(1, 300, 4, 1, 700), (1, 700, 8, 2, 0), (2, 500, 3, 1, 129), (1, 64, 2, 2, 2000),
+                                          (1, 65, 1, 1, 63), (1, 1000, 4, 1, 5), (1, 129, 8, 1, 1024), (9, 250, 32, 8, 321)])
+def test_attention_small_launches(B, S, Hq, Hkv, P):
+    check_attn(*attn_case((B, S), Hq, Hkv, 128, P, torch.bfloat16, 7 * S + P), impl=cb.IMPL_MFMA, n_frozen=min(P, 3))
+
+
+@pytest.mark.parametrize("lens,Hq,Hkv,P", [([700, 1, 90], 4, 1, 300), ([64, 64, 64], 2, 2, 1000), ([5, 3, 400, 131], 4, 2, 0)])
+def test_packed_small_launches(lens, Hq, Hkv, P):
+    q, k, v, zk, zv, do = attn_case((sum(lens),), Hq, Hkv, 128, P, torch.bfloat16, sum(lens) + P)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32)
+    n = [f64(t) for t in (q, k, v, zk, zv, do)]
+    ref = list(orc.attn_varlen_fwd(*n[:5], cu.numpy())) + list(orc.attn_varlen_bwd(*n, cu.numpy()))
+    a = [t.to(DEV) for t in (q, k, v, zk, zv, cu)]
+    if P == 0:
+        a[3] = a[4] = None
+    o, lse = cb.cart_attn_varlen_fwd(*a, max(lens))
+    out = [o, lse] + list(cb.cart_attn_varlen_bwd(*a, max(lens), o, lse, do.to(DEV)))
+    torch.cuda.synchronize()
+    for x, r in list(zip(out, ref))[: 5 if P == 0 else 7]:
+        assert rel_err(x, r) <= TOL[torch.bfloat16]
+
+
 # Loss: every width of the row kernel at its last size and just past it, rows that start at every
 # offset from a 16-byte boundary (odd vocabularies), more records than threads, more rows than the
 # launch has workgroups.  (data type, rows, vocabulary, records)
