@@ -18,6 +18,8 @@
 // per-request cartridges of App. A.3's serving protocol use the same two kernels: the shared
 // prefix is a list of segments, each split and run like a single cartridge (a segment is never
 // copied next to another), and a request's private cartridge is streamed like its own KV.
+#include <math.h>
+
 #include "attn_mfma.h"
 
 namespace cart {
@@ -28,21 +30,15 @@ constexpr int DEC_BN = 32;             // prefix keys per LDS tile
 #ifndef DEC_NBUF
 #define DEC_NBUF 4                     // prefix tiles in LDS: one read, one ready, the rest in flight
 #endif
-// Prefix workgroups aimed at.  Measured on the serving shape (128 requests, 8192 shared slots,
-// own caches U[1,1024]), fused kernel + merge: 96 -> 66.8 + 7.6 us, 128 -> 57.7 + 8.0, 160 ->
-// 59.3 + 8.8, 192 -> 53.0 + 9.0, 256 -> 60.8 + 10.0.  The prefix workgroups and the own-KV
-// workgroups that share their CUs are the last to finish; more, shorter prefix workgroups end
-// closer to the rest, until their extra partials cost more in the merge.
-constexpr int DEC_PREFIX_WGS = 192;
 constexpr int DEC_TILE_B = DEC_BN * ROW_B;
 constexpr int DEC_SUB = 32;            // own keys per wavefront step
 constexpr int DEC_SUB_B = DEC_SUB * ROW_B;
 
-#ifndef DEC_POOL_CHUNK
-#define DEC_POOL_CHUNK 256             // fewest keys per chunk of a private cartridge
-#endif
-constexpr int DEC_MIN_SHARE = 256;      // fewest token rows per own-KV range (a multiple of DEC_SUB)
+constexpr int DEC_MIN_SHARE = 64;       // fewest rows per streamed range (a multiple of DEC_SUB)
+constexpr int DEC_MAX_PARTS = 64;       // most ranges the longest request's own rows are cut into
+constexpr int DEC_FEW_ROWS = 2048;      // output rows up to which the merge takes four wavefronts a row
 constexpr int DEC_MAX_SEG = CART_MAX_SEGMENTS;
+constexpr size_t DEC_STATIC_BYTES = static_cast<size_t>(32) << 20;   // the library's own scratch array (cart_decode_static)
 
 // The shared prefix as a list of segments (one for a single cartridge), by value in the kernel
 // arguments.  Segment s is split along its slots into n_ps[s] parts of tiles_per_split[s] tiles;
@@ -58,23 +54,55 @@ struct PrefixTable {
 struct DecodePlan {
     PrefixTable tab;
     int G, n_rb, n_ps;                    // prefix: row blocks, partial slots of all segments
-    int chunk, n_cc;                      // private cartridge: keys per chunk, chunks
-    int share, n_oc, n_own_wg;            // own KV: token rows per range, most ranges a request reaches into, workgroups
+    // streamed rows (own tokens, then private cartridges): rows per range, most ranges one request's own
+    // rows / private cartridge reach into, first row of the private cartridges, workgroups
+    int share, n_oc, n_cc, n_own_wg;
+    long pool0;
     size_t part_o_bytes, part_l_bytes;
 };
 
 // seg_p[n_seg]: slots per shared segment; pool_p: slots of a private cartridge (0 = none);
 // T: rows of the packed own caches
-static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p) {
+// A plan whose partials exceed the library's own scratch array is made again with as few parts as keep
+// the chip busy (`lean`), so that finer cuts never keep a problem from cart_decode_static.
+static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p,
+                            bool lean = false) {
     DecodePlan p;
     p.G = Hq / Hkv;
     const int rows = B * p.G;
     p.n_rb = (rows + DEC_BM - 1) / DEC_BM;
     int total_tiles = 0;
     for (int s = 0; s < n_seg; ++s) total_tiles += (seg_p[s] + DEC_BN - 1) / DEC_BN;
-    int want = (DEC_PREFIX_WGS + Hkv * p.n_rb - 1) / (Hkv * p.n_rb);   // parts to reach that many workgroups
-    want = want < 1 ? 1 : (want > total_tiles ? total_tiles : want);
-    const int tps = total_tiles ? (total_tiles + want - 1) / want : 0;
+    // Into how many parts the prefix is split: the cheapest by an estimate of the fused kernel (the
+    // longer of a prefix workgroup and a streaming wavefront) plus the partials' way to the merge.  A
+    // prefix workgroup takes 8 us and 0.55 us per tile, 0.8 beside a long stream; a stream 1.8 us per
+    // step, or its bytes at 5.5 TB/s; a part of one output row 1 KB at 2 TB/s.  Measured, whole call
+    // (us): 128 requests, 8192 shared slots, own rows U[1,1024]: 3 parts 83, 6 parts 75; with 2048
+    // shared slots and a private cartridge of 2048 each: 6 parts 273, 3 parts 258, 1 part 252; 32
+    // requests, 8192 slots: 24 parts 34.4, 12 parts 32.6.
+    const long stream_rows = pool_p > 0 ? static_cast<long>(T) + static_cast<long>(B) * pool_p : T;
+    const float stream_us = static_cast<float>(stream_rows) * Hkv * 2 * ROW_B / 5.5e6f;
+    const long chip = 2L * device_cus();          // workgroups the chip keeps resident (256 threads, two per CU)
+    int tps = 0;
+    float tps_us = 0.f;
+    for (int parts = 1; parts <= 48 && parts <= total_tiles; parts += 1 + parts / 8) {
+        const int t = (total_tiles + parts - 1) / parts;
+        const long n_pre = static_cast<long>(Hkv) * p.n_rb * parts;
+        if (parts > 1 && n_pre > chip - 64) break;
+        const long waves = 4 * (chip - n_pre < 64 ? 64 : chip - n_pre);
+        const float steps = ceilf(static_cast<float>(stream_rows) * Hkv / (static_cast<float>(waves) * DEC_SUB));
+        const float pre = 8.f + (stream_us > 20.f ? 0.8f : 0.55f) * static_cast<float>(t);
+        const float stream = fmaxf(4.f + 1.8f * steps, stream_us);
+        const float us = fmaxf(pre, stream) + static_cast<float>(parts) * B * Hq * 2 * HD * 4 / 2.0e6f;
+        if (parts == 1 || us < tps_us) {
+            tps_us = us;
+            tps = t;
+        }
+    }
+    if (lean && total_tiles > 0) {
+        const int parts = (192 + Hkv * p.n_rb - 1) / (Hkv * p.n_rb);
+        tps = (total_tiles + parts - 1) / parts;
+    }
     p.tab.n_seg = 0;
     p.tab.blk0[0] = 0;
     p.n_ps = 0;
@@ -90,38 +118,34 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         p.tab.blk0[k + 1] = p.tab.blk0[k] + Hkv * p.n_rb * p.tab.n_ps[k];
         p.tab.zk[k] = p.tab.zv[k] = nullptr;                        // filled by the launcher
     }
-    // Own KV: the workgroups that stay resident beside the prefix workgroups, four wavefronts
-    // each, one wavefront per (range of token rows, KV head); the ranges cut T evenly, in whole
-    // steps of 32 rows.
+    // Streamed rows: the workgroups that stay resident beside the prefix workgroups, four wavefronts
+    // each, one wavefront per (range, KV head); the ranges cut the own rows of all requests followed
+    // by the private cartridges of all requests evenly, in whole steps of 32 rows.
     const int n_pre_wg = p.n_ps > 0 ? p.tab.blk0[p.tab.n_seg] : 0;
-    long wgs = 2L * device_cus() - n_pre_wg;      // (256 threads, two workgroups per CU)
+    long wgs = chip - n_pre_wg;
     if (wgs < 64) wgs = 64;
     long ranges = 4 * wgs / Hkv;
     if (ranges < 1) { ranges = 1; wgs = (Hkv + 3) / 4; }
-    // (not below DEC_MIN_SHARE rows: shorter ranges only multiply the partials a request leaves)
-    long share = ((static_cast<long>(T) + ranges - 1) / ranges + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
-    if (share < DEC_MIN_SHARE) share = DEC_MIN_SHARE;
-    const long used = (static_cast<long>(T) + share - 1) / share;            // ranges that hold rows
-    if (pool_p == 0 && (used * Hkv + 3) / 4 < wgs) wgs = (used * Hkv + 3) / 4;
-    // Private cartridges: chunks sized so that there is about one per wavefront (measured on 128
-    // requests x 2048 slots: chunks of 256 / 512 / 1024 / 2048 slots -> 0.268 / 0.259 / 0.254 /
-    // 0.248 ms: every chunk starts with a round trip nothing overlaps), not below DEC_POOL_CHUNK
-    p.chunk = DEC_POOL_CHUNK;
-    if (pool_p > 0) {
-        const long rows = static_cast<long>(B) * Hkv * pool_p;
-        long ck = ((rows + 4 * wgs - 1) / (4 * wgs) + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
-        const long whole = (static_cast<long>(pool_p) + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
-        if (ck < DEC_POOL_CHUNK) ck = DEC_POOL_CHUNK;
-        if (ck > whole) ck = whole;
-        p.chunk = static_cast<int>(ck);
-    }
-    p.n_cc = (pool_p + p.chunk - 1) / p.chunk;
+    p.pool0 = (static_cast<long>(T) + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
+    const long rows_all = pool_p > 0 ? p.pool0 + static_cast<long>(B) * pool_p : T;
+    // (not below DEC_MIN_SHARE rows, nor the longest request in more than DEC_MAX_PARTS ranges: shorter
+    // ranges only multiply the partials a request leaves.  8 requests of up to 500 tokens, us a call:
+    // at least 256 / 128 / 64 / 32 rows -> 23.0 / 18.7 / 17.9 / 17.8; one of 16000: 19 / 17.8 / 25.4 / 36.9)
+    long share = ((rows_all + ranges - 1) / ranges + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
+    const long least = (static_cast<long>(max_own_len) + DEC_MAX_PARTS - 1) / DEC_MAX_PARTS;
+    if (share < least) share = (least + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
+    if (share < (lean ? 4 * DEC_MIN_SHARE : DEC_MIN_SHARE)) share = lean ? 4 * DEC_MIN_SHARE : DEC_MIN_SHARE;
+    const long used = (rows_all + share - 1) / share;                        // ranges that hold rows
+    if ((used * Hkv + 3) / 4 < wgs) wgs = (used * Hkv + 3) / 4;
     p.share = static_cast<int>(share);
     p.n_own_wg = static_cast<int>(wgs);
     p.n_oc = static_cast<int>((max_own_len + share - 1) / share) + 1;
+    p.n_cc = pool_p > 0 ? static_cast<int>((pool_p + share - 1) / share) + 1 : 0;
     const size_t slots = static_cast<size_t>(p.n_ps + p.n_cc + p.n_oc) * B * Hq;
     p.part_o_bytes = (slots * HD * sizeof(float) + 255) & ~static_cast<size_t>(255);
     p.part_l_bytes = (slots * sizeof(float) + 255) & ~static_cast<size_t>(255);
+    if (!lean && p.part_o_bytes + p.part_l_bytes > DEC_STATIC_BYTES)
+        return make_plan(B, Hq, Hkv, max_own_len, T, seg_p, n_seg, pool_p, true);
     return p;
 }
 
@@ -512,44 +536,71 @@ __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __rest
     }
 }
 
-// One chunk of a request's private cartridge pool[cart_id[b]] ([Hkv,pool_p,128]; none when
-// cart_id is null or negative), streamed like own rows: item = (request b, chunk cc, KV head hk).
-__device__ __forceinline__ void decode_pool_item(char* sm, const bf16_t* __restrict__ q,
-                                                 const bf16_t* __restrict__ pool_k, const bf16_t* __restrict__ pool_v,
-                                                 const int32_t* __restrict__ cart_id, int pool_p,
-                                                 float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq,
-                                                 int Hkv, float c, int chunk, int n_cc, int n_ps, long item) {
+// The private cartridges pool[cart_id[b]] ([Hkv,pool_p,128]; none for a request whose cart_id is
+// negative), streamed by the same wavefronts as rows pool0 + b * pool_p ... behind the own rows: a
+// wavefront's range may begin with own rows, cross from one cartridge to the next, and every
+// (request, range) pair leaves one partial.  (Chunks of a cartridge dealt out round-robin left
+// wavefronts with two chunks beside others with one: 128 cartridges of 2048 slots beside 2048
+// shared ones took 371 us a call against 273, and 252 with the prefix in one part.)
+__device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __restrict__ q,
+                                                   const bf16_t* __restrict__ pool_k, const bf16_t* __restrict__ pool_v,
+                                                   const int32_t* __restrict__ cart_id, int pool_p, long pool0,
+                                                   float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq,
+                                                   int Hkv, float c, int slot0, int share, int wid) {
     const int G = Hq / Hkv;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int hk = item % Hkv; item /= Hkv;
-    const int cc = item % n_cc;
-    const int b = static_cast<int>(item / n_cc);
-    const int cid = cart_id ? cart_id[b] : -1;
-    if (cid < 0) return;
-    const int k0 = cc * chunk;
-    if (k0 >= pool_p) return;
-    const int nk = min(chunk, pool_p - k0);
-    const size_t row0 = (static_cast<size_t>(cid) * Hkv + hk) * pool_p + k0;
-    const char* k_b = reinterpret_cast<const char*>(pool_k) + row0 * ROW_B;
-    const char* v_b = reinterpret_cast<const char*>(pool_v) + row0 * ROW_B;
+    const int r = wid / Hkv, hk = wid - r * Hkv;
+    const long all = static_cast<long>(B) * pool_p;                 // positions among the cartridges' rows: [lo, hi)
+    long lo = static_cast<long>(r) * share - pool0;
+    const long hi = min(lo + share, all);
+    if (lo < 0) lo = 0;
+    if (lo >= hi) return;
     char* kt = sm + (2 * wv) * DEC_SUB_B;
     char* vt = kt + DEC_SUB_B;
+    // the rows of the first request from b on that has a cartridge: slots [s, end) of it
+    struct Run { int b, s, end; const char *k, *v; };
+    auto run_from = [&](int b, int s) __attribute__((always_inline)) {
+        Run w = {-1, 0, 0, nullptr, nullptr};
+        for (; b < B && static_cast<long>(b) * pool_p + s < hi; ++b, s = 0) {
+            const int cid = cart_id ? cart_id[b] : -1;
+            if (cid < 0) continue;
+            const size_t off = (static_cast<size_t>(cid) * Hkv + hk) * pool_p * ROW_B;
+            w.b = b;
+            w.s = s;
+            w.end = static_cast<int>(min(static_cast<long>(pool_p), hi - static_cast<long>(b) * pool_p));
+            w.k = reinterpret_cast<const char*>(pool_k) + off;
+            w.v = reinterpret_cast<const char*>(pool_v) + off;
+            break;
+        }
+        return w;
+    };
+    const int b0 = static_cast<int>(lo / pool_p);
+    Run cur = run_from(b0, static_cast<int>(lo - static_cast<long>(b0) * pool_p));
+    if (cur.b < 0) return;
     bf16x8 qf[8];
-    own_load_q(q, b, Hq, hk, G, lc, lg, qf);
     OwnState st;
-    own_reset(st);
-    own_issue(k_b, v_b, ROW_B, nk - 1, kt, vt, lane);
-    for (int j0 = 0; j0 < nk; j0 += DEC_SUB) {
-        bf16x8 ka[8], va[2][4];
-        dma_wait();
-        own_frags(kt, vt, ka, va, lane);
-        if (j0 + DEC_SUB < nk)
-            own_issue(k_b + static_cast<size_t>(j0 + DEC_SUB) * ROW_B, v_b + static_cast<size_t>(j0 + DEC_SUB) * ROW_B, ROW_B,
-                      nk - 1 - j0 - DEC_SUB, kt, vt, lane);
-        own_step(st, ka, va, qf, min(DEC_SUB, nk - j0), c, lg);
+    own_issue(cur.k + static_cast<size_t>(cur.s) * ROW_B, cur.v + static_cast<size_t>(cur.s) * ROW_B, ROW_B, cur.end - 1 - cur.s, kt, vt,
+              lane);
+    while (cur.b >= 0) {
+        own_load_q(q, cur.b, Hq, hk, G, lc, lg, qf);
+        own_reset(st);
+        const Run nxt = run_from(cur.b + 1, 0);
+        for (int s = cur.s; s < cur.end; s += DEC_SUB) {
+            bf16x8 ka[8], va[2][4];
+            dma_wait();
+            own_frags(kt, vt, ka, va, lane);
+            const bool last = s + DEC_SUB >= cur.end;
+            const char* kn = last ? nxt.k : cur.k;
+            const char* vn = last ? nxt.v : cur.v;
+            const int sn = last ? nxt.s : s + DEC_SUB, en = last ? nxt.end : cur.end;
+            if (kn) own_issue(kn + static_cast<size_t>(sn) * ROW_B, vn + static_cast<size_t>(sn) * ROW_B, ROW_B, en - 1 - sn, kt, vt, lane);
+            own_step(st, ka, va, qf, min(DEC_SUB, cur.end - s), c, lg);
+        }
+        const int j = r - static_cast<int>((pool0 + static_cast<long>(cur.b) * pool_p) / share);
+        own_store(st, part_o, part_l, (static_cast<size_t>(slot0 + j) * B + cur.b) * Hq + hk * G, G, lc, lg);
+        cur = nxt;
     }
-    own_store(st, part_o, part_l, (static_cast<size_t>(n_ps + cc) * B + b) * Hq + hk * G, G, lc, lg);
 }
 
 // Both roles in one launch, two workgroups per CU: prefix workgroups (matrix-core and LDS work
@@ -560,7 +611,7 @@ __global__ __launch_bounds__(256, 2) void decode_fused_kernel(
     const bf16_t* __restrict__ q, const PrefixTable tab, const bf16_t* __restrict__ k,
     const bf16_t* __restrict__ v, const int32_t* __restrict__ cu, const bf16_t* __restrict__ pool_k,
     const bf16_t* __restrict__ pool_v, const int32_t* __restrict__ cart_id, int pool_p,
-    float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq, int Hkv, float c, int n_rb, int chunk,
+    long pool0, float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq, int Hkv, float c, int n_rb,
     int n_cc, int n_oc, int share, int n_ps, int n_pre_wg, int n_own_wg) {
     constexpr int pre_b = 2 * DEC_NBUF * DEC_TILE_B, own_b = 4 * 2 * DEC_SUB_B;   // the two roles share one LDS block
     __shared__ __attribute__((aligned(16))) char sm[pre_b > own_b ? pre_b : own_b];
@@ -583,32 +634,35 @@ __global__ __launch_bounds__(256, 2) void decode_fused_kernel(
     // every wavefront on its own from here on: no barrier in this role
     const int wid = __builtin_amdgcn_readfirstlane(idx * 4 + static_cast<int>(threadIdx.x >> 6));
     decode_own_stream(sm, q, k, v, cu, part_o, part_l, B, Hq, Hkv, c, n_ps + n_cc, n_oc, share, wid);
-    if (n_cc > 0) {
-        const long n_items = static_cast<long>(B) * n_cc * Hkv;
-        for (long item = wid; item < n_items; item += 4L * n_own_wg)
-            decode_pool_item(sm, q, pool_k, pool_v, cart_id, pool_p, part_o, part_l, B, Hq, Hkv, c, chunk, n_cc, n_ps,
-                             item);
-    }
+    if (n_cc > 0)
+        decode_pool_stream(sm, q, pool_k, pool_v, cart_id, pool_p, pool0, part_o, part_l, B, Hq, Hkv, c, n_ps, share, wid);
 }
 
 // o[b,h,:] = sum_i w_i part_o[i] / sum_i w_i, w_i = exp(lse_i - max lse), over the partial slots
-// that exist for the request: the n_ps prefix parts, the chunks of its private cartridge (when it
-// has one), one per range of `share` token rows its own rows reach into.  One wavefront per
-// (b, h), the slots in groups of 64: lane i holds the lse and the weight of the group's slot i,
-// then every lane accumulates its two head elements over the group's slots with the loads of
-// eight slots in flight.
+// that exist for the request: the n_ps prefix parts, one per range of `share` rows its private
+// cartridge (when it has one) and its own rows reach into.  WPR wavefronts per (b, h): one where there
+// are rows for the whole chip, four where there are not (one request of 16000 own tokens: 19.9 -> 17.4
+// us a call; 8 of up to 16000: 59.0 -> 54.0; above DEC_FEW_ROWS 4096 rows: 75 -> 81).  Slots in
+// groups of 64: lane i holds the lse and the weight of the group's slot i, then every lane accumulates
+// its two head elements over the wavefront's share of the group, eight slots' loads in flight.
+template <int WPR>
 __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restrict__ part_o,
                                                            const float* __restrict__ part_l,
                                                            const int32_t* __restrict__ cu,
-                                                           const int32_t* __restrict__ cart_id, int pool_p,
+                                                           const int32_t* __restrict__ cart_id, int pool_p, long pool0,
                                                            bf16_t* __restrict__ o,
                                                            float* __restrict__ lse, int B, int Hq,
-                                                           int n_ps, int n_cc, int n_oc, int chunk, int share) {
-    const int lane = threadIdx.x & 63;
-    const long row = static_cast<long>(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    if (row >= static_cast<long>(B) * Hq) return;
+                                                           int n_ps, int n_cc, int n_oc, int share) {
+    __shared__ float2 sub_sum[4][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, sub = wv % WPR;
+    const long row = static_cast<long>(blockIdx.x) * (4 / WPR) + wv / WPR;
+    if (row >= static_cast<long>(B) * Hq) return;       // (WPR = 4: the whole workgroup)
     const int b = row / Hq;
-    const int priv = (n_cc > 0 && cart_id && cart_id[b] >= 0) ? (pool_p + chunk - 1) / chunk : 0;
+    int priv = 0;
+    if (n_cc > 0 && cart_id && cart_id[b] >= 0) {
+        const long p0 = pool0 + static_cast<long>(b) * pool_p;
+        priv = static_cast<int>((p0 + pool_p - 1) / share - p0 / share) + 1;
+    }
     const int own = min(n_oc, (cu[b + 1] - 1) / share - cu[b] / share + 1);
     const int n = n_ps + n_cc + n_oc;
     auto valid = [&](int i) { return i < n_ps || (i < n_ps + n_cc ? i - n_ps < priv : i - n_ps - n_cc < own); };
@@ -626,28 +680,30 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restri
         const bool mine = lane < cnt && valid(g0 + lane);
         const float wi = mine ? __expf(part_l[(g0 + lane) * stride + row] - m) : 0.f;
         wsum += wi;
-        int i = 0;
-        for (; i + 8 <= cnt; i += 8) {
+        for (int i = 8 * sub; i < cnt; i += 8 * WPR) {
             float2 x[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 x[j] = float2{0.f, 0.f};
-                if (valid(g0 + i + j))
+                if (i + j < cnt && valid(g0 + i + j))
                     x[j] = *reinterpret_cast<const float2*>(part_o + ((g0 + i + j) * stride + row) * HD + 2 * lane);
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                const float w = __shfl(wi, i + j);
+                const float w = __shfl(wi, (i + j) & 63);
                 a0 = fmaf(w, x[j].x, a0);
                 a1 = fmaf(w, x[j].y, a1);
             }
         }
-        for (; i < cnt; ++i) {
-            if (!valid(g0 + i)) continue;
-            const float w = __shfl(wi, i);
-            const float2 x = *reinterpret_cast<const float2*>(part_o + ((g0 + i) * stride + row) * HD + 2 * lane);
-            a0 = fmaf(w, x.x, a0);
-            a1 = fmaf(w, x.y, a1);
+    }
+    if constexpr (WPR == 4) {
+        sub_sum[wv][lane] = float2{a0, a1};
+        __syncthreads();
+        if (wv != 0) return;
+#pragma unroll
+        for (int w = 1; w < 4; ++w) {
+            a0 += sub_sum[w][lane].x;
+            a1 += sub_sum[w][lane].y;
         }
     }
     wsum = wave_sum(wsum);
@@ -693,13 +749,17 @@ static int run_decode(const DecodePlan& p, int B, int Hq, int Hkv, float scale, 
     trace_begin(st);   // kernel order: prefix + own (one launch), merge
     const int n_pre_wg = p.n_ps > 0 ? p.tab.blk0[p.tab.n_seg] : 0;
     hipLaunchKernelGGL(decode_fused_kernel, dim3(static_cast<unsigned>(n_pre_wg + p.n_own_wg)), dim3(256), 0, st, Q,
-                       p.tab, K, V, cu, PK, PV, cart_id, pool_p, part_o, part_l, B, Hq, Hkv, c, p.n_rb, p.chunk, p.n_cc,
-                       p.n_oc, p.share, p.n_ps, n_pre_wg, p.n_own_wg);
+                       p.tab, K, V, cu, PK, PV, cart_id, pool_p, p.pool0, part_o, part_l, B, Hq, Hkv, c, p.n_rb, p.n_cc, p.n_oc,
+                       p.share, p.n_ps, n_pre_wg, p.n_own_wg);
     trace_mark(st);
     const long rows = static_cast<long>(B) * Hq;
-    hipLaunchKernelGGL(decode_merge_kernel, dim3(static_cast<unsigned>((rows + 3) / 4)), dim3(256), 0, st, part_o,
-                       part_l, cu, cart_id, pool_p, static_cast<bf16_t*>(o), lse, B, Hq, p.n_ps, p.n_cc, p.n_oc,
-                       p.chunk, p.share);
+    auto merge = [&](auto kernel, int rows_per_wg) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rows + rows_per_wg - 1) / rows_per_wg)), dim3(256), 0, st, part_o,
+                           part_l, cu, cart_id, pool_p, p.pool0, static_cast<bf16_t*>(o), lse, B, Hq, p.n_ps, p.n_cc, p.n_oc,
+                           p.share);
+    };
+    if (rows <= DEC_FEW_ROWS) merge(decode_merge_kernel<4>, 1);
+    else                      merge(decode_merge_kernel<1>, 4);
     trace_mark(st);
     return static_cast<int>(hipGetLastError());
 }
@@ -719,7 +779,6 @@ int launch_decode_mfma(const cart_decode_desc& d, float scale, const void* q, co
 // The partial results of one call live in a file-scope device array instead of a caller-supplied
 // workspace.  Each GPU holds its own copy of the array at its own address, looked up once per
 // device; host code only ever uses that looked-up address, never the array's name.
-constexpr size_t DEC_STATIC_BYTES = static_cast<size_t>(32) << 20;
 static __device__ __align__(256) unsigned char scratch[DEC_STATIC_BYTES];
 constexpr int DEC_MAX_DEVICES = 64;
 static void* g_scratch_ptr[DEC_MAX_DEVICES];      // per device, nullptr until looked up

@@ -157,3 +157,35 @@ def test_topk_rows(dtype, N, V, K):
     torch.cuda.synchronize()
     assert np.array_equal(idx.cpu().numpy().astype(np.int64), idx_ref)
     assert np.abs(f64(lp) - lp_ref).max() <= 2e-6 * max(1.0, np.abs(lp_ref).max())
+
+
+# Decode: streamed ranges that cross from own rows into private cartridges and from one cartridge to
+# the next, requests without one in between, cartridges shorter than a step and longer than a range,
+# the merge with four wavefronts a row (few rows) and with one, a request cut into the most ranges.
+DECODE_CASES = [
+    # B, Hq, Hkv, shared slots, pool slots, longest own
+    (3, 4, 1, 0, 1, 40), (5, 8, 2, 33, 31, 70), (6, 8, 2, 700, 64, 1), (4, 6, 3, 100, 777, 65), (40, 8, 1, 64, 40, 3),
+    (70, 32, 8, 65, 33, 20), (2, 2, 1, 10, 3000, 5000), (1, 7, 1, 1, 0, 4161), (64, 32, 2, 0, 0, 90),
+]
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,P,pool_p,most", DECODE_CASES)
+def test_decode_ranges(B, Hq, Hkv, P, pool_p, most):
+    g = torch.Generator().manual_seed(B + P + pool_p)
+    rn = lambda *sz, std=1.0: (std * torch.randn(*sz, generator=g)).to(torch.bfloat16)
+    lens = torch.randint(1, most + 1, (B,), generator=g)
+    lens[-1] = most
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens.numpy())]), dtype=torch.int32)
+    q, k, v = rn(B, Hq, 128, std=0.6), rn(int(cu[-1]), Hkv, 128, std=0.6), rn(int(cu[-1]), Hkv, 128)
+    shared = [(rn(Hkv, P, 128, std=0.6), rn(Hkv, P, 128))] if P else []
+    pk = pv = cid = None
+    if pool_p:
+        pk, pv = rn(3, Hkv, pool_p, 128, std=0.6), rn(3, Hkv, pool_p, 128)
+        cid = torch.tensor([(2 * b) % 4 - 1 if b % 5 else -1 for b in range(B)], dtype=torch.int32)   # some without, some shared
+    dv = lambda t: None if t is None else t.to(DEV)
+    o, lse = cb.cart_decode_composed(dv(q), [(dv(a), dv(b)) for a, b in shared], dv(pk), dv(pv), dv(cid), dv(k), dv(v), dv(cu), most)
+    torch.cuda.synchronize()
+    z = lambda t: None if t is None else f64(t)
+    o_ref, lse_ref = orc.decode_composed(f64(q), [(f64(a), f64(b)) for a, b in shared], z(pk), z(pv),
+                                         None if cid is None else cid.numpy(), f64(k), f64(v), cu.numpy())
+    assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
