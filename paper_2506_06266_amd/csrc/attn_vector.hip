@@ -1,14 +1,364 @@
-// fp32 vector-ALU kernels for cartridge attention (Eq. 1 over the cache of Sec. 3.2), its
-// gradient, and decode (Sec. 3.3).  One 64-lane wavefront per output row; lane l owns head
-// elements l, l+64, ...  They serve fp32 problems and any head_dim <= 256, and are the
-// correctness baseline the MFMA kernels are compared with; no atomics, fixed summation order.
+// Cartridge attention (Eq. 1 over the cache of Sec. 3.2), its gradient, and decode (Sec. 3.3) in fp32
+// arithmetic, for fp32 problems and any head_dim <= 256 (bf16 inputs are widened); no atomics, fixed
+// summation order.  In-library baseline the bf16 matrix-core kernels are compared with.
+//
+// The attention kernels run on the fp32 matrix-core instruction v_mfma_f32_16x16x4_f32,
+// D(16x16) += A(16x4) B(4x16), all operands and sums fp32:
+//   A: lane l holds row l%16, k = l/16;  B: lane l holds column l%16, k = l/16;
+//   D: lane l holds column l%16, rows 4 (l/16) + r for r in [0,4).
+// Every product keeps the stationary index (a query, or a key) on the D column.  The index the next
+// product contracts over is then on the D rows: with its k-step r taken as rows {4g + r}, register r
+// of the result is that product's B operand in the same lane, and nothing passes through LDS.
+// Operands come straight from memory (16 rows x 64 bytes, or 4 rows x 64 bytes, per load).
+//
+// One workgroup owns 16 queries of one head (forward, dQ) or 16 keys of one KV head (dK, dV); its
+// wavefronts split what is contracted over in blocks of 16 and add up through LDS at the end.  A
+// small problem is bound by latency -- its launches, one round trip for the operands, one for the
+// sums -- and a large one by the matrix cores.  Against one wavefront per row or key, a serial chain of
+// shuffles and exponentials per key, us for forward and backward: 2 sequences of 64 tokens, 2 / 1
+// heads of 64, 32 slots: 175 -> 38 (launches); 4 of 256, 8 / 2 heads, 256 slots: head_dim 64 2268 -> 174,
+// head_dim 128 2855 -> 356.
 #include "cart_common.h"
 
 namespace cart {
 
-constexpr int VEC_MAXE = 4;          // head_dim <= 256
-constexpr int VEC_WAVES = 4;         // wavefronts per workgroup
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr float VEC_HIDDEN = -1.0e30f;
 
+__device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+// sum / maximum over the four lanes that hold the same column
+__device__ __forceinline__ float col_sum(float v) { v += __shfl_xor(v, 16, CART_WAVE); return v + __shfl_xor(v, 32, CART_WAVE); }
+__device__ __forceinline__ float col_max(float v) {
+    v = fmaxf(v, __shfl_xor(v, 16, CART_WAVE));
+    return fmaxf(v, __shfl_xor(v, 32, CART_WAVE));
+}
+
+// Row operand of a contraction over the head elements: k-step (s, e) is element 16 s + 4 (lane/16) + e
+template <int NB> struct RowFrag { f32x4 v[NB]; };
+__device__ __forceinline__ f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 load4(const bf16_t* p) {
+    const u32x2 w = *reinterpret_cast<const u32x2*>(p);
+    return f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
+                 __uint_as_float(w.y & 0xffff0000u)};
+}
+template <typename T, int NB>
+__device__ __forceinline__ RowFrag<NB> row_frag(const T* p, int D, int g) {
+    RowFrag<NB> f;
+    if (D == 16 * NB) {
+#pragma unroll
+        for (int s = 0; s < NB; ++s) f.v[s] = load4(p + 16 * s + 4 * g);
+    } else if ((D & 3) == 0) {
+#pragma unroll
+        for (int s = 0; s < NB; ++s) {
+            const int d = 16 * s + 4 * g;
+            f.v[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (d < D) f.v[s] = load4(p + d);
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < NB; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int d = 16 * s + 4 * g + e;
+                f.v[s][e] = d < D ? elem<T>::load(p + d) : 0.f;
+            }
+    }
+    return f;
+}
+template <int NB>
+__device__ __forceinline__ f32x4 contract(const RowFrag<NB>& a, const RowFrag<NB>& b) {
+    f32x4 c0 = {0.f, 0.f, 0.f, 0.f}, c1 = c0;      // two chains: a product's result is not the next one's input
+#pragma unroll
+    for (int s = 0; s < NB; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; e += 2) {
+            c0 = mma4(a.v[s][e], b.v[s][e], c0);
+            c1 = mma4(a.v[s][e + 1], b.v[s][e + 1], c1);
+        }
+    return c0 + c1;
+}
+// Column operand of a contraction over a block's rows: element 16 db + lane%16 of rows 4 (lane/16) + r
+template <int NB> struct ColFrag { f32x4 v[NB]; };
+template <typename T, int NB>
+__device__ __forceinline__ ColFrag<NB> col_frag(const T* const (&p)[4], int D, int c) {
+    ColFrag<NB> f;
+    if (D == 16 * NB) {         // (unguarded: all loads of the block in flight at one time)
+#pragma unroll
+        for (int db = 0; db < NB; ++db)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) f.v[db][r] = elem<T>::load(p[r] + 16 * db + c);
+    } else {
+#pragma unroll
+        for (int db = 0; db < NB; ++db)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) f.v[db][r] = 16 * db + c < D ? elem<T>::load(p[r] + 16 * db + c) : 0.f;
+    }
+    return f;
+}
+// acc[db] += X^T w, w the B operand that register r of a result is
+template <int NB>
+__device__ __forceinline__ void accumulate(f32x4 (&acc)[NB], const ColFrag<NB>& x, const f32x4& w) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int db = 0; db < NB; ++db) acc[db] = mma4(x.v[db][r], w[r], acc[db]);
+}
+template <int NB> __device__ __forceinline__ void clear(f32x4 (&acc)[NB]) {
+#pragma unroll
+    for (int db = 0; db < NB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
+}
+// a wavefront's 16 columns x head elements into LDS, [column][element]
+template <int NB> __device__ __forceinline__ void to_lds(float* dst, const f32x4 (&acc)[NB], int c, int g) {
+#pragma unroll
+    for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(dst + c * (16 * NB + 4) + 16 * db + 4 * g) = acc[db];
+}
+
+// key / value row j of the concatenated cache [prefix ; own] for (sequence b, KV head hk)
+template <typename T>
+__device__ __forceinline__ const T* cache_row(const T* z, const T* own, int j, int P, int S,
+                                              int Hkv, int D, int b, int hk) {
+    return j < P ? z + (static_cast<size_t>(hk) * P + j) * D
+                 : own + ((static_cast<size_t>(b) * S + (j - P)) * Hkv + hk) * D;
+}
+
+template <typename T, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ zk,
+    const T* __restrict__ zv, T* __restrict__ o, float* __restrict__ lse, int S, int Hq, int Hkv, int D, int P, float scale) {
+    constexpr int PITCH = 16 * NB + 4;
+    __shared__ float sm_o[NW][16 * PITCH], sm_m[NW][16], sm_l[NW][16];
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nQt = (S + 15) / 16;
+    int id = blockIdx.x;
+    const int i0 = 16 * (id % nQt); id /= nQt;
+    const int h = id % Hq, b = id / Hq, hk = h / (Hq / Hkv);
+    const int i = min(i0 + c, S - 1);
+    const RowFrag<NB> qf = row_frag<T, NB>(q + ((static_cast<size_t>(b) * S + i) * Hq + h) * D, D, g);
+    const float c2 = scale * CART_LOG2E;
+    const int nk = P + min(i0 + 16, S), last = P + i;      // keys of the block; last key the lane's query sees
+    f32x4 acc[NB];
+    clear(acc);
+    float m = VEC_HIDDEN, l = 0.f;
+    for (int j0 = 16 * wv; j0 < nk; j0 += 16 * NW) {
+        const RowFrag<NB> kf = row_frag<T, NB>(cache_row(zk, k, min(j0 + c, nk - 1), P, S, Hkv, D, b, hk), D, g);
+        const T* vr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) vr[r] = cache_row(zv, v, min(j0 + 4 * g + r, nk - 1), P, S, Hkv, D, b, hk);
+        const ColFrag<NB> vc = col_frag<T, NB>(vr, D, c);
+        f32x4 s = contract(kf, qf);
+        float tm = VEC_HIDDEN;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = j0 + 4 * g + r;
+            s[r] = j <= last ? s[r] * c2 : VEC_HIDDEN;
+            tm = fmaxf(tm, s[r]);
+        }
+        const float nm = fmaxf(m, col_max(tm)), alpha = fast_exp2(m - nm);
+        f32x4 p;
+        l *= alpha;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            p[r] = s[r] > 0.5f * VEC_HIDDEN ? fast_exp2(s[r] - nm) : 0.f;
+            l += p[r];
+        }
+        m = nm;
+#pragma unroll
+        for (int db = 0; db < NB; ++db) acc[db] *= alpha;
+        accumulate(acc, vc, p);
+    }
+    l = col_sum(l);
+    to_lds(sm_o[wv], acc, c, g);
+    if (g == 0) { sm_m[wv][c] = m; sm_l[wv][c] = l; }
+    __syncthreads();
+    // 16 threads per query, each every 16th head element
+    for (int t = threadIdx.x; t < 256; t += 64 * NW) {
+        const int qc = t >> 4;
+        if (i0 + qc >= S) continue;
+        float M = sm_m[0][qc], L = 0.f, w[NW];
+#pragma unroll
+        for (int u = 1; u < NW; ++u) M = fmaxf(M, sm_m[u][qc]);
+#pragma unroll
+        for (int u = 0; u < NW; ++u) {
+            w[u] = fast_exp2(sm_m[u][qc] - M);
+            L += w[u] * sm_l[u][qc];
+        }
+        const float inv = 1.f / L;
+        T* op = o + ((static_cast<size_t>(b) * S + i0 + qc) * Hq + h) * D;
+        for (int d = t & 15; d < D; d += 16) {
+            float a = 0.f;
+#pragma unroll
+            for (int u = 0; u < NW; ++u) a = fmaf(w[u], sm_o[u][qc * PITCH + d], a);
+            elem<T>::store(op + d, a * inv);
+        }
+        if ((t & 15) == 0) lse[(static_cast<size_t>(b) * Hq + h) * S + i0 + qc] = (M + fast_log2(L)) * CART_LN2;
+    }
+}
+
+// dQ; also forms delta[b,h,i] = dO_i . O_i for the key-side kernel
+template <typename T, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_dq_vector(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ zk,
+    const T* __restrict__ zv, const T* __restrict__ o, const float* __restrict__ lse, const T* __restrict__ d_o,
+    float* __restrict__ delta, T* __restrict__ dq, int S, int Hq, int Hkv, int D, int P, float scale) {
+    constexpr int PITCH = 16 * NB + 4;
+    __shared__ float sm_o[NW][16 * PITCH];
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nQt = (S + 15) / 16;
+    int id = blockIdx.x;
+    const int i0 = 16 * (id % nQt); id /= nQt;
+    const int h = id % Hq, b = id / Hq, hk = h / (Hq / Hkv);
+    const int i = min(i0 + c, S - 1);
+    const size_t row = ((static_cast<size_t>(b) * S + i) * Hq + h) * D;
+    const RowFrag<NB> qf = row_frag<T, NB>(q + row, D, g), gf = row_frag<T, NB>(d_o + row, D, g);
+    const size_t st = (static_cast<size_t>(b) * Hq + h) * S + i;
+    float dl = 0.f;
+    {
+        const RowFrag<NB> of = row_frag<T, NB>(o + row, D, g);
+#pragma unroll
+        for (int s = 0; s < NB; ++s)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dl = fmaf(of.v[s][e], gf.v[s][e], dl);
+        dl = col_sum(dl);
+    }
+    if (wv == 0 && g == 0 && i0 + c < S) delta[st] = dl;
+    const float c2 = scale * CART_LOG2E, l2 = lse[st] * CART_LOG2E;
+    const int nk = P + min(i0 + 16, S), last = P + i;
+    f32x4 acc[NB];
+    clear(acc);
+    for (int j0 = 16 * wv; j0 < nk; j0 += 16 * NW) {
+        const int jc = min(j0 + c, nk - 1);
+        const RowFrag<NB> kf = row_frag<T, NB>(cache_row(zk, k, jc, P, S, Hkv, D, b, hk), D, g);
+        const RowFrag<NB> vf = row_frag<T, NB>(cache_row(zv, v, jc, P, S, Hkv, D, b, hk), D, g);
+        const T* kr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) kr[r] = cache_row(zk, k, min(j0 + 4 * g + r, nk - 1), P, S, Hkv, D, b, hk);
+        const ColFrag<NB> kc = col_frag<T, NB>(kr, D, c);
+        const f32x4 s = contract(kf, qf), dp = contract(vf, gf);
+        f32x4 ds;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = j0 + 4 * g + r;
+            ds[r] = j <= last ? fast_exp2(fmaf(s[r], c2, -l2)) * (dp[r] - dl) : 0.f;
+        }
+        accumulate(acc, kc, ds);
+    }
+    to_lds(sm_o[wv], acc, c, g);
+    __syncthreads();
+    for (int t = threadIdx.x; t < 256; t += 64 * NW) {
+        const int qc = t >> 4;
+        if (i0 + qc >= S) continue;
+        T* op = dq + ((static_cast<size_t>(b) * S + i0 + qc) * Hq + h) * D;
+        for (int d = t & 15; d < D; d += 16) {
+            float a = 0.f;
+#pragma unroll
+            for (int u = 0; u < NW; ++u) a += sm_o[u][qc * PITCH + d];
+            elem<T>::store(op + d, a * scale);
+        }
+    }
+}
+
+// dK, dV of 16 keys: prefix slots (summed over every sequence, every query head of the group, every
+// token) or own keys of one sequence (the group's heads, tokens from the block's first key on).
+template <typename T, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(
+    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ zk,
+    const T* __restrict__ zv, const float* __restrict__ lse, const float* __restrict__ delta, const T* __restrict__ d_o,
+    T* __restrict__ dk, T* __restrict__ dv, float* __restrict__ dzk, float* __restrict__ dzv, int B, int S, int Hq, int Hkv,
+    int D, int P, float scale, int n_frozen, int accumulate_dz) {
+    constexpr int PITCH = 16 * NB + 4;
+    __shared__ float sm_k[NW][16 * PITCH], sm_v[NW][16 * PITCH];
+    const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int nPt = (P + 15) / 16, nSt = (S + 15) / 16, G = Hq / Hkv;
+    int id = blockIdx.x;
+    const bool prefix = id < nPt * Hkv;
+    if (!prefix) id -= nPt * Hkv;
+    const int hk = id % Hkv; id /= Hkv;
+    const int key0 = 16 * (prefix ? id : id % nSt), b_own = prefix ? 0 : id / nSt;
+    const int nkeys = prefix ? P : S;
+    auto key_row = [&](int j) { return prefix ? (static_cast<size_t>(hk) * P + j) * D
+                                              : ((static_cast<size_t>(b_own) * S + j) * Hkv + hk) * D; };
+    const size_t kr = key_row(min(key0 + c, nkeys - 1));
+    const RowFrag<NB> kf = row_frag<T, NB>((prefix ? zk : k) + kr, D, g), vf = row_frag<T, NB>((prefix ? zv : v) + kr, D, g);
+    const float c2 = scale * CART_LOG2E;
+    f32x4 ak[NB], av[NB];
+    clear(ak);
+    clear(av);
+    // blocks of 16 token rows: (sequence, head of the group, block), from the block's own diagonal on
+    const int it0 = prefix ? 0 : key0 / 16, nIt = nSt - it0, n = (prefix ? B : 1) * G * nIt;
+    for (int t = wv; t < n; t += NW) {
+        const int i0 = 16 * (it0 + t % nIt), h = hk * G + (t / nIt) % G, b = prefix ? t / (nIt * G) : b_own;
+        auto tok = [&](int i) { return ((static_cast<size_t>(b) * S + i) * Hq + h) * D; };
+        const size_t rc = tok(min(i0 + c, S - 1));
+        const RowFrag<NB> qf = row_frag<T, NB>(q + rc, D, g), gf = row_frag<T, NB>(d_o + rc, D, g);
+        const T *qr[4], *gr[4];
+        f32x4 l2, dl;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int ic = min(i0 + 4 * g + r, S - 1);
+            const size_t st = (static_cast<size_t>(b) * Hq + h) * S + ic;
+            l2[r] = lse[st] * CART_LOG2E;
+            dl[r] = delta[st];
+            qr[r] = q + tok(ic);
+            gr[r] = d_o + tok(ic);
+        }
+        // (head_dim above 128: not all four operands of a block fit the registers at one time)
+        ColFrag<NB> gc, qc;
+        if constexpr (NB <= 8) {
+            gc = col_frag<T, NB>(gr, D, c);
+            qc = col_frag<T, NB>(qr, D, c);
+        }
+        const f32x4 s = contract(qf, kf), dp = contract(gf, vf);
+        f32x4 p, ds;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + 4 * g + r;
+            p[r] = i < S && (prefix || i >= key0 + c) ? fast_exp2(fmaf(s[r], c2, -l2[r])) : 0.f;
+            ds[r] = p[r] * (dp[r] - dl[r]);
+        }
+        if constexpr (NB > 8) {
+            asm volatile("" ::: "memory");
+            gc = col_frag<T, NB>(gr, D, c);
+        }
+        accumulate(av, gc, p);
+        if constexpr (NB > 8) {
+            asm volatile("" ::: "memory");
+            qc = col_frag<T, NB>(qr, D, c);
+        }
+        accumulate(ak, qc, ds);
+    }
+    to_lds(sm_k[wv], ak, c, g);
+    to_lds(sm_v[wv], av, c, g);
+    __syncthreads();
+    for (int t = threadIdx.x; t < 256; t += 64 * NW) {
+        const int j = key0 + (t >> 4);
+        if (j >= nkeys) continue;
+        const size_t r = key_row(j);
+        for (int d = t & 15; d < D; d += 16) {
+            float gk = 0.f, gv = 0.f;
+#pragma unroll
+            for (int u = 0; u < NW; ++u) {
+                gk += sm_k[u][(t >> 4) * PITCH + d];
+                gv += sm_v[u][(t >> 4) * PITCH + d];
+            }
+            if (prefix) {
+                gk = j < n_frozen ? 0.f : gk * scale;
+                gv = j < n_frozen ? 0.f : gv;
+                if (accumulate_dz) { gk += dzk[r + d]; gv += dzv[r + d]; }
+                dzk[r + d] = gk;
+                dzv[r + d] = gv;
+            } else {
+                elem<T>::store(dk + r + d, gk * scale);
+                elem<T>::store(dv + r + d, gv);
+            }
+        }
+    }
+}
+
+// ---- decode: one wavefront per output row; lane l owns head elements l, l+64, ... ---------------
+constexpr int VEC_WAVES = 4;         // wavefronts per workgroup
 template <typename T, int E>
 __device__ __forceinline__ void load_row(const T* p, int D, int lane, float (&r)[E]) {
 #pragma unroll
@@ -23,167 +373,6 @@ __device__ __forceinline__ float dot_rows(const float (&a)[E], const float (&b)[
 #pragma unroll
     for (int e = 0; e < E; ++e) s = fmaf(a[e], b[e], s);
     return wave_sum(s);
-}
-
-// key / value row j of the concatenated cache [prefix ; own] for (sequence b, KV head hk)
-template <typename T>
-__device__ __forceinline__ const T* cache_row(const T* z, const T* own, int j, int P, int S,
-                                              int Hkv, int D, int b, int hk) {
-    return j < P ? z + (static_cast<size_t>(hk) * P + j) * D
-                 : own + ((static_cast<size_t>(b) * S + (j - P)) * Hkv + hk) * D;
-}
-
-template <typename T, int E>
-__global__ __launch_bounds__(64 * VEC_WAVES) void attn_fwd_vector(
-    const T* q, const T* k, const T* v, const T* zk, const T* zv, T* o, float* lse, int B, int S,
-    int Hq, int Hkv, int D, int P, float scale) {
-    const int lane = threadIdx.x & 63;
-    const long row = static_cast<long>(blockIdx.x) * VEC_WAVES + (threadIdx.x >> 6);
-    if (row >= static_cast<long>(B) * S * Hq) return;
-    const int h = row % Hq, i = (row / Hq) % S, b = row / (static_cast<long>(Hq) * S);
-    const int hk = h / (Hq / Hkv);
-    float qr[E], acc[E];
-    load_row<T, E>(q + row * D, D, lane, qr);
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = 0.f;
-    const float c = scale * CART_LOG2E;
-    float m = -3.0e38f, l = 0.f;
-    const int nk = P + i + 1;
-    for (int j = 0; j < nk; ++j) {
-        float kr[E], vr[E];
-        load_row<T, E>(cache_row(zk, k, j, P, S, Hkv, D, b, hk), D, lane, kr);
-        load_row<T, E>(cache_row(zv, v, j, P, S, Hkv, D, b, hk), D, lane, vr);
-        float s = dot_rows<E>(qr, kr) * c;
-        float nm = fmaxf(m, s);
-        float corr = fast_exp2(m - nm), pj = fast_exp2(s - nm);
-        l = l * corr + pj;
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[e] = acc[e] * corr + pj * vr[e];
-        m = nm;
-    }
-    const float inv = 1.f / l;
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        int d = lane + 64 * e;
-        if (d < D) elem<T>::store(o + row * D + d, acc[e] * inv);
-    }
-    if (lane == 0) lse[(static_cast<size_t>(b) * Hq + h) * S + i] = (m + fast_log2(l)) * CART_LN2;
-}
-
-// delta[b,h,i] = dO_i . O_i
-template <typename T, int E>
-__global__ __launch_bounds__(64 * VEC_WAVES) void attn_delta_vector(const T* o, const T* d_o,
-                                                                    float* delta, int B, int S,
-                                                                    int Hq, int D) {
-    const int lane = threadIdx.x & 63;
-    const long row = static_cast<long>(blockIdx.x) * VEC_WAVES + (threadIdx.x >> 6);
-    if (row >= static_cast<long>(B) * S * Hq) return;
-    const int h = row % Hq, i = (row / Hq) % S, b = row / (static_cast<long>(Hq) * S);
-    float a[E], g[E];
-    load_row<T, E>(o + row * D, D, lane, a);
-    load_row<T, E>(d_o + row * D, D, lane, g);
-    float s = dot_rows<E>(a, g);
-    if (lane == 0) delta[(static_cast<size_t>(b) * Hq + h) * S + i] = s;
-}
-
-template <typename T, int E>
-__global__ __launch_bounds__(64 * VEC_WAVES) void attn_bwd_dq_vector(
-    const T* q, const T* k, const T* v, const T* zk, const T* zv, const float* lse,
-    const float* delta, const T* d_o, T* dq, int B, int S, int Hq, int Hkv, int D, int P,
-    float scale) {
-    const int lane = threadIdx.x & 63;
-    const long row = static_cast<long>(blockIdx.x) * VEC_WAVES + (threadIdx.x >> 6);
-    if (row >= static_cast<long>(B) * S * Hq) return;
-    const int h = row % Hq, i = (row / Hq) % S, b = row / (static_cast<long>(Hq) * S);
-    const int hk = h / (Hq / Hkv);
-    float qr[E], gr[E], acc[E];
-    load_row<T, E>(q + row * D, D, lane, qr);
-    load_row<T, E>(d_o + row * D, D, lane, gr);
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] = 0.f;
-    const size_t st = (static_cast<size_t>(b) * Hq + h) * S + i;
-    const float c = scale * CART_LOG2E, l2 = lse[st] * CART_LOG2E, dl = delta[st];
-    const int nk = P + i + 1;
-    for (int j = 0; j < nk; ++j) {
-        float kr[E], vr[E];
-        load_row<T, E>(cache_row(zk, k, j, P, S, Hkv, D, b, hk), D, lane, kr);
-        load_row<T, E>(cache_row(zv, v, j, P, S, Hkv, D, b, hk), D, lane, vr);
-        float p = fast_exp2(dot_rows<E>(qr, kr) * c - l2);
-        float ds = p * (dot_rows<E>(gr, vr) - dl);
-#pragma unroll
-        for (int e = 0; e < E; ++e) acc[e] = fmaf(ds, kr[e], acc[e]);
-    }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        int d = lane + 64 * e;
-        if (d < D) elem<T>::store(dq + row * D + d, acc[e] * scale);
-    }
-}
-
-// One wavefront per key: rows [0, Hkv*P) are prefix slots (summed over every sequence, every
-// query head of the group, every token), the rest are own keys (b, j, hk), summed over the
-// group's heads and tokens i >= j.
-template <typename T, int E>
-__global__ __launch_bounds__(64 * VEC_WAVES) void attn_bwd_dkv_vector(
-    const T* q, const T* k, const T* v, const T* zk, const T* zv, const float* lse,
-    const float* delta, const T* d_o, T* dk, T* dv, float* dzk, float* dzv, int B, int S, int Hq,
-    int Hkv, int D, int P, float scale, int n_frozen, int accumulate) {
-    const int lane = threadIdx.x & 63;
-    const long key = static_cast<long>(blockIdx.x) * VEC_WAVES + (threadIdx.x >> 6);
-    const long n_prefix = static_cast<long>(Hkv) * P;
-    if (key >= n_prefix + static_cast<long>(B) * S * Hkv) return;
-    const bool prefix = key < n_prefix;
-    int hk, b0, b1, i0, slot = 0;
-    const T *kp, *vp;
-    if (prefix) {
-        hk = key / P; slot = key % P; b0 = 0; b1 = B; i0 = 0;
-        kp = zk + key * D; vp = zv + key * D;
-    } else {
-        long r = key - n_prefix;
-        hk = r % Hkv; i0 = (r / Hkv) % S; b0 = r / (static_cast<long>(Hkv) * S); b1 = b0 + 1;
-        kp = k + r * D; vp = v + r * D;
-    }
-    const int G = Hq / Hkv;
-    float kr[E], vr[E], ak[E], av[E];
-    load_row<T, E>(kp, D, lane, kr);
-    load_row<T, E>(vp, D, lane, vr);
-#pragma unroll
-    for (int e = 0; e < E; ++e) { ak[e] = 0.f; av[e] = 0.f; }
-    const float c = scale * CART_LOG2E;
-    for (int b = b0; b < b1; ++b)
-        for (int g = 0; g < G; ++g) {
-            const int h = hk * G + g;
-            for (int i = i0; i < S; ++i) {
-                const size_t row = (static_cast<size_t>(b) * S + i) * Hq + h;
-                const size_t st = (static_cast<size_t>(b) * Hq + h) * S + i;
-                float qr[E], gr[E];
-                load_row<T, E>(q + row * D, D, lane, qr);
-                load_row<T, E>(d_o + row * D, D, lane, gr);
-                float p = fast_exp2(dot_rows<E>(qr, kr) * c - lse[st] * CART_LOG2E);
-                float ds = p * (dot_rows<E>(gr, vr) - delta[st]);
-#pragma unroll
-                for (int e = 0; e < E; ++e) {
-                    av[e] = fmaf(p, gr[e], av[e]);
-                    ak[e] = fmaf(ds, qr[e], ak[e]);
-                }
-            }
-        }
-#pragma unroll
-    for (int e = 0; e < E; ++e) {
-        int d = lane + 64 * e;
-        if (d >= D) continue;
-        if (prefix) {
-            const bool frozen = slot < n_frozen;
-            float gk = frozen ? 0.f : ak[e] * scale, gv = frozen ? 0.f : av[e];
-            if (accumulate) { gk += dzk[key * D + d]; gv += dzv[key * D + d]; }
-            dzk[key * D + d] = gk;
-            dzv[key * D + d] = gv;
-        } else {
-            long r = key - n_prefix;
-            elem<T>::store(dk + r * D + d, ak[e] * scale);
-            elem<T>::store(dv + r * D + d, av[e]);
-        }
-    }
 }
 
 template <typename T, int E>
@@ -227,6 +416,13 @@ __global__ __launch_bounds__(64 * VEC_WAVES) void decode_vector(
 
 static inline unsigned blocks_for(long rows) { return static_cast<unsigned>((rows + VEC_WAVES - 1) / VEC_WAVES); }
 
+// Head elements in blocks of 16, wavefronts per workgroup: as many as their registers allow
+#define CART_DISPATCH_NB(D, BODY)                                                  \
+    do {                                                                           \
+        if ((D) <= 64) { constexpr int NB = 4, NW = 8; BODY; }                     \
+        else if ((D) <= 128) { constexpr int NB = 8, NW = 4; BODY; }               \
+        else { constexpr int NB = 16, NW = 4; BODY; }                              \
+    } while (0)
 #define CART_DISPATCH_E(D, BODY)                      \
     do {                                              \
         if ((D) <= 64) { constexpr int E = 1; BODY; } \
@@ -237,10 +433,9 @@ static inline unsigned blocks_for(long rows) { return static_cast<unsigned>((row
 template <typename T>
 static void fwd_t(const cart_attn_desc& d, float scale, const void* q, const void* k, const void* v,
                   const void* zk, const void* zv, void* o, float* lse, hipStream_t st) {
-    const long rows = static_cast<long>(d.B) * d.S * d.Hq;
-    CART_DISPATCH_E(d.D, hipLaunchKernelGGL((attn_fwd_vector<T, E>), dim3(blocks_for(rows)),
-        dim3(64 * VEC_WAVES), 0, st, (const T*)q, (const T*)k, (const T*)v, (const T*)zk,
-        (const T*)zv, (T*)o, lse, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale));
+    const unsigned wgs = static_cast<unsigned>((d.S + 15) / 16) * d.Hq * d.B;
+    CART_DISPATCH_NB(d.D, hipLaunchKernelGGL((attn_fwd_vector<T, NB, NW>), dim3(wgs), dim3(64 * NW), 0, st, (const T*)q,
+        (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (T*)o, lse, d.S, d.Hq, d.Hkv, d.D, d.P, scale));
 }
 
 int launch_attn_fwd_vector(const cart_attn_desc& d, float scale, const void* q, const void* k,
@@ -257,22 +452,17 @@ template <typename T>
 static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const void* k, const void* v,
                   const void* zk, const void* zv, const void* o, const float* lse, const void* d_o,
                   void* dq, void* dk, void* dv, float* dzk, float* dzv, void* ws, hipStream_t st) {
-    const long rows = static_cast<long>(d.B) * d.S * d.Hq;
-    const long keys = static_cast<long>(d.Hkv) * d.P + static_cast<long>(d.B) * d.S * d.Hkv;
+    const unsigned nSt = static_cast<unsigned>((d.S + 15) / 16), nPt = static_cast<unsigned>((d.P + 15) / 16);
     float* delta = static_cast<float*>(ws);
-    trace_begin(st);   // kernel order: delta, dq, dk/dv/dz
-    CART_DISPATCH_E(d.D, {
-        hipLaunchKernelGGL((attn_delta_vector<T, E>), dim3(blocks_for(rows)), dim3(64 * VEC_WAVES),
-                           0, st, (const T*)o, (const T*)d_o, delta, d.B, d.S, d.Hq, d.D);
+    trace_begin(st);   // kernel order: dq (+ delta), dk/dv/dz
+    CART_DISPATCH_NB(d.D, {
+        hipLaunchKernelGGL((attn_bwd_dq_vector<T, NB, NW>), dim3(nSt * d.Hq * d.B), dim3(64 * NW), 0, st, (const T*)q,
+                           (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (const T*)o, lse, (const T*)d_o, delta,
+                           (T*)dq, d.S, d.Hq, d.Hkv, d.D, d.P, scale);
         trace_mark(st);
-        hipLaunchKernelGGL((attn_bwd_dq_vector<T, E>), dim3(blocks_for(rows)), dim3(64 * VEC_WAVES),
-                           0, st, (const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv,
-                           lse, delta, (const T*)d_o, (T*)dq, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale);
-        trace_mark(st);
-        hipLaunchKernelGGL((attn_bwd_dkv_vector<T, E>), dim3(blocks_for(keys)), dim3(64 * VEC_WAVES),
-                           0, st, (const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv,
-                           lse, delta, (const T*)d_o, (T*)dk, (T*)dv, dzk, dzv, d.B, d.S, d.Hq,
-                           d.Hkv, d.D, d.P, scale, d.n_frozen, d.dz_accumulate);
+        hipLaunchKernelGGL((attn_bwd_dkv_vector<T, NB, NW>), dim3((nPt + nSt * d.B) * d.Hkv), dim3(64 * NW), 0, st,
+                           (const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, lse, delta, (const T*)d_o,
+                           (T*)dk, (T*)dv, dzk, dzv, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale, d.n_frozen, d.dz_accumulate);
         trace_mark(st);
     });
 }

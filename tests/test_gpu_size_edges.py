@@ -89,6 +89,20 @@ def test_packed_small_launches(lens, Hq, Hkv, P):
         assert rel_err(x, r) <= TOL[torch.bfloat16]
 
 
+
+# The fp32 kernels (any head_dim up to 256; bf16 inputs widened): head sizes around the operand blocks
+# of 16 and the three register layouts, tokens and slots around the blocks of 16, one token, no prefix.
+VECTOR_CASES = [(torch.float32, 2, 17, 2, 1, 5, 33), (torch.float32, 1, 16, 4, 2, 16, 16), (torch.float32, 3, 1, 2, 2, 64, 1),
+                (torch.float32, 2, 130, 4, 1, 64, 0), (torch.float32, 1, 65, 3, 1, 66, 15), (torch.float32, 2, 31, 2, 1, 128, 140),
+                (torch.float32, 1, 33, 2, 1, 132, 20), (torch.float32, 1, 20, 2, 1, 256, 17), (torch.bfloat16, 2, 40, 4, 2, 64, 50),
+                (torch.bfloat16, 1, 18, 2, 1, 37, 9), (torch.bfloat16, 1, 70, 2, 2, 128, 0)]
+
+
+@pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D,P", VECTOR_CASES, ids=lambda v: str(v).replace("torch.", ""))
+def test_attention_vector(dtype, B, S, Hq, Hkv, D, P):
+    check_attn(*attn_case((B, S), Hq, Hkv, D, P, dtype, S + D), impl=cb.IMPL_VECTOR, n_frozen=min(P, 2))
+
+
 # Loss: every width of the row kernel at its last size and just past it, rows that start at every
 # offset from a 16-byte boundary (odd vocabularies), more records than threads, more rows than the
 # launch has workgroups.  (data type, rows, vocabulary, records)
