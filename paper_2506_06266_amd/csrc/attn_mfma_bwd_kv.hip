@@ -625,7 +625,7 @@ static KvPlan search_plan(const cart_attn_desc& d, long tokens, int cus) {
         const long n_own = static_cast<long>(nOb) * d.B * hp;
         if (hp > 1 && n_own > 4L * M) break;            // (plenty of own-key workgroups as it is)
         int last = 0;
-        for (int n = 1; n <= 32; n += 1 + n / 8) {
+        for (int n = 1; n <= (d.P > 0 ? 32 : 1); n += 1 + n / 8) {
             KvPlan p;
             p.chunk = static_cast<int>((((tokens + n - 1) / n) + KV_TILE - 1) / KV_TILE * KV_TILE);
             p.n_part = static_cast<int>((tokens + p.chunk - 1) / p.chunk);
@@ -640,36 +640,29 @@ static KvPlan search_plan(const cart_attn_desc& d, long tokens, int cus) {
             auto own = [&](int kb) { return KV_BLOCK_US + bo * static_cast<float>((nT - 2 * kb) * (G / hp)); };
             const long q = n_pre / M, r = n_pre % M;
             float end = pre * static_cast<float>(q + (r ? 1 : 0));
+            float sum = pre * static_cast<float>(n_pre);
+            for (int kb = 0; kb < nOb; ++kb) sum += own(kb) * static_cast<float>(d.B * hp);
+            const float even = sum / static_cast<float>(M);
+            const float parts_us = KV_US_PER_MB * 1e-6f * 2.f * HD * 4.f * static_cast<float>(d.Hkv) *
+                                   (static_cast<float>(p.n_part) * d.P + (hp > 1 ? static_cast<float>(hp) * tokens : 0.f));
+            // (no cut ends before its longest prefix CU or an even spread of all its work: not played through
+            // when that is no better already)
+            if (best.chunk != 0 && fmaxf(end, even) + parts_us >= best_t) continue;
             if (n_own > 512) {
-                float sum = pre * static_cast<float>(n_pre);
-                for (int kb = 0; kb < nOb; ++kb) sum += own(kb) * static_cast<float>(d.B * hp);
-                const float even = sum / static_cast<float>(M) + 0.5f * own(0);
-                end = even > end ? even : end;
+                end = fmaxf(end, even + 0.5f * own(0));
             } else {
                 float cu[KV_MAX_CUS];                   // a heap of the times at which the CUs are free
                 for (int m = 0; m < M; ++m) cu[m] = pre * static_cast<float>(q + (m >= M - static_cast<int>(r) ? 1 : 0));
                 for (long j = 0; j < n_own; ++j) {
-                    const float t = cu[0] + own(static_cast<int>(j % nOb));
+                    const float t = run_next(cu, M, own(static_cast<int>(j % nOb)));
                     end = t > end ? t : end;
-                    int m = 0;
-                    for (;;) {
-                        int c = 2 * m + 1;
-                        if (c >= M) break;
-                        if (c + 1 < M && cu[c + 1] < cu[c]) ++c;
-                        if (cu[c] >= t) break;
-                        cu[m] = cu[c];
-                        m = c;
-                    }
-                    cu[m] = t;
                 }
             }
-            end += KV_US_PER_MB * 1e-6f * 2.f * HD * 4.f * static_cast<float>(d.Hkv) *
-                   (static_cast<float>(p.n_part) * d.P + (hp > 1 ? static_cast<float>(hp) * tokens : 0.f));
+            end += parts_us;
             if (best.chunk == 0 || end < best_t) {
                 best_t = end;
                 best = p;
             }
-            if (d.P == 0) break;
         }
     }
     return best;

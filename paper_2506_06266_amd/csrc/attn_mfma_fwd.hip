@@ -564,16 +564,10 @@ void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P,
         return (P + 63) / 64 + (own < own_cap ? own : own_cap);
     };
     float cu[MAX_SPLIT];                                    // when each CU is free
-    auto run = [&](float* c, float t) {
-        int m = 0;
-        for (int i = 1; i < slots; ++i) m = c[i] < c[m] ? i : m;
-        c[m] += t;
-        return c[m];
-    };
     for (int i = 0; i < slots; ++i) cu[i] = 0.f;
     float done = 0.f;                                       // when the whole rounds are done
     for (int e = 0; e < n - left; ++e) {
-        const float t = run(cu, a + b * tiles(e));
+        const float t = run_next(cu, slots, a + b * tiles(e));
         done = t > done ? t : done;
     }
     int tl[MAX_SPLIT], most = 0;
@@ -593,7 +587,7 @@ void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P,
         for (int i = 0; i < left; ++i) {
             const int np = (tl[i] + tps - 1) / tps;
             for (int p = 0; p < np; ++p) {
-                const float t = n == left ? a + b * ((tl[i] + np - 1) / np) : run(c, a + b * ((tl[i] + np - 1) / np));
+                const float us = a + b * ((tl[i] + np - 1) / np), t = n == left ? us : run_next(c, slots, us);
                 end = t > end ? t : end;
             }
         }
@@ -617,11 +611,21 @@ static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 bool attn_mfma_supported(const cart_attn_desc& d) {
     return d.dtype == CART_BF16 && d.D == 128;
 }
-// blocks per sequence, or over the packed rows (a packed batch with a prefix; T > 0)
+// Blocks per sequence, or over the packed rows (a packed batch with a prefix; T > 0).  A call asks twice,
+// for the workspace and for the launch: the thread's last split is kept with all that it depends on.
 void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, float a, float b) {
+    struct Key { int B, S, G, Hkv, P, own_cap, cus; float a, b; };
+    static thread_local Key last;
+    static thread_local QuerySplit kept;
     const int G = d.Hq / d.Hkv;
-    if (T > 0 && d.P > 0) plan_query_split(sp, 1, T, G, d.Hkv, d.P, (d.S + 255) / 64 + 2, a, b);
-    else                  plan_query_split(sp, d.B, d.S, G, d.Hkv, d.P, 1 << 30, a, b);
+    const bool rows = T > 0 && d.P > 0;
+    const Key k = {rows ? 1 : d.B, rows ? T : d.S, G, d.Hkv, d.P, rows ? (d.S + 255) / 64 + 2 : 1 << 30, device_cus(), a, b};
+    if (last.cus != k.cus || last.B != k.B || last.S != k.S || last.G != k.G || last.Hkv != k.Hkv || last.P != k.P ||
+        last.own_cap != k.own_cap || last.a != k.a || last.b != k.b) {
+        plan_query_split(kept, k.B, k.S, G, d.Hkv, d.P, k.own_cap, a, b);
+        last = k;
+    }
+    sp = kept;
 }
 // one overflow flag per wavefront; packed batches: + the first row of every row's sequence; + the
 // partial results of the split blocks
