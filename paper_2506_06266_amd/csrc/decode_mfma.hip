@@ -34,7 +34,7 @@ constexpr int DEC_TILE_B = DEC_BN * ROW_B;
 constexpr int DEC_SUB = 32;            // own keys per wavefront step
 constexpr int DEC_SUB_B = DEC_SUB * ROW_B;
 
-constexpr int DEC_MIN_SHARE = 64;       // fewest rows per streamed range (a multiple of DEC_SUB)
+constexpr int DEC_MIN_SHARE = 64;       // fewest rows per streamed range of requests that are not shorter
 constexpr int DEC_MAX_PARTS = 64;       // most ranges the longest request's own rows are cut into
 constexpr int DEC_FEW_ROWS = 2048;      // output rows up to which the merge takes four wavefronts a row
 constexpr int DEC_MAX_SEG = CART_MAX_SEGMENTS;
@@ -120,7 +120,7 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     }
     // Streamed rows: the workgroups that stay resident beside the prefix workgroups, four wavefronts
     // each, one wavefront per (range, KV head); the ranges cut the own rows of all requests followed
-    // by the private cartridges of all requests evenly, in whole steps of 32 rows.
+    // by the private cartridges of all requests evenly, in whole steps of 32 rows where they are that long.
     const int n_pre_wg = p.n_ps > 0 ? p.tab.blk0[p.tab.n_seg] : 0;
     long wgs = chip - n_pre_wg;
     if (wgs < 64) wgs = 64;
@@ -130,11 +130,18 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     const long rows_all = pool_p > 0 ? p.pool0 + static_cast<long>(B) * pool_p : T;
     // (not below DEC_MIN_SHARE rows, nor the longest request in more than DEC_MAX_PARTS ranges: shorter
     // ranges only multiply the partials a request leaves.  8 requests of up to 500 tokens, us a call:
-    // at least 256 / 128 / 64 / 32 rows -> 23.0 / 18.7 / 17.9 / 17.8; one of 16000: 19 / 17.8 / 25.4 / 36.9)
-    long share = ((rows_all + ranges - 1) / ranges + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
-    const long least = (static_cast<long>(max_own_len) + DEC_MAX_PARTS - 1) / DEC_MAX_PARTS;
-    if (share < least) share = (least + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
-    if (share < (lean ? 4 * DEC_MIN_SHARE : DEC_MIN_SHARE)) share = lean ? 4 * DEC_MIN_SHARE : DEC_MIN_SHARE;
+    // at least 256 / 128 / 64 / 32 rows -> 23.0 / 18.7 / 17.9 / 17.8; one of 16000: 19 / 17.8 / 25.4 / 36.9.
+    // Requests shorter than that on average take a step each however few their rows are, so a range then
+    // holds about one of them: 31 requests of up to 17 tokens beside 885 slots 26.2 -> 18.2, 128 of up to 16
+    // beside 1000 33.6 -> 22.2, 48 of up to 53 beside 516 20.9 -> 18.2)
+    auto up = [](long x, long to) { return (x + to - 1) / to * to; };
+    const long resident = (rows_all + ranges - 1) / ranges, least = (static_cast<long>(max_own_len) + DEC_MAX_PARTS - 1) / DEC_MAX_PARTS;
+    const long needed = resident > least ? resident : least, avg = up(T / B, 8);
+    long share = up(needed, DEC_SUB);
+    if (lean)                                       share = share > 4 * DEC_MIN_SHARE ? share : 4 * DEC_MIN_SHARE;
+    else if (pool_p == 0 && avg < DEC_MIN_SHARE)    share = avg > needed ? avg : up(needed, needed < DEC_SUB ? 8 : DEC_SUB);
+    else if (share < DEC_MIN_SHARE)                 share = DEC_MIN_SHARE;
+    if (share < 8) share = 8;
     const long used = (rows_all + share - 1) / share;                        // ranges that hold rows
     if ((used * Hkv + 3) / 4 < wgs) wgs = (used * Hkv + 3) / 4;
     p.share = static_cast<int>(share);

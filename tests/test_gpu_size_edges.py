@@ -180,6 +180,8 @@ DECODE_CASES = [
     # B, Hq, Hkv, shared slots, pool slots, longest own
     (3, 4, 1, 0, 1, 40), (5, 8, 2, 33, 31, 70), (6, 8, 2, 700, 64, 1), (4, 6, 3, 100, 777, 65), (40, 8, 1, 64, 40, 3),
     (70, 32, 8, 65, 33, 20), (2, 2, 1, 10, 3000, 5000), (1, 7, 1, 1, 0, 4161), (64, 32, 2, 0, 0, 90),
+    # ranges of about one short request: of 8 rows, one row each, more requests than ranges
+    (31, 32, 8, 100, 0, 12), (130, 4, 2, 40, 0, 1), (500, 8, 8, 33, 0, 30), (300, 16, 16, 0, 0, 100),
 ]
 
 
