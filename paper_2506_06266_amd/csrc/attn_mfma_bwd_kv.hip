@@ -67,8 +67,14 @@ struct KvArgs {
     float c, scale;
 };
 
+// A called function saves the callee-saved half of its registers on entry and reads it back on return:
+// 240 of them a wavefront, 240 KB a workgroup out and in again through scratch memory.  The compiler
+// drops that for a function of internal linkage whose calls are not marked as tail calls (it then knows
+// that the kernel holds nothing across the call), hence `static` and the attribute.
+// One sequence of 700 tokens, 32 / 8 heads, 1000 slots: 135 -> 127 us for forward and backward; 64 packed
+// conversations of up to 1024: 10.17 -> 10.00 ms; 16 x 2048 over 4096 slots: 9.81 -> 9.71.
 template <bool roleB>
-__device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
+[[clang::not_tail_called]] static __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
     const uint64_t au = reinterpret_cast<uint64_t>(args_generic);
     const uint32_t a_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(au >> 32)));
     const uint32_t a_lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(au)));
