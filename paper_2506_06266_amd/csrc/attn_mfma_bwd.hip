@@ -72,10 +72,54 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
         return;
     }
 
+    // tile order: see KeyTiles
+    const int nMain = kt.nMain, nT = kt.hi;
+    const char* zk_b = reinterpret_cast<const char*>(zk) + static_cast<size_t>(hk) * P * ROW_B;
+    const char* zv_b = reinterpret_cast<const char*>(zv) + static_cast<size_t>(hk) * P * ROW_B;
+    const uint32_t own_pitch = static_cast<uint32_t>(Hkv) * ROW_B;
+    const char* k_b = reinterpret_cast<const char*>(k) + (t0 * Hkv + hk) * ROW_B;
+    const char* v_b = reinterpret_cast<const char*>(v) + (t0 * Hkv + hk) * ROW_B;
+    auto tile_pre = [&](int t) __attribute__((always_inline)) { return kt.pre(t); };
+    auto tile_j0 = [&](int t) __attribute__((always_inline)) { return kt.j0(t); };
+    const uint32_t dma_c0 = (lane & 15) ^ (((lane >> 4) & 3) << 2);
+    struct TileSrc { const char* kb; const char* vb; int lim; uint32_t pitch; uint32_t lds_k, lds_v; };
+    auto tile_src = [&](int t, int buf) __attribute__((always_inline)) {
+        const bool pre = tile_pre(t);
+        const int j0 = tile_j0(t);
+        TileSrc ts;
+        ts.pitch = pre ? static_cast<uint32_t>(ROW_B) : own_pitch;
+        ts.kb = (pre ? zk_b : k_b) + static_cast<size_t>(j0) * ts.pitch;
+        ts.vb = (pre ? zv_b : v_b) + static_cast<size_t>(j0) * ts.pitch;
+        ts.lim = (pre ? P : S) - 1 - j0;
+        ts.lds_k = lds_addr(sm.t[buf].k);
+        ts.lds_v = lds_addr(sm.t[buf].v);
+        return ts;
+    };
+    auto dma_piece = [&](const TileSrc& ts, int n) __attribute__((always_inline)) {
+        const int i = n & 3;
+        const int r0 = (4 * wv + i) * 4;
+        const uint32_t voff = __umul24(min(r0 + (lane >> 4), ts.lim), ts.pitch) + ((dma_c0 ^ i) << 4);
+        if (n < 4) dma16(ts.kb, voff, ts.lds_k + r0 * ROW_B);
+        else       dma16(ts.vb, voff, ts.lds_v + r0 * ROW_B);
+    };
+    // The first two tiles are requested ahead of the queries, and the row statistics leave at the end: one
+    // round trip to memory ahead of the loop, not three and a store's (with the same in the dK / dV kernel,
+    // us a backward call: 5 x 333 tokens, 8 / 2 heads, 2500 slots 95.4 -> 92.7; 16 x 256, 32 / 8 heads, 1024
+    // slots 260.1 -> 257.6; 32 x 1024, 24 / 8 heads, 2048 slots 2969 -> 2940.  The forward, whose tiles already
+    // leave together, did not gain: 860 -> 893 on the last)
+    {
+        const TileSrc t0 = tile_src(kt.lo, 0);
+#pragma unroll
+        for (int n = 0; n < 8; ++n) dma_piece(t0, n);
+        const TileSrc t1 = tile_src(min(kt.lo + 1, nT - 1), 1);
+#pragma unroll
+        for (int n = 0; n < 8; ++n) dma_piece(t1, n);
+    }
+
     // The row statistics of the backward pass are formed here, where O and dO of every query row
     // pass through registers anyway: -delta = -rowsum(dO * O) and -lse2 = -lse * log2(e)
-    // (negated: they enter the products as init values).  They are also written out for the dK
-    // and dV kernels, which run after this one.
+    // (negated: they enter the products as init values).  They are also written out, at the end, for
+    // the dK / dV kernel, which runs after this one.
     u32x4 qf[2][8], gf[2][8];     // B operands: column = query, k = head element
     float nl2[2], ndl[2];         // -lse2, -delta of the lane's queries
     int lo_q[2] = {0, 0};         // first own key the lane's queries see
@@ -110,11 +154,6 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
         ds += partner(ds);
         nl2[cb] = -lse[sp.stat_b + h * sp.stat_h + qi] * CART_LOG2E;
         ndl[cb] = -ds;
-        if (lg == 0 && qi_raw < S && qb.part == qb.n_parts - 1) {      // (the last part is never empty) internal layout [Hq][all token rows], both input layouts
-            const size_t st = static_cast<size_t>(h) * n_tok + t0 + qi;
-            nlse2[st] = nl2[cb];
-            ndelta[st] = ndl[cb];
-        }
     }
     // -delta of the lane's queries in all 16 registers of a set: the dP^T products start from it
     // (their init value), so that dP^T - delta needs no instruction of its own
@@ -145,36 +184,6 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     };
     pin();
 
-    // tile order: see KeyTiles
-    const int nMain = kt.nMain, nT = kt.hi;
-    const char* zk_b = reinterpret_cast<const char*>(zk) + static_cast<size_t>(hk) * P * ROW_B;
-    const char* zv_b = reinterpret_cast<const char*>(zv) + static_cast<size_t>(hk) * P * ROW_B;
-    const uint32_t own_pitch = static_cast<uint32_t>(Hkv) * ROW_B;
-    const char* k_b = reinterpret_cast<const char*>(k) + (t0 * Hkv + hk) * ROW_B;
-    const char* v_b = reinterpret_cast<const char*>(v) + (t0 * Hkv + hk) * ROW_B;
-    auto tile_pre = [&](int t) __attribute__((always_inline)) { return kt.pre(t); };
-    auto tile_j0 = [&](int t) __attribute__((always_inline)) { return kt.j0(t); };
-    const uint32_t dma_c0 = (lane & 15) ^ (((lane >> 4) & 3) << 2);
-    struct TileSrc { const char* kb; const char* vb; int lim; uint32_t pitch; uint32_t lds_k, lds_v; };
-    auto tile_src = [&](int t, int buf) __attribute__((always_inline)) {
-        const bool pre = tile_pre(t);
-        const int j0 = tile_j0(t);
-        TileSrc ts;
-        ts.pitch = pre ? static_cast<uint32_t>(ROW_B) : own_pitch;
-        ts.kb = (pre ? zk_b : k_b) + static_cast<size_t>(j0) * ts.pitch;
-        ts.vb = (pre ? zv_b : v_b) + static_cast<size_t>(j0) * ts.pitch;
-        ts.lim = (pre ? P : S) - 1 - j0;
-        ts.lds_k = lds_addr(sm.t[buf].k);
-        ts.lds_v = lds_addr(sm.t[buf].v);
-        return ts;
-    };
-    auto dma_piece = [&](const TileSrc& ts, int n) __attribute__((always_inline)) {
-        const int i = n & 3;
-        const int r0 = (4 * wv + i) * 4;
-        const uint32_t voff = __umul24(min(r0 + (lane >> 4), ts.lim), ts.pitch) + ((dma_c0 ^ i) << 4);
-        if (n < 4) dma16(ts.kb, voff, ts.lds_k + r0 * ROW_B);
-        else       dma16(ts.vb, voff, ts.lds_v + r0 * ROW_B);
-    };
     // hidden entries of query block cb in the scores of the sub-tile whose first key is j0
     auto mask1 = [&](f32x16& x, int cb, bool pre, int j0) __attribute__((always_inline)) {
         mask_above(x, (pre ? P - 1 : wrow0 + 32 * cb + lc) - j0 - 4 * lg);
@@ -282,15 +291,9 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     };
     auto settle = [&]() __attribute__((always_inline)) { asm volatile("s_nop 15\n\ts_nop 7" ::: "memory"); };
 
-    {   // prologue: tiles 0 and 1 on their way, scores of sub-tile 0
-        const TileSrc t0 = tile_src(kt.lo, 0);
-#pragma unroll
-        for (int n = 0; n < 8; ++n) dma_piece(t0, n);
+    {   // prologue: scores of sub-tile 0
         dma_wait();
         __syncthreads();
-        const TileSrc t1 = tile_src(min(kt.lo + 1, nT - 1), 1);
-#pragma unroll
-        for (int n = 0; n < 8; ++n) dma_piece(t1, n);
 #pragma unroll
         for (int t8 = 0; t8 < 8; ++t8) { ka[t8] = ld_k(t8, 0); va[t8] = ld_v(t8, 0); }
 #pragma unroll
@@ -343,6 +346,16 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_dq_kernel(
     // turned around in LDS once nobody reads a tile or has a load in flight
     dma_wait();
     __syncthreads();
+    if (lg == 0 && qb.part == qb.n_parts - 1) {      // (the last part is never empty) internal layout [Hq][all token rows], both input layouts
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+            const int qi = wrow0 + 32 * cb + lc;
+            if (qi >= S) continue;
+            const size_t st = static_cast<size_t>(h) * n_tok + t0 + qi;
+            nlse2[st] = nl2[cb];
+            ndelta[st] = ndl[cb];
+        }
+    }
     char* const turn = reinterpret_cast<char*>(&sm) + wv * BUF_B;
     if (qb.n_parts == 1)
         store_rows64(turn, acc, scale, scale, dq + ((t0 + wrow0) * Hq + h) * HD, static_cast<size_t>(Hq) * HD, S - wrow0, lane);

@@ -130,14 +130,16 @@ template <bool roleB>
 
     // this wavefront's 64 keys as B operands (column = key, k = head element): K for A, V for B
     u32x4 sf[2][8];
+    auto load_keys = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int kc = 0; kc < 2; ++kc) {
-        const int key = min(wkey0 + 32 * kc + lc, nkeys - 1);
-        const size_t row = pre ? static_cast<size_t>(hk) * P + key : (t0 + key) * Hkv + hk;
-        const bf16_t* sp_ = (roleB ? (pre ? zv : v) : (pre ? zk : k)) + row * HD + 8 * lg;
+        for (int kc = 0; kc < 2; ++kc) {
+            const int key = min(wkey0 + 32 * kc + lc, nkeys - 1);
+            const size_t row = pre ? static_cast<size_t>(hk) * P + key : (t0 + key) * Hkv + hk;
+            const bf16_t* sp_ = (roleB ? (pre ? zv : v) : (pre ? zk : k)) + row * HD + 8 * lg;
 #pragma unroll
-        for (int t = 0; t < 8; ++t) sf[kc][t] = *reinterpret_cast<const u32x4*>(sp_ + 16 * t);
-    }
+            for (int t = 0; t < 8; ++t) sf[kc][t] = *reinterpret_cast<const u32x4*>(sp_ + 16 * t);
+        }
+    };
     f32x16 acc[4][2];   // dV^T (A) or dK^T (B): [head-element block][key block]
 #pragma unroll
     for (int db = 0; db < 4; ++db)
@@ -155,7 +157,6 @@ template <bool roleB>
 #pragma unroll
             for (int kc = 0; kc < 2; ++kc) asm volatile("" : "+a"(acc[db][kc]));
     };
-    pin();
 
     // The stream of query tiles (64 token rows of one head): per head the whole tiles entirely
     // after the block's last key need no mask, the tiles on the diagonal and the ragged last tile
@@ -355,12 +356,14 @@ template <bool roleB>
             i0_cur = t0s.i0;
 #pragma unroll
             for (int n = 0; n < KV_DMA; ++n) dma_piece(t0s, n);
-            dma_wait();
-            __syncthreads();
             const TileSrc t1s = next_tile(1);
             i0_nx = t1s.i0;
 #pragma unroll
             for (int n = 0; n < KV_DMA; ++n) dma_piece(t1s, n);
+            load_keys();      // (behind the tiles: one round trip to memory, not three)
+            pin();
+            dma_wait();
+            __syncthreads();
 #pragma unroll
             for (int t8 = 0; t8 < 8; ++t8) qa[t8] = lds_ld_frag(qofs[t8] - KV_BUF_B);        // sub-tile 0
             ld_rows_at(nl, rofs_c, 0);
@@ -525,6 +528,8 @@ template <bool roleB>
             __builtin_amdgcn_sched_barrier(0);
         };
 
+        load_keys();
+        pin();
         {   // prologue: A's barrier publishes tile 0; fragments and row values of sub-tile 0
             __syncthreads();
 #pragma unroll
