@@ -299,7 +299,7 @@ cart_status cart_attn_varlen_bwd(const cart_attn_varlen_desc *desc, const void *
  * variants) / cart_distill_kl_fwd_bwd / cart_decode call records events[0] on its stream before
  * its first kernel and events[i] after its i-th kernel (as many as `count` allows).  Kernel
  * order, bf16 / head_dim 128: attention forward = forward, finish (combines the
- * parts of split blocks, repairs overflows); backward = dQ (which also forms the row statistics),
+ * parts of split blocks; no kernel, only its event, when none is split); backward = dQ (which also forms the row statistics),
  * dK + dV (one kernel), the sums of the partials; loss = row kernel, scalar reduction; decode = prefix + own-KV (one launch), merge.  The array must stay valid while the
  * hook is set.  Process-global, not thread-safe; the caller owns the events and reads them after
  * synchronising the stream.

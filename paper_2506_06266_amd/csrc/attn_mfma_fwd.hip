@@ -14,8 +14,8 @@
 // running max and the O accumulators are never rescaled.  exp2 and the fp32 accumulators cover
 // 2^+-126 around that reference, so this is exact unless a later score exceeds the first
 // sub-tile's maximum by more than ~80 in natural-log units; then the row sum overflows to
-// inf/NaN, the workgroup raises a flag, and attn_fwd_finish_kernel recomputes that block of rows
-// with a plain running-max loop.  The hot loop is one straight-line block per sub-tile with two
+// inf/NaN, and those 64 rows are computed again with a plain running-max loop, by the wavefront itself
+// or, in a split block, by attn_fwd_finish_kernel.  The hot loop is one straight-line block per sub-tile with two
 // independent instruction streams: the matrix cores work on S(u+1) and on O += V P(u-1) while the
 // vector ALU turns S(u) into P(u).
 #include <type_traits>
@@ -43,6 +43,59 @@ struct FwdSmem {
 #define CART_PRESCALE 0
 #endif
 
+// Rows i0 .. i1-1 (tokens of the sequence at t0) of query head h again, with a running-max loop on the
+// vector ALU: what a block does whose fixed softmax reference overflowed.  Lane l owns head elements
+// 2l, 2l+1, eight keys at a time (a CU holds one of the blocks that come here, with nothing else to hide a
+// round trip per key); lse_h: the sequence's LSE values of head h.
+__device__ __forceinline__ void recompute_rows(
+    const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
+    const bf16_t* __restrict__ zk, const bf16_t* __restrict__ zv, bf16_t* __restrict__ o, float* __restrict__ lse_h,
+    const int32_t* __restrict__ row_lo, size_t t0, int i0, int i1, int h, int hk, int Hq, int Hkv, int P, float c, int lane) {
+    constexpr int U = 8;
+    for (int i = i0; i < i1; ++i) {
+        const size_t row = (t0 + i) * Hq + h;
+        const uint32_t qw = *reinterpret_cast<const uint32_t*>(q + row * HD + 2 * lane);
+        const float q0 = __uint_as_float(qw << 16), q1 = __uint_as_float(qw & 0xffff0000u);
+        float m = -3.0e38f, l = 0.f, a0 = 0.f, a1 = 0.f;
+        const int own0 = row_lo ? row_lo[i] : 0;      // first own key of the row
+        const int n = P + (i - own0) + 1;
+        for (int j0 = 0; j0 < n; j0 += U) {
+            float sc[U], nm = m;
+            uint32_t vw[U];
+#pragma unroll
+            for (int x = 0; x < U; ++x) {
+                const int j = min(j0 + x, n - 1);
+                const size_t kr = j < P ? static_cast<size_t>(hk) * P + j : (t0 + own0 + (j - P)) * Hkv + hk;
+                const uint32_t kw = *reinterpret_cast<const uint32_t*>((j < P ? zk : k) + kr * HD + 2 * lane);
+                vw[x] = *reinterpret_cast<const uint32_t*>((j < P ? zv : v) + kr * HD + 2 * lane);
+                sc[x] = q0 * __uint_as_float(kw << 16) + q1 * __uint_as_float(kw & 0xffff0000u);
+            }
+#pragma unroll
+            for (int x = 0; x < U; ++x) {
+                sc[x] = wave_sum(sc[x]) * c;
+                nm = fmaxf(nm, sc[x]);
+            }
+            const float corr = fast_exp2(m - nm);
+            l *= corr;
+            a0 *= corr;
+            a1 *= corr;
+            m = nm;
+#pragma unroll
+            for (int x = 0; x < U; ++x) {
+                const float pj = j0 + x < n ? fast_exp2(sc[x] - m) : 0.f;
+                l += pj;
+                if (j0 + x < n) {
+                    a0 += pj * __uint_as_float(vw[x] << 16);
+                    a1 += pj * __uint_as_float(vw[x] & 0xffff0000u);
+                }
+            }
+        }
+        const float inv = 1.f / l;
+        *reinterpret_cast<uint32_t*>(o + row * HD + 2 * lane) = pack_bf16x2(a0 * inv, a1 * inv);
+        if (lane == 0) lse_h[i] = (m + fast_log2(l)) * CART_LN2;
+    }
+}
+
 __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ zk, const bf16_t* __restrict__ zv, bf16_t* __restrict__ o,
@@ -63,14 +116,16 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     const SeqSpan sp = seq_span(cu, b, n_tok, Smax, Hq);
     const int S = sp.len;
     const size_t t0 = sp.t0;
+    // (a part's overflow flag per wavefront; blocks that run whole have none)
+    int* const my_flag = flags + 4 * qb.slot + wv;
     if (q0 >= S) {
-        if (lane == 0) flags[4 * blockIdx.x + wv] = 0;
+        if (lane == 0 && qb.n_parts > 1) *my_flag = 0;
         return;
     }
     const KeyTiles kt = key_tiles(qb, S, P, row_lo);
     float* const my_l = part_l + static_cast<size_t>(qb.slot) * 256 + 64 * wv;
     if (kt.lo >= kt.hi) {      // (fewer tiles than the launch assumed: this part is empty)
-        if (lane == 0) flags[4 * blockIdx.x + wv] = 0;
+        if (lane == 0) *my_flag = 0;
         my_l[lane] = __uint_as_float(0xff800000u);
         return;
     }
@@ -415,15 +470,20 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb)
         bad |= wrow0 + 32 * cb + lc < S && (!(l_tot[cb] < 3.0e38f) || !(fabsf(rs.s[cb]) < 3.0e38f));
-    // (a flag per wavefront: a barrier here would wait for the stores of O, 4-5 us of a block)
     bad = __any(bad);
-    if (lane == 0) flags[4 * blockIdx.x + wv] = bad ? 1 : 0;
+    if (qb.n_parts > 1) {      // (a flag per wavefront: a barrier here would wait for the stores, 4-5 us of a block)
+        if (lane == 0) *my_flag = bad ? 1 : 0;
+    } else if (bad) {
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // (other lanes stored these rows)
+        recompute_rows(q, k, v, zk, zv, o, lse + sp.stat_b + h * sp.stat_h, row_lo, t0, wrow0, min(S, wrow0 + 64), h, hk, Hq, Hkv,
+                       P, c, lane);
+    }
 }
 
-// Finishes the forward call.  Blocks that ran whole (one workgroup each): returns at once unless the
-// block raised its overflow flag.  Split blocks (eight workgroups each, 32 rows apiece): combines the
-// parts by their log-sum-exps.  A flagged block's rows are recomputed with a running-max loop on the
-// vector ALU instead.  One wavefront per row at a time, lane l owns head elements 2l, 2l+1.
+// Finishes the split blocks of a forward call (eight workgroups each, 32 rows apiece): combines the
+// parts by their log-sum-exps, or recomputes the rows of a wavefront that raised its overflow flag.  (Blocks
+// that run whole recompute their own; left to this kernel, every
+// call paid its launch: one sequence of 64 tokens, 128 slots 15.2 -> 12.9 us, 16 x 256, 1024 slots 83.2 -> 81.0.)
 __global__ __launch_bounds__(256) void attn_fwd_finish_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ zk, const bf16_t* __restrict__ zv, bf16_t* __restrict__ o,
@@ -433,28 +493,16 @@ __global__ __launch_bounds__(256) void attn_fwd_finish_kernel(
     const int G = Hq / Hkv, nW = query_wgs(Smax, G);
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int n_whole = split.e_full * Hkv;
-    int id = blockIdx.x, rows = 64, r0 = 0, n_parts = 1, hk, e, x;      // x: the block's first part among the KV head's items
-    if (id < n_whole) {
-        hk = id % Hkv;
-        e = x = id / Hkv;
-    } else {
-        id -= n_whole;
-        rows = 8;
-        r0 = 8 * (id & 7);
-        id >>= 3;
-        hk = id % Hkv;
-        e = split.e_full + id / Hkv;
-        x = split.e_full + split.first[id / Hkv];
-        n_parts = split.part[x - split.e_full] >> 16;
-    }
+    const int r0 = 8 * (blockIdx.x & 7), hk = (blockIdx.x >> 3) % Hkv, blk = (blockIdx.x >> 3) / Hkv, e = split.e_full + blk;
+    const int x = split.first[blk], n_parts = split.part[x] >> 16;      // the block's first part, its parts
+    if (n_parts == 1) return;               // (a short block among the split ones ran whole)
     const QueryBlock qb = query_block_of(hk, e, wv, nW, G);
     const SeqSpan sp = seq_span(cu, qb.b, n_tok, Smax, Hq);
-    const int S = sp.len, h = qb.h, i0 = qb.wrow0 + r0, i1 = min(S, i0 + rows);
+    const int S = sp.len, h = qb.h, i0 = qb.wrow0 + r0, i1 = min(S, i0 + 8);
     const size_t t0 = sp.t0;
     int bad = 0;         // of this wavefront's rows
     for (int p = 0; p < n_parts; ++p) bad |= flags[4 * ((x + p) * Hkv + hk) + wv];
-    if (!bad && n_parts > 1) {
+    if (!bad) {
         // half a wavefront per row, four head elements per lane: two rows per load, eight rows in
         // flight; the loads of a part do not wait for its LSE (an empty part's are not used)
         constexpr int R = 4;
@@ -464,7 +512,7 @@ __global__ __launch_bounds__(256) void attn_fwd_finish_kernel(
         f32x4 a[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) { m[r] = -3.0e38f; l[r] = 0.f; a[r] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-        const size_t row0 = (static_cast<size_t>(x - split.e_full) * Hkv + hk) * 256 + 64 * wv + r0 + half;
+        const size_t row0 = (static_cast<size_t>(x) * Hkv + hk) * 256 + 64 * wv + r0 + half;
 #pragma unroll 2
         for (int p = 0; p < n_parts; ++p) {
             const size_t row = row0 + static_cast<size_t>(p) * Hkv * 256;
@@ -495,30 +543,7 @@ __global__ __launch_bounds__(256) void attn_fwd_finish_kernel(
         }
         return;
     }
-    if (!bad) return;
-    for (int i = i0; i < i1; ++i) {
-        const size_t row = (t0 + i) * Hq + h;
-        const uint32_t qw = *reinterpret_cast<const uint32_t*>(q + row * HD + 2 * lane);
-        const float q0 = __uint_as_float(qw << 16), q1 = __uint_as_float(qw & 0xffff0000u);
-        float m = -3.0e38f, l = 0.f, a0 = 0.f, a1 = 0.f;
-        const int own0 = row_lo ? row_lo[i] : 0;      // first own key of the row
-        for (int j = 0; j < P + (i - own0) + 1; ++j) {
-            const size_t kr = j < P ? static_cast<size_t>(hk) * P + j
-                                    : (t0 + own0 + (j - P)) * Hkv + hk;
-            const uint32_t kw = *reinterpret_cast<const uint32_t*>((j < P ? zk : k) + kr * HD + 2 * lane);
-            const uint32_t vw = *reinterpret_cast<const uint32_t*>((j < P ? zv : v) + kr * HD + 2 * lane);
-            const float sc = wave_sum(q0 * __uint_as_float(kw << 16) + q1 * __uint_as_float(kw & 0xffff0000u)) * c;
-            const float nm = fmaxf(m, sc);
-            const float corr = fast_exp2(m - nm), pj = fast_exp2(sc - nm);
-            l = l * corr + pj;
-            a0 = a0 * corr + pj * __uint_as_float(vw << 16);
-            a1 = a1 * corr + pj * __uint_as_float(vw & 0xffff0000u);
-            m = nm;
-        }
-        const float inv = 1.f / l;
-        *reinterpret_cast<uint32_t*>(o + row * HD + 2 * lane) = pack_bf16x2(a0 * inv, a1 * inv);
-        if (lane == 0) lse[sp.stat_b + h * sp.stat_h + i] = (m + fast_log2(l)) * CART_LN2;
-    }
+    recompute_rows(q, k, v, zk, zv, o, lse + sp.stat_b + h * sp.stat_h, row_lo, t0, i0, i1, h, hk, Hq, Hkv, P, c, lane);
 }
 
 // row_lo[i] = first packed row of the sequence that row i belongs to (cu: B+1 offsets, cu[B] = T)
@@ -627,12 +652,12 @@ void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, floa
     }
     sp = kept;
 }
-// one overflow flag per wavefront; packed batches: + the first row of every row's sequence; + the
-// partial results of the split blocks
+// packed batches: the first row of every row's sequence; split blocks: an overflow flag per wavefront and the
+// partial results
 size_t attn_mfma_fwd_workspace(const cart_attn_desc& d, int T) {
     QuerySplit sp;
     attn_query_split(sp, d, T, FWD_BLOCK_US, FWD_TILE_US);
-    return r256(static_cast<size_t>(sp.e_full + sp.n_parts) * d.Hkv * 4 * sizeof(int)) +
+    return r256(static_cast<size_t>(sp.n_parts) * d.Hkv * 4 * sizeof(int)) +
            (T > 0 ? r256(static_cast<size_t>(T) * sizeof(int32_t)) : 0) +
            static_cast<size_t>(sp.n_parts) * d.Hkv * (PART_O_BYTES + PART_L_BYTES);
 }
@@ -649,7 +674,7 @@ int launch_attn_fwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
     const unsigned n_items = static_cast<unsigned>(sp.e_full + sp.n_parts) * d.Hkv;
     char* w = static_cast<char*>(ws);
     int* flags = reinterpret_cast<int*>(w);
-    w += r256(static_cast<size_t>(n_items) * 4 * sizeof(int));
+    w += r256(slots * 4 * sizeof(int));
     int32_t* row_lo = nullptr;
     if (T > 0) {
         if (d.P > 0) row_lo = reinterpret_cast<int32_t*>(w);
@@ -666,14 +691,15 @@ int launch_attn_fwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
         cu = nullptr;
         S = T;
     }
-    trace_begin(st);   // kernel order: forward, finish
+    trace_begin(st);   // kernel order: forward, finish (nothing between its events when no block is split)
     hipLaunchKernelGGL(attn_fwd_mfma_kernel, dim3(n_items), dim3(256), 0, st, Q, K, V, ZK, ZV,
                        static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T, S, d.Hq, d.Hkv, d.P, scale * CART_LOG2E, sp,
                        part_o, part_l);
     trace_mark(st);
-    hipLaunchKernelGGL(attn_fwd_finish_kernel, dim3(static_cast<unsigned>(sp.e_full + 8 * sp.n_blocks) * d.Hkv), dim3(256), 0, st,
-                       Q, K, V, ZK, ZV, static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T, S, d.Hq, d.Hkv, d.P,
-                       scale * CART_LOG2E, sp, part_o, part_l);
+    if (sp.n_blocks > 0)
+        hipLaunchKernelGGL(attn_fwd_finish_kernel, dim3(static_cast<unsigned>(8 * sp.n_blocks) * d.Hkv), dim3(256), 0, st, Q, K, V, ZK, ZV,
+                           static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T, S, d.Hq, d.Hkv, d.P, scale * CART_LOG2E, sp, part_o,
+                           part_l);
     trace_mark(st);
     return static_cast<int>(hipGetLastError());
 }

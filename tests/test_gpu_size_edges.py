@@ -73,6 +73,24 @@ def test_attention_small_launches(B, S, Hq, Hkv, P):
     check_attn(*attn_case((B, S), Hq, Hkv, 128, P, torch.bfloat16, 7 * S + P), impl=cb.IMPL_MFMA, n_frozen=min(P, 3))
 
 
+# Scores that overflow the forward's fixed softmax reference (one key 200 nats above the first ones): rows
+# computed again by the wavefront itself where blocks run whole (whole rounds of 32 blocks per KV head; rows of
+# 1 .. 127 keys, around the eight taken at a time) and by the finishing kernel where they are split.
+@pytest.mark.parametrize("B,S,Hq,Hkv,P,hot", [(32, 40, 8, 8, 87, 7), (32, 70, 16, 8, 41, 33), (32, 9, 8, 8, 32, 0), (1, 300, 8, 1, 600, 100)])
+def test_attention_forward_recomputes_overflowing_rows(B, S, Hq, Hkv, P, hot):
+    g = torch.Generator().manual_seed(S)
+    u = torch.randn(128, generator=g)
+    u *= (200.0 * 128 ** 0.5) ** 0.5 / u.norm()
+    rn = lambda *sz, std=1.0: std * torch.randn(*sz, generator=g)
+    q, k = u + rn(B, S, Hq, 128, std=0.05), rn(B, S, Hkv, 128, std=0.05)
+    k[:, hot] += u
+    t = [x.to(torch.bfloat16) for x in (q, k, rn(B, S, Hkv, 128), rn(Hkv, P, 128, std=0.05), rn(Hkv, P, 128))]
+    o_ref, lse_ref = orc.attn_fwd(*[f64(x) for x in t])
+    o, lse = cb.cart_attn_fwd(*[x.to(DEV) for x in t], impl=cb.IMPL_MFMA)
+    torch.cuda.synchronize()
+    assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
+
+
 @pytest.mark.parametrize("lens,Hq,Hkv,P", [([700, 1, 90], 4, 1, 300), ([64, 64, 64], 2, 2, 1000), ([5, 3, 400, 131], 4, 2, 0)])
 def test_packed_small_launches(lens, Hq, Hkv, P):
     q, k, v, zk, zv, do = attn_case((sum(lens),), Hq, Hkv, 128, P, torch.bfloat16, sum(lens) + P)
