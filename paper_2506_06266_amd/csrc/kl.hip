@@ -102,21 +102,41 @@ template <typename T> __device__ __forceinline__ u32x4 kl_vec_grad(const u32x4& 
     return r;
 }
 
+// A row's vectors in slots that start at a 128-byte line of the tensor: the first `lead` slots of a row
+// that starts inside a line belong to the row before it (they are loaded, never used nor stored), and a
+// wavefront's store covers whole lines.  With the row's first vector in slot 0 every wavefront wrote two
+// parts of lines (4096 rows, us a call: 50257 bf16 181 -> 170, fp32 354 -> 322; 80001 bf16 327 -> 309, fp32
+// 551 -> 493).  Rows that nearly fill the registers start at a half or a quarter of a line instead: a wider workgroup, or
+// reading the last slots twice, costs more (4096 x 4099 bf16 22.5 us; at twice the width 31.6).
+struct KlRow : LogitRow {
+    int lead, nslot;    // nslot = lead + nvec
+};
+template <typename T> __device__ __forceinline__ KlRow kl_row(int n, int V, int lead_mask) {
+    KlRow r;
+    static_cast<LogitRow&>(r) = logit_row<T>(n, V);
+    r.lead = r.nvec > 0 ? static_cast<int>((r.row + r.head) / LogitVec<T>::N) & (lead_mask & 7) : 0;
+    r.nslot = r.lead + r.nvec;
+    return r;
+}
 // the thread (of THREADS) that stores element id
-template <typename T, int THREADS> __device__ __forceinline__ int kl_owner(const LogitRow& r, int id) {
+template <typename T, int THREADS> __device__ __forceinline__ int kl_owner(const KlRow& r, int id) {
     const int e = id - r.head, v = e / LogitVec<T>::N;
-    return e < 0 ? id : v < r.nvec ? v & (THREADS - 1) : id - r.nvec * LogitVec<T>::N;
+    return e < 0 ? id : v < r.nvec ? (v + r.lead) & (THREADS - 1) : id - r.nvec * LogitVec<T>::N;
 }
 
-// The body of a row as a buffer resource: a load past its end returns 0 and a store past it is
+// The slots of a row as a buffer resource: a load past its end returns 0 and a store past it is
 // dropped, and an access takes one 32-bit offset instead of a 64-bit address and a predicate.
 struct KlBuf {
     __amdgpu_buffer_rsrc_t r;
 };
-template <typename T> __device__ __forceinline__ KlBuf kl_buf(const T* base, const LogitRow& r) {
-    return KlBuf{__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base + r.row + r.head), 0,
-                                                   static_cast<int>(static_cast<uint32_t>(r.nvec) * 16u), 0x00027000)};
+template <typename T> __device__ __forceinline__ const T* kl_slots(const T* base, const KlRow& r) {
+    return base + (r.row + r.head - static_cast<size_t>(r.lead) * LogitVec<T>::N);
 }
+template <typename T> __device__ __forceinline__ KlBuf kl_buf(const T* base, const KlRow& r) {
+    return KlBuf{__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(kl_slots(base, r)), 0,
+                                                   static_cast<int>(static_cast<uint32_t>(r.nslot) * 16u), 0x00027000)};
+}
+constexpr int KL_DROP = 0x7ffffff0;  // an offset past every row
 constexpr int KL_NT = 2;             // cache policy: non-temporal
 template <int AUX> __device__ __forceinline__ u32x4 kl_ld(const KlBuf& b, int off) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b.r, off, 0, AUX));
@@ -146,7 +166,7 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
 template <typename T, int THREADS, int NV, int NL>
 __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const T* logits, const int32_t* idx,
                                                               const float* logp, T* dlogits, float* row_kl,
-                                                              int N, int V, int K, float scale, int rest) {
+                                                              int N, int V, int K, float scale, int mode /* rest bucket | lead mask << 1 */) {
     constexpr int GRP = NV < 8 ? NV : 8;
     constexpr int NW = THREADS / CART_WAVE, VE = LogitVec<T>::N;
     const KlTeacher tc = kl_teacher(K);
@@ -156,12 +176,12 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     int n = blockIdx.x;
     if (n >= N) return;
-    LogitRow R = logit_row<T>(n, V);
+    KlRow R = kl_row<T>(n, V, mode >> 1);
 
     // vector i of the next row's LDS part, straight into the thread's own slot (clamped to the row)
-    auto lds_fetch = [&](const T* base, const LogitRow& r, int i) __attribute__((always_inline)) {
-        const int v = min((NV + i) * THREADS + tid, max(r.nvec - 1, 0));
-        mfma::dma16(reinterpret_cast<const char*>(base + r.row + r.head), static_cast<uint32_t>(v) * 16u,
+    auto lds_fetch = [&](const T* base, const KlRow& r, int i) __attribute__((always_inline)) {
+        const int v = min((NV + i) * THREADS + tid, max(r.nslot - 1, 0));
+        mfma::dma16(reinterpret_cast<const char*>(kl_slots(base, r)), static_cast<uint32_t>(v) * 16u,
                     mfma::lds_addr(lds_x + i * THREADS + wv * CART_WAVE));
     };
     u32x4 x[NV];
@@ -222,14 +242,15 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         float mx = fmaxf(xs, -2.0e38f);
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            if ((i + 1) * THREADS > R.nvec && i * THREADS + tid >= R.nvec) x[i] = kl_fill<T>();
+            if ((i + 1) * THREADS > R.nslot && i * THREADS + tid >= R.nslot) x[i] = kl_fill<T>();
+            if (i == 0 && tid < R.lead) x[0] = kl_fill<T>();
             mx = kl_vec_max<T>(mx, x[i]);
         }
         if constexpr (NL > 0) {
             mfma::dma_wait();            // the LDS part (each thread reads only what its own lane fetched)
 #pragma unroll
             for (int i = 0; i < NL; ++i)
-                if ((NV + i) * THREADS + tid < R.nvec) mx = kl_vec_max<T>(mx, lds_x[i * THREADS + tid]);
+                if ((NV + i) * THREADS + tid < R.nslot) mx = kl_vec_max<T>(mx, lds_x[i * THREADS + tid]);
         }
         KL_FORGET(x);
         // sweep 2: sum of 2^((x - reference) log2e)
@@ -237,14 +258,14 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         float s0 = fast_exp2(fmaf(xs, CART_LOG2E, c0)), s1 = 0.f;
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
-            if (i * THREADS < R.nvec) kl_vec_sum<T>(s0, s1, x[i], c0);
+            if (i * THREADS < R.nslot) kl_vec_sum<T>(s0, s1, x[i], c0);
             asm volatile("" : "+v"(s0), "+v"(s1));   // summed here: the compiler would sink the adds behind all the exponentials
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (NL > 0) {
 #pragma unroll
             for (int i = 0; i < NL; ++i) {
-                if ((NV + i) * THREADS + tid < R.nvec) kl_vec_sum<T>(s0, s1, lds_x[i * THREADS + tid], c0);
+                if ((NV + i) * THREADS + tid < R.nslot) kl_vec_sum<T>(s0, s1, lds_x[i * THREADS + tid], c0);
                 asm volatile("" : "+v"(s0), "+v"(s1));
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -252,7 +273,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         KL_FORGET(x);
         float sum = s0 + s1;
         const KlBuf src = kl_buf(logits, R), dst = kl_buf(dlogits, R);
-        for (int v = (NV + NL) * THREADS + tid; v < R.nvec; v += THREADS) {   // what is not resident
+        for (int v = (NV + NL) * THREADS + tid; v < R.nslot; v += THREADS) {   // what is not resident
             const u32x4 w = kl_ld<0>(src, v * 16);
             const float m1 = kl_vec_max<T>(mx, w);
             if (m1 > mx) {
@@ -284,27 +305,27 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         // memory bus around too often (16384 rows of 128256 bf16 logits, us: groups of 1 / 2 / 4 / 8 /
         // 16 vectors -> 1674 / 1672 / 1627 / 1605 / 1603; 2048 fp32 rows: 434 / 433 / 426 / 419 / 415).
         float coef = M, extra = 0.f;
-        if (rest) {
+        if (mode & 1) {
             kl_rest_terms(tc, K, lse2, M, rest_terms);
             __syncthreads();
             coef = rest_terms[0];
             extra = rest_terms[1];
         }
         const KlGrad g = kl_grad_coef<T>(scale * coef, lse2);
-        const LogitRow Rn = logit_row<T>(more ? n_next : n, V);
+        const KlRow Rn = kl_row<T>(more ? n_next : n, V, mode >> 1);
         if (more) fetch_logit(Rn);
         if (tid < R.head + R.tail)
             elem<T>::store(dlogits + R.row + logit_single<T>(R, tid), g.c * fast_exp2(fmaf(xs, CART_LOG2E, -lse2)));
         xs = -3.0e38f;
         if (more && tid < Rn.head + Rn.tail) xs = elem<T>::load(logits + Rn.row + logit_single<T>(Rn, tid));
-        for (int v = (NV + NL) * THREADS + tid; v < R.nvec; v += THREADS)
+        for (int v = (NV + NL) * THREADS + tid; v < R.nslot; v += THREADS)
             kl_st(dst, kl_vec_grad<T>(kl_ld<KL_NT>(src, v * 16), g), v * 16);
         const KlBuf src_next = kl_buf(logits, Rn);
 #pragma unroll
         for (int i0 = 0; i0 < NV; i0 += GRP) {
 #pragma unroll
             for (int i = i0; i < i0 + GRP; ++i) {
-                if (i * THREADS < R.nvec) kl_st(dst, kl_vec_grad<T>(x[i], g), voff + i * STEP);
+                if (i * THREADS < R.nslot) kl_st(dst, kl_vec_grad<T>(x[i], g), i == 0 && tid < R.lead ? KL_DROP : voff + i * STEP);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (more) {
@@ -331,7 +352,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             const int id = tc.idx[j];
             if (id >= 0 && kl_owner<T, THREADS>(R, id) == tid) {
                 const float s = fast_exp2(fmaf(tc.x[j], CART_LOG2E, -lse2));
-                elem<T>::store(dlogits + R.row + id, scale * ((rest ? 1.f : M) * s - tc.t[j]));
+                elem<T>::store(dlogits + R.row + id, scale * ((mode & 1 ? 1.f : M) * s - tc.t[j]));
             }
         }
         kl_row_value(tc, K, lse2 * CART_LN2, extra, row_kl + n);
@@ -366,9 +387,11 @@ template <typename T, int THREADS, int NV, int NL>
 static void resident(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
                      float* rows, hipStream_t st) {
     const int slots = 256 * ((NV > 4 ? 1024 : 2048) / THREADS);      // workgroups an MI355X keeps resident
+    const int spare = (NV + NL) * THREADS - d.V / LogitVec<T>::N;
+    const int lead_mask = spare < 0 || spare >= 7 ? 7 : spare >= 3 ? 3 : spare >= 1 ? 1 : 0;
     hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
                        dim3(THREADS), static_cast<unsigned>(d.K) * 16u, st, static_cast<const T*>(logits), idx, logp,
-                       static_cast<T*>(d_logits), rows, d.N, d.V, d.K, d.scale, d.mode == CART_KL_REST ? 1 : 0);
+                       static_cast<T*>(d_logits), rows, d.N, d.V, d.K, d.scale, (d.mode == CART_KL_REST ? 1 : 0) | lead_mask << 1);
 }
 template <typename T, int NL>
 static void launch_rows(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,

@@ -122,7 +122,7 @@ def test_attention_vector(dtype, B, S, Hq, Hkv, D, P):
 
 
 # Loss: every width of the row kernel at its last size and just past it, rows that start at every
-# offset from a 16-byte boundary (odd vocabularies), more records than threads, more rows than the
+# offset from a 16-byte boundary and a 128-byte line (odd vocabularies), more records than threads, more rows than the
 # launch has workgroups.  (data type, rows, vocabulary, records)
 LOSS_CASES = [
     (torch.bfloat16, 9, 5, 3), (torch.bfloat16, 5, 4096, 20), (torch.bfloat16, 9, 4107, 200), (torch.bfloat16, 3, 8199, 20),
@@ -131,6 +131,9 @@ LOSS_CASES = [
     (torch.float32, 7, 3, 2), (torch.float32, 5, 2048, 140), (torch.float32, 5, 2055, 20), (torch.float32, 5, 4099, 20),
     (torch.float32, 3, 16385, 20), (torch.float32, 3, 32771, 20), (torch.float32, 2, 65536, 20), (torch.float32, 5, 65541, 1024),
     (torch.float32, 300, 65541, 5), (torch.float32, 3, 98307, 20), (torch.float32, 3, 120001, 20), (torch.float32, 2050, 2060, 4),
+    # (slots counted from a 128-byte line, up to seven more than vectors: the fullest rows of each width)
+    (torch.bfloat16, 9, 4047, 20), (torch.bfloat16, 9, 4049, 20), (torch.bfloat16, 9, 32719, 20), (torch.bfloat16, 9, 65487, 20),
+    (torch.bfloat16, 9, 131023, 20), (torch.float32, 33, 2023, 20), (torch.float32, 33, 16359, 20), (torch.float32, 9, 98279, 20),
 ]
 
 
