@@ -133,9 +133,10 @@ typedef struct {
 } cart_attn_varlen_desc;
 
 /* Bytes of workspace each entry point needs for the given descriptor (0 on an invalid one).  The
- * decode figures depend on the number of CUs of the current device as well (the own-KV part is cut
- * into as many ranges as the chip keeps wavefronts resident): ask with the device current that the
- * call will run on. */
+ * attention and decode figures depend on the number of CUs of the current device as well (work is cut
+ * into as many parts as the chip keeps resident): ask with the device current that the call will run
+ * on.  They do not grow with the sizes: a small problem is cut into more parts than one that fills the
+ * chip, so a workspace kept for several descriptors takes the largest of their figures. */
 size_t cart_attn_fwd_workspace(const cart_attn_desc *desc);
 size_t cart_attn_bwd_workspace(const cart_attn_desc *desc);
 size_t cart_attn_varlen_fwd_workspace(const cart_attn_varlen_desc *desc);

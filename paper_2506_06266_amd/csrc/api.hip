@@ -343,6 +343,6 @@ const char* cart_status_str(cart_status s) {
     return "unknown status";
 }
 
-int cart_version(void) { return 150; }   // 1.5: + cart_decode_static, calibration hooks; backward in two kernels
+int cart_version(void) { return 160; }   // 1.6: split launches, one loss and one top-k kernel, fp32 attention on the matrix cores
 
 }  // extern "C"
