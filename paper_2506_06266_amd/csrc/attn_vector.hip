@@ -16,14 +16,14 @@
 // small problem is bound by latency -- its launches, one round trip for the operands, one for the
 // sums -- and a large one by the matrix cores.  Against one wavefront per row or key, a serial chain of
 // shuffles and exponentials per key, us for forward and backward: 2 sequences of 64 tokens, 2 / 1
-// heads of 64, 32 slots: 175 -> 38 (launches); 4 of 256, 8 / 2 heads, 256 slots: head_dim 64 2268 -> 174,
+// heads of 64, 32 slots: 175 -> 31 (launches); 4 of 256, 8 / 2 heads, 256 slots: head_dim 64 2268 -> 174,
 // head_dim 128 2855 -> 356.
 #include "cart_common.h"
 
 namespace cart {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr float VEC_HIDDEN = -1.0e30f;
+constexpr float VEC_HIDDEN = -3.0e38f;
 
 __device__ __forceinline__ f32x4 mma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 // sum / maximum over the four lanes that hold the same column
@@ -103,6 +103,40 @@ __device__ __forceinline__ void accumulate(f32x4 (&acc)[NB], const ColFrag<NB>& 
 #pragma unroll
         for (int db = 0; db < NB; ++db) acc[db] = mma4(x.v[db][r], w[r], acc[db]);
 }
+// A hidden pair's weight is 0, and 0 times a NaN or an infinity of the hidden row (padding behind a
+// sequence's last token, say) is not.  So a block with hidden pairs and such a row adds its rows one at a
+// time, each to the columns that see it.  vis: which of the lane's four rows its column sees.
+template <int NB> __device__ __forceinline__ bool any_nonfinite(const ColFrag<NB>& x) {
+    float t = 0.f;
+#pragma unroll
+    for (int db = 0; db < NB; ++db)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) t += x.v[db][r] - x.v[db][r];
+    return __any(t != 0.f);
+}
+template <int NB>
+__device__ __forceinline__ void accumulate_visible(f32x4 (&acc)[NB], const ColFrag<NB>& x, const f32x4& w, uint32_t vis, bool hidden,
+                                                   int c, int g) {
+    if (!hidden || !any_nonfinite(x)) {
+        accumulate(acc, x, w);
+        return;
+    }
+#pragma unroll 1
+    for (int u = 0; u < 4; ++u) {
+        const uint32_t sees = __shfl(vis, 16 * u + c, CART_WAVE);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const float wr = __shfl(w[r], 16 * u + c, CART_WAVE);
+#pragma unroll
+            for (int db = 0; db < NB; ++db)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float xe = __shfl(x.v[db][r], 16 * u + 4 * g + e, CART_WAVE);
+                    acc[db][e] = (sees >> r) & 1 ? fmaf(wr, xe, acc[db][e]) : acc[db][e];
+                }
+        }
+    }
+}
 template <int NB> __device__ __forceinline__ void clear(f32x4 (&acc)[NB]) {
 #pragma unroll
     for (int db = 0; db < NB; ++db) acc[db] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -148,10 +182,12 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
         const ColFrag<NB> vc = col_frag<T, NB>(vr, D, c);
         f32x4 s = contract(kf, qf);
         float tm = VEC_HIDDEN;
+        uint32_t vis = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int j = j0 + 4 * g + r;
-            s[r] = j <= last ? s[r] * c2 : VEC_HIDDEN;
+            const bool sees = j0 + 4 * g + r <= last;
+            vis |= sees ? 1u << r : 0u;
+            s[r] = sees ? s[r] * c2 : VEC_HIDDEN;
             tm = fmaxf(tm, s[r]);
         }
         const float nm = fmaxf(m, col_max(tm)), alpha = fast_exp2(m - nm);
@@ -159,13 +195,13 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
         l *= alpha;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            p[r] = s[r] > 0.5f * VEC_HIDDEN ? fast_exp2(s[r] - nm) : 0.f;
+            p[r] = (vis >> r) & 1 ? fast_exp2(s[r] - nm) : 0.f;      // (a NaN score reaches the row)
             l += p[r];
         }
         m = nm;
 #pragma unroll
         for (int db = 0; db < NB; ++db) acc[db] *= alpha;
-        accumulate(acc, vc, p);
+        accumulate_visible(acc, vc, p, vis, j0 + 15 > P + i0, c, g);
     }
     l = col_sum(l);
     to_lds(sm_o[wv], acc, c, g);
@@ -237,12 +273,14 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_vector(
         const ColFrag<NB> kc = col_frag<T, NB>(kr, D, c);
         const f32x4 s = contract(kf, qf), dp = contract(vf, gf);
         f32x4 ds;
+        uint32_t vis = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int j = j0 + 4 * g + r;
-            ds[r] = j <= last ? fast_exp2(fmaf(s[r], c2, -l2)) * (dp[r] - dl) : 0.f;
+            const bool sees = j0 + 4 * g + r <= last;
+            vis |= sees ? 1u << r : 0u;
+            ds[r] = sees ? fast_exp2(fmaf(s[r], c2, -l2)) * (dp[r] - dl) : 0.f;
         }
-        accumulate(acc, kc, ds);
+        accumulate_visible(acc, kc, ds, vis, j0 + 15 > P + i0, c, g);
     }
     to_lds(sm_o[wv], acc, c, g);
     __syncthreads();
@@ -312,22 +350,26 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(
         }
         const f32x4 s = contract(qf, kf), dp = contract(gf, vf);
         f32x4 p, ds;
+        uint32_t vis = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = i0 + 4 * g + r;
-            p[r] = i < S && (prefix || i >= key0 + c) ? fast_exp2(fmaf(s[r], c2, -l2[r])) : 0.f;
-            ds[r] = p[r] * (dp[r] - dl[r]);
+            const bool seen = i < S && (prefix || i >= key0 + c);
+            vis |= seen ? 1u << r : 0u;
+            p[r] = seen ? fast_exp2(fmaf(s[r], c2, -l2[r])) : 0.f;
+            ds[r] = seen ? p[r] * (dp[r] - dl[r]) : 0.f;
         }
+        const bool hidden = i0 + 16 > S || (!prefix && i0 == key0);
         if constexpr (NB > 8) {
             asm volatile("" ::: "memory");
             gc = col_frag<T, NB>(gr, D, c);
         }
-        accumulate(av, gc, p);
+        accumulate_visible(av, gc, p, vis, hidden, c, g);
         if constexpr (NB > 8) {
             asm volatile("" ::: "memory");
             qc = col_frag<T, NB>(qr, D, c);
         }
-        accumulate(ak, qc, ds);
+        accumulate_visible(ak, qc, ds, vis, hidden, c, g);
     }
     to_lds(sm_k[wv], ak, c, g);
     to_lds(sm_v[wv], av, c, g);

@@ -121,6 +121,36 @@ def test_attention_vector(dtype, B, S, Hq, Hkv, D, P):
     check_attn(*attn_case((B, S), Hq, Hkv, D, P, dtype, S + D), impl=cb.IMPL_VECTOR, n_frozen=min(P, 2))
 
 
+# A NaN or an infinity reaches exactly the results whose sums hold it: tokens 11 .. leave the rows before
+# them alone (padding behind a sequence's end), tokens .. 4 the gradients of the keys behind them.
+@pytest.mark.parametrize("D", [64, 128, 256])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_attention_vector_hidden_nonfinite(D, bad):
+    t = attn_case((2, 21), 2, 1, D, 5, torch.float32, D)
+    n = [f64(x) for x in t]
+    o_ref, lse_ref = orc.attn_fwd(*n[:5])
+    g_ref = orc.attn_bwd(*n)
+    q, k, v, zk, zv, do = (x.to(DEV) for x in t)
+    o0, lse0 = cb.cart_attn_fwd(q, k, v, zk, zv, impl=cb.IMPL_VECTOR)
+    kb, vb = k.clone(), v.clone()
+    kb[:, 11:] = bad
+    vb[:, 11:] = bad
+    o, lse = cb.cart_attn_fwd(q, kb, vb, zk, zv, impl=cb.IMPL_VECTOR)
+    dq = cb.cart_attn_bwd(q, kb, vb, zk, zv, o0, lse0, do, impl=cb.IMPL_VECTOR)[0]
+    qb, db = q.clone(), do.clone()
+    qb[:, :5] = bad
+    db[:, :5] = bad
+    _, dk, dv, _, _ = cb.cart_attn_bwd(qb, k, v, zk, zv, o0, lse0, db, impl=cb.IMPL_VECTOR)
+    torch.cuda.synchronize()
+    tol = TOL[torch.float32]
+    assert rel_err(o[:, :11], o_ref[:, :11]) <= tol and rel_err(lse[:, :, :11], lse_ref[:, :, :11]) <= tol
+    assert rel_err(dq[:, :11], g_ref[0][:, :11]) <= tol
+    assert rel_err(dk[:, 5:], g_ref[1][:, 5:]) <= tol and rel_err(dv[:, 5:], g_ref[2][:, 5:]) <= tol
+    assert not torch.isfinite(o[:, 11:]).any() and not torch.isfinite(dk[:, :5]).any()
+    if bad != bad:
+        assert torch.isnan(o[:, 11:]).all() and torch.isnan(dq[:, 11:]).all() and torch.isnan(dv[:, :5]).all()
+
+
 # Loss: every width of the row kernel at its last size and just past it, rows that start at every
 # offset from a 16-byte boundary and a 128-byte line (odd vocabularies), more records than threads, more rows than the
 # launch has workgroups.  (data type, rows, vocabulary, records)
