@@ -105,19 +105,20 @@ __device__ __forceinline__ void accumulate(f32x4 (&acc)[NB], const ColFrag<NB>& 
 }
 // A hidden pair's weight is 0, and 0 times a NaN or an infinity of the hidden row (padding behind a
 // sequence's last token, say) is not.  So a block with hidden pairs and such a row adds its rows one at a
-// time, each to the columns that see it.  vis: which of the lane's four rows its column sees.
+// time, each to the columns that see it.  (A second pass over all blocks by a wavefront whose sums are
+// not finite, instead of this check, measured the same on the smallest problem: 31.2 us against 30.2.)  vis: which of the lane's four rows its column sees.
 template <int NB> __device__ __forceinline__ bool any_nonfinite(const ColFrag<NB>& x) {
-    float t = 0.f;
+    f32x4 t = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int db = 0; db < NB; ++db)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) t += x.v[db][r] - x.v[db][r];
-    return __any(t != 0.f);
+        for (int r = 0; r < 4; ++r) t[r] = fmaf(x.v[db][r], 0.f, t[r]);
+    return __any(t[0] + t[1] + t[2] + t[3] != 0.f);
 }
 template <int NB>
 __device__ __forceinline__ void accumulate_visible(f32x4 (&acc)[NB], const ColFrag<NB>& x, const f32x4& w, uint32_t vis, bool hidden,
                                                    int c, int g) {
-    if (!hidden || !any_nonfinite(x)) {
+    if (__builtin_expect(!hidden || !any_nonfinite(x), 1)) {
         accumulate(acc, x, w);
         return;
     }
