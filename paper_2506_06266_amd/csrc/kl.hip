@@ -125,18 +125,19 @@ template <typename T, int THREADS> __device__ __forceinline__ int kl_owner(const
 }
 
 // The slots of a row as a buffer resource: a load past its end returns 0 and a store past it is
-// dropped, and an access takes one 32-bit offset instead of a 64-bit address and a predicate.
+// dropped, and an access takes one 32-bit offset instead of a 64-bit address and a predicate.  Rows of more
+// than 1 GB (LONG) reach only their first vectors so: a resource ends below KL_DROP and its offsets below 4 GB.
 struct KlBuf {
     __amdgpu_buffer_rsrc_t r;
 };
+constexpr int KL_DROP = 0x7ffffff0;  // an offset past every resource
 template <typename T> __device__ __forceinline__ const T* kl_slots(const T* base, const KlRow& r) {
     return base + (r.row + r.head - static_cast<size_t>(r.lead) * LogitVec<T>::N);
 }
-template <typename T> __device__ __forceinline__ KlBuf kl_buf(const T* base, const KlRow& r) {
+template <bool LONG, typename T> __device__ __forceinline__ KlBuf kl_buf(const T* base, const KlRow& r) {
     return KlBuf{__builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(kl_slots(base, r)), 0,
-                                                   static_cast<int>(static_cast<uint32_t>(r.nslot) * 16u), 0x00027000)};
+                                                   (LONG ? KL_DROP / 16 : r.nslot) * 16, 0x00027000)};
 }
-constexpr int KL_DROP = 0x7ffffff0;  // an offset past every row
 constexpr int KL_NT = 2;             // cache policy: non-temporal
 template <int AUX> __device__ __forceinline__ u32x4 kl_ld(const KlBuf& b, int off) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b.r, off, 0, AUX));
@@ -163,7 +164,7 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
 //   16384 x 128256 bf16  1649 -> 1593 (5.28 TB/s)     4096 x 32000 bf16  153 -> 100
 //    1024 x  50257 bf16   146 ->   47                16384 x  1000 fp32   54 ->  47
 //    2048 x 128256 fp32   785 ->  412 (423 without the LDS part)
-template <typename T, int THREADS, int NV, int NL>
+template <typename T, int THREADS, int NV, int NL, bool LONG = false>
 __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const T* logits, const int32_t* idx,
                                                               const float* logp, T* dlogits, float* row_kl,
                                                               int N, int V, int K, float scale, int mode /* rest bucket | lead mask << 1 */) {
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         if (my_id >= 0) my_x = elem<T>::load(logits + r.row + my_id);
     };
     {
-        const KlBuf src = kl_buf(logits, R);
+        const KlBuf src = kl_buf<LONG>(logits, R);
         fetch_record(n);          // (ahead of the row: what depends on it need not wait for the row)
 #pragma unroll
         for (int i = 0; i < NV; ++i) x[i] = kl_ld<KL_NT>(src, voff + i * STEP);
@@ -272,9 +273,9 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         }
         KL_FORGET(x);
         float sum = s0 + s1;
-        const KlBuf src = kl_buf(logits, R), dst = kl_buf(dlogits, R);
+        const KlBuf src = kl_buf<LONG>(logits, R), dst = kl_buf<LONG>(dlogits, R);
         for (int v = (NV + NL) * THREADS + tid; v < R.nslot; v += THREADS) {   // what is not resident
-            const u32x4 w = kl_ld<0>(src, v * 16);
+            const u32x4 w = LONG ? reinterpret_cast<const u32x4*>(kl_slots(logits, R))[v] : kl_ld<0>(src, v * 16);
             const float m1 = kl_vec_max<T>(mx, w);
             if (m1 > mx) {
                 const float c1 = -m1 * CART_LOG2E;
@@ -318,9 +319,14 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             elem<T>::store(dlogits + R.row + logit_single<T>(R, tid), g.c * fast_exp2(fmaf(xs, CART_LOG2E, -lse2)));
         xs = -3.0e38f;
         if (more && tid < Rn.head + Rn.tail) xs = elem<T>::load(logits + Rn.row + logit_single<T>(Rn, tid));
-        for (int v = (NV + NL) * THREADS + tid; v < R.nslot; v += THREADS)
-            kl_st(dst, kl_vec_grad<T>(kl_ld<KL_NT>(src, v * 16), g), v * 16);
-        const KlBuf src_next = kl_buf(logits, Rn);
+        for (int v = (NV + NL) * THREADS + tid; v < R.nslot; v += THREADS) {
+            if constexpr (LONG)
+                reinterpret_cast<u32x4*>(const_cast<T*>(kl_slots(dlogits, R)))[v] =
+                    kl_vec_grad<T>(reinterpret_cast<const u32x4*>(kl_slots(logits, R))[v], g);
+            else
+                kl_st(dst, kl_vec_grad<T>(kl_ld<KL_NT>(src, v * 16), g), v * 16);
+        }
+        const KlBuf src_next = kl_buf<LONG>(logits, Rn);
 #pragma unroll
         for (int i0 = 0; i0 < NV; i0 += GRP) {
 #pragma unroll
@@ -383,13 +389,13 @@ __global__ __launch_bounds__(1024) void kl_reduce_rows(const float* row_kl, int 
     }
 }
 
-template <typename T, int THREADS, int NV, int NL>
+template <typename T, int THREADS, int NV, int NL, bool LONG = false>
 static void resident(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
                      float* rows, hipStream_t st) {
     const int slots = 256 * ((NV > 4 ? 1024 : 2048) / THREADS);      // workgroups an MI355X keeps resident
     const int spare = (NV + NL) * THREADS - d.V / LogitVec<T>::N;
     const int lead_mask = spare < 0 || spare >= 7 ? 7 : spare >= 3 ? 3 : spare >= 1 ? 1 : 0;
-    hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
+    hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL, LONG>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
                        dim3(THREADS), static_cast<unsigned>(d.K) * 16u, st, static_cast<const T*>(logits), idx, logp,
                        static_cast<T*>(d_logits), rows, d.N, d.V, d.K, d.scale, (d.mode == CART_KL_REST ? 1 : 0) | lead_mask << 1);
 }
@@ -402,7 +408,8 @@ static void launch_rows(const cart_kl_desc& d, const void* logits, const int32_t
     else if (nvec <= 256 * 16) resident<T, 256, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec <= 512 * 16) resident<T, 512, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec <= 1024 * 16) resident<T, 1024, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
-    else resident<T, 1024, 16, NL>(d, logits, idx, logp, d_logits, rows, st);
+    else if (nvec < 1L << 26) resident<T, 1024, 16, NL>(d, logits, idx, logp, d_logits, rows, st);
+    else resident<T, 1024, 16, NL, true>(d, logits, idx, logp, d_logits, rows, st);
 }
 
 int launch_kl(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp,

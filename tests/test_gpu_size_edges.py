@@ -198,6 +198,37 @@ def test_loss_rows(dtype, N, V, K):
         assert rel_err(row, kl_ref) <= 1e-4 + ill
 
 
+# Rows of more than 2 GB (bf16; the second starts inside a 128-byte line) and more than 4 GB (fp32): past what
+# a 31-bit and a 32-bit offset reach.
+@pytest.mark.parametrize("dtype,N,V", [(torch.bfloat16, 2, 2 ** 30 + 9), (torch.float32, 1, 2 ** 30 + 5)], ids=["bf16", "f32"])
+def test_loss_rows_past_two_and_four_gigabytes(dtype, N, V):
+    chunk = 2 ** 26
+    x = torch.empty(N, V, dtype=dtype, device=DEV)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    for n in range(N):
+        for c in x[n].split(chunk):
+            c.copy_(torch.randn(c.numel(), generator=g, device=DEV))
+    idx = torch.tensor([[3, V // 2 + 1, V - 2]] * N, dtype=torch.int32, device=DEV)
+    lp = torch.log(torch.tensor([[0.5, 0.3, 0.1]] * N, device=DEV))
+    scale = float(2 ** 30)
+    row = torch.empty(N, device=DEV)
+    loss, dl = cb.cart_distill_kl_fwd_bwd(x, idx, lp, scale, row_kl=row)
+    t, M = lp.double().exp(), lp.double().exp().sum(1)
+    for n in range(N):
+        lse = torch.logsumexp(torch.stack([torch.logsumexp(c.double(), 0) for c in x[n].split(chunk)]), 0)
+        kl = (t[n] * (lp[n].double() - x[n, idx[n].long()].double() + lse)).sum()
+        assert abs(row[n].item() - kl.item()) <= 1e-4 * abs(kl.item())
+        for c0 in range(0, V, chunk):
+            ref = scale * M[n] * torch.exp(x[n, c0:c0 + chunk].double() - lse)
+            for j in range(3):
+                i = int(idx[n, j]) - c0
+                if 0 <= i < ref.numel():
+                    ref[i] -= scale * t[n, j]
+            got = dl[n, c0:c0 + chunk].double()
+            # (every element on its own: one rounding of the result, and the exponent's rounding, 2^-24 of |x log2 e - lse2| < 64)
+            assert ((got - ref).abs() <= (2.0 ** -8 if dtype == torch.bfloat16 else 2e-5) * ref.abs()).all(), (n, c0)
+
+
 # Teacher records: the three widths of the row kernel at and past their last size, rows starting at
 # every offset, K at the edges of the widths and beyond the finite logits of a row, rows made of ties.
 TOPK_CASES = [
