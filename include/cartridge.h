@@ -135,8 +135,8 @@ typedef struct {
 /* Bytes of workspace each entry point needs for the given descriptor (0 on an invalid one).  The
  * attention and decode figures depend on the number of CUs of the current device as well (work is cut
  * into as many parts as the chip keeps resident): ask with the device current that the call will run
- * on.  They do not grow with the sizes: a small problem is cut into more parts than one that fills the
- * chip, so a workspace kept for several descriptors takes the largest of their figures. */
+ * on.  An attention workspace also serves every call of the same heads, dtype and layout none of whose
+ * sizes (B, S, P; T, B, max_seqlen, P) is larger: one sized for a program's largest batch can be kept. */
 size_t cart_attn_fwd_workspace(const cart_attn_desc *desc);
 size_t cart_attn_bwd_workspace(const cart_attn_desc *desc);
 size_t cart_attn_varlen_fwd_workspace(const cart_attn_varlen_desc *desc);

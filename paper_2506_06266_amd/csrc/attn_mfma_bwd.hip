@@ -426,12 +426,14 @@ bool attn_mfma_bwd_supported(const cart_attn_desc& d) { return d.dtype == CART_B
 
 // the fused dK + dV kernel (attn_mfma_bwd_kv.hip)
 KvPlan plan_bwd_kv(const cart_attn_desc& d, long tokens);
+size_t bwd_kv_most(const cart_attn_desc& d, long tokens);
 void launch_attn_bwd_kv(const cart_attn_desc& d, float scale, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
                         const bf16_t* ZK, const bf16_t* ZV, const bf16_t* DO, const float* lse2, const float* delta,
                         bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, float* own_k, float* own_v, const int32_t* cu,
                         int n_tok, const KvPlan& plan, hipStream_t st);
 // the split of the query blocks (attn_mfma_fwd.hip)
 void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, float a, float b);
+size_t attn_query_parts(const cart_attn_desc& d, int T);
 
 static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 
@@ -441,23 +443,23 @@ static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 struct BwdLayout {
     KvPlan kv;
     QuerySplit split;
-    size_t rows, part, dq, own, row_lo;
-    size_t total() const { return 2 * rows + 2 * part + dq + 2 * own + row_lo; }
+    size_t rows, part, dq, own;
 };
+static size_t bwd_rows_bytes(const cart_attn_desc& d, long tokens) { return r256(static_cast<size_t>(tokens) * d.Hq * sizeof(float)); }
 static void bwd_layout(BwdLayout& w, const cart_attn_desc& d, int T) {
     const long tokens = T > 0 ? T : static_cast<long>(d.B) * d.S;
     w.kv = plan_bwd_kv(d, tokens);
     attn_query_split(w.split, d, T, DQ_BLOCK_US, DQ_TILE_US);
-    w.rows = r256(static_cast<size_t>(tokens) * d.Hq * sizeof(float));
+    w.rows = bwd_rows_bytes(d, tokens);
     w.part = r256(static_cast<size_t>(w.kv.n_part) * d.Hkv * d.P * HD * sizeof(float));
     w.dq = static_cast<size_t>(w.split.n_parts) * d.Hkv * PART_O_BYTES;
     w.own = w.kv.head_parts > 1 ? r256(static_cast<size_t>(w.kv.head_parts) * tokens * d.Hkv * HD * sizeof(float)) : 0;
-    w.row_lo = T > 0 ? r256(static_cast<size_t>(T) * sizeof(int32_t)) : 0;
 }
-size_t attn_mfma_bwd_workspace(const cart_attn_desc& d, long tokens) {
-    BwdLayout w;
-    bwd_layout(w, d, tokens >= 0 ? static_cast<int>(tokens) : 0);
-    return w.total() - w.rows;      // (beyond the delta array)
+// (beyond the delta array; the partials at their most for this problem or any smaller one)
+size_t attn_mfma_bwd_workspace(const cart_attn_desc& d, int T) {
+    const long tokens = T > 0 ? T : static_cast<long>(d.B) * d.S;
+    return bwd_rows_bytes(d, tokens) + bwd_kv_most(d, tokens) + attn_query_parts(d, T) * d.Hkv * PART_O_BYTES +
+           (T > 0 ? r256(static_cast<size_t>(T) * sizeof(int32_t)) : 0);
 }
 
 int launch_attn_bwd_mfma(const cart_attn_desc& d, float scale, const void* q, const void* k,
@@ -481,7 +483,7 @@ int launch_attn_bwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
     // one sequence of T rows and the first row of every row's sequence)
     int32_t* row_lo = nullptr;
     if (cu && d.P > 0) {
-        row_lo = reinterpret_cast<int32_t*>(take(L.row_lo));
+        row_lo = reinterpret_cast<int32_t*>(w);
         launch_row_lo(cu, d.B, T, row_lo, st);
     }
     const int32_t* q_cu = row_lo ? nullptr : cu;

@@ -623,6 +623,21 @@ __global__ __launch_bounds__(256, 1) void attn_bwd_kv_kernel(KvArgs args) {
 //   B 3  S 1659 32 / 8 heads P 723    n1/h1 616  n2/h1 459  n3/h1 512  n6/h1 473
 constexpr float KV_BLOCK_US = 10.f, KV_LIGHT_US = 1.4f, KV_FULL_US = 1.8f, KV_US_PER_MB = 0.6f;
 constexpr int KV_MAX_CUS = 256;
+constexpr int KV_MAX_CHUNKS = 32;
+// Partials beyond the first chunk's: 192 MB at most (the cheapest cuts of 6000 problems of up to 8192 slots had
+// 178 at most, 99.8 % of them 128)
+constexpr size_t KV_MOST_EXTRA = static_cast<size_t>(192) << 20;
+static size_t kv_chunk_bytes(const cart_attn_desc& d) { return 2 * static_cast<size_t>(d.Hkv) * d.P * HD * sizeof(float); }
+static size_t kv_own_bytes(const cart_attn_desc& d, long tokens, int head_parts) {
+    return head_parts > 1 ? 2 * static_cast<size_t>(head_parts) * tokens * d.Hkv * HD * sizeof(float) : 0;
+}
+// bytes of the partials at their most, for this problem or any smaller one
+size_t bwd_kv_most(const cart_attn_desc& d, long tokens) {
+    const long chunks = (tokens + KV_MIN_CHUNK - 1) / KV_MIN_CHUNK;
+    const size_t extra = static_cast<size_t>((chunks < KV_MAX_CHUNKS ? chunks : KV_MAX_CHUNKS) - 1) * kv_chunk_bytes(d) +
+                         kv_own_bytes(d, tokens, d.Hq / d.Hkv);
+    return kv_chunk_bytes(d) + (extra < KV_MOST_EXTRA ? extra : KV_MOST_EXTRA);
+}
 
 static KvPlan search_plan(const cart_attn_desc& d, long tokens, int cus) {
     const int G = d.Hq / d.Hkv, nT = (d.S + KV_TILE - 1) / KV_TILE;
@@ -636,13 +651,14 @@ static KvPlan search_plan(const cart_attn_desc& d, long tokens, int cus) {
         const long n_own = static_cast<long>(nOb) * d.B * hp;
         if (hp > 1 && n_own > 4L * M) break;            // (plenty of own-key workgroups as it is)
         int last = 0;
-        for (int n = 1; n <= (d.P > 0 ? 32 : 1); n += 1 + n / 8) {
+        for (int n = 1; n <= (d.P > 0 ? KV_MAX_CHUNKS : 1); n += 1 + n / 8) {
             KvPlan p;
             p.chunk = static_cast<int>((((tokens + n - 1) / n) + KV_TILE - 1) / KV_TILE * KV_TILE);
             p.n_part = static_cast<int>((tokens + p.chunk - 1) / p.chunk);
             p.head_parts = hp;
             if (p.n_part == last || (n > 1 && p.chunk < KV_MIN_CHUNK)) break;
             last = p.n_part;
+            if (static_cast<size_t>(p.n_part - 1) * kv_chunk_bytes(d) + kv_own_bytes(d, tokens, hp) > KV_MOST_EXTRA) break;
             const long n_pre = static_cast<long>(nPb) * p.n_part;
             const bool full_pre = 4 * n_pre >= 3L * M, full_own = 4 * n_own >= 3L * M;
             const float bp = full_pre ? KV_FULL_US : (4 * (n_pre + n_own) >= 3L * M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);

@@ -573,11 +573,16 @@ int launch_row_lo(const int32_t* cu, int B, int T, int32_t* row_lo, hipStream_t 
 // different lengths (long sequences, short prefix) even each other out: not split.
 constexpr float SPLIT_FIX = 4.f, SPLIT_PER = 0.05f;
 
+// blocks per KV head the chip runs at one time
+static int query_slots(int Hkv) {
+    const int n = device_cus() / Hkv;
+    return n < 1 ? 1 : (n > MAX_SPLIT ? MAX_SPLIT : n);
+}
+
 void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, float a, float b) {
     const int nW = query_wgs(S, G);
     const long n_all = static_cast<long>(B) * nW;
-    int slots = device_cus() / Hkv;                         // blocks per KV head the chip runs at one time
-    slots = slots < 1 ? 1 : (slots > MAX_SPLIT ? MAX_SPLIT : slots);
+    const int slots = query_slots(Hkv);
     sp.e_full = static_cast<int>(n_all);
     sp.n_blocks = sp.n_parts = 0;
     if (n_all > 4L * slots || n_all > 2 * MAX_SPLIT) return;
@@ -652,14 +657,21 @@ void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, floa
     }
     sp = kept;
 }
+// The most parts per KV head that this problem or any smaller one is split into: the workspace holds that
+// many, so that one kept for a program's largest batch serves its smaller ones (which are split further).
+size_t attn_query_parts(const cart_attn_desc& d, int T) {
+    const int G = d.Hq / d.Hkv;
+    const long by_seq = static_cast<long>(d.B) * query_wgs(d.S, G), by_row = T > 0 ? query_wgs(T, G) : 0;
+    const long tiles = (static_cast<long>(d.P) + 63) / 64 + (d.S + 63) / 64 + 6;        // (own_cap at most 6 more than S's)
+    const long all = (by_seq > by_row ? by_seq : by_row) * tiles, slots = query_slots(d.Hkv);
+    return static_cast<size_t>(all < slots ? all : slots);
+}
 // packed batches: the first row of every row's sequence; split blocks: an overflow flag per wavefront and the
 // partial results
 size_t attn_mfma_fwd_workspace(const cart_attn_desc& d, int T) {
-    QuerySplit sp;
-    attn_query_split(sp, d, T, FWD_BLOCK_US, FWD_TILE_US);
-    return r256(static_cast<size_t>(sp.n_parts) * d.Hkv * 4 * sizeof(int)) +
-           (T > 0 ? r256(static_cast<size_t>(T) * sizeof(int32_t)) : 0) +
-           static_cast<size_t>(sp.n_parts) * d.Hkv * (PART_O_BYTES + PART_L_BYTES);
+    const size_t slots = attn_query_parts(d, T) * d.Hkv;
+    return r256(slots * 4 * sizeof(int)) + (T > 0 ? r256(static_cast<size_t>(T) * sizeof(int32_t)) : 0) +
+           slots * (PART_O_BYTES + PART_L_BYTES);
 }
 
 // cu == nullptr: batched layout [B,S,...].  Otherwise the packed layout: d.S is the longest

@@ -1,0 +1,53 @@
+"""One workspace kept for a program's largest call has to serve its smaller ones (host only)."""
+import ctypes as C
+import math
+import random
+
+import pytest
+
+from paper_2506_06266_amd import binding as cb
+
+HEADS = [(32, 8), (24, 8), (8, 2), (4, 1), (16, 16), (64, 8)]
+
+
+@pytest.fixture(scope="module")
+def lib():
+    return cb.load()
+
+
+def _log(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _batched(lib, B, S, Hq, Hkv, P):
+    d = cb.AttnDesc(B, S, Hq, Hkv, 128, P, cb.CART_BF16, 0.0, 0, 0, cb.IMPL_AUTO)
+    return lib.cart_attn_fwd_workspace(C.byref(d)), lib.cart_attn_bwd_workspace(C.byref(d))
+
+
+def _packed(lib, T, B, most, Hq, Hkv, P):
+    d = cb.AttnVarlenDesc(T, B, most, Hq, Hkv, 128, P, cb.CART_BF16, 0.0, 0, 0)
+    return lib.cart_attn_varlen_fwd_workspace(C.byref(d)), lib.cart_attn_varlen_bwd_workspace(C.byref(d))
+
+
+def _covers(big, small, what):
+    assert min(big + small) >= 0 and all(b >= s for b, s in zip(big, small)), (what, big, small)
+
+
+def test_the_training_batch_covers_a_short_last_batch(lib):
+    _covers(_batched(lib, 16, 2048, 32, 8, 4096), _batched(lib, 1, 700, 32, 8, 4096), "16 x 2048, 1 x 700")
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_attention_workspace_never_grows_towards_smaller_problems(lib, seed):
+    rng = random.Random(seed)
+    for _ in range(500):
+        Hq, Hkv = rng.choice(HEADS)
+        P = rng.choice([0, _log(rng, 1, 16384)])
+        P2 = rng.choice([P, rng.randint(0, P)])
+        B, S = _log(rng, 1, 64), _log(rng, 1, 4096)
+        B2, S2 = rng.choice([B, rng.randint(1, B)]), rng.choice([S, rng.randint(1, S)])
+        _covers(_batched(lib, B, S, Hq, Hkv, P), _batched(lib, B2, S2, Hq, Hkv, P2), (B, S, Hq, Hkv, P, B2, S2, P2))
+        T = rng.randint(S, B * S)
+        T2 = rng.randint(S2, T) if rng.random() < 0.5 else T
+        if T2 >= B2:
+            _covers(_packed(lib, T, B, S, Hq, Hkv, P), _packed(lib, T2, B2, S2, Hq, Hkv, P2), (T, B, S, Hq, Hkv, P, T2, B2, S2, P2))
