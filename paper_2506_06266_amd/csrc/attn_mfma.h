@@ -187,6 +187,8 @@ inline float run_next(float* free_at, int n, float t) {
 // own_cap own-key tiles (packed rows: bounded by the longest sequence),
 // and the time of a whole block, a + b per key tile (us).
 void plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, float a, float b);
+enum QueryKernel { QUERY_FWD, QUERY_DQ };
+constexpr float FWD_BLOCK_US = 10.f, FWD_TILE_US = 1.4f, DQ_BLOCK_US = 11.f, DQ_TILE_US = 1.95f;    // a block's set-up and store, each key tile
 // The cut of the key-stationary launch: token rows per dZ partial, the partials, and into how many parts the
 // query heads that read an own key are split
 struct KvPlan { int chunk, n_part, head_parts; };

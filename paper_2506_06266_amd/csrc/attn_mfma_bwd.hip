@@ -38,7 +38,6 @@ constexpr int BWD_TILE_B = BWD_TILE * ROW_B;
 // fragments of the previous sub-tile are fetched about ten groups ahead, so a tile is read over
 // three tile iterations: four buffers.
 constexpr int DQ_NBUF = 4;
-constexpr float DQ_BLOCK_US = 11.f, DQ_TILE_US = 1.95f;     // a block's time: set-up and store, each key tile (see plan_query_split)
 struct DqSmem {
     struct { char k[BWD_TILE_B]; char v[BWD_TILE_B]; } t[DQ_NBUF];
 };
@@ -432,7 +431,7 @@ void launch_attn_bwd_kv(const cart_attn_desc& d, float scale, const bf16_t* Q, c
                         bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, float* own_k, float* own_v, const int32_t* cu,
                         int n_tok, const KvPlan& plan, hipStream_t st);
 // the split of the query blocks (attn_mfma_fwd.hip)
-void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, float a, float b);
+void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind);
 size_t attn_query_parts(const cart_attn_desc& d, int T);
 
 static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
@@ -449,7 +448,7 @@ static size_t bwd_rows_bytes(const cart_attn_desc& d, long tokens) { return r256
 static void bwd_layout(BwdLayout& w, const cart_attn_desc& d, int T) {
     const long tokens = T > 0 ? T : static_cast<long>(d.B) * d.S;
     w.kv = plan_bwd_kv(d, tokens);
-    attn_query_split(w.split, d, T, DQ_BLOCK_US, DQ_TILE_US);
+    attn_query_split(w.split, d, T, QUERY_DQ);
     w.rows = bwd_rows_bytes(d, tokens);
     w.part = r256(static_cast<size_t>(w.kv.n_part) * d.Hkv * d.P * HD * sizeof(float));
     w.dq = static_cast<size_t>(w.split.n_parts) * d.Hkv * PART_O_BYTES;

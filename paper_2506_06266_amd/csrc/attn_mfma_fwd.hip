@@ -28,7 +28,6 @@ using namespace mfma;
 constexpr int FWD_BN = 64;    // keys per LDS tile, consumed as two sub-tiles of 32
 constexpr int FWD_NBUF = 4;     // tile t in buffer t % 4; loads run two tiles ahead of the barrier that publishes them
 constexpr int FWD_TILE_B = FWD_BN * ROW_B;
-constexpr float FWD_BLOCK_US = 10.f, FWD_TILE_US = 1.4f;   // a block's time: set-up and store, each key tile
 
 struct FwdSmem {
     char k[FWD_NBUF][FWD_TILE_B];
@@ -641,21 +640,23 @@ static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 bool attn_mfma_supported(const cart_attn_desc& d) {
     return d.dtype == CART_BF16 && d.D == 128;
 }
-// Blocks per sequence, or over the packed rows (a packed batch with a prefix; T > 0).  A call asks twice,
-// for the workspace and for the launch: the thread's last split is kept with all that it depends on.
-void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, float a, float b) {
-    struct Key { int B, S, G, Hkv, P, own_cap, cus; float a, b; };
-    static thread_local Key last;
-    static thread_local QuerySplit kept;
+// Blocks per sequence, or over the packed rows (a packed batch with a prefix; T > 0).  The layers of a step
+// ask for the same two splits in turn, forward's and dQ's: the thread's last one of either kind is kept with
+// all that it depends on (planned again at each call, 32 sequences of 516 tokens, 8 / 2 heads: 18 us a layer).
+void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind) {
+    struct Key { int B, S, G, Hkv, P, own_cap, cus; };
+    static thread_local Key last[2];
+    static thread_local QuerySplit kept[2];
     const int G = d.Hq / d.Hkv;
     const bool rows = T > 0 && d.P > 0;
-    const Key k = {rows ? 1 : d.B, rows ? T : d.S, G, d.Hkv, d.P, rows ? (d.S + 255) / 64 + 2 : 1 << 30, device_cus(), a, b};
-    if (last.cus != k.cus || last.B != k.B || last.S != k.S || last.G != k.G || last.Hkv != k.Hkv || last.P != k.P ||
-        last.own_cap != k.own_cap || last.a != k.a || last.b != k.b) {
-        plan_query_split(kept, k.B, k.S, G, d.Hkv, d.P, k.own_cap, a, b);
-        last = k;
+    const Key k = {rows ? 1 : d.B, rows ? T : d.S, G, d.Hkv, d.P, rows ? (d.S + 255) / 64 + 2 : 1 << 30, device_cus()};
+    Key& l = last[kind];
+    if (l.cus != k.cus || l.B != k.B || l.S != k.S || l.G != k.G || l.Hkv != k.Hkv || l.P != k.P || l.own_cap != k.own_cap) {
+        plan_query_split(kept[kind], k.B, k.S, G, d.Hkv, d.P, k.own_cap, kind == QUERY_DQ ? DQ_BLOCK_US : FWD_BLOCK_US,
+                         kind == QUERY_DQ ? DQ_TILE_US : FWD_TILE_US);
+        l = k;
     }
-    sp = kept;
+    sp = kept[kind];
 }
 // The most parts per KV head that this problem or any smaller one is split into: the workspace holds that
 // many, so that one kept for a program's largest batch serves its smaller ones (which are split further).
@@ -681,7 +682,7 @@ int launch_attn_fwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
                          void* ws, hipStream_t st, const int32_t* cu, int T) {
     if (!cu) T = 0;
     QuerySplit sp;
-    attn_query_split(sp, d, T, FWD_BLOCK_US, FWD_TILE_US);
+    attn_query_split(sp, d, T, QUERY_FWD);
     const size_t slots = static_cast<size_t>(sp.n_parts) * d.Hkv;
     const unsigned n_items = static_cast<unsigned>(sp.e_full + sp.n_parts) * d.Hkv;
     char* w = static_cast<char*>(ws);
