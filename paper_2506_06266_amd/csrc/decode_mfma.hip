@@ -63,10 +63,9 @@ struct DecodePlan {
 
 // seg_p[n_seg]: slots per shared segment; pool_p: slots of a private cartridge (0 = none);
 // T: rows of the packed own caches
-// A plan whose partials exceed the library's own scratch array is made again with as few parts as keep
-// the chip busy (`lean`), so that finer cuts never keep a problem from cart_decode_static.
-static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p,
-                            bool lean = false) {
+// lean > 0: prefix workgroups for the chip and no more, and no range below 256 rows; 1: in no more parts than
+// the estimate takes either.
+static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p, int lean) {
     DecodePlan p;
     p.G = Hq / Hkv;
     const int rows = B * p.G;
@@ -100,8 +99,8 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         }
     }
     if (lean && total_tiles > 0) {
-        const int parts = (192 + Hkv * p.n_rb - 1) / (Hkv * p.n_rb);
-        tps = (total_tiles + parts - 1) / parts;
+        const int parts = (192 + Hkv * p.n_rb - 1) / (Hkv * p.n_rb), t = (total_tiles + parts - 1) / parts;
+        tps = lean == 1 && t < tps ? tps : t;
     }
     p.tab.n_seg = 0;
     p.tab.blk0[0] = 0;
@@ -151,8 +150,20 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     const size_t slots = static_cast<size_t>(p.n_ps + p.n_cc + p.n_oc) * B * Hq;
     p.part_o_bytes = (slots * HD * sizeof(float) + 255) & ~static_cast<size_t>(255);
     p.part_l_bytes = (slots * sizeof(float) + 255) & ~static_cast<size_t>(255);
-    if (!lean && p.part_o_bytes + p.part_l_bytes > DEC_STATIC_BYTES)
-        return make_plan(B, Hq, Hkv, max_own_len, T, seg_p, n_seg, pool_p, true);
+    return p;
+}
+// A plan whose partials exceed the library's own scratch array gives way to a lean one that fits it, so that
+// finer cuts never keep a problem from cart_decode_static (whose bits are cart_decode's); with private
+// cartridges there is no such entry point.  The finer cut is no faster at those sizes (128 requests, 512 slots,
+// 9000 own rows at most: 400 us either way; 96, 1000 slots, 12000: 393; 256, 2048, 3000: 85), but 208 requests of
+// up to 40 own rows, 47 shared slots and cartridges of 786 lost 32 us of 262 to a lean plan.
+static DecodePlan decode_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p) {
+    const DecodePlan p = make_plan(B, Hq, Hkv, max_own_len, T, seg_p, n_seg, pool_p, 0);
+    if (pool_p == 0 && p.part_o_bytes + p.part_l_bytes > DEC_STATIC_BYTES)
+        for (int lean = 1; lean <= 2; ++lean) {
+            const DecodePlan l = make_plan(B, Hq, Hkv, max_own_len, T, seg_p, n_seg, 0, lean);
+            if (l.part_o_bytes + l.part_l_bytes <= DEC_STATIC_BYTES) return l;
+        }
     return p;
 }
 
@@ -724,7 +735,7 @@ bool decode_mfma_supported(const cart_decode_desc& d) {
 }
 
 size_t decode_mfma_workspace(const cart_decode_desc& d) {
-    const DecodePlan p = make_plan(d.B, d.Hq, d.Hkv, d.max_own_len, d.total_own_tokens, &d.P, d.P > 0 ? 1 : 0, 0);
+    const DecodePlan p = decode_plan(d.B, d.Hq, d.Hkv, d.max_own_len, d.total_own_tokens, &d.P, d.P > 0 ? 1 : 0, 0);
     return p.part_o_bytes + p.part_l_bytes;
 }
 
@@ -735,7 +746,7 @@ bool decode_composed_supported(const cart_decode_composed_desc& d) {
 static DecodePlan composed_plan(const cart_decode_composed_desc& d, const cart_segment* shared) {
     int seg_p[DEC_MAX_SEG];
     for (int s = 0; s < d.n_shared; ++s) seg_p[s] = shared[s].p;
-    return make_plan(d.B, d.Hq, d.Hkv, d.max_own_len, d.total_own_tokens, seg_p, d.n_shared,
+    return decode_plan(d.B, d.Hq, d.Hkv, d.max_own_len, d.total_own_tokens, seg_p, d.n_shared,
                      d.n_pool > 0 ? d.pool_p : 0);
 }
 
@@ -774,7 +785,7 @@ static int run_decode(const DecodePlan& p, int B, int Hq, int Hkv, float scale, 
 int launch_decode_mfma(const cart_decode_desc& d, float scale, const void* q, const void* zk,
                        const void* zv, const void* k, const void* v, const int32_t* cu, void* o,
                        float* lse, void* ws, hipStream_t st) {
-    DecodePlan p = make_plan(d.B, d.Hq, d.Hkv, d.max_own_len, d.total_own_tokens, &d.P, d.P > 0 ? 1 : 0, 0);
+    DecodePlan p = decode_plan(d.B, d.Hq, d.Hkv, d.max_own_len, d.total_own_tokens, &d.P, d.P > 0 ? 1 : 0, 0);
     if (p.tab.n_seg > 0) {
         p.tab.zk[0] = static_cast<const bf16_t*>(zk);
         p.tab.zv[0] = static_cast<const bf16_t*>(zv);

@@ -51,3 +51,17 @@ def test_attention_workspace_never_grows_towards_smaller_problems(lib, seed):
         T2 = rng.randint(S2, T) if rng.random() < 0.5 else T
         if T2 >= B2:
             _covers(_packed(lib, T, B, S, Hq, Hkv, P), _packed(lib, T2, B2, S2, Hq, Hkv, P2), (T, B, S, Hq, Hkv, P, T2, B2, S2, P2))
+
+
+# Partials beyond cart_decode_static's 32 MiB are cut again only where that makes them fit, and never where a
+# caller's workspace is the only one there is (private cartridges).  B, Hq, Hkv, slots, longest, own rows -> most MB
+@pytest.mark.parametrize("B,Hq,Hkv,P,most,T,mb", [(32, 32, 8, 8192, 16384, 30000, 41.8), (128, 32, 8, 512, 9000, 568051, 33.6)])
+def test_decode_is_cut_again_only_where_that_fits(lib, B, Hq, Hkv, P, most, T, mb):
+    d = cb.DecodeDesc(B, Hq, Hkv, 128, P, T, most, cb.CART_BF16, 0.0, cb.IMPL_AUTO)
+    assert lib.cart_decode_workspace(C.byref(d)) <= mb * 1e6
+
+
+def test_decode_with_private_cartridges_keeps_the_estimated_cut(lib):
+    seg = (cb.Segment * 1)(cb.Segment(0x1000, 0x1000, 47))
+    d = cb.DecodeComposedDesc(208, 64, 8, 128, 1, 208, 786, 3973, 40, cb.CART_BF16, 0.0)
+    assert 0 < lib.cart_decode_composed_workspace(C.byref(d), seg) <= 34.4e6
