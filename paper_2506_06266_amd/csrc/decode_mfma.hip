@@ -54,10 +54,9 @@ struct PrefixTable {
 struct DecodePlan {
     PrefixTable tab;
     int G, n_rb, n_ps;                    // prefix: row blocks, partial slots of all segments
-    // streamed rows (own tokens, then private cartridges): rows per range, most ranges one request's own
-    // rows / private cartridge reach into, first row of the private cartridges, workgroups
-    int share, n_oc, n_cc, n_own_wg;
-    long pool0;
+    // streamed rows (own tokens, then private cartridges): rows per range of either, most ranges one request's
+    // own rows / private cartridge reach into, first range of the private cartridges, workgroups
+    int share, pool_share, n_oc, n_cc, pool_r0, n_own_wg;
     size_t part_o_bytes, part_l_bytes;
 };
 
@@ -118,15 +117,13 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         p.tab.zk[k] = p.tab.zv[k] = nullptr;                        // filled by the launcher
     }
     // Streamed rows: the workgroups that stay resident beside the prefix workgroups, four wavefronts
-    // each, one wavefront per (range, KV head); the ranges cut the own rows of all requests followed
-    // by the private cartridges of all requests evenly, in whole steps of 32 rows where they are that long.
+    // each, one wavefront per (range, KV head); the ranges cut the own rows of all requests, then the
+    // private cartridges of all requests evenly, in whole steps of 32 rows where they are that long.
     const int n_pre_wg = p.n_ps > 0 ? p.tab.blk0[p.tab.n_seg] : 0;
     long wgs = chip - n_pre_wg;
     if (wgs < 64) wgs = 64;
     long ranges = 4 * wgs / Hkv;
     if (ranges < 1) { ranges = 1; wgs = (Hkv + 3) / 4; }
-    p.pool0 = (static_cast<long>(T) + DEC_SUB - 1) / DEC_SUB * DEC_SUB;
-    const long rows_all = pool_p > 0 ? p.pool0 + static_cast<long>(B) * pool_p : T;
     // (not below DEC_MIN_SHARE rows, nor the longest request in more than DEC_MAX_PARTS ranges: shorter
     // ranges only multiply the partials a request leaves.  8 requests of up to 500 tokens, us a call:
     // at least 256 / 128 / 64 / 32 rows -> 23.0 / 18.7 / 17.9 / 17.8; one of 16000: 19 / 17.8 / 25.4 / 36.9.
@@ -134,19 +131,40 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     // holds about one of them: 31 requests of up to 17 tokens beside 885 slots 26.2 -> 18.2, 128 of up to 16
     // beside 1000 33.6 -> 22.2, 48 of up to 53 beside 516 20.9 -> 18.2)
     auto up = [](long x, long to) { return (x + to - 1) / to * to; };
-    const long resident = (rows_all + ranges - 1) / ranges, least = (static_cast<long>(max_own_len) + DEC_MAX_PARTS - 1) / DEC_MAX_PARTS;
-    const long needed = resident > least ? resident : least, avg = up(T / B, 8);
-    long share = up(needed, DEC_SUB);
-    if (lean)                                       share = share > 4 * DEC_MIN_SHARE ? share : 4 * DEC_MIN_SHARE;
-    else if (pool_p == 0 && avg < DEC_MIN_SHARE)    share = avg > needed ? avg : up(needed, needed < DEC_SUB ? 8 : DEC_SUB);
-    else if (share < DEC_MIN_SHARE)                 share = DEC_MIN_SHARE;
-    if (share < 8) share = 8;
-    const long used = (rows_all + share - 1) / share;                        // ranges that hold rows
+    const long least = (static_cast<long>(max_own_len) + DEC_MAX_PARTS - 1) / DEC_MAX_PARTS;
+    long share, used;                                                        // rows per own range, ranges that hold rows
+    p.pool_share = p.pool_r0 = p.n_cc = 0;
+    if (pool_p == 0) {
+        const long resident = (static_cast<long>(T) + ranges - 1) / ranges, needed = resident > least ? resident : least, avg = up(T / B, 8);
+        share = up(needed, DEC_SUB);
+        if (lean)                         share = share > 4 * DEC_MIN_SHARE ? share : 4 * DEC_MIN_SHARE;
+        else if (avg < DEC_MIN_SHARE)     share = avg > needed ? avg : up(needed, needed < DEC_SUB ? 8 : DEC_SUB);
+        else if (share < DEC_MIN_SHARE)   share = DEC_MIN_SHARE;
+        if (share < 8) share = 8;
+        used = (static_cast<long>(T) + share - 1) / share;
+    } else {
+        // Beside private cartridges: by steps, so that a range of short requests (a step each) takes as long as
+        // one of cartridge rows.  Cut by rows alone (us a call): 208 requests of up to 40 own rows, cartridges of 786
+        // slots 230, now 179; 121 requests, cartridges of 389 265, now 70; 223 requests, cartridges of one slot 458, now 63.
+        const float rows = static_cast<float>(T) / static_cast<float>(B);
+        const float own_steps = fmaxf(rows / DEC_SUB + 0.5f, 1.f), pool_steps = ceilf(static_cast<float>(pool_p) / DEC_SUB);
+        const float each = fmaxf(static_cast<float>(B) * (own_steps + pool_steps) / static_cast<float>(ranges > 4 ? ranges - 2 : ranges),
+                                 static_cast<float>(DEC_MIN_SHARE / DEC_SUB));        // steps per range
+        auto cut = [&](float x, long at_least) {
+            const long r = static_cast<long>(x) > at_least ? static_cast<long>(x) : at_least;
+            return up(r < 8 ? 8 : r, r <= DEC_SUB ? 8 : DEC_SUB);
+        };
+        share = cut(each * rows / own_steps, least);
+        p.pool_share = static_cast<int>(cut(each * static_cast<float>(pool_p) / pool_steps, 0));
+        p.pool_r0 = static_cast<int>((static_cast<long>(T) + share - 1) / share);
+        used = p.pool_r0 + (static_cast<long>(B) * pool_p + p.pool_share - 1) / p.pool_share;
+        p.n_cc = (pool_p + p.pool_share - 1) / p.pool_share + 1;
+        wgs = (used * Hkv + 3) / 4;
+    }
     if ((used * Hkv + 3) / 4 < wgs) wgs = (used * Hkv + 3) / 4;
     p.share = static_cast<int>(share);
     p.n_own_wg = static_cast<int>(wgs);
     p.n_oc = static_cast<int>((max_own_len + share - 1) / share) + 1;
-    p.n_cc = pool_p > 0 ? static_cast<int>((pool_p + share - 1) / share) + 1 : 0;
     const size_t slots = static_cast<size_t>(p.n_ps + p.n_cc + p.n_oc) * B * Hq;
     p.part_o_bytes = (slots * HD * sizeof(float) + 255) & ~static_cast<size_t>(255);
     p.part_l_bytes = (slots * sizeof(float) + 255) & ~static_cast<size_t>(255);
@@ -489,11 +507,10 @@ __device__ __forceinline__ void own_load_q(const bf16_t* __restrict__ q, int b, 
 __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                   const bf16_t* __restrict__ v, const int32_t* __restrict__ cu,
                                                   float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq,
-                                                  int Hkv, float c, int slot0, int n_oc, int share, int wid) {
+                                                  int Hkv, float c, int slot0, int n_oc, int share, int r, int hk) {
     const int G = Hq / Hkv;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r = wid / Hkv, hk = wid - r * Hkv;
     const int T = cu[B];
     const long t_lo_l = static_cast<long>(r) * share;
     if (t_lo_l >= T) return;
@@ -555,24 +572,20 @@ __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __rest
 }
 
 // The private cartridges pool[cart_id[b]] ([Hkv,pool_p,128]; none for a request whose cart_id is
-// negative), streamed by the same wavefronts as rows pool0 + b * pool_p ... behind the own rows: a
-// wavefront's range may begin with own rows, cross from one cartridge to the next, and every
-// (request, range) pair leaves one partial.  (Chunks of a cartridge dealt out round-robin left
+// negative), streamed like own rows, as rows b * pool_p ...: a wavefront's range r may cross from one
+// cartridge to the next, and every (request, range) pair leaves one partial.  (Chunks of a cartridge dealt out round-robin left
 // wavefronts with two chunks beside others with one: 128 cartridges of 2048 slots beside 2048
 // shared ones took 371 us a call against 273, and 252 with the prefix in one part.)
 __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __restrict__ q,
                                                    const bf16_t* __restrict__ pool_k, const bf16_t* __restrict__ pool_v,
-                                                   const int32_t* __restrict__ cart_id, int pool_p, long pool0,
+                                                   const int32_t* __restrict__ cart_id, int pool_p,
                                                    float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq,
-                                                   int Hkv, float c, int slot0, int share, int wid) {
+                                                   int Hkv, float c, int slot0, int share, int r, int hk) {
     const int G = Hq / Hkv;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int r = wid / Hkv, hk = wid - r * Hkv;
-    const long all = static_cast<long>(B) * pool_p;                 // positions among the cartridges' rows: [lo, hi)
-    long lo = static_cast<long>(r) * share - pool0;
-    const long hi = min(lo + share, all);
-    if (lo < 0) lo = 0;
+    const long lo = static_cast<long>(r) * share;                   // positions among the cartridges' rows: [lo, hi)
+    const long hi = min(lo + share, static_cast<long>(B) * pool_p);
     if (lo >= hi) return;
     char* kt = sm + (2 * wv) * DEC_SUB_B;
     char* vt = kt + DEC_SUB_B;
@@ -615,7 +628,7 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
             if (kn) own_issue(kn + static_cast<size_t>(sn) * ROW_B, vn + static_cast<size_t>(sn) * ROW_B, ROW_B, en - 1 - sn, kt, vt, lane);
             own_step(st, ka, va, qf, min(DEC_SUB, cur.end - s), c, lg);
         }
-        const int j = r - static_cast<int>((pool0 + static_cast<long>(cur.b) * pool_p) / share);
+        const int j = r - static_cast<int>(static_cast<long>(cur.b) * pool_p / share);
         own_store(st, part_o, part_l, (static_cast<size_t>(slot0 + j) * B + cur.b) * Hq + hk * G, G, lc, lg);
         cur = nxt;
     }
@@ -629,7 +642,7 @@ __global__ __launch_bounds__(256, 2) void decode_fused_kernel(
     const bf16_t* __restrict__ q, const PrefixTable tab, const bf16_t* __restrict__ k,
     const bf16_t* __restrict__ v, const int32_t* __restrict__ cu, const bf16_t* __restrict__ pool_k,
     const bf16_t* __restrict__ pool_v, const int32_t* __restrict__ cart_id, int pool_p,
-    long pool0, float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq, int Hkv, float c, int n_rb,
+    int pool_r0, int pool_share, float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq, int Hkv, float c, int n_rb,
     int n_cc, int n_oc, int share, int n_ps, int n_pre_wg, int n_own_wg) {
     constexpr int pre_b = 2 * DEC_NBUF * DEC_TILE_B, own_b = 4 * 2 * DEC_SUB_B;   // the two roles share one LDS block
     __shared__ __attribute__((aligned(16))) char sm[pre_b > own_b ? pre_b : own_b];
@@ -651,14 +664,16 @@ __global__ __launch_bounds__(256, 2) void decode_fused_kernel(
     }
     // every wavefront on its own from here on: no barrier in this role
     const int wid = __builtin_amdgcn_readfirstlane(idx * 4 + static_cast<int>(threadIdx.x >> 6));
-    decode_own_stream(sm, q, k, v, cu, part_o, part_l, B, Hq, Hkv, c, n_ps + n_cc, n_oc, share, wid);
-    if (n_cc > 0)
-        decode_pool_stream(sm, q, pool_k, pool_v, cart_id, pool_p, pool0, part_o, part_l, B, Hq, Hkv, c, n_ps, share, wid);
+    const int r = wid / Hkv, hk = wid - r * Hkv;
+    if (n_cc > 0 && r >= pool_r0)
+        decode_pool_stream(sm, q, pool_k, pool_v, cart_id, pool_p, part_o, part_l, B, Hq, Hkv, c, n_ps, pool_share, r - pool_r0, hk);
+    else
+        decode_own_stream(sm, q, k, v, cu, part_o, part_l, B, Hq, Hkv, c, n_ps + n_cc, n_oc, share, r, hk);
 }
 
 // o[b,h,:] = sum_i w_i part_o[i] / sum_i w_i, w_i = exp(lse_i - max lse), over the partial slots
-// that exist for the request: the n_ps prefix parts, one per range of `share` rows its private
-// cartridge (when it has one) and its own rows reach into.  WPR wavefronts per (b, h): one where there
+// that exist for the request: the n_ps prefix parts, one per range of `pool_share` rows its private
+// cartridge (when it has one) and of `share` rows its own rows reach into.  WPR wavefronts per (b, h): one where there
 // are rows for the whole chip, four where there are not (one request of 16000 own tokens: 19.9 -> 17.4
 // us a call; 8 of up to 16000: 59.0 -> 54.0; above DEC_FEW_ROWS 4096 rows: 75 -> 81).  Slots in
 // groups of 64: lane i holds the lse and the weight of the group's slot i, then every lane accumulates
@@ -667,7 +682,7 @@ template <int WPR>
 __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restrict__ part_o,
                                                            const float* __restrict__ part_l,
                                                            const int32_t* __restrict__ cu,
-                                                           const int32_t* __restrict__ cart_id, int pool_p, long pool0,
+                                                           const int32_t* __restrict__ cart_id, int pool_p, int pool_share,
                                                            bf16_t* __restrict__ o,
                                                            float* __restrict__ lse, int B, int Hq,
                                                            int n_ps, int n_cc, int n_oc, int share) {
@@ -678,8 +693,8 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restri
     const int b = row / Hq;
     int priv = 0;
     if (n_cc > 0 && cart_id && cart_id[b] >= 0) {
-        const long p0 = pool0 + static_cast<long>(b) * pool_p;
-        priv = static_cast<int>((p0 + pool_p - 1) / share - p0 / share) + 1;
+        const long p0 = static_cast<long>(b) * pool_p;
+        priv = static_cast<int>((p0 + pool_p - 1) / pool_share - p0 / pool_share) + 1;
     }
     const int own = min(n_oc, (cu[b + 1] - 1) / share - cu[b] / share + 1);
     const int n = n_ps + n_cc + n_oc;
@@ -767,13 +782,13 @@ static int run_decode(const DecodePlan& p, int B, int Hq, int Hkv, float scale, 
     trace_begin(st);   // kernel order: prefix + own (one launch), merge
     const int n_pre_wg = p.n_ps > 0 ? p.tab.blk0[p.tab.n_seg] : 0;
     hipLaunchKernelGGL(decode_fused_kernel, dim3(static_cast<unsigned>(n_pre_wg + p.n_own_wg)), dim3(256), 0, st, Q,
-                       p.tab, K, V, cu, PK, PV, cart_id, pool_p, p.pool0, part_o, part_l, B, Hq, Hkv, c, p.n_rb, p.n_cc, p.n_oc,
+                       p.tab, K, V, cu, PK, PV, cart_id, pool_p, p.pool_r0, p.pool_share, part_o, part_l, B, Hq, Hkv, c, p.n_rb, p.n_cc, p.n_oc,
                        p.share, p.n_ps, n_pre_wg, p.n_own_wg);
     trace_mark(st);
     const long rows = static_cast<long>(B) * Hq;
     auto merge = [&](auto kernel, int rows_per_wg) {
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((rows + rows_per_wg - 1) / rows_per_wg)), dim3(256), 0, st, part_o,
-                           part_l, cu, cart_id, pool_p, p.pool0, static_cast<bf16_t*>(o), lse, B, Hq, p.n_ps, p.n_cc, p.n_oc,
+                           part_l, cu, cart_id, pool_p, p.pool_share, static_cast<bf16_t*>(o), lse, B, Hq, p.n_ps, p.n_cc, p.n_oc,
                            p.share);
     };
     if (rows <= DEC_FEW_ROWS) merge(decode_merge_kernel<4>, 1);

@@ -264,6 +264,9 @@ DECODE_CASES = [
     (70, 32, 8, 65, 33, 20), (2, 2, 1, 10, 3000, 5000), (1, 7, 1, 1, 0, 4161), (64, 32, 2, 0, 0, 90),
     # ranges of about one short request: of 8 rows, one row each, more requests than ranges
     (31, 32, 8, 100, 0, 12), (130, 4, 2, 40, 0, 1), (500, 8, 8, 33, 0, 30), (300, 16, 16, 0, 0, 100),
+    # own rows and private cartridges cut at different lengths: short requests beside long cartridges, cartridges of a
+    # slot or two, one long request among them
+    (200, 16, 8, 47, 786, 20), (223, 8, 8, 100, 1, 9), (60, 8, 1, 0, 7, 2), (30, 4, 2, 10, 3, 2000), (5, 8, 8, 0, 33, 300),
 ]
 
 
