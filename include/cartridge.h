@@ -136,7 +136,8 @@ typedef struct {
  * attention and decode figures depend on the number of CUs of the current device as well (work is cut
  * into as many parts as the chip keeps resident): ask with the device current that the call will run
  * on.  An attention workspace also serves every call of the same heads, dtype and layout none of whose
- * sizes (B, S, P; T, B, max_seqlen, P) is larger: one sized for a program's largest batch can be kept. */
+ * sizes (B, S, P; T, B, max_seqlen, P) is larger: one sized for a program's largest batch can be kept.  So
+ * does a decode workspace of up to 32 MiB (B, T, max_own_len, segments and pool_p). */
 size_t cart_attn_fwd_workspace(const cart_attn_desc *desc);
 size_t cart_attn_bwd_workspace(const cart_attn_desc *desc);
 size_t cart_attn_varlen_fwd_workspace(const cart_attn_varlen_desc *desc);
@@ -228,7 +229,7 @@ cart_status cart_decode(const cart_decode_desc *desc, const void *q, const void 
  *   - bf16 with D = 128 only (the matrix-core decode kernels): CART_ERR_UNSUPPORTED otherwise.
  *   - A problem whose cart_decode_workspace() exceeds cart_decode_static_capacity() is refused
  *     with CART_ERR_WORKSPACE before anything is launched (the 128-request, 8192-slot serving
- *     shape needs 21.1 MB).
+ *     shape fits).
  *   - Every call on a GPU uses that GPU's one array: calls that overlap in time on the same GPU
  *     (two streams, two threads) race; calls on one stream do not.  Nothing in it has to be
  *     cleared between calls: every partial result is written before it is read.

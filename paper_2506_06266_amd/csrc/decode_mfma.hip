@@ -35,6 +35,7 @@ constexpr int DEC_SUB = 32;            // own keys per wavefront step
 constexpr int DEC_SUB_B = DEC_SUB * ROW_B;
 
 constexpr int DEC_MIN_SHARE = 64;       // fewest rows per streamed range of requests that are not shorter
+constexpr int DEC_MAX_SPLIT = 48;       // most parts the shared prefix is split into
 constexpr int DEC_MAX_PARTS = 64;       // most ranges the longest request's own rows are cut into
 constexpr int DEC_FEW_ROWS = 2048;      // output rows up to which the merge takes four wavefronts a row
 constexpr int DEC_MAX_SEG = CART_MAX_SEGMENTS;
@@ -83,7 +84,7 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     const long chip = 2L * device_cus();          // workgroups the chip keeps resident (256 threads, two per CU)
     int tps = 0;
     float tps_us = 0.f;
-    for (int parts = 1; parts <= 48 && parts <= total_tiles; parts += 1 + parts / 8) {
+    for (int parts = 1; parts <= DEC_MAX_SPLIT && parts <= total_tiles; parts += 1 + parts / 8) {
         const int t = (total_tiles + parts - 1) / parts;
         const long n_pre = static_cast<long>(Hkv) * p.n_rb * parts;
         if (parts > 1 && n_pre > chip - 64) break;
@@ -745,13 +746,28 @@ __global__ __launch_bounds__(256) void decode_merge_kernel(const float* __restri
     if (lane == 0 && lse) lse[row] = m + __logf(wsum);
 }
 
+// What the workspace queries return: the plan's bytes, or more, so that a workspace kept for a server's
+// largest step serves its smaller ones (which are cut further): the most a cut of this problem or a smaller
+// one can take, up to the size of the static array.  (A problem beyond that is asked for as it is.)
+static size_t workspace_bytes(const DecodePlan& p, int B, int Hq, int max_own_len, const int* seg_p, int n_seg, int pool_p) {
+    long tiles = 0;
+    for (int s = 0; s < n_seg; ++s) tiles += (seg_p[s] + DEC_BN - 1) / DEC_BN;
+    const long own = (static_cast<long>(max_own_len) + 7) / 8;
+    const long slots = (tiles < DEC_MAX_SPLIT + n_seg ? tiles : DEC_MAX_SPLIT + n_seg) + (own < DEC_MAX_PARTS ? own : DEC_MAX_PARTS) + 1 +
+                       (pool_p > 0 ? pool_p / DEC_SUB + 2 : 0);
+    const size_t most = static_cast<size_t>(slots) * B * Hq * (HD + 1) * sizeof(float) + 512, bytes = p.part_o_bytes + p.part_l_bytes;
+    const size_t kept = most < DEC_STATIC_BYTES ? most : DEC_STATIC_BYTES;
+    return bytes > kept ? bytes : kept;
+}
+
 bool decode_mfma_supported(const cart_decode_desc& d) {
     return d.dtype == CART_BF16 && d.D == 128 && d.Hq / d.Hkv <= 32;
 }
 
 size_t decode_mfma_workspace(const cart_decode_desc& d) {
-    const DecodePlan p = decode_plan(d.B, d.Hq, d.Hkv, d.max_own_len, d.total_own_tokens, &d.P, d.P > 0 ? 1 : 0, 0);
-    return p.part_o_bytes + p.part_l_bytes;
+    const int n_seg = d.P > 0 ? 1 : 0;
+    return workspace_bytes(decode_plan(d.B, d.Hq, d.Hkv, d.max_own_len, d.total_own_tokens, &d.P, n_seg, 0), d.B, d.Hq, d.max_own_len,
+                           &d.P, n_seg, 0);
 }
 
 bool decode_composed_supported(const cart_decode_composed_desc& d) {
@@ -766,8 +782,9 @@ static DecodePlan composed_plan(const cart_decode_composed_desc& d, const cart_s
 }
 
 size_t decode_composed_workspace(const cart_decode_composed_desc& d, const cart_segment* shared) {
-    const DecodePlan p = composed_plan(d, shared);
-    return p.part_o_bytes + p.part_l_bytes;
+    int seg_p[DEC_MAX_SEG];
+    for (int s = 0; s < d.n_shared; ++s) seg_p[s] = shared[s].p;
+    return workspace_bytes(composed_plan(d, shared), d.B, d.Hq, d.max_own_len, seg_p, d.n_shared, d.n_pool > 0 ? d.pool_p : 0);
 }
 
 // prefix parts + private-cartridge chunks + own ranges (one launch), then the merge

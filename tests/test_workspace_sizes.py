@@ -53,6 +53,27 @@ def test_attention_workspace_never_grows_towards_smaller_problems(lib, seed):
             _covers(_packed(lib, T, B, S, Hq, Hkv, P), _packed(lib, T2, B2, S2, Hq, Hkv, P2), (T, B, S, Hq, Hkv, P, T2, B2, S2, P2))
 
 
+# (the partials of a problem and those of a smaller one: as long as neither exceeds the static array)
+@pytest.mark.parametrize("seed", range(4))
+def test_decode_workspace_never_grows_towards_smaller_problems(lib, seed):
+    rng = random.Random(seed)
+    cap = lib.cart_decode_static_capacity()
+    for _ in range(800):
+        Hq, Hkv = rng.choice(HEADS)
+        B, most, P, pool = _log(rng, 1, 256), _log(rng, 1, 16384), rng.choice([0, _log(rng, 1, 8192)]), rng.choice([0, _log(rng, 1, 4096)])
+        B2, most2, P2 = (rng.choice([x, rng.randint(min(x, 1), x)]) for x in (B, most, P))
+        T = rng.randint(max(B, most), B * most) if B * most > max(B, most) else max(B, most)
+        T2 = min(T, rng.randint(max(B2, most2), max(B2 * most2, B2, most2)))
+        need = []
+        for b, t, m, p in ((B, T, most, P), (B2, T2, most2, P2)):
+            d = cb.DecodeDesc(b, Hq, Hkv, 128, p, t, m, cb.CART_BF16, 0.0, cb.IMPL_AUTO)
+            seg = (cb.Segment * 1)(cb.Segment(0x1000, 0x1000, p))
+            c = cb.DecodeComposedDesc(b, Hq, Hkv, 128, 1, b if pool else 0, pool, t, m, cb.CART_BF16, 0.0)
+            need.append((lib.cart_decode_workspace(C.byref(d)), lib.cart_decode_composed_workspace(C.byref(c), seg)))
+        for big, small in zip(*need):
+            assert 0 < small and (small <= big or max(small, big) > cap), (B, Hq, Hkv, P, pool, T, most, B2, T2, most2, P2, big, small)
+
+
 # Partials beyond cart_decode_static's 32 MiB are cut again only where that makes them fit, and never where a
 # caller's workspace is the only one there is (private cartridges).  B, Hq, Hkv, slots, longest, own rows -> most MB
 @pytest.mark.parametrize("B,Hq,Hkv,P,most,T,mb", [(32, 32, 8, 8192, 16384, 30000, 41.8), (128, 32, 8, 512, 9000, 568051, 33.6)])
