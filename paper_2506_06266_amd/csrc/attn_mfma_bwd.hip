@@ -371,7 +371,7 @@ struct BwdReduce {
     float* dz[2];
     bf16_t *dq, *own[2];
     long dz_n4, own_n4;                 // vectors per partial
-    int dz_parts, own_parts, dz_wgs, dq_wgs;
+    int dz_parts, own_parts, dz_wgs, dq_wgs, wgs;
     int P, n_frozen, accumulate;
     const int32_t* cu;
     int n_tok, Smax, Hq, Hkv;
@@ -385,7 +385,8 @@ __device__ __forceinline__ f32x4 sum_parts(const f32x4* __restrict__ src, long i
 __device__ __forceinline__ u32x2 pack4(const f32x4& a) { return u32x2{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3])}; }
 
 __global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(BwdReduce r, QuerySplit split) {
-    int id = blockIdx.x;
+    int id = workgroup_id();
+    if (id >= r.wgs) return;
     if (id < r.dz_wgs) {
         const int which = id >= r.dz_wgs / 2;
         const long i = static_cast<long>(id - which * (r.dz_wgs / 2)) * 256 + threadIdx.x;
@@ -512,8 +513,9 @@ int launch_attn_bwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
     r.cu = q_cu; r.n_tok = n_tok; r.Smax = q_S; r.Hq = d.Hq; r.Hkv = d.Hkv;
     const long own_wgs = L.kv.head_parts > 1 ? (r.own_n4 + 255) / 256 * 2 : 0;
     const long wgs = r.dz_wgs + r.dq_wgs + own_wgs;
+    r.wgs = static_cast<int>(wgs);
     if (wgs > 0) {
-        hipLaunchKernelGGL(attn_bwd_reduce_kernel, dim3(static_cast<unsigned>(wgs)), dim3(256), 0, st, r, L.split);
+        hipLaunchKernelGGL(attn_bwd_reduce_kernel, grid_of(wgs), dim3(256), 0, st, r, L.split);
         trace_mark(st);
     }
     return static_cast<int>(hipGetLastError());

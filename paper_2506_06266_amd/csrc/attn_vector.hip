@@ -159,15 +159,16 @@ __device__ __forceinline__ const T* cache_row(const T* z, const T* own, int j, i
 template <typename T, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ zk,
-    const T* __restrict__ zv, T* __restrict__ o, float* __restrict__ lse, int S, int Hq, int Hkv, int D, int P, float scale) {
+    const T* __restrict__ zv, T* __restrict__ o, float* __restrict__ lse, int B, int S, int Hq, int Hkv, int D, int P, float scale) {
     constexpr int PITCH = 16 * NB + 4;
     __shared__ float sm_o[NW][16 * PITCH], sm_m[NW][16], sm_l[NW][16];
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nQt = (S + 15) / 16;
-    int id = blockIdx.x;
+    int id = workgroup_id();
     const int i0 = 16 * (id % nQt); id /= nQt;
     const int h = id % Hq, b = id / Hq, hk = h / (Hq / Hkv);
+    if (b >= B) return;
     const int i = min(i0 + c, S - 1);
     const RowFrag<NB> qf = row_frag<T, NB>(q + ((static_cast<size_t>(b) * S + i) * Hq + h) * D, D, g);
     const float c2 = scale * CART_LOG2E;
@@ -237,15 +238,16 @@ template <typename T, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_vector(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ zk,
     const T* __restrict__ zv, const T* __restrict__ o, const float* __restrict__ lse, const T* __restrict__ d_o,
-    float* __restrict__ delta, T* __restrict__ dq, int S, int Hq, int Hkv, int D, int P, float scale) {
+    float* __restrict__ delta, T* __restrict__ dq, int B, int S, int Hq, int Hkv, int D, int P, float scale) {
     constexpr int PITCH = 16 * NB + 4;
     __shared__ float sm_o[NW][16 * PITCH];
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nQt = (S + 15) / 16;
-    int id = blockIdx.x;
+    int id = workgroup_id();
     const int i0 = 16 * (id % nQt); id /= nQt;
     const int h = id % Hq, b = id / Hq, hk = h / (Hq / Hkv);
+    if (b >= B) return;
     const int i = min(i0 + c, S - 1);
     const size_t row = ((static_cast<size_t>(b) * S + i) * Hq + h) * D;
     const RowFrag<NB> qf = row_frag<T, NB>(q + row, D, g), gf = row_frag<T, NB>(d_o + row, D, g);
@@ -311,11 +313,12 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nPt = (P + 15) / 16, nSt = (S + 15) / 16, G = Hq / Hkv;
-    int id = blockIdx.x;
+    int id = workgroup_id();
     const bool prefix = id < nPt * Hkv;
     if (!prefix) id -= nPt * Hkv;
     const int hk = id % Hkv; id /= Hkv;
     const int key0 = 16 * (prefix ? id : id % nSt), b_own = prefix ? 0 : id / nSt;
+    if (b_own >= B) return;
     const int nkeys = prefix ? P : S;
     auto key_row = [&](int j) { return prefix ? (static_cast<size_t>(hk) * P + j) * D
                                               : ((static_cast<size_t>(b_own) * S + j) * Hkv + hk) * D; };
@@ -476,9 +479,9 @@ static inline unsigned blocks_for(long rows) { return static_cast<unsigned>((row
 template <typename T>
 static void fwd_t(const cart_attn_desc& d, float scale, const void* q, const void* k, const void* v,
                   const void* zk, const void* zv, void* o, float* lse, hipStream_t st) {
-    const unsigned wgs = static_cast<unsigned>((d.S + 15) / 16) * d.Hq * d.B;
-    CART_DISPATCH_NB(d.D, hipLaunchKernelGGL((attn_fwd_vector<T, NB, NW>), dim3(wgs), dim3(64 * NW), 0, st, (const T*)q,
-        (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (T*)o, lse, d.S, d.Hq, d.Hkv, d.D, d.P, scale));
+    const long wgs = static_cast<long>((d.S + 15) / 16) * d.Hq * d.B;
+    CART_DISPATCH_NB(d.D, hipLaunchKernelGGL((attn_fwd_vector<T, NB, NW>), grid_of(wgs), dim3(64 * NW), 0, st, (const T*)q,
+        (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (T*)o, lse, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale));
 }
 
 int launch_attn_fwd_vector(const cart_attn_desc& d, float scale, const void* q, const void* k,
@@ -495,15 +498,15 @@ template <typename T>
 static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const void* k, const void* v,
                   const void* zk, const void* zv, const void* o, const float* lse, const void* d_o,
                   void* dq, void* dk, void* dv, float* dzk, float* dzv, void* ws, hipStream_t st) {
-    const unsigned nSt = static_cast<unsigned>((d.S + 15) / 16), nPt = static_cast<unsigned>((d.P + 15) / 16);
+    const long nSt = (d.S + 15) / 16, nPt = (d.P + 15) / 16;
     float* delta = static_cast<float*>(ws);
     trace_begin(st);   // kernel order: dq (+ delta), dk/dv/dz
     CART_DISPATCH_NB(d.D, {
-        hipLaunchKernelGGL((attn_bwd_dq_vector<T, NB, NW>), dim3(nSt * d.Hq * d.B), dim3(64 * NW), 0, st, (const T*)q,
+        hipLaunchKernelGGL((attn_bwd_dq_vector<T, NB, NW>), grid_of(nSt * d.Hq * d.B), dim3(64 * NW), 0, st, (const T*)q,
                            (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (const T*)o, lse, (const T*)d_o, delta,
-                           (T*)dq, d.S, d.Hq, d.Hkv, d.D, d.P, scale);
+                           (T*)dq, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale);
         trace_mark(st);
-        hipLaunchKernelGGL((attn_bwd_dkv_vector<T, NB, NW>), dim3((nPt + nSt * d.B) * d.Hkv), dim3(64 * NW), 0, st,
+        hipLaunchKernelGGL((attn_bwd_dkv_vector<T, NB, NW>), grid_of((nPt + nSt * d.B) * d.Hkv), dim3(64 * NW), 0, st,
                            (const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, lse, delta, (const T*)d_o,
                            (T*)dk, (T*)dv, dzk, dzv, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale, d.n_frozen, d.dz_accumulate);
         trace_mark(st);

@@ -81,6 +81,15 @@ inline void trace_mark(hipStream_t st) {
 
 int device_cus();      // compute units of the current device (looked up once per device)
 
+// A launch of n workgroups whose number follows the rows of the problem.  One grid dimension of 2^32 threads or
+// more neither fails nor runs whole (8.4 million rows in workgroups of 512: most of the results were never
+// written), so workgroups past GRID_X go into the second dimension; its last row may reach past n.
+constexpr unsigned GRID_X = 1u << 21;       // (x 1024 threads)
+inline dim3 grid_of(long n) {
+    return n <= static_cast<long>(GRID_X) ? dim3(static_cast<unsigned>(n)) : dim3(GRID_X, static_cast<unsigned>((n + GRID_X - 1) / GRID_X));
+}
+__device__ __forceinline__ int workgroup_id() { return static_cast<int>(blockIdx.x + blockIdx.y * GRID_X); }
+
 // ---- internal launchers (host side), one per kernel family; all return hipError_t as int ----
 int launch_kl(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp,
               float* loss, void* d_logits, float* row_kl, void* ws, hipStream_t st);

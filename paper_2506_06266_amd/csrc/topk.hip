@@ -72,7 +72,7 @@ __device__ __forceinline__ void select_rounds(const T* row, int V, int K, uint64
 // vectors and fp32 rows used to take the selection rounds: 1024 x 50257 bf16 1422 -> 26 us, 2048 x
 // 128256 fp32 6320 -> 178 us (5.9 TB/s).
 template <typename T, int THREADS, int CAP>
-__global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t* idx_out, float* logp_out, int V, int K) {
+__global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t* idx_out, float* logp_out, int N, int V, int K) {
     constexpr int NW = THREADS / CART_WAVE, VE = LogitVec<T>::N, PER_LANE = THREADS / CART_WAVE;
     constexpr int LOW_BIT = sizeof(T) == 2 ? 16 : 0;      // (the keys of bf16 values differ in their upper halves)
     __shared__ float red_max[NW], red_sum[NW];
@@ -81,7 +81,8 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
     __shared__ uint32_t list_key[CAP], list_idx[CAP];
     __shared__ int list_n;
     __shared__ uint32_t tau_s;
-    const int n = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int n = workgroup_id(), tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    if (n >= N) return;
     const LogitRow R = logit_row<T>(n, V);
     const T* row = logits + R.row;
     const u32x4* src = reinterpret_cast<const u32x4*>(row + R.head);
@@ -215,11 +216,11 @@ static void launch_rows(const cart_topk_desc& d, const void* logits, int32_t* id
     // K = half the threads; above 512 the 1024-thread kernel often falls back to selection rounds.
     const long nvec = d.V / LogitVec<T>::N;
     if (nvec <= 4096 && d.K <= 128)
-        hipLaunchKernelGGL((topk_row<T, 256, 1024>), dim3(d.N), dim3(256), 0, st, x, idx, logp, d.V, d.K);
+        hipLaunchKernelGGL((topk_row<T, 256, 1024>), grid_of(d.N), dim3(256), 0, st, x, idx, logp, d.N, d.V, d.K);
     else if (nvec <= 12288 && d.K <= 256)
-        hipLaunchKernelGGL((topk_row<T, 512, 2048>), dim3(d.N), dim3(512), 0, st, x, idx, logp, d.V, d.K);
+        hipLaunchKernelGGL((topk_row<T, 512, 2048>), grid_of(d.N), dim3(512), 0, st, x, idx, logp, d.N, d.V, d.K);
     else
-        hipLaunchKernelGGL((topk_row<T, 1024, 4096>), dim3(d.N), dim3(1024), 0, st, x, idx, logp, d.V, d.K);
+        hipLaunchKernelGGL((topk_row<T, 1024, 4096>), grid_of(d.N), dim3(1024), 0, st, x, idx, logp, d.N, d.V, d.K);
 }
 
 int launch_topk(const cart_topk_desc& d, const void* logits, int32_t* idx, float* logp, hipStream_t st) {

@@ -290,3 +290,35 @@ def test_decode_ranges(B, Hq, Hkv, P, pool_p, most):
     o_ref, lse_ref = orc.decode_composed(f64(q), [(f64(a), f64(b)) for a, b in shared], z(pk), z(pv),
                                          None if cid is None else cid.numpy(), f64(k), f64(v), cu.numpy())
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
+
+
+# Launches of more than 2^32 threads (8.4 million rows in workgroups of 512): every row is computed.
+def test_topk_of_millions_of_rows():
+    N, V, K = 8_400_000, 136, 130
+    x = torch.empty(N, V, dtype=torch.bfloat16, device=DEV)
+    g = torch.Generator(device=DEV).manual_seed(1)
+    for c in x.split(2 ** 20):
+        c.copy_(torch.randn(c.shape, generator=g, device=DEV))
+    idx = torch.full((N, K), -1, dtype=torch.int32, device=DEV)
+    cb.cart_teacher_topk(x, K, teacher_idx=idx)
+    for c, i in zip(x.split(2 ** 20), idx.split(2 ** 20)):
+        ref = torch.sort(c.float(), dim=1, descending=True, stable=True)[1][:, :K]
+        assert torch.equal(i.long(), ref)
+
+
+def test_attention_vector_of_millions_of_workgroups():
+    B, H, D, P = 270_000, 32, 64, 2
+    g = torch.Generator(device=DEV).manual_seed(2)
+    q, k, v, do = (torch.randn(B, 1, H, D, generator=g, device=DEV) for _ in range(4))
+    zk, zv = (torch.randn(H, P, D, generator=g, device=DEV) for _ in range(2))
+    outs = [torch.full_like(q, float("nan")) for _ in range(4)]
+    lse = torch.full((B, H, 1), float("nan"), device=DEV)
+    cb.cart_attn_fwd(q, k, v, zk, zv, o=outs[0], lse=lse)
+    cb.cart_attn_bwd(q, k, v, zk, zv, outs[0], lse, do, d_q=outs[1], d_k_own=outs[2], d_v_own=outs[3])
+    torch.cuda.synchronize()
+    assert all(torch.isfinite(t).all() for t in outs + [lse])
+    for b in (0, B // 2, B - 1):
+        n = [f64(t[b:b + 1]) for t in (q, k, v)] + [f64(zk), f64(zv), f64(do[b:b + 1])]
+        ref = [*orc.attn_fwd(*n[:5]), *orc.attn_bwd(*n)[:3]]
+        for x, r in zip([outs[0][b:b + 1], lse[b:b + 1]] + [t[b:b + 1] for t in outs[1:]], ref):
+            assert rel_err(x, r) <= TOL[torch.float32]
