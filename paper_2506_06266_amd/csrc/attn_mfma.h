@@ -423,6 +423,29 @@ __device__ __forceinline__ RowSums store_rows64(char* lds, const f32x16 (&acc)[4
     return rs;
 }
 
+// The same rows straight from the registers (bf16), for a workgroup with few of them
+__device__ __forceinline__ RowSums store_rows64_direct(const f32x16 (&acc)[4][2], float mul0, float mul1, bf16_t* __restrict__ out,
+                                                       size_t pitch, int n_rows, int lane) {
+    const int lg = lane >> 5, lc = lane & 31;
+    RowSums rs = {};
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+        if (32 * cb + lc >= n_rows) continue;
+        const float mul = cb ? mul1 : mul0;
+        bf16_t* const row = out + (32 * cb + lc) * pitch + 4 * lg;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int r4 = 0; r4 < 4; ++r4) {
+                const float v0 = acc[db][cb][4 * r4] * mul, v1 = acc[db][cb][4 * r4 + 1] * mul,
+                            v2 = acc[db][cb][4 * r4 + 2] * mul, v3 = acc[db][cb][4 * r4 + 3] * mul;
+                rs.s[cb] += (v0 + v1) + (v2 + v3);
+                *reinterpret_cast<u32x2*>(row + 32 * db + 8 * r4) = u32x2{pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
+            }
+    }
+    return rs;
+}
+
 // ---- direct-to-LDS loads --------------------------------------------------------------------
 // The loads are written as inline assembly so that the wait for them sits where the pipeline
 // wants it (one s_waitcnt vmcnt(0) in front of the barrier that publishes the tile, a whole

@@ -95,6 +95,9 @@ __device__ __forceinline__ void recompute_rows(
     }
 }
 
+// FEW: launches whose blocks have rows for two wavefronts at most and run whole (see launch_attn_fwd_mfma).
+// Two wavefronts' stores straight from the registers end sooner than their way through LDS.
+template <bool FEW>
 __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, const bf16_t* __restrict__ v,
     const bf16_t* __restrict__ zk, const bf16_t* __restrict__ zv, bf16_t* __restrict__ o,
@@ -104,7 +107,8 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     __shared__ FwdSmem sm;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform, in a scalar register
-    const QueryBlock qb = query_block(blockIdx.x, wv, Smax, Hq, Hkv, split);
+    const QueryBlock qb = FEW ? query_block_of(blockIdx.x % Hkv, blockIdx.x / Hkv, wv, 1, Hq / Hkv)
+                              : query_block(blockIdx.x, wv, Smax, Hq, Hkv, split);
     const int hk = qb.hk, b = qb.b, h = qb.h, q0 = qb.q0, wrow0 = qb.wrow0;
     // Rows of sequence b: [t0, t0 + S).  Batched layout: S rows each; packed layout (cu given):
     // rows cu[b] .. cu[b+1]-1 of T, the grid is sized for the longest sequence and a workgroup
@@ -445,7 +449,7 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
 
     // normalise and store, turned around in LDS once nobody reads a tile or has a load in flight
     dma_wait();
-    __syncthreads();
+    if (!FEW) __syncthreads();
     float l_tot[2], inv[2];
 #pragma unroll
     for (int cb = 0; cb < 2; ++cb) {
@@ -460,7 +464,9 @@ __global__ __launch_bounds__(256, 1) void attn_fwd_mfma_kernel(
     }
     char* const turn = reinterpret_cast<char*>(&sm) + wv * (2 * FWD_TILE_B);
     RowSums rs;
-    if (qb.n_parts == 1)
+    if (FEW)
+        rs = store_rows64_direct(acc, inv[0], inv[1], o + ((t0 + wrow0) * Hq + h) * HD, static_cast<size_t>(Hq) * HD, S - wrow0, lane);
+    else if (qb.n_parts == 1)
         rs = store_rows64(turn, acc, inv[0], inv[1], o + ((t0 + wrow0) * Hq + h) * HD, static_cast<size_t>(Hq) * HD, S - wrow0, lane);
     else
         rs = store_rows64(turn, acc, inv[0], inv[1], part_o + (static_cast<size_t>(qb.slot) * 256 + 64 * wv) * HD, HD, S - wrow0, lane);
@@ -705,9 +711,16 @@ int launch_attn_fwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
         S = T;
     }
     trace_begin(st);   // kernel order: forward, finish (nothing between its events when no block is split)
-    hipLaunchKernelGGL(attn_fwd_mfma_kernel, dim3(n_items), dim3(256), 0, st, Q, K, V, ZK, ZV,
-                       static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T, S, d.Hq, d.Hkv, d.P, scale * CART_LOG2E, sp,
-                       part_o, part_l);
+    // Sequences of at most two units (64 tokens of one query head of the KV group), one block each.  With the stores
+    // through LDS (us a forward call): 256 sequences of 64 tokens, 16 / 16 heads, 64 slots 148.0, now 130.8; 128 of 128,
+    // 32 / 32 heads 198.5, now 178.7.  With four wavefronts' rows LDS is the faster way (see store_rows64).
+    const bool few = !row_lo && sp.n_parts == 0 && (S + 63) / 64 * (d.Hq / d.Hkv) <= 2;
+    auto forward = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(n_items), dim3(256), 0, st, Q, K, V, ZK, ZV, static_cast<bf16_t*>(o), lse, flags, cu, row_lo, T,
+                           S, d.Hq, d.Hkv, d.P, scale * CART_LOG2E, sp, part_o, part_l);
+    };
+    if (few) forward(attn_fwd_mfma_kernel<true>);
+    else     forward(attn_fwd_mfma_kernel<false>);
     trace_mark(st);
     if (sp.n_blocks > 0)
         hipLaunchKernelGGL(attn_fwd_finish_kernel, dim3(static_cast<unsigned>(8 * sp.n_blocks) * d.Hkv), dim3(256), 0, st, Q, K, V, ZK, ZV,

@@ -63,6 +63,14 @@ def test_attention_query_blocks(B, S, Hq, Hkv, P):
 
 
 
+# Sequences of one or two units (64 tokens of one query head of the group), enough of them that blocks run whole:
+# one wavefront's rows or two's, a unit of one row, and just past two units.
+@pytest.mark.parametrize("B,S,Hq,Hkv,P", [(300, 64, 1, 1, 3), (270, 65, 1, 1, 64), (260, 128, 2, 2, 5), (260, 33, 2, 1, 70), (280, 1, 2, 1, 1),
+                                          (260, 129, 1, 1, 3), (260, 64, 3, 1, 3), (130, 40, 4, 2, 0)])
+def test_attention_of_many_short_sequences(B, S, Hq, Hkv, P):
+    check_attn(*attn_case((B, S), Hq, Hkv, 128, P, torch.bfloat16, 13 * S + P), impl=cb.IMPL_MFMA)
+
+
 # Small launches: query blocks split along their key tiles (forward, dQ), the key-stationary kernel cut
 # into chunks of token rows and parts of the heads.  Many short parts, parts with a ragged prefix tile
 # or nothing but masked tiles, blocks of one part among split ones, no prefix, one token block, a
