@@ -186,12 +186,13 @@ inline float run_next(float* free_at, int n, float t) {
     free_at[m] = end;
     return end;
 }
-// (host) the split of a query-stationary launch: B sequences of at most S tokens, blocks of at most
-// own_cap own-key tiles (packed rows: bounded by the longest sequence),
-// and the time of a whole block, a + b per key tile (us).
-void plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, float a, float b);
+// (host) the split of a query-stationary launch: B sequences of at most S tokens; packed rows: own_cap, the most
+// own-key tiles of a block (bounded by the longest sequence; 0: batched layout), and whether sequences meet inside blocks.
+// us: a block's set-up and store, each key tile, and what a split adds: to the call, for each part of a block
+// (the sums run over them in turn), for each workgroup.
 enum QueryKernel { QUERY_FWD, QUERY_DQ };
-constexpr float FWD_BLOCK_US = 10.f, FWD_TILE_US = 1.4f, DQ_BLOCK_US = 11.f, DQ_TILE_US = 1.95f;    // a block's set-up and store, each key tile
+struct SplitCost { float block, tile, fix, part, wg; };
+void plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, bool meet, const SplitCost& us);
 // The cut of the key-stationary launch: token rows per dZ partial, the partials, and into how many parts the
 // query heads that read an own key are split
 struct KvPlan { int chunk, n_part, head_parts; };

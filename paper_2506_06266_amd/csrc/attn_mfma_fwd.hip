@@ -569,14 +569,18 @@ int launch_row_lo(const int32_t* cu, int B, int T, int32_t* row_lo, hipStream_t 
 }
 
 // Whether and how far to split is decided by playing the launch through: blocks go to the CU that is
-// free first, in order.  Splitting costs the finishing kernel's second role and the partials' way
-// through memory (SPLIT_FIX, SPLIT_PER us): measured on one sequence of 128 tokens with 1024 prefix
-// slots (16 blocks of 18 tiles), 16 / 64 / 96 / 160 workgroups -> 31.0 / 24.7 / 26.4 / 30.9 us a
-// forward call; 700 tokens, 1000 slots (88 blocks of 17-27 tiles), 88 / 160 / 192 / 248 workgroups -> 44.4
-// / 43.0 / 40.4 / 38.3; 8 sequences of 512, 24 heads, 4096 slots (384 blocks, 1.5 rounds): the last half
-// round in two parts 209 -> 190.  With many rounds there is little to gain, and blocks of very
-// different lengths (long sequences, short prefix) even each other out: not split.
-constexpr float SPLIT_FIX = 4.f, SPLIT_PER = 0.05f;
+// free first, in order.  With many rounds there is little to gain, and blocks of very different lengths (long
+// sequences, short prefix) even each other out: not split.
+// The forward's times, from calls with every number of parts (us; tiles of the longest block, blocks -> whole;
+// 2, 3, 4, 6 parts; * taken):
+//   1 x   64 tokens, 32 / 8 heads, 2000 slots  33,  8 -> 48.6; 35.3 30.6 27.8 26.5*     1 x 256, 32 / 8,  512  12, 32 -> 23.6*; 25.8 25.6 27.6 29.4
+//   1 x  128,        32 / 8,       1024        18, 16 -> 30.6; 27.5 25.4* 24.6 26.2     1 x  32,  8 / 8,  300   6,  8 -> 15.6*; 17.6 18.4 18.4 20.5
+//   1 x  700,        32 / 8,       1000        27, 88 -> 41.9; 40.0 38.0* -             6 x  90, 16 / 4,  700  13, 48 -> 24.2*; 26.7 26.7 29.4 30.2
+//   1 x 1024,         8 / 2,          0        16, 32 -> 28.4; 25.6 24.5 24.0* 25.6     2 x  64,  8 / 2,  600  11,  4 -> 22.8; 21.8 20.2 20.7* 22.2
+//   1 x 2048,         8 / 2,        256        36, 64 -> 51.8; 39.8 34.4 32.4 31.4      2 x 333,  3 / 3,   31   7, 12 -> 18.1*; 23.7 24.3 25.0 24.9
+// Only unmasked tiles are divided (see key_tiles): a part that ends in ten masked ones is no shorter for it (three packed
+// sequences of 700, 1 and 90 tokens, 32 / 8 heads, 300 slots: whole 40.6, 2 parts 49.7).
+constexpr SplitCost SPLIT_COST[2] = {{9.2f, 1.21f, 3.5f, 0.7f, 0.045f}, {11.f, 1.95f, 4.f, 0.f, 0.05f}};
 
 // blocks per KV head the chip runs at one time
 static int query_slots(int Hkv) {
@@ -584,7 +588,7 @@ static int query_slots(int Hkv) {
     return n < 1 ? 1 : (n > MAX_SPLIT ? MAX_SPLIT : n);
 }
 
-void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, float a, float b) {
+void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, bool meet, const SplitCost& us) {
     const int nW = query_wgs(S, G);
     const long n_all = static_cast<long>(B) * nW;
     const int slots = query_slots(Hkv);
@@ -593,40 +597,49 @@ void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P,
     if (n_all > 4L * slots || n_all > 2 * MAX_SPLIT) return;
     const int n = static_cast<int>(n_all), left = n % slots;       // the blocks left over after whole rounds
     if (left == 0) return;
+    struct Tiles { int all, masked; };
     auto tiles = [&](int e) {
-        const int w = nW - 1 - e % nW, q_end = 64 * ((4 * w + 3) / G) + 64;
-        const int own = ((q_end < S ? q_end : S) + 63) / 64;
-        return (P + 63) / 64 + (own < own_cap ? own : own_cap);
+        const int w = nW - 1 - e % nW, q_end = 64 * ((4 * w + 3) / G) + 64, tD = 4 * w / G;
+        const int upto = ((q_end < S ? q_end : S) + 63) / 64, own = own_cap > 0 && own_cap < upto ? own_cap : upto;
+        // (a block in which sequences meet: none of its own tiles is seen whole by all of its rows)
+        return Tiles{(P + 63) / 64 + own, (P % 64 ? 1 : 0) + (meet ? own : upto - tD < own ? upto - tD : own)};
+    };
+    // the longest of np parts
+    auto longest = [](const Tiles& t, int np) {
+        const int step = (t.all + np - 1) / np, last = t.all - t.masked - 1, from = (np - 1) * step < last ? (np - 1) * step : last;
+        return np == 1 ? t.all : t.all - (from > 0 ? from : 0) > step ? t.all - (from > 0 ? from : 0) : step;
     };
     float cu[MAX_SPLIT];                                    // when each CU is free
     for (int i = 0; i < slots; ++i) cu[i] = 0.f;
     float done = 0.f;                                       // when the whole rounds are done
     for (int e = 0; e < n - left; ++e) {
-        const float t = run_next(cu, slots, a + b * tiles(e));
+        const float t = run_next(cu, slots, us.block + us.tile * tiles(e).all);
         done = t > done ? t : done;
     }
-    int tl[MAX_SPLIT], most = 0;
+    Tiles tl[MAX_SPLIT];
+    int most = 0;
     for (int i = 0; i < left; ++i) {
         tl[i] = tiles(n - left + i);
-        most = tl[i] > most ? tl[i] : most;
+        most = tl[i].all > most ? tl[i].all : most;
     }
     int best = 0;                                           // tiles per part, 0: whole
     float best_t = 0.f;
     for (int parts = 1; parts <= 32 && parts <= most; ++parts) {
         const int tps = (most + parts - 1) / parts;
         int items = 0;
-        for (int i = 0; i < left; ++i) items += (tl[i] + tps - 1) / tps;
+        for (int i = 0; i < left; ++i) items += (tl[i].all + tps - 1) / tps;
         if (items > slots) break;
         float c[MAX_SPLIT], end = done;
         for (int i = 0; i < slots; ++i) c[i] = cu[i];
         for (int i = 0; i < left; ++i) {
-            const int np = (tl[i] + tps - 1) / tps;
+            const int np = (tl[i].all + tps - 1) / tps;
             for (int p = 0; p < np; ++p) {
-                const float us = a + b * ((tl[i] + np - 1) / np), t = n == left ? us : run_next(c, slots, us);
+                const float len = us.block + us.tile * (p == np - 1 ? longest(tl[i], np) : (tl[i].all + np - 1) / np);
+                const float t = n == left ? len : run_next(c, slots, len);
                 end = t > end ? t : end;
             }
         }
-        if (parts > 1) end += SPLIT_FIX + SPLIT_PER * items * Hkv;
+        if (parts > 1) end += us.fix + us.part * ((most + tps - 1) / tps) + us.wg * items * Hkv;
         if (parts == 1 || end < best_t) {
             best_t = end;
             best = parts == 1 ? 0 : tps;
@@ -636,7 +649,7 @@ void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P,
     sp.e_full = n - left;
     sp.n_blocks = left;
     for (int i = 0; i < left; ++i) {
-        const uint32_t np = static_cast<uint32_t>((tl[i] + best - 1) / best);
+        const uint32_t np = static_cast<uint32_t>((tl[i].all + best - 1) / best);
         sp.first[i] = static_cast<uint32_t>(sp.n_parts);
         for (uint32_t p = 0; p < np; ++p) sp.part[sp.n_parts++] = static_cast<uint32_t>(i) | p << 8 | np << 16;
     }
@@ -650,16 +663,18 @@ bool attn_mfma_supported(const cart_attn_desc& d) {
 // ask for the same two splits in turn, forward's and dQ's: the thread's last one of either kind is kept with
 // all that it depends on (planned again at each call, 32 sequences of 516 tokens, 8 / 2 heads: 18 us a layer).
 void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind) {
-    struct Key { int B, S, G, Hkv, P, own_cap, cus; };
+    struct Key { int B, S, G, Hkv, P, own_cap, meet, cus; };
     static thread_local Key last[2];
     static thread_local QuerySplit kept[2];
     const int G = d.Hq / d.Hkv;
     const bool rows = T > 0 && d.P > 0;
-    const Key k = {rows ? 1 : d.B, rows ? T : d.S, G, d.Hkv, d.P, rows ? (d.S + 255) / 64 + 2 : 1 << 30, device_cus()};
+    // (packed: a block's rows and those of the first one's sequence before it, and the tiles they begin and end inside)
+    const int block_rows = 4 % G == 0 ? 256 / G : G % 4 == 0 ? 64 : 128;
+    const Key k = {rows ? 1 : d.B, rows ? T : d.S, G, d.Hkv, d.P, rows ? (d.S + block_rows + 126) / 64 : 0, rows && d.B > 1, device_cus()};
     Key& l = last[kind];
-    if (l.cus != k.cus || l.B != k.B || l.S != k.S || l.G != k.G || l.Hkv != k.Hkv || l.P != k.P || l.own_cap != k.own_cap) {
-        plan_query_split(kept[kind], k.B, k.S, G, d.Hkv, d.P, k.own_cap, kind == QUERY_DQ ? DQ_BLOCK_US : FWD_BLOCK_US,
-                         kind == QUERY_DQ ? DQ_TILE_US : FWD_TILE_US);
+    if (l.cus != k.cus || l.B != k.B || l.S != k.S || l.G != k.G || l.Hkv != k.Hkv || l.P != k.P || l.own_cap != k.own_cap ||
+        l.meet != k.meet) {
+        plan_query_split(kept[kind], k.B, k.S, G, d.Hkv, d.P, k.own_cap, k.meet != 0, SPLIT_COST[kind]);
         l = k;
     }
     sp = kept[kind];
