@@ -26,6 +26,19 @@ def rel_err(x, ref):
     return float(np.abs(x - ref).max() / max(np.abs(ref).max(), 1e-300))
 
 
+def best_us(call, runs=5):
+    call()
+    best = float("inf")
+    for _ in range(runs):
+        t = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        t[0].record()
+        call()
+        t[1].record()
+        t[1].synchronize()
+        best = min(best, 1e3 * t[0].elapsed_time(t[1]))
+    return best
+
+
 def attn_case(rows, Hq, Hkv, D, P, dtype, seed):
     g = torch.Generator().manual_seed(seed)
     rn = lambda *sz, std=1.0: (std * torch.randn(*sz, generator=g)).to(dtype)
@@ -204,6 +217,21 @@ def test_loss_rows(dtype, N, V, K):
         assert rel_err(dl, dl_ref) <= TOL[dtype] + ill
         assert abs(loss.item() - loss_ref) <= (1e-4 + ill) * max(abs(loss_ref), 1e-3)
         assert rel_err(row, kl_ref) <= 1e-4 + ill
+
+
+# The records of a row are passed by all of its threads: a thousand of them may cost a few times the row, not more
+# (3.4 and 2.4 times the 20 records' time; 8.2 and 7.3 with one record after the other).
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+def test_loss_time_of_many_records(dtype):
+    N, V = 4096, 32000
+    x = torch.randn(N, V, device=DEV).to(dtype)
+    d = torch.empty_like(x)
+    us = []
+    for K in (20, 1000):
+        idx = torch.arange(K, dtype=torch.int32, device=DEV).expand(N, K).contiguous()
+        lp = torch.full((N, K), -8.0, device=DEV)
+        us.append(best_us(lambda: cb.cart_distill_kl_fwd_bwd(x, idx, lp, 1.0, d_logits=d)))
+    assert us[1] < 5.0 * us[0], us
 
 
 # Rows of more than 2 GB (bf16; the second starts inside a 128-byte line) and more than 4 GB (fp32): past what
