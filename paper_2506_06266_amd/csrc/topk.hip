@@ -22,40 +22,108 @@ __device__ __forceinline__ float f32_key_value(uint32_t key) {
 __device__ __forceinline__ uint64_t order_word(uint32_t key, uint32_t idx) {
     return (static_cast<uint64_t>(key) << 32) | (0xffffffffu - idx);
 }
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const uint64_t w = __shfl_xor(v, o, CART_WAVE);
-        v = w > v ? w : v;
+__device__ __forceinline__ uint32_t word_index(uint64_t w) { return 0xffffffffu - static_cast<uint32_t>(w); }
+
+// Every listed logit counts the listed ones that precede it: that is its output position (positions from K on are dropped).
+template <int THREADS>
+__device__ __forceinline__ void write_ranked(const uint64_t* list, int cnt, int K, int32_t* idx_out, float* logp_out, float lse) {
+    const ulonglong2* pairs = reinterpret_cast<const ulonglong2*>(list);
+    for (int t = threadIdx.x; t < cnt; t += THREADS) {
+        const uint64_t me = list[t];
+        int rank = 0;
+#pragma unroll 4
+        for (int j = 0; j < cnt / 2; ++j) {
+            const ulonglong2 w = pairs[j];
+            rank += (w.x > me) + (w.y > me);
+        }
+        if (cnt & 1) rank += list[cnt - 1] > me;
+        if (rank < K) {
+            idx_out[rank] = static_cast<int32_t>(word_index(me));
+            logp_out[rank] = f32_key_value(static_cast<uint32_t>(me >> 32)) - lse;
+        }
     }
-    return v;
 }
 
-// K rounds of "the row's best order word strictly below the previous winner", straight from memory
-template <typename T, int NW>
-__device__ __forceinline__ void select_rounds(const T* row, int V, int K, uint64_t* red, int32_t* idx_out, float* logp_out,
-                                              float lse) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    uint64_t prev = ~0ull;
-    for (int j = 0; j < K; ++j) {
-        uint64_t best = 0;
-        for (int v = threadIdx.x; v < V; v += NW * CART_WAVE) {
-            const uint64_t ow = order_word(f32_key(elem<T>::load(row + v)), static_cast<uint32_t>(v));
-            if (ow < prev && ow > best) best = ow;
-        }
-        best = wave_max_u64(best);
-        if (lane == 0) red[wv] = best;
-        __syncthreads();
-        best = red[0];
+// Lists the K best of a row, whatever it holds, and at most a quarter more (or 128); returns how many.  The K-th largest key two
+// bits at a time, and where too many logits reach it the index of the last of its equals that belongs, two bits at a
+// time too; each step counts the row's logits against three candidates.  The row is read again for every step, from
+// cache: 16 steps at most for the key of an fp32 (8 of a bf16), fewer where a candidate leaves few enough.  (K rounds of "the best one below the last winner" instead, us: 4096
+// rows of 1024 bf16 logits, K = 1024 15300, now 268; of 4096, K = 600 10780, now 191;
+// of 32000, K = 1000 10460, now 3420; 16384 of 256, K = 40 404, now 59.)
+template <typename T, int THREADS, int CAP>
+__device__ __forceinline__ int list_best(const T* row, const LogitRow& R, int V, int K, int (*count)[4], uint64_t* list, int* list_n) {
+    constexpr int VE = LogitVec<T>::N, LOW_BIT = sizeof(T) == 2 ? 16 : 0;      // (the keys of bf16 values differ in their upper halves)
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const u32x4* src = reinterpret_cast<const u32x4*>(row + R.head);
+    // f(upper bits of the key, index, whether there is such a logit), whole wavefronts at a time
+    auto each = [&](auto f) __attribute__((always_inline)) {
+        for (int v0 = wv * CART_WAVE; v0 < R.nvec; v0 += THREADS) {
+            const int v = v0 + lane;
+            const bool ok = v < R.nvec;
+            const u32x4 w = src[ok ? v : 0];
 #pragma unroll
-        for (int w = 1; w < NW; ++w) best = red[w] > best ? red[w] : best;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            idx_out[j] = static_cast<int32_t>(0xffffffffu - static_cast<uint32_t>(best));
-            logp_out[j] = f32_key_value(static_cast<uint32_t>(best >> 32)) - lse;
+            for (int e = 0; e < VE; ++e)
+                f(f32_key(__uint_as_float(LogitVec<T>::bits(w, e))) >> LOW_BIT, static_cast<uint32_t>(R.head + VE * v + e), ok);
         }
-        prev = best;
+        if (wv == 0) {
+            const bool ok = lane < R.head + R.tail;
+            const int i = ok ? logit_single<T>(R, lane) : 0;
+            f(f32_key(elem<T>::load(row + i)) >> LOW_BIT, static_cast<uint32_t>(i), ok);
+        }
+    };
+    // The row's logits for which each of three conditions holds.  Counters in rotation: those of the next step
+    // are cleared while everyone is past the barrier behind which they were last read.
+    int step = 0;
+    auto count3 = [&](auto cond, int (&c)[3]) __attribute__((always_inline)) {
+        int n[3] = {0, 0, 0};
+        each([&](uint32_t key, uint32_t i, bool ok) __attribute__((always_inline)) {
+#pragma unroll
+            for (int j = 0; j < 3; ++j) n[j] += __popcll(__ballot(ok && cond(key, i, j)));
+        });
+        const int next = step == 2 ? 0 : step + 1;
+        if (tid < 3) count[next][tid] = 0;
+        if (lane < 3) atomicAdd(&count[step][lane], lane == 0 ? n[0] : lane == 1 ? n[1] : n[2]);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 3; ++j) c[j] = count[step][j];
+        step = next;
+    };
+    __syncthreads();                        // (the counters and the list's may still be read)
+    if (tid < 3) count[0][tid] = 0;
+    if (tid == 0) *list_n = 0;
+    __syncthreads();
+    // t: the K-th key as far as decided, reached by `ge` logits; `gt` logits lie above all keys that begin like it
+    uint32_t t = 0, upto = 0xffffffffu;
+    const int most = min(max(K + K / 4, 128), CAP);          // (ranking 128 is cheaper than a step)
+    int ge = V, gt = 0;
+    for (int bit = 30 - LOW_BIT; bit >= 0 && ge > most; bit -= 2) {
+        int c[3];
+        count3([&](uint32_t key, uint32_t, int j) __attribute__((always_inline)) { return key >= (t | static_cast<uint32_t>(j + 1) << bit); }, c);
+        const int j = (c[0] >= K) + (c[1] >= K) + (c[2] >= K);
+        gt = j == 0 ? c[0] : j == 1 ? c[1] : j == 2 ? c[2] : gt;
+        ge = j == 0 ? ge : c[j - 1];
+        t |= static_cast<uint32_t>(j) << bit;
     }
+    if (ge > most) {                        // t is the K-th key itself: of its equals the K - gt with the lowest indices
+        uint32_t last = 0;
+        for (int bit = (31 - __clz(V)) & ~1; bit >= 0; bit -= 2) {
+            int c[3];
+            count3([&](uint32_t key, uint32_t i, int j) __attribute__((always_inline)) {
+                return key == t && i < (last | static_cast<uint32_t>(j + 1) << bit);
+            }, c);
+            last |= static_cast<uint32_t>((c[0] < K - gt) + (c[1] < K - gt) + (c[2] < K - gt)) << bit;
+        }
+        upto = last;
+        ge = K;
+    }
+    each([&](uint32_t key, uint32_t i, bool ok) __attribute__((always_inline)) {
+        if (ok && (key > t || (key == t && i <= upto))) {
+            const int pos = atomicAdd(list_n, 1);
+            list[pos] = order_word(f32_key(elem<T>::load(row + i)), i);
+        }
+    });
+    __syncthreads();
+    return ge;
 }
 
 // One pass: the log-sum-exp and, per thread, the maxima of its three best vectors and which the
@@ -63,8 +131,8 @@ __device__ __forceinline__ void select_rounds(const T* row, int V, int K, uint64
 // every winner is.  The logits >= tau (K plus a few) are listed: a thread whose best (two) vectors
 // reach tau reads those vectors again, one whose third reaches it too reads all of its vectors.
 // Each listed logit then counts the listed logits that precede it; that is its output position.
-// A row whose list does not fit (thousands of ties at the top), or with fewer than K threads that
-// hold a logit above -inf, takes K selection rounds over the row instead.
+// A row whose list does not fit (thousands of ties at the top, K near the number of threads), or with fewer than K
+// threads that hold a logit above -inf, takes list_best's instead.
 //   Bound by HBM (one read of the row) with the arithmetic close behind: the exponential of every
 // logit, and for the candidates eight plain instructions per VECTOR (three of them v_med3 / v_max
 // on the maxima).  Keeping the two best LOGITS of a thread instead took seven per logit in 87 % of
@@ -76,9 +144,9 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
     constexpr int NW = THREADS / CART_WAVE, VE = LogitVec<T>::N, PER_LANE = THREADS / CART_WAVE;
     constexpr int LOW_BIT = sizeof(T) == 2 ? 16 : 0;      // (the keys of bf16 values differ in their upper halves)
     __shared__ float red_max[NW], red_sum[NW];
-    __shared__ uint64_t red_w[NW];
+    __shared__ int counts[3][4];
     __shared__ uint32_t all_kmax[THREADS];
-    __shared__ uint32_t list_key[CAP], list_idx[CAP];
+    __shared__ __attribute__((aligned(16))) uint64_t list[CAP];
     __shared__ int list_n;
     __shared__ uint32_t tau_s;
     const int n = workgroup_id(), tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
@@ -169,7 +237,7 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
         auto put = [&](float x, uint32_t i) __attribute__((always_inline)) {
             if (x >= tau) {
                 const int pos = atomicAdd(&list_n, 1);
-                if (pos < CAP) { list_key[pos] = f32_key(x); list_idx[pos] = i; }
+                if (pos < CAP) list[pos] = order_word(f32_key(x), i);
             }
         };
         auto put_vec = [&](int pv) __attribute__((always_inline)) {
@@ -189,20 +257,9 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
         }
     }
     __syncthreads();
-    const int cnt = list_n;
-    if (listed && cnt >= K && cnt <= CAP) {
-        for (int t = tid; t < cnt; t += THREADS) {
-            const uint64_t me = order_word(list_key[t], list_idx[t]);
-            int rank = 0;
-            for (int j = 0; j < cnt; ++j) rank += order_word(list_key[j], list_idx[j]) > me;
-            if (rank < K) {
-                idx_out[rank] = static_cast<int32_t>(list_idx[t]);
-                logp_out[rank] = f32_key_value(list_key[t]) - lse;
-            }
-        }
-        return;
-    }
-    select_rounds<T, NW>(row, V, K, red_w, idx_out, logp_out, lse);
+    int cnt = list_n;
+    if (!listed || cnt < K || cnt > CAP) cnt = list_best<T, THREADS, CAP>(row, R, V, K, counts, list, &list_n);
+    write_ranked<THREADS>(list, cnt, K, idx_out, logp_out, lse);
 }
 
 template <typename T>
@@ -212,15 +269,19 @@ static void launch_rows(const cart_topk_desc& d, const void* logits, int32_t* id
     // its loads (reductions, tau, list) against the workgroups a CU overlaps.  256 / 512 / 1024
     // threads, us for 4096 rows of V bf16 logits: V 128256 207 / 188 / 191 (16384 rows 724 / 703 /
     // 693, 1024 fp32 rows 140 / 107 / 97), 50257 84 / 81 / 106, 16000 35 / 45 / 71, 4096 15 / 24 / 56;
-    // 256 rows of 128256: 45 / 25 / 18.  Every list has room for K records and their like only up to
-    // K = half the threads; above 512 the 1024-thread kernel often falls back to selection rounds.
+    // 256 rows of 128256: 45 / 25 / 18.  K records take K threads with a vector each, so
+    // 512 or 1024 from half of the threads on.  Rows of fewer vectors than records are listed by list_best at any width: narrow
+    // where there are rows for the chip, wide where one row's time counts.  256 / 512 / 1024 threads, bf16 rows of 1024 logits:
+    // 4096 rows, K = 257 84 / 119 / 247, K = 1000 301 / 320 / 418; 256 rows, K = 600 46 / 39 / 36, K = 1000 75 / 51 / 45 (before rows
+    // of little more than K logits were listed whole).
     const long nvec = d.V / LogitVec<T>::N;
-    if (nvec <= 4096 && d.K <= 128)
-        hipLaunchKernelGGL((topk_row<T, 256, 1024>), grid_of(d.N), dim3(256), 0, st, x, idx, logp, d.N, d.V, d.K);
-    else if (nvec <= 12288 && d.K <= 256)
-        hipLaunchKernelGGL((topk_row<T, 512, 2048>), grid_of(d.N), dim3(512), 0, st, x, idx, logp, d.N, d.V, d.K);
-    else
-        hipLaunchKernelGGL((topk_row<T, 1024, 4096>), grid_of(d.N), dim3(1024), 0, st, x, idx, logp, d.N, d.V, d.K);
+    const int few = d.K > nvec ? (d.K <= 256 ? 256 : d.N <= device_cus() ? 1024 : d.K <= 512 ? 256 : 512) : 0;
+    auto launch = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, grid_of(d.N), dim3(threads), 0, st, x, idx, logp, d.N, d.V, d.K);
+    };
+    if (few == 256 || (few == 0 && nvec <= 4096 && d.K <= 128))       launch(topk_row<T, 256, 1024>, 256);
+    else if (few == 512 || (few == 0 && nvec <= 12288 && d.K <= 256)) launch(topk_row<T, 512, 2048>, 512);
+    else                                                              launch(topk_row<T, 1024, 4096>, 1024);
 }
 
 int launch_topk(const cart_topk_desc& d, const void* logits, int32_t* idx, float* logp, hipStream_t st) {

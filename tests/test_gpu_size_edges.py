@@ -272,6 +272,9 @@ TOPK_CASES = [
     (torch.bfloat16, 3, 98311, 256), (torch.bfloat16, 3, 98320, 64), (torch.bfloat16, 9, 131, 131), (torch.bfloat16, 3, 20003, 512),
     (torch.float32, 9, 7, 7), (torch.float32, 5, 16387, 128), (torch.float32, 5, 16389, 20), (torch.float32, 3, 49155, 257),
     (torch.float32, 3, 49161, 20), (torch.float32, 2, 130001, 64),
+    # more records than vectors, all of a row, as many as threads
+    (torch.bfloat16, 5, 1024, 1024), (torch.bfloat16, 5, 4096, 600), (torch.bfloat16, 3, 32000, 1000), (torch.bfloat16, 3, 8195, 1023),
+    (torch.float32, 5, 1025, 1024), (torch.float32, 5, 2003, 1000), (torch.float32, 3, 5000, 1024), (torch.float32, 9, 3, 1), (torch.float32, 9, 30, 29),
 ]
 
 
@@ -289,6 +292,41 @@ def test_topk_rows(dtype, N, V, K):
     torch.cuda.synchronize()
     assert np.array_equal(idx.cpu().numpy().astype(np.int64), idx_ref)
     assert np.abs(f64(lp) - lp_ref).max() <= 2e-6 * max(1.0, np.abs(lp_ref).max())
+
+
+# As many records as logits: the time may be some tens of times that of 20 of them, not hundreds (22; 1275 with a pass
+# over the row for every record).
+def test_topk_time_of_all_records():
+    x = torch.randn(4096, 1024, device=DEV).to(torch.bfloat16)
+    us = [best_us(lambda: cb.cart_teacher_topk(x, K)) for K in (20, 1024)]
+    assert us[1] < 100.0 * us[0], us
+
+
+# Rows with fewer finite logits than records (the lowest indices of the rest follow), of one value, of two with the
+# border inside the records; signed zeros are one value.
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
+@pytest.mark.parametrize("V,K", [(700, 300), (9001, 40), (20000, 700)])
+def test_topk_rows_of_few_values(dtype, V, K):
+    x = torch.zeros(6, V)
+    x[0] = float("-inf")
+    x[0, torch.randperm(V, generator=torch.Generator().manual_seed(V))[:K // 2]] = torch.randn(K // 2)
+    x[1] = -3.5
+    x[2] = 12.0
+    x[3, 1::2] = -0.0
+    x[4, V - K // 2:] = 1.0
+    x[5] = -1.0
+    x[5, ::7] = -0.5
+    x = x.to(dtype)
+    idx, lp = cb.cart_teacher_topk(x.to(DEV), K)
+    xs = np.where(x.float().numpy() == 0, 0.0, f64(x))
+    ref = np.argsort(-xs, axis=1, kind="stable")[:, :K]
+    assert np.array_equal(idx.cpu().numpy(), ref)
+    with np.errstate(divide="ignore"):
+        top = xs.max(1, keepdims=True)
+        want = np.take_along_axis(xs, ref, 1) - top - np.log(np.exp(xs - top).sum(1, keepdims=True))
+    got, fin = f64(lp), np.isfinite(want)
+    # (fp32: the log-sum-exp's rounding, 2^-23 of at most 24, and its sum's, a few 2^-24)
+    assert (got[~fin] == want[~fin]).all() and np.abs(got[fin] - want[fin]).max() <= 5e-6
 
 
 # Decode: streamed ranges that cross from own rows into private cartridges and from one cartridge to
