@@ -74,14 +74,19 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     for (int s = 0; s < n_seg; ++s) total_tiles += (seg_p[s] + DEC_BN - 1) / DEC_BN;
     // Into how many parts the prefix is split: the cheapest by an estimate of the fused kernel (the
     // longer of a prefix workgroup and a streaming wavefront) plus the partials' way to the merge.  A
-    // prefix workgroup takes 8 us and 0.55 us per tile, 0.8 beside a long stream; a stream 1.8 us per
+    // prefix workgroup takes 8 us and 0.55 us per tile, 0.8 on a CU it shares; a stream 1.8 us per
     // step, or its bytes at 5.5 TB/s; a part of one output row 1 KB at 2 TB/s.  Measured, whole call
     // (us): 128 requests, 8192 shared slots, own rows U[1,1024]: 3 parts 83, 6 parts 75; with 2048
     // shared slots and a private cartridge of 2048 each: 6 parts 273, 3 parts 258, 1 part 252; 32
-    // requests, 8192 slots: 24 parts 34.4, 12 parts 32.6.
+    // requests, 8192 slots: 24 parts 34.4, 12 parts 32.6; 128 requests of up to 100 own rows, 8192 slots: 6 parts, each workgroup
+    // on a CU of its own, 35.3, more of them sharing CUs 42.1.
     const long stream_rows = pool_p > 0 ? static_cast<long>(T) + static_cast<long>(B) * pool_p : T;
     const float stream_us = static_cast<float>(stream_rows) * Hkv * 2 * ROW_B / 5.5e6f;
     const long chip = 2L * device_cus();          // workgroups the chip keeps resident (256 threads, two per CU)
+    // steps of the own rows: a request takes at least one, half a step more than its rows on average
+    const float own_steps = static_cast<float>(B) * fmaxf(static_cast<float>(T) / (static_cast<float>(B) * DEC_SUB) + 0.5f, 1.f);
+    // one wavefront over all of them: 1.8 us per 32 rows and 1.3 per request (its query rows, its partial), never below 2.2
+    const float own_us = fmaxf(1.8f * static_cast<float>(T) / DEC_SUB + 1.3f * static_cast<float>(B), 2.2f * static_cast<float>(B));
     int tps = 0;
     float tps_us = 0.f;
     for (int parts = 1; parts <= DEC_MAX_SPLIT && parts <= total_tiles; parts += 1 + parts / 8) {
@@ -90,9 +95,13 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         if (parts > 1 && n_pre > chip - 64) break;
         const long waves = 4 * (chip - n_pre < 64 ? 64 : chip - n_pre);
         const float steps = ceilf(static_cast<float>(stream_rows) * Hkv / (static_cast<float>(waves) * DEC_SUB));
-        const float pre = 8.f + (stream_us > 20.f ? 0.8f : 0.55f) * static_cast<float>(t);
         const float stream = fmaxf(4.f + 1.8f * steps, stream_us);
-        const float us = fmaxf(pre, stream) + static_cast<float>(parts) * B * Hq * 2 * HD * 4 / 2.0e6f;
+        float us = fmaxf(8.f + (pool_p == 0 || stream_us > 20.f ? 0.8f : 0.55f) * static_cast<float>(t), stream);
+        if (pool_p == 0 && stream_us <= 20.f && n_pre < chip / 2) {      // (every workgroup on a CU of its own)
+            const float alone = 4.f + own_us * static_cast<float>(Hkv) / static_cast<float>(4 * (chip / 2 - n_pre));
+            us = fminf(us, fmaxf(8.f + 0.55f * static_cast<float>(t), alone));
+        }
+        us += static_cast<float>(parts) * B * Hq * 2 * HD * 4 / 2.0e6f;
         if (parts == 1 || us < tps_us) {
             tps_us = us;
             tps = t;
@@ -143,19 +152,30 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         else if (share < DEC_MIN_SHARE)   share = DEC_MIN_SHARE;
         if (share < 8) share = 8;
         used = (static_cast<long>(T) + share - 1) / share;
+        // From the workgroup on that shares a CU the prefix role takes longer (the 0.55 and 0.8 us above): longer ranges
+        // where they leave every workgroup its own CU and end before the prefix does.  212 requests, 8 / 2 heads, 10891
+        // slots, up to 184 own rows: ranges of 64 rows (360 workgroups) 38.5 us a call, of 192 (238) 31.6; 200 requests,
+        // 4096 slots, up to 300 rows 28.1, now 26.2.
+        const long room = device_cus() - n_pre_wg, fewer = room > 0 ? 4 * room / Hkv : 0;
+        if (n_pre_wg > 0 && !lean && fewer > 0 && used > fewer) {
+            const long longer = up((static_cast<long>(T) + fewer - 1) / fewer, DEC_SUB);
+            if (4.f + own_us * static_cast<float>(longer) / static_cast<float>(T) <= 8.f + 0.55f * static_cast<float>(tps)) {
+                share = longer;
+                used = (static_cast<long>(T) + share - 1) / share;
+            }
+        }
     } else {
         // Beside private cartridges: by steps, so that a range of short requests (a step each) takes as long as
         // one of cartridge rows.  Cut by rows alone (us a call): 208 requests of up to 40 own rows, cartridges of 786
         // slots 230, now 179; 121 requests, cartridges of 389 265, now 70; 223 requests, cartridges of one slot 458, now 63.
-        const float rows = static_cast<float>(T) / static_cast<float>(B);
-        const float own_steps = fmaxf(rows / DEC_SUB + 0.5f, 1.f), pool_steps = ceilf(static_cast<float>(pool_p) / DEC_SUB);
-        const float each = fmaxf(static_cast<float>(B) * (own_steps + pool_steps) / static_cast<float>(ranges > 4 ? ranges - 2 : ranges),
+        const float pool_steps = ceilf(static_cast<float>(pool_p) / DEC_SUB);
+        const float each = fmaxf((own_steps + static_cast<float>(B) * pool_steps) / static_cast<float>(ranges > 4 ? ranges - 2 : ranges),
                                  static_cast<float>(DEC_MIN_SHARE / DEC_SUB));        // steps per range
         auto cut = [&](float x, long at_least) {
             const long r = static_cast<long>(x) > at_least ? static_cast<long>(x) : at_least;
             return up(r < 8 ? 8 : r, r <= DEC_SUB ? 8 : DEC_SUB);
         };
-        share = cut(each * rows / own_steps, least);
+        share = cut(each * static_cast<float>(T) / own_steps, least);
         p.pool_share = static_cast<int>(cut(each * static_cast<float>(pool_p) / pool_steps, 0));
         p.pool_r0 = static_cast<int>((static_cast<long>(T) + share - 1) / share);
         used = p.pool_r0 + (static_cast<long>(B) * pool_p + p.pool_share - 1) / p.pool_share;
