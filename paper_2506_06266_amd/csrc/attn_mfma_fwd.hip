@@ -580,6 +580,7 @@ int launch_row_lo(const int32_t* cu, int B, int T, int32_t* row_lo, hipStream_t 
 //   1 x 2048,         8 / 2,        256        36, 64 -> 51.8; 39.8 34.4 32.4 31.4      2 x 333,  3 / 3,   31   7, 12 -> 18.1*; 23.7 24.3 25.0 24.9
 // Only unmasked tiles are divided (see key_tiles): a part that ends in ten masked ones is no shorter for it (three packed
 // sequences of 700, 1 and 90 tokens, 32 / 8 heads, 300 slots: whole 40.6, 2 parts 49.7).
+constexpr int SPLIT_MIN_TILES = 4;      // (dQ: 1.95 (n - 1) > 4 + 2 x 0.05; the forward: 6)
 constexpr SplitCost SPLIT_COST[2] = {{9.2f, 1.21f, 3.5f, 0.7f, 0.045f}, {11.f, 1.95f, 4.f, 0.f, 0.05f}};
 
 // blocks per KV head the chip runs at one time
@@ -594,7 +595,7 @@ void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P,
     const int slots = query_slots(Hkv);
     sp.e_full = static_cast<int>(n_all);
     sp.n_blocks = sp.n_parts = 0;
-    if (n_all > 4L * slots || n_all > 2 * MAX_SPLIT) return;
+    if (n_all > 4L * slots || n_all > 2 * MAX_SPLIT || (P + 63) / 64 + (S + 63) / 64 < SPLIT_MIN_TILES) return;
     const int n = static_cast<int>(n_all), left = n % slots;       // the blocks left over after whole rounds
     if (left == 0) return;
     struct Tiles { int all, masked; };
@@ -686,6 +687,9 @@ size_t attn_query_parts(const cart_attn_desc& d, int T) {
     const long by_seq = static_cast<long>(d.B) * query_wgs(d.S, G), by_row = T > 0 ? query_wgs(T, G) : 0;
     const long tiles = (static_cast<long>(d.P) + 63) / 64 + (d.S + 63) / 64 + 6;        // (own_cap at most 6 more than S's)
     const long all = (by_seq > by_row ? by_seq : by_row) * tiles, slots = query_slots(d.Hkv);
+    // (No workspace at all for the smallest calls, whose time is the host's: allocating one that is never used took 1.1 us
+    // of 10.0.  Parts of one tile each cost more than the tiles saved up to SPLIT_MIN_TILES - 1 of them.)
+    if (T == 0 && tiles - 6 < SPLIT_MIN_TILES) return 0;
     return static_cast<size_t>(all < slots ? all : slots);
 }
 // packed batches: the first row of every row's sequence; split blocks: an overflow flag per wavefront and the

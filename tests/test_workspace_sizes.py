@@ -37,6 +37,12 @@ def test_the_training_batch_covers_a_short_last_batch(lib):
     _covers(_batched(lib, 16, 2048, 32, 8, 4096), _batched(lib, 1, 700, 32, 8, 4096), "16 x 2048, 1 x 700")
 
 
+# (allocating a workspace that is never used is a tenth of the smallest calls' time)
+@pytest.mark.parametrize("B,S,Hq,Hkv,P", [(5, 9, 48, 4, 0), (1, 64, 32, 8, 0), (4, 64, 8, 2, 33), (1, 128, 32, 8, 64)])
+def test_the_smallest_forward_calls_need_no_workspace(lib, B, S, Hq, Hkv, P):
+    assert _batched(lib, B, S, Hq, Hkv, P)[0] == 0
+
+
 @pytest.mark.parametrize("seed", range(4))
 def test_attention_workspace_never_grows_towards_smaller_problems(lib, seed):
     rng = random.Random(seed)
