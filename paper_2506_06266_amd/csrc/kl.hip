@@ -15,22 +15,22 @@
 
 namespace cart {
 
-// A row's K teacher records staged in LDS (5 arrays of K words, dynamic: at K = 20 they must not
+// A row's K teacher records staged in LDS (four arrays of K words and one of halves, dynamic: at K = 20 they must not
 // limit how many workgroups share a CU)
 struct KlTeacher {
-    int* own;           // the thread that stores the token's element (kl_owner), -1 for ignored entries; up to a multiple of 4
+    uint16_t* own;      // the thread that stores the token's element (kl_owner), 0xffff for ignored entries; up to a multiple of 8
     int* idx;           // token, -1 for ignored entries
     float* t;           // exp(logp), 0 for ignored entries
     float* lp;
     float* x;           // student logit at idx (read before anything is overwritten)
 };
 extern __shared__ __attribute__((aligned(16))) int kl_records[];
-__host__ __device__ inline int kl_up4(int K) { return (K + 3) & ~3; }
-inline unsigned kl_record_bytes(int K) { return static_cast<unsigned>(kl_up4(K) + 4 * K) * 4u; }
+__host__ __device__ inline int kl_up8(int K) { return (K + 7) & ~7; }
+inline unsigned kl_record_bytes(int K) { return static_cast<unsigned>(kl_up8(K)) * 2u + static_cast<unsigned>(K) * 16u; }
 __device__ __forceinline__ KlTeacher kl_teacher(int K) {
-    int* idx = kl_records + kl_up4(K);
+    int* idx = kl_records + kl_up8(K) / 2;
     float* f = reinterpret_cast<float*>(idx);
-    return KlTeacher{kl_records, idx, f + K, f + 2 * K, f + 3 * K};
+    return KlTeacher{reinterpret_cast<uint16_t*>(kl_records), idx, f + K, f + 2 * K, f + 3 * K};
 }
 
 // KL_n = sum_j t_j (logp_j - x_j + lse) (+ extra, the rest-bucket term), by the first wavefront
@@ -232,14 +232,14 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
                 xj = id >= 0 ? elem<T>::load(logits + R.row + id) : 0.f;
             }
             const float t = id >= 0 ? __expf(lp) : 0.f;
-            tc.own[j] = id >= 0 ? kl_owner<T, THREADS>(R, id) : -1;
+            tc.own[j] = static_cast<uint16_t>(id >= 0 ? kl_owner<T, THREADS>(R, id) : 0xffff);
             tc.idx[j] = id >= 0 ? id : -1;
             tc.t[j] = t;
             tc.lp[j] = id >= 0 ? lp : 0.f;
             tc.x[j] = id >= 0 ? xj : 0.f;
             m_part += t;
         }
-        if (tid < kl_up4(K) - K) tc.own[K + tid] = -1;
+        if (tid < kl_up8(K) - K) tc.own[K + tid] = 0xffff;
         const int n_next = n + static_cast<int>(gridDim.x);
         const bool more = n_next < N;
         if (more) fetch_record(n_next);
@@ -359,21 +359,24 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             }
         }
         // recorded tokens: the thread that stored the element's vector rewrites that element, so
-        // the two stores to one address are in program order.  (Every thread passes every record: four owners a
-        // read, several reads in flight.  One record after the other, its owner worked out on the spot:
-        // 1000 records, 4096 rows of 32000 fp32 logits 1425 us, now 444; 20 records, 1024 x 50257 bf16 47.5, now 43.8)
-        const int4* const own4 = reinterpret_cast<const int4*>(tc.own);
-#pragma unroll 4
-        for (int j4 = 0; j4 < kl_up4(K) / 4; ++j4) {
-            const int4 o = own4[j4];
-            const int mine[4] = {o.x, o.y, o.z, o.w};
+        // the two stores to one address are in program order.  Every thread passes every record, eight owners
+        // a read, and a wavefront's threads rewrite the first of their own at one time, then the second.  (One
+        // record after the other, its owner worked out on the spot: 1000 records, 4096 rows of 32000 fp32 logits 1425 us, now 390; 20
+        // records, 1024 x 50257 bf16 47.5, now 42.9.  Reading further ahead or sixteen owners at a time costs spills: 4096 x 4104
+        // bf16, 20 records 24.8, sixteen 29.3.)
+#pragma unroll 1
+        for (int j0 = 0; j0 < K; j0 += 8) {
+            const u32x4 o = *reinterpret_cast<const u32x4*>(tc.own + j0);
+            uint32_t mine = 0u;
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (mine[e] == tid) {
-                    const int j = 4 * j4 + e;
-                    const float s = fast_exp2(fmaf(tc.x[j], CART_LOG2E, -lse2));
-                    elem<T>::store(dlogits + R.row + tc.idx[j], scale * ((mode & 1 ? 1.f : M) * s - tc.t[j]));
-                }
+            for (int e = 0; e < 8; ++e)
+                if (((o[e >> 1] >> (16 * (e & 1))) & 0xffffu) == static_cast<uint32_t>(tid)) mine |= 1u << e;
+            while (mine) {
+                const int j = j0 + __builtin_ctz(mine);
+                mine &= mine - 1;
+                const float s = fast_exp2(fmaf(tc.x[j], CART_LOG2E, -lse2));
+                elem<T>::store(dlogits + R.row + tc.idx[j], scale * ((mode & 1 ? 1.f : M) * s - tc.t[j]));
+            }
         }
         kl_row_value(tc, K, lse2 * CART_LN2, extra, row_kl + n);
         if (!more) break;
