@@ -2,6 +2,8 @@
 // every argument passed validation; the library never allocates or synchronises.
 #include <math.h>
 
+#include <atomic>
+
 #include "cart_common.h"
 
 namespace cart {
@@ -10,15 +12,15 @@ Trace& trace() {
     return t;
 }
 int device_cus() {
-    static int cached[64];
+    static std::atomic<int> cached[64];     // (looked up by any thread; the same value each time)
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (!cached[dev]) {
-        int cus = 0;
+    int cus = cached[dev].load(std::memory_order_relaxed);
+    if (cus == 0) {
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-        cached[dev] = cus;
+        cached[dev].store(cus, std::memory_order_relaxed);
     }
-    return cached[dev];
+    return cus;
 }
 }  // namespace cart
 

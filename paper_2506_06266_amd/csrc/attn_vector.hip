@@ -346,7 +346,8 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(
             qr[r] = q + tok(ic);
             gr[r] = d_o + tok(ic);
         }
-        // (head_dim above 128: not all four operands of a block fit the registers at one time)
+        // (head_dim above 128: not all four operands of a block fit the registers at one time.  52 registers of fp32
+        // problems, 128 of bf16 ones, still spill, about 200 bytes of scratch a lane)
         ColFrag<NB> gc, qc;
         if constexpr (NB <= 8) {
             gc = col_frag<T, NB>(gr, D, c);

@@ -156,10 +156,10 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
     _Pragma("unroll") for (int i_ = 0; i_ < NV; ++i_)                                   \
         asm volatile("" : "+v"(x[i_]))
 
-// One row per workgroup at a time: THREADS x (16 vectors in registers + NL in LDS) are resident,
-// the rest of a longer row is read twice.  A CU holds 1024 such threads (128 registers each), so the
-// launcher takes the smallest THREADS whose registers hold the row: 256 (four workgroups per CU
-// cover each other's loads and reductions), 512, or 1024.  At 1024 nothing else runs on the CU:
+// One row per workgroup at a time: THREADS x (NV vectors in registers + NL in LDS) are resident, the
+// rest of a longer row is read twice.  The launcher takes the smallest of 128 x 4 and 256 x 4 (2048 such threads a CU, 64
+// registers each), 256 x 16 (four workgroups per CU cover each other's loads and reductions), 512 x 16 and
+// 1024 x 16 (1024 a CU, 128 registers each) whose registers hold the row.  At 1024 nothing else runs on the CU:
 // the workgroup walks rows n, n + gridDim.x, ... and fetches the next row's vectors and teacher
 // records into the registers (LDS slots) of the current row as its last sweep releases them.
 // Bound by HBM, one read and one write of the tensor.  Kernel time in us against one-workgroup-per-
@@ -168,6 +168,8 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
 //   16384 x 128256 bf16  1649 -> 1593 (5.28 TB/s)     4096 x 32000 bf16  153 -> 100
 //    1024 x  50257 bf16   146 ->   47                16384 x  1000 fp32   54 ->  47
 //    2048 x 128256 fp32   785 ->  412 (423 without the LDS part)
+// Some of the set-up's values live in scratch (up to 4 registers; 15 at 1024 threads, 26 with the LDS part): stored once,
+// loaded once a row between the sweeps.
 template <typename T, int THREADS, int NV, int NL, bool LONG = false>
 __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const T* logits, const int32_t* idx,
                                                               const float* logp, T* dlogits, float* row_kl,
@@ -409,7 +411,7 @@ __global__ __launch_bounds__(1024) void kl_reduce_rows(const float* row_kl, int 
 template <typename T, int THREADS, int NV, int NL, bool LONG = false>
 static void resident(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
                      float* rows, hipStream_t st) {
-    const int slots = 256 * ((NV > 4 ? 1024 : 2048) / THREADS);      // workgroups an MI355X keeps resident
+    const int slots = device_cus() * ((NV > 4 ? 1024 : 2048) / THREADS);      // workgroups the chip keeps resident
     const int spare = (NV + NL) * THREADS - d.V / LogitVec<T>::N;
     const int lead_mask = spare < 0 || spare >= 7 ? 7 : spare >= 3 ? 3 : spare >= 1 ? 1 : 0;
     hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL, LONG>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
