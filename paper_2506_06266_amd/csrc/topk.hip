@@ -209,7 +209,10 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
     if (lane == 0) { red_max[wv] = wref; red_sum[wv] = sum; }
     __syncthreads();
     // tau, bit by bit from the top, by the first wavefront
-    if (wv == 0) {
+    // (rows of up to 128 logits and fewer vectors than records are listed whole: us, 16884 rows of 3 fp32, K = 1 34, now 19.6;
+    // 20000 of 120, K = 100 66, now 48)
+    const bool whole = V <= 128 && K > V / VE;
+    if (wv == 0 && !whole) {
         uint32_t mine[PER_LANE];
 #pragma unroll
         for (int j = 0; j < PER_LANE; ++j) mine[j] = all_kmax[64 * j + lane];
@@ -231,7 +234,7 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
     for (int w = 0; w < NW; ++w) sum += red_sum[w] * fast_exp2(red_max[w] - gref);
     const float lse = (gref + fast_log2(sum)) * CART_LN2;
     __syncthreads();
-    const float tau = f32_key_value(tau_s);
+    const float tau = whole ? ninf : f32_key_value(tau_s);
     const bool listed = tau > ninf;
     if (listed && t1 >= tau) {
         auto put = [&](float x, uint32_t i) __attribute__((always_inline)) {
