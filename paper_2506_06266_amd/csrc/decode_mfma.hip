@@ -63,7 +63,7 @@ struct DecodePlan {
 
 // seg_p[n_seg]: slots per shared segment; pool_p: slots of a private cartridge (0 = none);
 // T: rows of the packed own caches
-// lean > 0: prefix workgroups for the chip and no more, and no range below 256 rows; 1: in no more parts than
+// lean > 0: prefix workgroups for the chip and no more, and long ranges; 1: in no more parts than
 // the estimate takes either.
 static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p, int lean) {
     DecodePlan p;
@@ -85,8 +85,14 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     const long chip = 2L * device_cus();          // workgroups the chip keeps resident (256 threads, two per CU)
     // steps of the own rows: a request takes at least one, half a step more than its rows on average
     const float own_steps = static_cast<float>(B) * fmaxf(static_cast<float>(T) / (static_cast<float>(B) * DEC_SUB) + 0.5f, 1.f);
-    // one wavefront over all of them: 1.8 us per 32 rows and 1.3 per request (its query rows, its partial), never below 2.2
-    const float own_us = fmaxf(1.8f * static_cast<float>(T) / DEC_SUB + 1.3f * static_cast<float>(B), 2.2f * static_cast<float>(B));
+    const float row_us = 2.5f * own_steps / static_cast<float>(T);       // of a wavefront's range, where it waits for memory
+    // Rows per own range that leave every workgroup a CU of its own (0: none do, or the requests are so short that
+    // such a range holds many of them: 205 requests of up to 10 own rows, 8 / 8 heads, 4103 slots 27.7 us a call, 32.3 so)
+    auto unshared = [&](long n_pre) {
+        const long room = chip / 2 - n_pre, ranges = room > 0 && (lean || T >= 16L * B) ? 4 * room / Hkv : 0;
+        const long rows = ranges > 0 ? (static_cast<long>(T) + ranges - 1) / ranges : 0, to = rows < DEC_SUB ? 8 : DEC_SUB;
+        return (rows + to - 1) / to * to;
+    };
     int tps = 0;
     float tps_us = 0.f;
     for (int parts = 1; parts <= DEC_MAX_SPLIT && parts <= total_tiles; parts += 1 + parts / 8) {
@@ -96,11 +102,9 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         const long waves = 4 * (chip - n_pre < 64 ? 64 : chip - n_pre);
         const float steps = ceilf(static_cast<float>(stream_rows) * Hkv / (static_cast<float>(waves) * DEC_SUB));
         const float stream = fmaxf(4.f + 1.8f * steps, stream_us);
-        float us = fmaxf(8.f + (pool_p == 0 || stream_us > 20.f ? 0.8f : 0.55f) * static_cast<float>(t), stream);
-        if (pool_p == 0 && stream_us <= 20.f && n_pre < chip / 2) {      // (every workgroup on a CU of its own)
-            const float alone = 4.f + own_us * static_cast<float>(Hkv) / static_cast<float>(4 * (chip / 2 - n_pre));
-            us = fminf(us, fmaxf(8.f + 0.55f * static_cast<float>(t), alone));
-        }
+        float us = fmaxf(8.f + (stream_us > 20.f || (pool_p == 0 && T >= 16L * B) ? 0.8f : 0.55f) * static_cast<float>(t), stream);
+        const long own = pool_p == 0 && stream_us <= 20.f ? unshared(n_pre) : 0;
+        if (own > 0) us = fminf(us, fmaxf(8.f + 0.55f * static_cast<float>(t), 4.f + row_us * static_cast<float>(own)));
         us += static_cast<float>(parts) * B * Hq * 2 * HD * 4 / 2.0e6f;
         if (parts == 1 || us < tps_us) {
             tps_us = us;
@@ -147,19 +151,26 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     if (pool_p == 0) {
         const long resident = (static_cast<long>(T) + ranges - 1) / ranges, needed = resident > least ? resident : least, avg = up(T / B, 8);
         share = up(needed, DEC_SUB);
-        if (lean)                         share = share > 4 * DEC_MIN_SHARE ? share : 4 * DEC_MIN_SHARE;
-        else if (avg < DEC_MIN_SHARE)     share = avg > needed ? avg : up(needed, needed < DEC_SUB ? 8 : DEC_SUB);
-        else if (share < DEC_MIN_SHARE)   share = DEC_MIN_SHARE;
+        if (lean) {
+            // (a range as long as the longest request takes no fewer partials: up to 256 rows were 256 steps where every
+            // request had one: 404 requests, 28 / 4 heads, 3161 slots 549 us a call, 46 so)
+            const long most = up(max_own_len, DEC_SUB);
+            const long wanted = most < 4 * DEC_MIN_SHARE ? most : 4 * DEC_MIN_SHARE;
+            share = share > wanted ? share : wanted;
+        }
+        else if (avg < DEC_MIN_SHARE) share = avg > needed ? avg : up(needed, needed < DEC_SUB ? 8 : DEC_SUB);
+        else if (share < DEC_MIN_SHARE) share = DEC_MIN_SHARE;
         if (share < 8) share = 8;
         used = (static_cast<long>(T) + share - 1) / share;
         // From the workgroup on that shares a CU the prefix role takes longer (the 0.55 and 0.8 us above): longer ranges
-        // where they leave every workgroup its own CU and end before the prefix does.  212 requests, 8 / 2 heads, 10891
+        // where they leave every workgroup its own CU and the launch ends sooner for it.  212 requests, 8 / 2 heads, 10891
         // slots, up to 184 own rows: ranges of 64 rows (360 workgroups) 38.5 us a call, of 192 (238) 31.6; 200 requests,
         // 4096 slots, up to 300 rows 28.1, now 26.2.
-        const long room = device_cus() - n_pre_wg, fewer = room > 0 ? 4 * room / Hkv : 0;
-        if (n_pre_wg > 0 && !lean && fewer > 0 && used > fewer) {
-            const long longer = up((static_cast<long>(T) + fewer - 1) / fewer, DEC_SUB);
-            if (4.f + own_us * static_cast<float>(longer) / static_cast<float>(T) <= 8.f + 0.55f * static_cast<float>(tps)) {
+        const long longer = n_pre_wg > 0 ? unshared(n_pre_wg) : 0;
+        if (longer > share) {
+            const float tiles = static_cast<float>(tps);
+            if (1.1f * fmaxf(8.f + 0.55f * tiles, 4.f + row_us * static_cast<float>(longer)) <=
+                fmaxf(8.f + 0.8f * tiles, 4.f + row_us * static_cast<float>(share))) {
                 share = longer;
                 used = (static_cast<long>(T) + share - 1) / share;
             }
