@@ -495,4 +495,16 @@ __device__ __forceinline__ void tile_load_async(char* tile, const char* base, in
 }
 
 }  // namespace mfma
+
+// ---- what the two backward files and the forward's planner share (host) ----
+// the split of the query blocks, the most parts it can take (attn_mfma_fwd.hip)
+void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind);
+size_t attn_query_parts(const cart_attn_desc& d, int T);
+// the fused dK + dV kernel, its cut, the most bytes its partials can take (attn_mfma_bwd_kv.hip)
+mfma::KvPlan plan_bwd_kv(const cart_attn_desc& d, long tokens);
+size_t bwd_kv_most(const cart_attn_desc& d, long tokens);
+void launch_attn_bwd_kv(const cart_attn_desc& d, float scale, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
+                        const bf16_t* ZK, const bf16_t* ZV, const bf16_t* DO, const float* lse2, const float* delta,
+                        bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, float* own_k, float* own_v, const int32_t* cu,
+                        int n_tok, const mfma::KvPlan& plan, hipStream_t st);
 }  // namespace cart

@@ -424,17 +424,6 @@ __global__ __launch_bounds__(256) void attn_bwd_reduce_kernel(BwdReduce r, Query
 
 bool attn_mfma_bwd_supported(const cart_attn_desc& d) { return d.dtype == CART_BF16 && d.D == 128; }
 
-// the fused dK + dV kernel (attn_mfma_bwd_kv.hip)
-KvPlan plan_bwd_kv(const cart_attn_desc& d, long tokens);
-size_t bwd_kv_most(const cart_attn_desc& d, long tokens);
-void launch_attn_bwd_kv(const cart_attn_desc& d, float scale, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
-                        const bf16_t* ZK, const bf16_t* ZV, const bf16_t* DO, const float* lse2, const float* delta,
-                        bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, float* own_k, float* own_v, const int32_t* cu,
-                        int n_tok, const KvPlan& plan, hipStream_t st);
-// the split of the query blocks (attn_mfma_fwd.hip)
-void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind);
-size_t attn_query_parts(const cart_attn_desc& d, int T);
-
 static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 
 // The workspace of a backward call: -delta and -lse2 (one value per token and head), the dZ partials

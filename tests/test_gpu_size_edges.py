@@ -129,6 +129,50 @@ def test_packed_small_launches(lens, Hq, Hkv, P):
 
 
 
+# A packed launch of more than one round of blocks: 35 blocks of a KV head's 32 CUs, the 32 with the last rows run whole and
+# the first 192 rows are split along the prefix (its last tile ragged).  HOT: one key 200 nats above the first ones,
+# in the last sequence, whose rows lie in whole blocks, and in the first one, whose rows are split.
+MIXED_LENS, MIXED_P = [64, 300, 500, 1, 70, 640, 200, 465], 1501
+
+
+def mixed_case(hot):
+    T, Hq, Hkv = sum(MIXED_LENS), 32, 8
+    q, k, v, zk, zv, do = attn_case((T,), Hq, Hkv, 128, MIXED_P, torch.bfloat16, 77)
+    if hot:
+        g = torch.Generator().manual_seed(3)
+        u = torch.randn(128, generator=g)
+        u *= (200.0 * 128 ** 0.5) ** 0.5 / u.norm()
+        q = (u + 0.05 * torch.randn(T, Hq, 128, generator=g)).to(torch.bfloat16)
+        zk = (0.05 * torch.randn(Hkv, MIXED_P, 128, generator=g)).to(torch.bfloat16)
+        k = 0.05 * torch.randn(T, Hkv, 128, generator=g)
+        k[[9, T - 400]] += u
+        k = k.to(torch.bfloat16)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(MIXED_LENS)]), dtype=torch.int32)
+    return [q, k, v, zk, zv, cu], do
+
+
+def test_packed_whole_and_split_blocks():
+    a, do = mixed_case(False)
+    n = [f64(t) for t in a[:5]]
+    ref = [*orc.attn_varlen_fwd(*n, a[5].numpy()), *orc.attn_varlen_bwd(*n, f64(do), a[5].numpy())]
+    d = [t.to(DEV) for t in a]
+    o, lse = cb.cart_attn_varlen_fwd(*d, max(MIXED_LENS))
+    out = [o, lse, *cb.cart_attn_varlen_bwd(*d, max(MIXED_LENS), o, lse, do.to(DEV))]
+    torch.cuda.synchronize()
+    for x, r in zip(out, ref):
+        assert rel_err(x, r) <= TOL[torch.bfloat16]
+
+
+def test_packed_whole_and_split_blocks_overflowing():
+    a, _ = mixed_case(True)
+    o_ref, lse_ref = orc.attn_varlen_fwd(*[f64(t) for t in a[:5]], a[5].numpy())
+    o, lse = cb.cart_attn_varlen_fwd(*[t.to(DEV) for t in a], max(MIXED_LENS))
+    torch.cuda.synchronize()
+    T = sum(MIXED_LENS)
+    assert lse_ref[:, T - 300].min() > 150 and lse_ref[:, 20].min() > 150 and lse_ref[:, 100].max() < 20
+    assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
+
+
 # The fp32 kernels (any head_dim up to 256; bf16 inputs widened): head sizes around the operand blocks
 # of 16 and the three register layouts, tokens and slots around the blocks of 16, one token, no prefix.
 VECTOR_CASES = [(torch.float32, 2, 17, 2, 1, 5, 33), (torch.float32, 1, 16, 4, 2, 16, 16), (torch.float32, 3, 1, 2, 2, 64, 1),

@@ -34,3 +34,10 @@ def test_forward_runs_whole_where_parts_cost_more(B, S, Hq, Hkv, P, T):
 def test_forward_is_split_where_that_is_faster(B, S, Hq, Hkv, P, T, least):
     whole, blocks, parts = _parts(B, S, Hq, Hkv, P, T)
     assert blocks > 0 and parts > (least - 1) * blocks
+
+
+# (the packed launch of whole and split blocks that the GPU tests run)
+def test_packed_launch_of_whole_and_split_blocks():
+    for kind in (0, 1):
+        whole, blocks, parts = _parts(8, 640, 32, 8, 1501, 2240, kind)
+        assert (whole, blocks) == (32, 3) and parts > blocks
