@@ -16,8 +16,8 @@
 // small problem is bound by latency -- its launches, one round trip for the operands, one for the
 // sums -- and a large one by the matrix cores.  Against one wavefront per row or key, a serial chain of
 // shuffles and exponentials per key, us for forward and backward: 2 sequences of 64 tokens, 2 / 1
-// heads of 64, 32 slots: 175 -> 31 (launches); 4 of 256, 8 / 2 heads, 256 slots: head_dim 64 2268 -> 174,
-// head_dim 128 2855 -> 356.
+// heads of 64, 32 slots: 175 -> 26 (launches); 4 of 256, 8 / 2 heads, 256 slots: head_dim 64 2268 -> 156,
+// head_dim 128 2855 -> 327.
 #include "cart_common.h"
 
 namespace cart {
@@ -148,6 +148,12 @@ template <int NB> __device__ __forceinline__ void to_lds(float* dst, const f32x4
     for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(dst + c * (16 * NB + 4) + 16 * db + 4 * g) = acc[db];
 }
 
+// Head_dim 65 to 128: one wavefront per SIMD, which requests each operand's next block as soon as its products are out
+// (us, 4 x 256 tokens, 8 / 2 heads of 128, 256 slots: forward 37.6 -> 34.6, backward 319 -> 290).  Two wavefronts on a
+// SIMD cover each other (head_dim up to 64: backward 22.7 -> 25.3 at 2 x 64 tokens, 64 slots), and above 128 there are
+// no registers for it (forward 14.0 -> 14.6, 2 x 64 tokens, 4 / 2 heads of 200).
+template <int NB> constexpr bool VEC_AHEAD = NB == 8;
+
 // key / value row j of the concatenated cache [prefix ; own] for (sequence b, KV head hk)
 template <typename T>
 __device__ __forceinline__ const T* cache_row(const T* z, const T* own, int j, int P, int S,
@@ -176,13 +182,23 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
     f32x4 acc[NB];
     clear(acc);
     float m = VEC_HIDDEN, l = 0.f;
-    for (int j0 = 16 * wv; j0 < nk; j0 += 16 * NW) {
-        const RowFrag<NB> kf = row_frag<T, NB>(cache_row(zk, k, min(j0 + c, nk - 1), P, S, Hkv, D, b, hk), D, g);
+    auto load_k = [&](int j0) __attribute__((always_inline)) {
+        return row_frag<T, NB>(cache_row(zk, k, min(j0 + c, nk - 1), P, S, Hkv, D, b, hk), D, g);
+    };
+    auto load_v = [&](int j0) __attribute__((always_inline)) {
         const T* vr[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) vr[r] = cache_row(zv, v, min(j0 + 4 * g + r, nk - 1), P, S, Hkv, D, b, hk);
-        const ColFrag<NB> vc = col_frag<T, NB>(vr, D, c);
+        return col_frag<T, NB>(vr, D, c);
+    };
+    RowFrag<NB> kf;
+    ColFrag<NB> vc;
+    if (VEC_AHEAD<NB>) { kf = load_k(16 * wv); vc = load_v(16 * wv); }
+    for (int j0 = 16 * wv; j0 < nk; j0 += 16 * NW) {
+        const bool more = VEC_AHEAD<NB> && j0 + 16 * NW < nk;
+        if (!VEC_AHEAD<NB>) { kf = load_k(j0); vc = load_v(j0); }
         f32x4 s = contract(kf, qf);
+        if (more) kf = load_k(j0 + 16 * NW);
         float tm = VEC_HIDDEN;
         uint32_t vis = 0;
 #pragma unroll
@@ -204,6 +220,7 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
 #pragma unroll
         for (int db = 0; db < NB; ++db) acc[db] *= alpha;
         accumulate_visible(acc, vc, p, vis, j0 + 15 > P + i0, c, g);
+        if (more) vc = load_v(j0 + 16 * NW);
     }
     l = col_sum(l);
     to_lds(sm_o[wv], acc, c, g);
@@ -233,48 +250,80 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
     }
 }
 
-// dQ; also forms delta[b,h,i] = dO_i . O_i for the key-side kernel
-template <typename T, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_bwd_dq_vector(
-    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ zk,
-    const T* __restrict__ zv, const T* __restrict__ o, const float* __restrict__ lse, const T* __restrict__ d_o,
-    float* __restrict__ delta, T* __restrict__ dq, int B, int S, int Hq, int Hkv, int D, int P, float scale) {
+// ---- backward: dQ blocks and dK / dV blocks -----------------------------------------------------
+template <typename T>
+struct VecBwd {
+    const T *q, *k, *v, *zk, *zv, *o, *d_o;
+    const float* lse;
+    float* delta;                       // [B,Hq,S], written by the dQ blocks of the two-launch form
+    T *dq, *dk, *dv;
+    float *dzk, *dzv;
+    int B, S, Hq, Hkv, D, P;
+    float scale;
+    int n_frozen, accumulate;
+};
+template <int NB> constexpr int VEC_TURN = 16 * (16 * NB + 4);      // floats of one wavefront's sums in LDS
+
+// delta = dO . O of the lane's row, from its quarter of the head elements
+template <int NB>
+__device__ __forceinline__ float row_delta(const RowFrag<NB>& of, const RowFrag<NB>& gf) {
+    float dl = 0.f;
+#pragma unroll
+    for (int s = 0; s < NB; ++s)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dl = fmaf(of.v[s][e], gf.v[s][e], dl);
+    return col_sum(dl);
+}
+
+// dQ of 16 queries of one head; with WRITE_DELTA also delta[b,h,i] for the dK / dV launch that follows
+template <typename T, int NB, int NW, bool WRITE_DELTA>
+__device__ __forceinline__ void dq_block(const VecBwd<T>& a, int id, float (*sm_o)[VEC_TURN<NB>]) {
     constexpr int PITCH = 16 * NB + 4;
-    __shared__ float sm_o[NW][16 * PITCH];
+    const int B = a.B, S = a.S, Hq = a.Hq, Hkv = a.Hkv, D = a.D, P = a.P;
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nQt = (S + 15) / 16;
-    int id = workgroup_id();
     const int i0 = 16 * (id % nQt); id /= nQt;
     const int h = id % Hq, b = id / Hq, hk = h / (Hq / Hkv);
     if (b >= B) return;
     const int i = min(i0 + c, S - 1);
     const size_t row = ((static_cast<size_t>(b) * S + i) * Hq + h) * D;
-    const RowFrag<NB> qf = row_frag<T, NB>(q + row, D, g), gf = row_frag<T, NB>(d_o + row, D, g);
     const size_t st = (static_cast<size_t>(b) * Hq + h) * S + i;
-    float dl = 0.f;
-    {
-        const RowFrag<NB> of = row_frag<T, NB>(o + row, D, g);
-#pragma unroll
-        for (int s = 0; s < NB; ++s)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dl = fmaf(of.v[s][e], gf.v[s][e], dl);
-        dl = col_sum(dl);
-    }
-    if (wv == 0 && g == 0 && i0 + c < S) delta[st] = dl;
-    const float c2 = scale * CART_LOG2E, l2 = lse[st] * CART_LOG2E;
     const int nk = P + min(i0 + 16, S), last = P + i;
+    RowFrag<NB> kf, vf;
+    ColFrag<NB> kc;
+    auto load_rows = [&](int j0) __attribute__((always_inline)) {
+        const int jc = min(j0 + c, nk - 1);
+        kf = row_frag<T, NB>(cache_row(a.zk, a.k, jc, P, S, Hkv, D, b, hk), D, g);
+        vf = row_frag<T, NB>(cache_row(a.zv, a.v, jc, P, S, Hkv, D, b, hk), D, g);
+    };
+    auto load_cols = [&](int j0) __attribute__((always_inline)) {
+        const T* kr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) kr[r] = cache_row(a.zk, a.k, min(j0 + 4 * g + r, nk - 1), P, S, Hkv, D, b, hk);
+        kc = col_frag<T, NB>(kr, D, c);
+    };
+    const RowFrag<NB> qf = row_frag<T, NB>(a.q + row, D, g), gf = row_frag<T, NB>(a.d_o + row, D, g);
+    const float c2 = a.scale * CART_LOG2E, l2 = a.lse[st] * CART_LOG2E;
+    // (the first keys are requested ahead of delta's wait for O and dO; head_dim above 128 has no registers for it)
+    float dl;
+    {
+        const RowFrag<NB> of = row_frag<T, NB>(a.o + row, D, g);
+        if constexpr (NB <= 8) {
+            load_rows(16 * wv);
+            load_cols(16 * wv);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        dl = row_delta(of, gf);
+    }
+    if (WRITE_DELTA && wv == 0 && g == 0 && i0 + c < S) a.delta[st] = dl;
     f32x4 acc[NB];
     clear(acc);
     for (int j0 = 16 * wv; j0 < nk; j0 += 16 * NW) {
-        const int jc = min(j0 + c, nk - 1);
-        const RowFrag<NB> kf = row_frag<T, NB>(cache_row(zk, k, jc, P, S, Hkv, D, b, hk), D, g);
-        const RowFrag<NB> vf = row_frag<T, NB>(cache_row(zv, v, jc, P, S, Hkv, D, b, hk), D, g);
-        const T* kr[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) kr[r] = cache_row(zk, k, min(j0 + 4 * g + r, nk - 1), P, S, Hkv, D, b, hk);
-        const ColFrag<NB> kc = col_frag<T, NB>(kr, D, c);
+        const bool more = VEC_AHEAD<NB> && j0 + 16 * NW < nk;
+        if (NB > 8 || (!VEC_AHEAD<NB> && j0 != 16 * wv)) { load_rows(j0); load_cols(j0); }
         const f32x4 s = contract(kf, qf), dp = contract(vf, gf);
+        if (more) load_rows(j0 + 16 * NW);
         f32x4 ds;
         uint32_t vis = 0;
 #pragma unroll
@@ -284,36 +333,33 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_vector(
             ds[r] = sees ? fast_exp2(fmaf(s[r], c2, -l2)) * (dp[r] - dl) : 0.f;
         }
         accumulate_visible(acc, kc, ds, vis, j0 + 15 > P + i0, c, g);
+        if (more) load_cols(j0 + 16 * NW);
     }
     to_lds(sm_o[wv], acc, c, g);
     __syncthreads();
-    for (int t = threadIdx.x; t < 256; t += 64 * NW) {
-        const int qc = t >> 4;
+    for (int t16 = threadIdx.x; t16 < 256; t16 += 64 * NW) {
+        const int qc = t16 >> 4;
         if (i0 + qc >= S) continue;
-        T* op = dq + ((static_cast<size_t>(b) * S + i0 + qc) * Hq + h) * D;
-        for (int d = t & 15; d < D; d += 16) {
-            float a = 0.f;
+        T* op = a.dq + ((static_cast<size_t>(b) * S + i0 + qc) * Hq + h) * D;
+        for (int d = t16 & 15; d < D; d += 16) {
+            float x = 0.f;
 #pragma unroll
-            for (int u = 0; u < NW; ++u) a += sm_o[u][qc * PITCH + d];
-            elem<T>::store(op + d, a * scale);
+            for (int u = 0; u < NW; ++u) x += sm_o[u][qc * PITCH + d];
+            elem<T>::store(op + d, x * a.scale);
         }
     }
 }
 
 // dK, dV of 16 keys: prefix slots (summed over every sequence, every query head of the group, every
 // token) or own keys of one sequence (the group's heads, tokens from the block's first key on).
-template <typename T, int NB, int NW>
-__global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(
-    const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ zk,
-    const T* __restrict__ zv, const float* __restrict__ lse, const float* __restrict__ delta, const T* __restrict__ d_o,
-    T* __restrict__ dk, T* __restrict__ dv, float* __restrict__ dzk, float* __restrict__ dzv, int B, int S, int Hq, int Hkv,
-    int D, int P, float scale, int n_frozen, int accumulate_dz) {
+// OWN_DELTA: the rows' delta is formed here from O and dO (the same sum in the same order), not read.
+template <typename T, int NB, int NW, bool OWN_DELTA>
+__device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm_k)[VEC_TURN<NB>], float (*sm_v)[VEC_TURN<NB>]) {
     constexpr int PITCH = 16 * NB + 4;
-    __shared__ float sm_k[NW][16 * PITCH], sm_v[NW][16 * PITCH];
+    const int B = a.B, S = a.S, Hq = a.Hq, Hkv = a.Hkv, D = a.D, P = a.P;
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nPt = (P + 15) / 16, nSt = (S + 15) / 16, G = Hq / Hkv;
-    int id = workgroup_id();
     const bool prefix = id < nPt * Hkv;
     if (!prefix) id -= nPt * Hkv;
     const int hk = id % Hkv; id /= Hkv;
@@ -323,58 +369,87 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(
     auto key_row = [&](int j) { return prefix ? (static_cast<size_t>(hk) * P + j) * D
                                               : ((static_cast<size_t>(b_own) * S + j) * Hkv + hk) * D; };
     const size_t kr = key_row(min(key0 + c, nkeys - 1));
-    const RowFrag<NB> kf = row_frag<T, NB>((prefix ? zk : k) + kr, D, g), vf = row_frag<T, NB>((prefix ? zv : v) + kr, D, g);
-    const float c2 = scale * CART_LOG2E;
+    const RowFrag<NB> kf = row_frag<T, NB>((prefix ? a.zk : a.k) + kr, D, g), vf = row_frag<T, NB>((prefix ? a.zv : a.v) + kr, D, g);
+    const float c2 = a.scale * CART_LOG2E;
     f32x4 ak[NB], av[NB];
     clear(ak);
     clear(av);
     // blocks of 16 token rows: (sequence, head of the group, block), from the block's own diagonal on
     const int it0 = prefix ? 0 : key0 / 16, nIt = nSt - it0, n = (prefix ? B : 1) * G * nIt;
-    for (int t = wv; t < n; t += NW) {
-        const int i0 = 16 * (it0 + t % nIt), h = hk * G + (t / nIt) % G, b = prefix ? t / (nIt * G) : b_own;
-        auto tok = [&](int i) { return ((static_cast<size_t>(b) * S + i) * Hq + h) * D; };
-        const size_t rc = tok(min(i0 + c, S - 1));
-        const RowFrag<NB> qf = row_frag<T, NB>(q + rc, D, g), gf = row_frag<T, NB>(d_o + rc, D, g);
-        const T *qr[4], *gr[4];
-        f32x4 l2, dl;
+    // Of a block: its rows for the scores, lse, delta; then the same rows as columns for the sums
+    struct Block { int i0, h, b; };
+    auto block = [&](int t) __attribute__((always_inline)) {
+        const int u = t / nIt;
+        return Block{16 * (it0 + t - u * nIt), hk * G + u % G, prefix ? u / G : b_own};
+    };
+    auto tok = [&](const Block& x, int i) __attribute__((always_inline)) {
+        return ((static_cast<size_t>(x.b) * S + min(i, S - 1)) * Hq + x.h) * D;
+    };
+    RowFrag<NB> qf, gf, of;
+    ColFrag<NB> gc, qc;
+    f32x4 l2, dl;
+    auto load_rows = [&](const Block& x) __attribute__((always_inline)) {
+        const size_t rc = tok(x, x.i0 + c);
+        qf = row_frag<T, NB>(a.q + rc, D, g);
+        gf = row_frag<T, NB>(a.d_o + rc, D, g);
+        if constexpr (OWN_DELTA) of = row_frag<T, NB>(a.o + rc, D, g);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int ic = min(i0 + 4 * g + r, S - 1);
-            const size_t st = (static_cast<size_t>(b) * Hq + h) * S + ic;
-            l2[r] = lse[st] * CART_LOG2E;
-            dl[r] = delta[st];
-            qr[r] = q + tok(ic);
-            gr[r] = d_o + tok(ic);
+            const size_t st = (static_cast<size_t>(x.b) * Hq + x.h) * S + min(x.i0 + 4 * g + r, S - 1);
+            l2[r] = a.lse[st] * CART_LOG2E;
+            if (!OWN_DELTA) dl[r] = a.delta[st];
         }
-        // (head_dim above 128: not all four operands of a block fit the registers at one time.  52 registers of fp32
-        // problems, 128 of bf16 ones, still spill, about 200 bytes of scratch a lane)
-        ColFrag<NB> gc, qc;
-        if constexpr (NB <= 8) {
-            gc = col_frag<T, NB>(gr, D, c);
-            qc = col_frag<T, NB>(qr, D, c);
+    };
+    auto load_cols = [&](const Block& x, ColFrag<NB>& f, const T* src) __attribute__((always_inline)) {
+        const T* pr[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) pr[r] = src + tok(x, x.i0 + 4 * g + r);
+        f = col_frag<T, NB>(pr, D, c);
+    };
+    Block cur = block(min(wv, n - 1));
+    if constexpr (VEC_AHEAD<NB>) {
+        load_rows(cur);
+        load_cols(cur, gc, a.d_o);
+        load_cols(cur, qc, a.q);
+    }
+    for (int t = wv; t < n; t += NW) {
+        // (The block after the last is the last again: loads under a condition are all waited for at its end.  The columns
+        // not requested ahead come behind the scores: head_dim above 128 has no registers for all four operands of a block --
+        // 52 registers of fp32 problems, 128 of bf16 ones, spill as it is -- and two wavefronts on a SIMD are faster so:
+        // backward 148 -> 135 us at 4 x 256 tokens, 8 / 2 heads of 64, 256 slots)
+        const Block nx = block(VEC_AHEAD<NB> ? min(t + NW, n - 1) : t);
+        if constexpr (!VEC_AHEAD<NB>) { cur = nx; load_rows(cur); }
+        if constexpr (OWN_DELTA) {
+            const float rd = row_delta(of, gf);      // of row i0 + c
+#pragma unroll
+            for (int r = 0; r < 4; ++r) dl[r] = __shfl(rd, 4 * g + r, CART_WAVE);
         }
         const f32x4 s = contract(qf, kf), dp = contract(gf, vf);
         f32x4 p, ds;
         uint32_t vis = 0;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = i0 + 4 * g + r;
+            const int i = cur.i0 + 4 * g + r;
             const bool seen = i < S && (prefix || i >= key0 + c);
             vis |= seen ? 1u << r : 0u;
             p[r] = seen ? fast_exp2(fmaf(s[r], c2, -l2[r])) : 0.f;
             ds[r] = seen ? p[r] * (dp[r] - dl[r]) : 0.f;
         }
-        const bool hidden = i0 + 16 > S || (!prefix && i0 == key0);
-        if constexpr (NB > 8) {
+        if constexpr (VEC_AHEAD<NB>) load_rows(nx);
+        const bool hidden = cur.i0 + 16 > S || (!prefix && cur.i0 == key0);
+        if constexpr (!VEC_AHEAD<NB>) {
             asm volatile("" ::: "memory");
-            gc = col_frag<T, NB>(gr, D, c);
+            load_cols(cur, gc, a.d_o);
         }
         accumulate_visible(av, gc, p, vis, hidden, c, g);
-        if constexpr (NB > 8) {
+        if constexpr (VEC_AHEAD<NB>) load_cols(nx, gc, a.d_o);
+        if constexpr (!VEC_AHEAD<NB>) {
             asm volatile("" ::: "memory");
-            qc = col_frag<T, NB>(qr, D, c);
+            load_cols(cur, qc, a.q);
         }
         accumulate_visible(ak, qc, ds, vis, hidden, c, g);
+        if constexpr (VEC_AHEAD<NB>) load_cols(nx, qc, a.q);
+        cur = nx;
     }
     to_lds(sm_k[wv], ak, c, g);
     to_lds(sm_v[wv], av, c, g);
@@ -391,17 +466,36 @@ __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(
                 gv += sm_v[u][(t >> 4) * PITCH + d];
             }
             if (prefix) {
-                gk = j < n_frozen ? 0.f : gk * scale;
-                gv = j < n_frozen ? 0.f : gv;
-                if (accumulate_dz) { gk += dzk[r + d]; gv += dzv[r + d]; }
-                dzk[r + d] = gk;
-                dzv[r + d] = gv;
+                gk = j < a.n_frozen ? 0.f : gk * a.scale;
+                gv = j < a.n_frozen ? 0.f : gv;
+                if (a.accumulate) { gk += a.dzk[r + d]; gv += a.dzv[r + d]; }
+                a.dzk[r + d] = gk;
+                a.dzv[r + d] = gv;
             } else {
-                elem<T>::store(dk + r + d, gk * scale);
-                elem<T>::store(dv + r + d, gv);
+                elem<T>::store(a.dk + r + d, gk * a.scale);
+                elem<T>::store(a.dv + r + d, gv);
             }
         }
     }
+}
+
+template <typename T, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_dq_vector(VecBwd<T> a) {
+    __shared__ float sm[NW][VEC_TURN<NB>];
+    dq_block<T, NB, NW, true>(a, workgroup_id(), sm);
+}
+template <typename T, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(VecBwd<T> a) {
+    __shared__ float sm[2][NW][VEC_TURN<NB>];
+    dkv_block<T, NB, NW, false>(a, workgroup_id(), sm[0], sm[1]);
+}
+// Both in one launch, the dK / dV blocks (the longer ones) first
+template <typename T, int NB, int NW>
+__global__ __launch_bounds__(64 * NW) void attn_bwd_vector(VecBwd<T> a, int n_kv) {
+    __shared__ float sm[2][NW][VEC_TURN<NB>];
+    const int id = workgroup_id();
+    if (id < n_kv) dkv_block<T, NB, NW, true>(a, id, sm[0], sm[1]);
+    else           dq_block<T, NB, NW, false>(a, id - n_kv, sm[0]);
 }
 
 // ---- decode: one wavefront per output row; lane l owns head elements l, l+64, ... ---------------
@@ -500,16 +594,23 @@ static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const voi
                   const void* zk, const void* zv, const void* o, const float* lse, const void* d_o,
                   void* dq, void* dk, void* dv, float* dzk, float* dzv, void* ws, hipStream_t st) {
     const long nSt = (d.S + 15) / 16, nPt = (d.P + 15) / 16;
-    float* delta = static_cast<float*>(ws);
-    trace_begin(st);   // kernel order: dq (+ delta), dk/dv/dz
+    const long n_q = nSt * d.Hq * d.B, n_kv = (nPt + nSt * d.B) * d.Hkv;
+    const VecBwd<T> a = {(const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (const T*)o, (const T*)d_o, lse,
+                         static_cast<float*>(ws), (T*)dq, (T*)dk, (T*)dv, dzk, dzv, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale,
+                         d.n_frozen, d.dz_accumulate};
+    trace_begin(st);   // kernel order: dq (+ delta), dk/dv/dz; or both in one (nothing between the second's events)
     CART_DISPATCH_NB(d.D, {
-        hipLaunchKernelGGL((attn_bwd_dq_vector<T, NB, NW>), grid_of(nSt * d.Hq * d.B), dim3(64 * NW), 0, st, (const T*)q,
-                           (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (const T*)o, lse, (const T*)d_o, delta,
-                           (T*)dq, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale);
-        trace_mark(st);
-        hipLaunchKernelGGL((attn_bwd_dkv_vector<T, NB, NW>), grid_of((nPt + nSt * d.B) * d.Hkv), dim3(64 * NW), 0, st,
-                           (const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, lse, delta, (const T*)d_o,
-                           (T*)dk, (T*)dv, dzk, dzv, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale, d.n_frozen, d.dz_accumulate);
+        if constexpr (NB <= 8) {
+            // One launch, each dK / dV block forming the delta of its rows itself: it does not wait for the dQ blocks, and a
+            // launch fewer.  Against two (us, fp32): 2 x 64 tokens, 2 / 1 heads of 64, 32 slots 21.0 -> 17.0; 4 x 256, 8 / 2, 256
+            // slots 162 -> 134; of 128 375 -> 339; 16 x 512, 1000 slots 3968 -> 3251.  (Above 128: no registers for O's rows.)
+            hipLaunchKernelGGL((attn_bwd_vector<T, NB, NW>), grid_of(n_q + n_kv), dim3(64 * NW), 0, st, a, static_cast<int>(n_kv));
+            trace_mark(st);
+        } else {
+            hipLaunchKernelGGL((attn_bwd_dq_vector<T, NB, NW>), grid_of(n_q), dim3(64 * NW), 0, st, a);
+            trace_mark(st);
+            hipLaunchKernelGGL((attn_bwd_dkv_vector<T, NB, NW>), grid_of(n_kv), dim3(64 * NW), 0, st, a);
+        }
         trace_mark(st);
     });
 }

@@ -178,7 +178,9 @@ def test_packed_whole_and_split_blocks_overflowing():
 VECTOR_CASES = [(torch.float32, 2, 17, 2, 1, 5, 33), (torch.float32, 1, 16, 4, 2, 16, 16), (torch.float32, 3, 1, 2, 2, 64, 1),
                 (torch.float32, 2, 130, 4, 1, 64, 0), (torch.float32, 1, 65, 3, 1, 66, 15), (torch.float32, 2, 31, 2, 1, 128, 140),
                 (torch.float32, 1, 33, 2, 1, 132, 20), (torch.float32, 1, 20, 2, 1, 256, 17), (torch.bfloat16, 2, 40, 4, 2, 64, 50),
-                (torch.bfloat16, 1, 18, 2, 1, 37, 9), (torch.bfloat16, 1, 70, 2, 2, 128, 0)]
+                (torch.bfloat16, 1, 18, 2, 1, 37, 9), (torch.bfloat16, 1, 70, 2, 2, 128, 0),
+                # a wavefront's blocks of token rows in dK / dV: many and not all wavefronts the same, head_dim below its registers'
+                (torch.float32, 3, 50, 4, 1, 100, 33), (torch.float32, 3, 45, 4, 1, 40, 20), (torch.bfloat16, 5, 19, 3, 1, 72, 40)]
 
 
 @pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D,P", VECTOR_CASES, ids=lambda v: str(v).replace("torch.", ""))
