@@ -500,11 +500,30 @@ __device__ __forceinline__ void tile_load_async(char* tile, const char* base, in
 // the split of the query blocks, the most parts it can take (attn_mfma_fwd.hip)
 void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind);
 size_t attn_query_parts(const cart_attn_desc& d, int T);
-// the fused dK + dV kernel, its cut, the most bytes its partials can take (attn_mfma_bwd_kv.hip)
-mfma::KvPlan plan_bwd_kv(const cart_attn_desc& d, long tokens);
+// key tiles of each workgroup of a KV head in the split launch's order; how many, -1: more than `most`
+// every block in `parts` parts (1: whole); false: more than `most` of them
+bool attn_query_split_all(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, int parts, int most);
+int attn_query_tiles(const cart_attn_desc& d, int T, const mfma::QuerySplit& sp, int* tiles, int most);
+// the fused dK + dV kernel, its cut, the most bytes its partials can take; dQ beside it in one launch (attn_mfma_bwd_kv.hip)
+struct KvArgs {
+    const bf16_t *q, *k, *v, *zk, *zv, *d_o;
+    const float *nlse2, *ndelta;
+    bf16_t *dk_own, *dv_own;
+    float *part_k, *part_v;             // dZ partials, one per chunk of token rows
+    float *own_k, *own_v;               // partials of own keys, one per part of the heads (head_parts > 1)
+    const int32_t* cu;
+    int n_tok, chunk, head_parts, Smax, Hq, Hkv, P;
+    int own_cols;                       // own-key blocks: 0: a (sequence, part of the heads)'s one after the other; else the first of all own_cols of these, then the second ..
+    float c, scale;
+};
+struct DqArgs;
+// one_launch: dQ beside dK and dV, behind the first kv_front blocks of the key side (per KV head)
+struct BwdPlan { mfma::KvPlan kv; mfma::QuerySplit split; bool one_launch; int kv_front; };
+const BwdPlan& plan_bwd(const cart_attn_desc& d, int T);
 size_t bwd_kv_most(const cart_attn_desc& d, long tokens);
-void launch_attn_bwd_kv(const cart_attn_desc& d, float scale, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
-                        const bf16_t* ZK, const bf16_t* ZV, const bf16_t* DO, const float* lse2, const float* delta,
-                        bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, float* own_k, float* own_v, const int32_t* cu,
-                        int n_tok, const mfma::KvPlan& plan, hipStream_t st);
+unsigned bwd_kv_grid(const cart_attn_desc& d, const mfma::KvPlan& plan);
+void launch_attn_bwd_kv(const KvArgs& a, unsigned grid, hipStream_t st);
+void launch_attn_bwd_stats(const bf16_t* o, const bf16_t* d_o, const float* lse, float* nlse2, float* ndelta, int n_tok, int S, int Hq,
+                           hipStream_t st);
+void launch_attn_bwd_both(const KvArgs& ka, const DqArgs& qa, const mfma::QuerySplit& sp, unsigned kv_grid, int kv_front, hipStream_t st);
 }  // namespace cart

@@ -19,7 +19,7 @@
 // (direct loads, four buffers), each iteration is 32 fenced groups of one matrix-core instruction
 // plus its share of LDS reads and vector-ALU work, tiles that need no mask run through a loop
 // without masking code, and prefix-slot gradients leave as fp32 partials per chunk of token rows.
-#include "attn_mfma.h"
+#include "attn_bwd_dq.h"
 
 namespace cart {
 using namespace mfma;
@@ -42,7 +42,10 @@ struct KvSmem {
 
 // One LDS block for the workgroup, at file scope: the two roles are separate (not inlined)
 // functions, each with a register allocation of its own, that address the same memory.
-__shared__ KvSmem kv_sm;
+__shared__ union BwdSmem {
+    KvSmem kv;
+    DqSmem dq;
+} bwd_sm;
 
 // The workgroup barrier without the wait for every outstanding LDS and memory operation that
 // __syncthreads() puts in front of it: in the hot loop a wavefront only has to have finished what
@@ -51,21 +54,29 @@ __shared__ KvSmem kv_sm;
 __device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 __device__ __forceinline__ void lds_wait0() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// The kernel's arguments.  The role functions are real calls, and a call passes its arguments in
-// vector registers; they get one pointer -- the kernel-argument segment, taken in the kernel itself
+// The kernels' arguments (KvArgs and what the one-launch form adds).  The role functions are real calls, and a call passes
+// its arguments in vector registers; they get one pointer -- the kernel-argument segment, taken in the kernel itself
 // (the builtin that returns it is only meaningful there: inside a called function it yields a null
 // pointer) -- make it wave-uniform again and read this block through the scalar cache, so that
 // every pointer and size stays in scalar registers.
-struct KvArgs {
-    const bf16_t *q, *k, *v, *zk, *zv, *d_o;
-    const float *nlse2, *ndelta;
-    bf16_t *dk_own, *dv_own;
-    float *part_k, *part_v;             // dZ partials, one per chunk of token rows
-    float *own_k, *own_v;               // partials of own keys, one per part of the heads (head_parts > 1)
-    const int32_t* cu;
-    int n_tok, chunk, head_parts, Smax, Hq, Hkv, P;
-    float c, scale;
+struct BwdArgs {
+    KvArgs kv;
+    DqArgs dq;
+    unsigned n_front, n_dq;             // workgroups: key-side ones ahead of dQ's, dQ's
+    QuerySplit split;
 };
+#if defined(__HIP_DEVICE_COMPILE__)
+#define CART_KERNARG(T) const __attribute__((address_space(4))) T
+#else
+#define CART_KERNARG(T) const T         // (host pass: never runs)
+#endif
+template <typename T>
+__device__ __forceinline__ CART_KERNARG(T)* kernarg(const T* generic) {
+    const uint64_t u = reinterpret_cast<uint64_t>(generic);
+    const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u >> 32)));
+    const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(u)));
+    return (CART_KERNARG(T)*)((static_cast<uint64_t>(hi) << 32) | static_cast<uint64_t>(lo));
+}
 
 // A called function saves the callee-saved half of its registers on entry and reads it back on return:
 // 240 of them a wavefront, 240 KB a workgroup out and in again through scratch memory.  The compiler
@@ -74,16 +85,8 @@ struct KvArgs {
 // One sequence of 700 tokens, 32 / 8 heads, 1000 slots: 135 -> 127 us for forward and backward; 64 packed
 // conversations of up to 1024: 10.17 -> 10.00 ms; 16 x 2048 over 4096 slots: 9.81 -> 9.71.
 template <bool roleB>
-[[clang::not_tail_called]] static __device__ __attribute__((noinline)) void kv_role(const KvArgs* args_generic) {
-    const uint64_t au = reinterpret_cast<uint64_t>(args_generic);
-    const uint32_t a_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(au >> 32)));
-    const uint32_t a_lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(au)));
-    const uint64_t as = (static_cast<uint64_t>(a_hi) << 32) | static_cast<uint64_t>(a_lo);
-#if defined(__HIP_DEVICE_COMPILE__)
-    const KvArgs a = *(const __attribute__((address_space(4))) KvArgs*)as;
-#else
-    const KvArgs a = *reinterpret_cast<const KvArgs*>(as);      // (host pass: never runs)
-#endif
+[[clang::not_tail_called]] static __device__ __attribute__((noinline)) void kv_role(const KvArgs* args, int block) {
+    const KvArgs a = *kernarg(args);
     const bf16_t* __restrict__ q = a.q; const bf16_t* __restrict__ k = a.k; const bf16_t* __restrict__ v = a.v;
     const bf16_t* __restrict__ zk = a.zk; const bf16_t* __restrict__ zv = a.zv; const bf16_t* __restrict__ d_o = a.d_o;
     const float* __restrict__ nlse2 = a.nlse2; const float* __restrict__ ndelta = a.ndelta;
@@ -92,12 +95,12 @@ template <bool roleB>
     const int32_t* __restrict__ cu = a.cu;
     const int n_tok = a.n_tok, chunk = a.chunk, Smax = a.Smax, Hq = a.Hq, Hkv = a.Hkv, P = a.P;
     const float c = a.c, scale = a.scale;
-    KvSmem& sm = kv_sm;
+    KvSmem& sm = bwd_sm.kv;
     const int G = Hq / Hkv;
     const int nPb = (P + KV_WG_KEYS - 1) / KV_WG_KEYS, nOb = (Smax + KV_WG_KEYS - 1) / KV_WG_KEYS;
     // workgroup -> (KV head, key block, chunk of token rows | sequence and part of the heads): KV head
     // fastest; the prefix blocks (long streams: every token row of a chunk, all G heads) first
-    int id = blockIdx.x;
+    int id = __builtin_amdgcn_readfirstlane(block);
     const int hk = id % Hkv; id /= Hkv;
     int kb_, b_, g0 = 0, g1 = G;
     SeqSpan sp;
@@ -110,7 +113,8 @@ template <bool roleB>
         sp.stat_b = sp.stat_h = 0;
     } else {
         id -= nPb * nChunk;
-        kb_ = nPb + id % nOb; id /= nOb;
+        kb_ = nPb + (a.own_cols ? id / a.own_cols : id % nOb);
+        id = a.own_cols ? id % a.own_cols : id / nOb;
         b_ = id / a.head_parts;
         g0 = (id % a.head_parts) * (G / a.head_parts);
         g1 = g0 + G / a.head_parts;
@@ -598,15 +602,71 @@ template <bool roleB>
     }
 }
 
-__global__ __launch_bounds__(256, 1) void attn_bwd_kv_kernel(KvArgs args) {
+// odd wavefronts take role B, even ones role A (wave-uniform: a scalar branch)
+__device__ __forceinline__ void kv_block(const KvArgs* args, int block) {
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 1) kv_role<true>(args, block);
+    else                                                      kv_role<false>(args, block);
+}
 #if defined(__HIP_DEVICE_COMPILE__)
-    const KvArgs* ap = (const KvArgs*)__builtin_amdgcn_kernarg_segment_ptr();      // = &args
+#define CART_ARGS_PTR(T, args) (const T*)__builtin_amdgcn_kernarg_segment_ptr()       // = &args, the first argument
 #else
-    const KvArgs* ap = &args;
+#define CART_ARGS_PTR(T, args) &args
 #endif
-    // odd wavefronts take role B, even ones role A (wave-uniform: a scalar branch)
-    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 1) kv_role<true>(ap);
-    else                                                      kv_role<false>(ap);
+__global__ __launch_bounds__(256, 1) void attn_bwd_kv_kernel(KvArgs args) { kv_block(CART_ARGS_PTR(KvArgs, args), blockIdx.x); }
+
+// dQ beside dK and dV: a workgroup of either fills a CU, and apart each launch leaves CUs idle in its last round -- or, of
+// a problem with fewer blocks than CUs, for its whole length.  The longest blocks first: prefix blocks, own-key blocks with
+// more rows behind them than a dQ block has keys, dQ's, the other own-key blocks.
+[[clang::not_tail_called]] static __device__ __attribute__((noinline)) void dq_role(const BwdArgs* args, int block) {
+    CART_KERNARG(BwdArgs)* const ap = kernarg(args);
+    const DqArgs a = ap->dq;
+    const int id = __builtin_amdgcn_readfirstlane(block), wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int G = a.Hq / a.Hkv, hk = id % a.Hkv, x = id / a.Hkv, e_full = ap->split.e_full;
+    const uint32_t it = x < e_full ? 0x10000u : ap->split.part[x - e_full];
+    QueryBlock qb = query_block_of(hk, x < e_full ? x : e_full + (it & 255), wv, query_wgs(a.Smax, G), G);
+    qb.part = (it >> 8) & 255;
+    qb.n_parts = it >> 16;
+    qb.slot = (x - e_full) * a.Hkv + hk;
+    dq_block<false>(a, qb, reinterpret_cast<char*>(&bwd_sm), lds_addr(&bwd_sm));
+}
+__global__ __launch_bounds__(256, 1) void attn_bwd_both_kernel(BwdArgs args) {
+    const BwdArgs* const ap = CART_ARGS_PTR(BwdArgs, args);
+    const unsigned id = blockIdx.x, n_front = args.n_front, n_dq = args.n_dq;
+    if (id < n_front || id >= n_front + n_dq) kv_block(&ap->kv, id < n_front ? id : id - n_dq);
+    else                                      dq_role(ap, id - n_front);
+}
+
+// -lse log2(e) and -delta = -dO . O of every (token, head), [Hq][all token rows]: 16 lanes a row, 64 tokens of one head a
+// workgroup, heads fastest (they are next to each other in memory).  S: tokens per lse row
+__global__ __launch_bounds__(256) void attn_bwd_stats_kernel(const bf16_t* __restrict__ o, const bf16_t* __restrict__ d_o,
+                                                             const float* __restrict__ lse, float* __restrict__ nlse2,
+                                                             float* __restrict__ ndelta, int n_tok, int S, int Hq) {
+    const int id = workgroup_id(), h = id % Hq, i0 = id / Hq * 64 + (threadIdx.x >> 6) * 16 + ((threadIdx.x & 63) >> 4);
+    const int c = threadIdx.x & 15;
+    u32x4 ow[4], gw[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const size_t row = (static_cast<size_t>(min(i0 + 4 * r, n_tok - 1)) * Hq + h) * HD + 8 * c;
+        ow[r] = *reinterpret_cast<const u32x4*>(o + row);
+        gw[r] = *reinterpret_cast<const u32x4*>(d_o + row);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float x = 0.f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            x = fmaf(__uint_as_float(ow[r][e] << 16), __uint_as_float(gw[r][e] << 16), x);
+            x = fmaf(__uint_as_float(ow[r][e] & 0xffff0000u), __uint_as_float(gw[r][e] & 0xffff0000u), x);
+        }
+#pragma unroll
+        for (int m = 8; m > 0; m >>= 1) x += __shfl_xor(x, m, 16);
+        const int i = i0 + 4 * r;
+        if (c == 0 && i < n_tok) {
+            const size_t st = static_cast<size_t>(h) * n_tok + i;
+            ndelta[st] = -x;
+            nlse2[st] = -lse[(static_cast<size_t>(i / S) * Hq + h) * S + i % S] * CART_LOG2E;
+        }
+    }
 }
 
 // How the key-stationary launch is cut: token rows per dZ partial (prefix blocks stream chunks of the
@@ -639,13 +699,10 @@ size_t bwd_kv_most(const cart_attn_desc& d, long tokens) {
     return kv_chunk_bytes(d) + (extra < KV_MOST_EXTRA ? extra : KV_MOST_EXTRA);
 }
 
-static KvPlan search_plan(const cart_attn_desc& d, long tokens, int cus) {
-    const int G = d.Hq / d.Hkv, nT = (d.S + KV_TILE - 1) / KV_TILE;
-    const int nPb = (d.P + KV_WG_KEYS - 1) / KV_WG_KEYS, nOb = (d.S + KV_WG_KEYS - 1) / KV_WG_KEYS;
-    int M = cus / d.Hkv;
-    M = M < 1 ? 1 : (M > KV_MAX_CUS ? KV_MAX_CUS : M);
-    KvPlan best = {};
-    float best_t = 0.f;
+// The cuts that are considered: f(plan, own-key workgroups per KV head, microseconds of the partials' way)
+template <typename F>
+static void each_cut(const cart_attn_desc& d, long tokens, int M, F&& f) {
+    const int G = d.Hq / d.Hkv, nOb = (d.S + KV_WG_KEYS - 1) / KV_WG_KEYS;
     for (int hp = 1; hp <= G; ++hp) {
         if (G % hp) continue;
         const long n_own = static_cast<long>(nOb) * d.B * hp;
@@ -659,69 +716,190 @@ static KvPlan search_plan(const cart_attn_desc& d, long tokens, int cus) {
             if (p.n_part == last || (n > 1 && p.chunk < KV_MIN_CHUNK)) break;
             last = p.n_part;
             if (static_cast<size_t>(p.n_part - 1) * kv_chunk_bytes(d) + kv_own_bytes(d, tokens, hp) > KV_MOST_EXTRA) break;
-            const long n_pre = static_cast<long>(nPb) * p.n_part;
-            const bool full_pre = 4 * n_pre >= 3L * M, full_own = 4 * n_own >= 3L * M;
-            const float bp = full_pre ? KV_FULL_US : (4 * (n_pre + n_own) >= 3L * M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);
-            const float bo = full_own ? KV_FULL_US : (n_pre % M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);
-            const float pre = KV_BLOCK_US + bp * static_cast<float>(p.chunk / KV_TILE * G);
-            auto own = [&](int kb) { return KV_BLOCK_US + bo * static_cast<float>((nT - 2 * kb) * (G / hp)); };
-            const long q = n_pre / M, r = n_pre % M;
-            float end = pre * static_cast<float>(q + (r ? 1 : 0));
-            float sum = pre * static_cast<float>(n_pre);
-            for (int kb = 0; kb < nOb; ++kb) sum += own(kb) * static_cast<float>(d.B * hp);
-            const float even = sum / static_cast<float>(M);
-            const float parts_us = KV_US_PER_MB * 1e-6f * 2.f * HD * 4.f * static_cast<float>(d.Hkv) *
-                                   (static_cast<float>(p.n_part) * d.P + (hp > 1 ? static_cast<float>(hp) * tokens : 0.f));
-            // (no cut ends before its longest prefix CU or an even spread of all its work: not played through
-            // when that is no better already)
-            if (best.chunk != 0 && fmaxf(end, even) + parts_us >= best_t) continue;
-            if (n_own > 512) {
-                end = fmaxf(end, even + 0.5f * own(0));
-            } else {
-                float cu[KV_MAX_CUS];                   // a heap of the times at which the CUs are free
-                for (int m = 0; m < M; ++m) cu[m] = pre * static_cast<float>(q + (m >= M - static_cast<int>(r) ? 1 : 0));
-                for (long j = 0; j < n_own; ++j) {
-                    const float t = run_next(cu, M, own(static_cast<int>(j % nOb)));
-                    end = t > end ? t : end;
-                }
-            }
-            end += parts_us;
-            if (best.chunk == 0 || end < best_t) {
-                best_t = end;
-                best = p;
-            }
+            f(p, n_own, KV_US_PER_MB * 1e-6f * 2.f * HD * 4.f * static_cast<float>(d.Hkv) *
+                            (static_cast<float>(p.n_part) * d.P + (hp > 1 ? static_cast<float>(hp) * tokens : 0.f)));
         }
     }
+}
+
+// The times (us) of the workgroups of one KV head of a cut; full: the other kinds' workgroups fill the chip beside them
+struct KvTimes {
+    long n_pre, n_own;
+    float pre, own_tile;                // a prefix block; 64 query rows of an own-key block
+    int nT, nOb, heads;
+    float own(int i) const { return KV_BLOCK_US + own_tile * static_cast<float>((nT - 2 * (i % nOb)) * heads); }
+    float sum(int B_hp) const {
+        float t = pre * static_cast<float>(n_pre);
+        for (int kb = 0; kb < nOb; ++kb) t += own(kb) * static_cast<float>(B_hp);
+        return t;
+    }
+};
+static KvTimes kv_times(const cart_attn_desc& d, const KvPlan& p, int M, bool full) {
+    const int G = d.Hq / d.Hkv;
+    KvTimes t;
+    t.nT = (d.S + KV_TILE - 1) / KV_TILE;
+    t.nOb = (d.S + KV_WG_KEYS - 1) / KV_WG_KEYS;
+    t.heads = G / p.head_parts;
+    t.n_pre = static_cast<long>((d.P + KV_WG_KEYS - 1) / KV_WG_KEYS) * p.n_part;
+    t.n_own = static_cast<long>(t.nOb) * d.B * p.head_parts;
+    const bool full_pre = full || 4 * t.n_pre >= 3L * M, full_own = full || 4 * t.n_own >= 3L * M;
+    const float bp = full_pre ? KV_FULL_US : (4 * (t.n_pre + t.n_own) >= 3L * M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);
+    t.own_tile = full_own ? KV_FULL_US : (t.n_pre % M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);
+    t.pre = KV_BLOCK_US + bp * static_cast<float>(p.chunk / KV_TILE * G);
+    return t;
+}
+
+// the cut of a launch of its own, and when it ends with its partials summed
+static KvPlan search_plan(const cart_attn_desc& d, long tokens, int M, float* us) {
+    KvPlan best = {};
+    float best_t = 0.f;
+    each_cut(d, tokens, M, [&](const KvPlan& p, long n_own, float parts_us) {
+        const KvTimes t = kv_times(d, p, M, false);
+        const long q = t.n_pre / M, r = t.n_pre % M;
+        float end = t.pre * static_cast<float>(q + (r ? 1 : 0));
+        const float even = t.sum(d.B * p.head_parts) / static_cast<float>(M);
+        // (no cut ends before its longest prefix CU or an even spread of all its work: not played through
+        // when that is no better already)
+        if (best.chunk != 0 && fmaxf(end, even) + parts_us >= best_t) return;
+        if (n_own > 512) {
+            end = fmaxf(end, even + 0.5f * t.own(0));
+        } else {
+            float cu[KV_MAX_CUS];                   // a heap of the times at which the CUs are free
+            for (int m = 0; m < M; ++m) cu[m] = t.pre * static_cast<float>(q + (m >= M - static_cast<int>(r) ? 1 : 0));
+            for (long j = 0; j < n_own; ++j) {
+                const float e = run_next(cu, M, t.own(static_cast<int>(j)));
+                end = e > end ? e : end;
+            }
+        }
+        end += parts_us;
+        if (best.chunk == 0 || end < best_t) {
+            best_t = end;
+            best = p;
+        }
+    });
+    *us = best_t;
     return best;
 }
 
-KvPlan plan_bwd_kv(const cart_attn_desc& d, long tokens) {
-    // (a call asks twice, for the workspace and for the launch: the thread's last plan is kept with the
-    // sizes it depends on)
-    struct Key { long tokens; int B, S, Hq, Hkv, P, cus; };
+// dQ, dK and dV in one launch, or dQ and then dK and dV: whichever ends first by playing both through, the one launch for
+// the two cuts of each split of dQ that look best by their work spread evenly.  Launches of many rounds are not looked at:
+// their ends leave less idle than the statistics' own launch costs (32 x 1024 tokens, 24 / 8 heads, 2048 slots: 2943 us in
+// two, 2970 in one).  Measured, a backward call (us, two launches -> one):
+//   1 x 128, 32 / 8 heads, 1024 slots  52 -> 37     2 x 333, 32 / 8, 4096  191 -> 171     1 x 2048, 8 / 2, 256   88 -> 66
+//   1 x 700, 32 / 8, 1000              86 -> 82     3 x 1659, 32 / 8, 723  429 -> 393     1 x 2048, 32 / 8, 8192  863 -> 830
+//   packed: 4 of up to 272, 8 / 2, 1000  61 -> 41;  8 of up to 638, 32 / 8, 1501  307 -> 263
+// (own-key blocks as the two launches number them, a sequence's one after the other and all behind dQ's: 1 x 700 92, 3 x 1659 451)
+constexpr float DQ_BLOCK_US = 11.f, DQ_TILE_US = 1.95f, DQ_SPLIT_US = 4.f, DQ_PART_US = 0.05f;       // (SPLIT_COST of the dQ launch)
+constexpr int BOTH_ITEMS = 1024;        // most workgroups of a KV head that are played through
+static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, float kv_us, BwdPlan& best) {
+    const int most_parts = static_cast<int>(attn_query_parts(d, T));
+    int tiles[BOTH_ITEMS];
+    auto dq_items = [&](const QuerySplit& sp) { return attn_query_tiles(d, T, sp, tiles, BOTH_ITEMS); };
+    auto dq_extra = [&](const QuerySplit& sp) { return sp.n_blocks > 0 ? DQ_SPLIT_US + DQ_PART_US * static_cast<float>(sp.n_parts * d.Hkv) : 0.f; };
+    int n_dq = dq_items(best.split);
+    if (n_dq < 0 || best.split.e_full > 4 * M) return false;
+    float cu[KV_MAX_CUS];
+    float end = 0.f;
+    auto start = [&]() { for (int m = 0; m < M; ++m) cu[m] = 0.f; end = 0.f; };
+    auto run = [&](float t) { t = run_next(cu, M, t); end = t > end ? t : end; };
+    start();
+    for (int i = 0; i < n_dq; ++i) run(DQ_BLOCK_US + DQ_TILE_US * static_cast<float>(tiles[i]));
+    float best_t = end + dq_extra(best.split) + kv_us;
+    bool one = false;
+    const float stats_us = 4.f + static_cast<float>(tokens) * d.Hq * (2 * ROW_B) / 4.0e6f;
+    for (int parts = 1; parts <= 6; ++parts) {
+        QuerySplit sp;
+        if (!attn_query_split_all(sp, d, T, parts, most_parts)) break;
+        n_dq = dq_items(sp);
+        if (n_dq < 0) break;
+        float dq_sum = 0.f, dq_most = 0.f;
+        for (int i = 0; i < n_dq; ++i) {
+            const float t = DQ_BLOCK_US + DQ_TILE_US * static_cast<float>(tiles[i]);
+            dq_sum += t;
+            dq_most = t > dq_most ? t : dq_most;
+        }
+        // of this split, the two cuts with the least bound
+        struct { KvPlan p; float bound, extra; } c[2] = {};
+        int n = 0;
+        each_cut(d, tokens, M, [&](const KvPlan& p, long n_own, float parts_us) {
+            const KvTimes t = kv_times(d, p, M, true);
+            if (t.n_pre + n_own > BOTH_ITEMS) return;
+            const float longest = fmaxf(dq_most, fmaxf(t.n_pre > 0 ? t.pre : 0.f, t.own(0)));
+            const float extra = parts_us + dq_extra(sp) + stats_us;
+            const float bound = fmaxf(longest, (dq_sum + t.sum(d.B * p.head_parts)) / static_cast<float>(M)) + extra;
+            if (bound >= best_t) return;
+            const int at = n == 0 || bound < c[0].bound ? 0 : n == 1 || bound < c[1].bound ? 1 : 2;
+            if (at == 0) c[1] = c[0];
+            if (at < 2) { c[at].p = p; c[at].bound = bound; c[at].extra = extra; }
+            if (n < 2) ++n;
+        });
+        for (int i = 0; i < n; ++i) {
+            if (c[i].bound >= best_t) continue;
+            const KvTimes t = kv_times(d, c[i].p, M, true);
+            const long cols = static_cast<long>(d.B) * c[i].p.head_parts;
+            int kb1 = 0;                                // own-key blocks 0 .. kb1 - 1 of each column go ahead of dQ
+            while (kb1 < t.nOb && t.own(kb1) > dq_most) ++kb1;
+            start();
+            for (long j = 0; j < t.n_pre; ++j) run(t.pre);
+            for (int kb = 0; kb < t.nOb; ++kb) {
+                if (kb == kb1)
+                    for (int j = 0; j < n_dq; ++j) run(DQ_BLOCK_US + DQ_TILE_US * static_cast<float>(tiles[j]));
+                for (long j = 0; j < cols; ++j) run(t.own(kb));
+            }
+            if (kb1 == t.nOb)
+                for (int j = 0; j < n_dq; ++j) run(DQ_BLOCK_US + DQ_TILE_US * static_cast<float>(tiles[j]));
+            if (end + c[i].extra < best_t) {
+                best_t = end + c[i].extra;
+                best.kv = c[i].p;
+                best.split = sp;
+                best.kv_front = static_cast<int>(t.n_pre + kb1 * cols);
+                one = true;
+            }
+        }
+    }
+    return one;
+}
+
+// (the thread's last plan is kept with all that it depends on: the layers of a step ask for the same one in turn)
+const BwdPlan& plan_bwd(const cart_attn_desc& d, int T) {
+    struct Key { int T, B, S, Hq, Hkv, P, cus; };
     static thread_local Key key;
-    static thread_local KvPlan plan;
-    const Key k = {tokens, d.B, d.S, d.Hq, d.Hkv, d.P, device_cus()};
-    if (plan.chunk == 0 || key.tokens != k.tokens || key.B != k.B || key.S != k.S || key.Hq != k.Hq || key.Hkv != k.Hkv ||
-        key.P != k.P || key.cus != k.cus) {
-        plan = search_plan(d, tokens, k.cus);
+    static thread_local BwdPlan plan;
+    const Key k = {T, d.B, d.S, d.Hq, d.Hkv, d.P, device_cus()};
+    if (key.cus != k.cus || key.T != k.T || key.B != k.B || key.S != k.S || key.Hq != k.Hq || key.Hkv != k.Hkv || key.P != k.P) {
+        const long tokens = T > 0 ? T : static_cast<long>(d.B) * d.S;
+        int M = k.cus / d.Hkv;
+        M = M < 1 ? 1 : (M > KV_MAX_CUS ? KV_MAX_CUS : M);
+        float kv_us;
+        attn_query_split(plan.split, d, T, QUERY_DQ);
+        plan.kv = search_plan(d, tokens, M, &kv_us);
+        plan.one_launch = plan_one_launch(d, T, tokens, M, kv_us, plan);
         key = k;
     }
     return plan;
 }
 
-void launch_attn_bwd_kv(const cart_attn_desc& d, float scale, const bf16_t* Q, const bf16_t* K, const bf16_t* V,
-                        const bf16_t* ZK, const bf16_t* ZV, const bf16_t* DO, const float* lse2, const float* delta,
-                        bf16_t* dk, bf16_t* dv, float* part_k, float* part_v, float* own_k, float* own_v, const int32_t* cu,
-                        int n_tok, const KvPlan& plan, hipStream_t st) {
+unsigned bwd_kv_grid(const cart_attn_desc& d, const KvPlan& plan) {
     const long nPb = (d.P + KV_WG_KEYS - 1) / KV_WG_KEYS, nOb = (d.S + KV_WG_KEYS - 1) / KV_WG_KEYS;
-    const unsigned grid = static_cast<unsigned>((nPb * plan.n_part + nOb * d.B * plan.head_parts) * d.Hkv);
-    KvArgs a;
-    a.q = Q; a.k = K; a.v = V; a.zk = ZK; a.zv = ZV; a.d_o = DO; a.nlse2 = lse2; a.ndelta = delta;
-    a.dk_own = dk; a.dv_own = dv; a.part_k = part_k; a.part_v = part_v; a.own_k = own_k; a.own_v = own_v; a.cu = cu;
-    a.n_tok = n_tok; a.chunk = plan.chunk; a.head_parts = plan.head_parts; a.Smax = d.S; a.Hq = d.Hq; a.Hkv = d.Hkv; a.P = d.P;
-    a.c = scale * CART_LOG2E; a.scale = scale;
+    return static_cast<unsigned>((nPb * plan.n_part + nOb * d.B * plan.head_parts) * d.Hkv);
+}
+
+void launch_attn_bwd_kv(const KvArgs& a, unsigned grid, hipStream_t st) {
     hipLaunchKernelGGL(attn_bwd_kv_kernel, dim3(grid), dim3(256), 0, st, a);
+}
+void launch_attn_bwd_stats(const bf16_t* o, const bf16_t* d_o, const float* lse, float* nlse2, float* ndelta, int n_tok, int S, int Hq,
+                           hipStream_t st) {
+    hipLaunchKernelGGL(attn_bwd_stats_kernel, grid_of(static_cast<long>((n_tok + 63) / 64) * Hq), dim3(256), 0, st, o, d_o, lse, nlse2,
+                       ndelta, n_tok, S, Hq);
+}
+void launch_attn_bwd_both(const KvArgs& ka, const DqArgs& qa, const QuerySplit& sp, unsigned kv_grid, int kv_front, hipStream_t st) {
+    BwdArgs a;
+    a.kv = ka;
+    a.dq = qa;
+    a.n_front = static_cast<unsigned>(kv_front) * ka.Hkv;
+    a.n_dq = static_cast<unsigned>(sp.e_full + sp.n_parts) * ka.Hkv;
+    a.split = sp;
+    hipLaunchKernelGGL(attn_bwd_both_kernel, dim3(kv_grid + a.n_dq), dim3(256), 0, st, a);
 }
 
 }  // namespace cart

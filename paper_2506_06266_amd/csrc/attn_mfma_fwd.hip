@@ -589,6 +589,20 @@ static int query_slots(int Hkv) {
     return n < 1 ? 1 : (n > MAX_SPLIT ? MAX_SPLIT : n);
 }
 
+// key tiles of block e of a KV head, the masked ones among them
+struct Tiles { int all, masked; };
+static Tiles block_tiles(int e, int S, int G, int P, int own_cap, bool meet) {
+    const int nW = query_wgs(S, G), w = nW - 1 - e % nW, q_end = 64 * ((4 * w + 3) / G) + 64, tD = 4 * w / G;
+    const int upto = ((q_end < S ? q_end : S) + 63) / 64, own = own_cap > 0 && own_cap < upto ? own_cap : upto;
+    // (a block in which sequences meet: none of its own tiles is seen whole by all of its rows)
+    return Tiles{(P + 63) / 64 + own, (P % 64 ? 1 : 0) + (meet ? own : upto - tD < own ? upto - tD : own)};
+}
+// the longest of np parts
+static int longest(const Tiles& t, int np) {
+    const int step = (t.all + np - 1) / np, last = t.all - t.masked - 1, from = (np - 1) * step < last ? (np - 1) * step : last;
+    return np == 1 ? t.all : t.all - (from > 0 ? from : 0) > step ? t.all - (from > 0 ? from : 0) : step;
+}
+
 void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, bool meet, const SplitCost& us) {
     const int nW = query_wgs(S, G);
     const long n_all = static_cast<long>(B) * nW;
@@ -598,18 +612,7 @@ void mfma::plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P,
     if (n_all > 4L * slots || n_all > 2 * MAX_SPLIT || (P + 63) / 64 + (S + 63) / 64 < SPLIT_MIN_TILES) return;
     const int n = static_cast<int>(n_all), left = n % slots;       // the blocks left over after whole rounds
     if (left == 0) return;
-    struct Tiles { int all, masked; };
-    auto tiles = [&](int e) {
-        const int w = nW - 1 - e % nW, q_end = 64 * ((4 * w + 3) / G) + 64, tD = 4 * w / G;
-        const int upto = ((q_end < S ? q_end : S) + 63) / 64, own = own_cap > 0 && own_cap < upto ? own_cap : upto;
-        // (a block in which sequences meet: none of its own tiles is seen whole by all of its rows)
-        return Tiles{(P + 63) / 64 + own, (P % 64 ? 1 : 0) + (meet ? own : upto - tD < own ? upto - tD : own)};
-    };
-    // the longest of np parts
-    auto longest = [](const Tiles& t, int np) {
-        const int step = (t.all + np - 1) / np, last = t.all - t.masked - 1, from = (np - 1) * step < last ? (np - 1) * step : last;
-        return np == 1 ? t.all : t.all - (from > 0 ? from : 0) > step ? t.all - (from > 0 ? from : 0) : step;
-    };
+    auto tiles = [&](int e) { return block_tiles(e, S, G, P, own_cap, meet); };
     float cu[MAX_SPLIT];                                    // when each CU is free
     for (int i = 0; i < slots; ++i) cu[i] = 0.f;
     float done = 0.f;                                       // when the whole rounds are done
@@ -660,19 +663,59 @@ static size_t r256(size_t n) { return (n + 255) & ~static_cast<size_t>(255); }
 bool attn_mfma_supported(const cart_attn_desc& d) {
     return d.dtype == CART_BF16 && d.D == 128;
 }
-// Blocks per sequence, or over the packed rows (a packed batch with a prefix; T > 0).  The layers of a step
-// ask for the same two splits in turn, forward's and dQ's: the thread's last one of either kind is kept with
-// all that it depends on (planned again at each call, 32 sequences of 516 tokens, 8 / 2 heads: 18 us a layer).
-void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind) {
-    struct Key { int B, S, G, Hkv, P, own_cap, meet, cus; };
-    static thread_local Key last[2];
-    static thread_local QuerySplit kept[2];
+// What a split depends on: blocks per sequence, or over the packed rows (a packed batch with a prefix; T > 0)
+struct SplitKey { int B, S, G, Hkv, P, own_cap, meet, cus; };
+static SplitKey split_key(const cart_attn_desc& d, int T) {
     const int G = d.Hq / d.Hkv;
     const bool rows = T > 0 && d.P > 0;
     // (packed: a block's rows and those of the first one's sequence before it, and the tiles they begin and end inside)
     const int block_rows = 4 % G == 0 ? 256 / G : G % 4 == 0 ? 64 : 128;
-    const Key k = {rows ? 1 : d.B, rows ? T : d.S, G, d.Hkv, d.P, rows ? (d.S + block_rows + 126) / 64 : 0, rows && d.B > 1, device_cus()};
-    Key& l = last[kind];
+    return {rows ? 1 : d.B, rows ? T : d.S, G, d.Hkv, d.P, rows ? (d.S + block_rows + 126) / 64 : 0, rows && d.B > 1, device_cus()};
+}
+bool attn_query_split_all(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, int parts, int most) {
+    const SplitKey k = split_key(d, T);
+    const long n = static_cast<long>(k.B) * query_wgs(k.S, k.G);
+    sp.n_blocks = sp.n_parts = 0;
+    sp.e_full = static_cast<int>(n);
+    if (parts == 1) return true;
+    most = most < MAX_SPLIT ? most : MAX_SPLIT;
+    if (n > most) return false;
+    int all = 0;
+    for (int e = 0; e < n; ++e) {
+        const int t = block_tiles(e, k.S, k.G, k.P, k.own_cap, k.meet != 0).all;
+        all = t > all ? t : all;
+    }
+    const int step = (all + parts - 1) / parts;             // tiles per part, the same for every block
+    sp.e_full = 0;
+    sp.n_blocks = static_cast<int>(n);
+    for (int e = 0; e < n; ++e) {
+        const int np = (block_tiles(e, k.S, k.G, k.P, k.own_cap, k.meet != 0).all + step - 1) / step;
+        if (sp.n_parts + np > most) return false;
+        sp.first[e] = static_cast<uint32_t>(sp.n_parts);
+        for (int p = 0; p < np; ++p) sp.part[sp.n_parts++] = static_cast<uint32_t>(e | p << 8 | np << 16);
+    }
+    return true;
+}
+int attn_query_tiles(const cart_attn_desc& d, int T, const mfma::QuerySplit& sp, int* tiles, int most) {
+    const SplitKey k = split_key(d, T);
+    const int n = sp.e_full + sp.n_parts;
+    if (n > most) return -1;
+    for (int i = 0; i < n; ++i) {
+        const uint32_t it = i < sp.e_full ? 0x10000u : sp.part[i - sp.e_full];
+        const Tiles t = block_tiles(i < sp.e_full ? i : sp.e_full + static_cast<int>(it & 255), k.S, k.G, k.P, k.own_cap, k.meet != 0);
+        const int np = static_cast<int>(it >> 16);
+        tiles[i] = static_cast<int>((it >> 8) & 255) == np - 1 ? longest(t, np) : (t.all + np - 1) / np;
+    }
+    return n;
+}
+// The layers of a step ask for the same two splits in turn, forward's and dQ's: the thread's last one of either kind is kept with
+// all that it depends on (planned again at each call, 32 sequences of 516 tokens, 8 / 2 heads: 18 us a layer).
+void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind) {
+    static thread_local SplitKey last[2];
+    static thread_local QuerySplit kept[2];
+    const int G = d.Hq / d.Hkv;
+    const SplitKey k = split_key(d, T);
+    SplitKey& l = last[kind];
     if (l.cus != k.cus || l.B != k.B || l.S != k.S || l.G != k.G || l.Hkv != k.Hkv || l.P != k.P || l.own_cap != k.own_cap ||
         l.meet != k.meet) {
         plan_query_split(kept[kind], k.B, k.S, G, d.Hkv, d.P, k.own_cap, k.meet != 0, SPLIT_COST[kind]);

@@ -94,6 +94,15 @@ def test_attention_small_launches(B, S, Hq, Hkv, P):
     check_attn(*attn_case((B, S), Hq, Hkv, 128, P, torch.bfloat16, 7 * S + P), impl=cb.IMPL_MFMA, n_frozen=min(P, 3))
 
 
+# Backward in one launch: own-key blocks all ahead of dQ's blocks, all behind them, some of either (one sequence of 2100
+# tokens), dQ whole and split beside chunks of the token rows and parts of the heads; and in two (more blocks than the CUs of
+# a KV head take in four rounds; above, the smaller launches no longer come there).
+@pytest.mark.parametrize("B,S,Hq,Hkv,P", [(4, 200, 8, 2, 300), (3, 130, 8, 1, 900), (1, 300, 24, 8, 0), (1, 2100, 2, 1, 200), (140, 24, 4, 4, 3),
+                                          (130, 40, 32, 8, 70)])
+def test_attention_backward_launches(B, S, Hq, Hkv, P):
+    check_attn(*attn_case((B, S), Hq, Hkv, 128, P, torch.bfloat16, 5 * S + P), impl=cb.IMPL_MFMA, n_frozen=min(P, 1))
+
+
 # Scores that overflow the forward's fixed softmax reference (one key 200 nats above the first ones): rows
 # computed again by the wavefront itself where blocks run whole (whole rounds of 32 blocks per KV head; rows of
 # 1 .. 127 keys, around the eight taken at a time) and by the finishing kernel where they are split.
@@ -112,7 +121,9 @@ def test_attention_forward_recomputes_overflowing_rows(B, S, Hq, Hkv, P, hot):
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
 
 
-@pytest.mark.parametrize("lens,Hq,Hkv,P", [([700, 1, 90], 4, 1, 300), ([64, 64, 64], 2, 2, 1000), ([5, 3, 400, 131], 4, 2, 0)])
+# (the last: backward in two launches)
+@pytest.mark.parametrize("lens,Hq,Hkv,P", [([700, 1, 90], 4, 1, 300), ([64, 64, 64], 2, 2, 1000), ([5, 3, 400, 131], 4, 2, 0),
+                                           ([29] * 295, 32, 8, 20)])
 def test_packed_small_launches(lens, Hq, Hkv, P):
     q, k, v, zk, zv, do = attn_case((sum(lens),), Hq, Hkv, 128, P, torch.bfloat16, sum(lens) + P)
     cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32)
