@@ -35,6 +35,9 @@ constexpr int DEC_SUB = 32;            // own keys per wavefront step
 constexpr int DEC_SUB_B = DEC_SUB * ROW_B;
 
 constexpr int DEC_MIN_SHARE = 64;       // fewest rows per streamed range of requests that are not shorter
+constexpr int DEC_FINE_LEN = 512;       // longest request whose ranges may be of one step
+constexpr int DEC_LEAN_SHARE = 256;     // the lean plans' (unless no request is that long)
+constexpr int DEC_POOL_STEPS = 2;       // fewest steps per range beside private cartridges
 constexpr int DEC_MAX_SPLIT = 48;       // most parts the shared prefix is split into
 constexpr int DEC_MAX_PARTS = 64;       // most ranges the longest request's own rows are cut into
 constexpr int DEC_FEW_ROWS = 2048;      // output rows up to which the merge takes four wavefronts a row
@@ -141,6 +144,10 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     // (not below DEC_MIN_SHARE rows, nor the longest request in more than DEC_MAX_PARTS ranges: shorter
     // ranges only multiply the partials a request leaves.  8 requests of up to 500 tokens, us a call:
     // at least 256 / 128 / 64 / 32 rows -> 23.0 / 18.7 / 17.9 / 17.8; one of 16000: 19 / 17.8 / 25.4 / 36.9.
+    // A step each where every workgroup still has a CU of its own and no request leaves many partials: a launch of few
+    // requests ends with its longest range, whose steps follow one another.  us from a graph, 64 rows -> 32: 4 requests of up
+    // to 150 rows, 2048 slots 13.8 -> 11.8; 8 of up to 300, 8 / 2 heads, 4096 slots 14.0 -> 12.1; 16 of up to 150 15.7 -> 14.5;
+    // but 99 of up to 134 without a cartridge, which then share CUs, 16.8 -> 19.0, 7 of up to 1930 12.7 -> 13.3.
     // Requests shorter than that on average take a step each however few their rows are, so a range then
     // holds about one of them: 31 requests of up to 17 tokens beside 885 slots 26.2 -> 18.2, 128 of up to 16
     // beside 1000 33.6 -> 22.2, 48 of up to 53 beside 516 20.9 -> 18.2)
@@ -155,11 +162,15 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
             // (a range as long as the longest request takes no fewer partials: up to 256 rows were 256 steps where every
             // request had one: 404 requests, 28 / 4 heads, 3161 slots 549 us a call, 46 so)
             const long most = up(max_own_len, DEC_SUB);
-            const long wanted = most < 4 * DEC_MIN_SHARE ? most : 4 * DEC_MIN_SHARE;
+            const long wanted = most < DEC_LEAN_SHARE ? most : DEC_LEAN_SHARE;
             share = share > wanted ? share : wanted;
         }
-        else if (avg < DEC_MIN_SHARE) share = avg > needed ? avg : up(needed, needed < DEC_SUB ? 8 : DEC_SUB);
-        else if (share < DEC_MIN_SHARE) share = DEC_MIN_SHARE;
+        else {
+            const bool fine = max_own_len <= DEC_FINE_LEN && n_pre_wg + (((static_cast<long>(T) + share - 1) / share) * Hkv + 3) / 4 <= chip / 2;
+            const long min_share = fine ? DEC_SUB : DEC_MIN_SHARE;
+            if (avg < min_share) share = avg > needed ? avg : up(needed, needed < DEC_SUB ? 8 : DEC_SUB);
+            else if (share < min_share) share = min_share;
+        }
         if (share < 8) share = 8;
         used = (static_cast<long>(T) + share - 1) / share;
         // From the workgroup on that shares a CU the prefix role takes longer (the 0.55 and 0.8 us above): longer ranges
@@ -181,7 +192,7 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         // slots 230, now 179; 121 requests, cartridges of 389 265, now 70; 223 requests, cartridges of one slot 458, now 63.
         const float pool_steps = ceilf(static_cast<float>(pool_p) / DEC_SUB);
         const float each = fmaxf((own_steps + static_cast<float>(B) * pool_steps) / static_cast<float>(ranges > 4 ? ranges - 2 : ranges),
-                                 static_cast<float>(DEC_MIN_SHARE / DEC_SUB));        // steps per range
+                                 static_cast<float>(DEC_POOL_STEPS));        // steps per range
         auto cut = [&](float x, long at_least) {
             const long r = static_cast<long>(x) > at_least ? static_cast<long>(x) : at_least;
             return up(r < 8 ? 8 : r, r <= DEC_SUB ? 8 : DEC_SUB);

@@ -398,6 +398,8 @@ DECODE_CASES = [
     # own rows and private cartridges cut at different lengths: short requests beside long cartridges, cartridges of a
     # slot or two, one long request among them
     (200, 16, 8, 47, 786, 20), (223, 8, 8, 100, 1, 9), (60, 8, 1, 0, 7, 2), (30, 4, 2, 10, 3, 2000), (5, 8, 8, 0, 33, 300),
+    # ranges of one step: few requests, the longest one that has them and one just past it, ranges that straddle requests
+    (4, 32, 8, 2048, 0, 150), (3, 8, 2, 200, 0, 512), (3, 8, 2, 200, 0, 513), (9, 8, 2, 0, 0, 33), (20, 6, 2, 70, 0, 100),
 ]
 
 
