@@ -1,12 +1,14 @@
-"""ctypes binding over libcartridge.so (the C ABI declared in include/cartridge.h).
+"""Binding over libcartridge.so (the C ABI declared in include/cartridge.h): ctypes, and csrc/pycall.cpp for the entry
+points whose smallest calls are bound by the host.
 
 Argument marshalling only: every step of the path runs in the library's HIP kernels.
-PyTorch supplies device memory and the stream.  There is no fallback: if the library is
+PyTorch supplies device memory and the stream.  There is no fallback: if the library or the binding's native half is
 missing, or a call returns a non-zero status, an exception is raised.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional, Tuple
 
@@ -75,11 +77,23 @@ class CartridgeError(RuntimeError):
 
 
 _lib = None
+_native = None
+
+
+def _load_native(lib: C.CDLL):
+    path = os.path.join(_HERE, "_pycall.so")
+    if not os.path.exists(path):
+        raise FileNotFoundError("%s not found: build it with `python -m paper_2506_06266_amd.build`" % path)
+    spec = importlib.util.spec_from_file_location("_pycall", path)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    mod.init(lib._handle, _stream)
+    return mod
 
 
 def load() -> C.CDLL:
     """Loads the in-tree library; raises if it has not been built."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -124,6 +138,7 @@ def load() -> C.CDLL:
     lib.cart_calib_read.argtypes = [vp, sz, vp, vp]
     lib.cart_status_str.restype, lib.cart_status_str.argtypes = C.c_char_p, [C.c_int]
     lib.cart_version.restype, lib.cart_version.argtypes = C.c_int, []
+    _native = _load_native(lib)
     _lib = lib
     return lib
 
@@ -172,6 +187,13 @@ def _check(status: int, what: str):
         raise CartridgeError(status, what)
 
 
+def _outputs(r, what: str):
+    """What a function of csrc/pycall.cpp returned: the outputs, or the status of a call that failed."""
+    if type(r) is int:
+        raise CartridgeError(r, what)
+    return r
+
+
 # ------------------------------------------------------------------------------------------------
 def attn_desc(q: torch.Tensor, k_own: torch.Tensor, p: int, scale: float = 0.0, n_frozen: int = 0,
               dz_accumulate: bool = False, impl: int = IMPL_AUTO) -> AttnDesc:
@@ -183,45 +205,17 @@ def attn_desc(q: torch.Tensor, k_own: torch.Tensor, p: int, scale: float = 0.0, 
 def cart_attn_fwd(q, k_own, v_own, z_k, z_v, *, scale: float = 0.0, impl: int = IMPL_AUTO,
                   o=None, lse=None, workspace=None, stream=None) -> Tuple[torch.Tensor, torch.Tensor]:
     """q [B,S,Hq,D]; k_own, v_own [B,S,Hkv,D]; z_k, z_v [Hkv,P,D] -> (o [B,S,Hq,D], lse [B,Hq,S])."""
-    lib = load()
-    p = 0 if z_k is None else z_k.shape[1]
-    d = attn_desc(q, k_own, p, scale, impl=impl)
-    B, S, Hq, D = q.shape
-    o = torch.empty_like(q) if o is None else o
-    lse = torch.empty(B, Hq, S, dtype=torch.float32, device=q.device) if lse is None else lse
-    need = lib.cart_attn_fwd_workspace(C.byref(d))
-    ws, ws_ptr, ws_bytes = _workspace(need, workspace, q.device)
-    st = lib.cart_attn_fwd(C.byref(d), _ptr(q), _ptr(k_own), _ptr(v_own), _ptr(z_k), _ptr(z_v),
-                           _ptr(o), _ptr(lse), ws_ptr, ws_bytes,
-                           _stream(stream))
-    _check(st, "cart_attn_fwd")
-    return o, lse
+    load()
+    return _outputs(_native.attn_fwd(q, k_own, v_own, z_k, z_v, scale, impl, o, lse, workspace, stream), "cart_attn_fwd")
 
 
 def cart_attn_bwd(q, k_own, v_own, z_k, z_v, o, lse, d_o, *, scale: float = 0.0, n_frozen: int = 0,
                   d_z_k=None, d_z_v=None, dz_accumulate: bool = False, impl: int = IMPL_AUTO,
                   d_q=None, d_k_own=None, d_v_own=None, workspace=None, stream=None):
     """Returns (d_q, d_k_own, d_v_own, d_z_k, d_z_v); d_z_* are fp32 [Hkv,P,D]."""
-    lib = load()
-    p = 0 if z_k is None else z_k.shape[1]
-    d = attn_desc(q, k_own, p, scale, n_frozen, dz_accumulate, impl)
-    d_q = torch.empty_like(q) if d_q is None else d_q
-    d_k_own = torch.empty_like(k_own) if d_k_own is None else d_k_own
-    d_v_own = torch.empty_like(v_own) if d_v_own is None else d_v_own
-    if p > 0:
-        if d_z_k is None:
-            if dz_accumulate:
-                raise ValueError("dz_accumulate needs d_z_k / d_z_v")
-            d_z_k = torch.empty(z_k.shape, dtype=torch.float32, device=q.device)
-            d_z_v = torch.empty(z_v.shape, dtype=torch.float32, device=q.device)
-    need = lib.cart_attn_bwd_workspace(C.byref(d))
-    ws, ws_ptr, ws_bytes = _workspace(need, workspace, q.device)
-    st = lib.cart_attn_bwd(C.byref(d), _ptr(q), _ptr(k_own), _ptr(v_own), _ptr(z_k), _ptr(z_v),
-                           _ptr(o), _ptr(lse), _ptr(d_o), _ptr(d_q), _ptr(d_k_own), _ptr(d_v_own),
-                           _ptr(d_z_k), _ptr(d_z_v), ws_ptr, ws_bytes,
-                           _stream(stream))
-    _check(st, "cart_attn_bwd")
-    return d_q, d_k_own, d_v_own, d_z_k, d_z_v
+    load()
+    return _outputs(_native.attn_bwd(q, k_own, v_own, z_k, z_v, o, lse, d_o, scale, n_frozen, d_z_k, d_z_v, dz_accumulate, impl,
+                                     d_q, d_k_own, d_v_own, workspace, stream), "cart_attn_bwd")
 
 
 def cart_attn_varlen_fwd(q, k_own, v_own, z_k, z_v, cu_seqlens, max_seqlen: int, *, scale: float = 0.0,
@@ -277,35 +271,18 @@ def cart_distill_kl_fwd_bwd(logits, teacher_idx, teacher_logp, scale: float, *, 
     """logits [N,V]; teacher_idx [N,K] int32; teacher_logp [N,K] fp32 or None (all zero: with
     K = 1 that is next-token cross-entropy on the labels teacher_idx[:,0]) ->
     (loss [1] fp32 device tensor, d_logits [N,V]).  Pass d_logits=logits to work in place."""
-    lib = load()
-    N, V = logits.shape
-    d = KlDesc(N, V, teacher_idx.shape[1], _dtype_code(logits), scale, mode)
-    d_logits = torch.empty_like(logits) if d_logits is None else d_logits
-    loss = torch.empty(1, dtype=torch.float32, device=logits.device) if loss is None else loss
-    need = lib.cart_kl_workspace(C.byref(d))
-    ws, ws_ptr, ws_bytes = _workspace(need, workspace, logits.device)
-    st = lib.cart_distill_kl_fwd_bwd(C.byref(d), _ptr(logits), _ptr(teacher_idx), _ptr(teacher_logp),
-                                     _ptr(loss), _ptr(d_logits), _ptr(row_kl), ws_ptr, ws_bytes, _stream(stream))
-    _check(st, "cart_distill_kl_fwd_bwd")
-    return loss, d_logits
+    load()
+    return _outputs(_native.distill_kl(logits, teacher_idx, teacher_logp, scale, mode, d_logits, loss, row_kl, workspace,
+                                       stream), "cart_distill_kl_fwd_bwd")
 
 
 def cart_decode(q, z_k, z_v, k_own, v_own, cu_lens, max_own_len: int, *, scale: float = 0.0,
                 impl: int = IMPL_AUTO, o=None, lse=None, workspace=None, stream=None):
     """q [B,Hq,D]; z_k, z_v [Hkv,P,D]; k_own, v_own [T,Hkv,D]; cu_lens [B+1] int32 (device) ->
     (o [B,Hq,D], lse [B,Hq])."""
-    lib = load()
-    B, Hq, D = q.shape
-    p = 0 if z_k is None else z_k.shape[1]
-    d = DecodeDesc(B, Hq, k_own.shape[1], D, p, k_own.shape[0], max_own_len, _dtype_code(q), scale, impl)
-    o = torch.empty_like(q) if o is None else o
-    lse = torch.empty(B, Hq, dtype=torch.float32, device=q.device) if lse is None else lse
-    need = lib.cart_decode_workspace(C.byref(d))
-    ws, ws_ptr, ws_bytes = _workspace(need, workspace, q.device)
-    st = lib.cart_decode(C.byref(d), _ptr(q), _ptr(z_k), _ptr(z_v), _ptr(k_own), _ptr(v_own),
-                         _ptr(cu_lens), _ptr(o), _ptr(lse), ws_ptr, ws_bytes, _stream(stream))
-    _check(st, "cart_decode")
-    return o, lse
+    load()
+    return _outputs(_native.decode(q, z_k, z_v, k_own, v_own, cu_lens, max_own_len, scale, impl, o, lse, workspace,
+                                   stream), "cart_decode")
 
 
 def cart_decode_static(q, z_k, z_v, k_own, v_own, cu_lens, max_own_len: int, *, scale: float = 0.0,
@@ -326,14 +303,8 @@ def cart_decode_static(q, z_k, z_v, k_own, v_own, cu_lens, max_own_len: int, *, 
 
 def cart_teacher_topk(logits, k: int, *, teacher_idx=None, teacher_logp=None, stream=None):
     """logits [N,V] -> (teacher_idx [N,k] int32, teacher_logp [N,k] fp32), by descending probability."""
-    lib = load()
-    N, V = logits.shape
-    d = TopkDesc(N, V, k, _dtype_code(logits))
-    idx = torch.empty(N, k, dtype=torch.int32, device=logits.device) if teacher_idx is None else teacher_idx
-    lp = torch.empty(N, k, dtype=torch.float32, device=logits.device) if teacher_logp is None else teacher_logp
-    st = lib.cart_teacher_topk(C.byref(d), _ptr(logits), _ptr(idx), _ptr(lp), _stream(stream))
-    _check(st, "cart_teacher_topk")
-    return idx, lp
+    load()
+    return _outputs(_native.teacher_topk(logits, k, teacher_idx, teacher_logp, stream), "cart_teacher_topk")
 
 
 def cart_decode_composed(q, shared, pool_k, pool_v, cart_id, k_own, v_own, cu_lens, max_own_len: int, *,

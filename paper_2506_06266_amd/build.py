@@ -1,7 +1,7 @@
-"""Builds libcartridge.so (hand-written HIP for gfx950) in-tree with hipcc.
+"""Builds libcartridge.so (hand-written HIP for gfx950) in-tree with hipcc, and the binding's native half with g++.
 
 `python -m paper_2506_06266_amd.build` compiles every csrc/*.hip to an object file and links
-them; objects are rebuilt only when a source or header is newer unless force=True.
+them, and csrc/pycall.cpp; they are rebuilt only when a source or header is newer unless force=True.
 """
 from __future__ import annotations
 
@@ -9,12 +9,14 @@ import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.environ.get("CART_LIB_OUT", os.path.join(HERE, "libcartridge.so"))
+PYCALL = os.path.join(HERE, "_pycall.so")
 OBJ_DIR = os.environ.get("CART_OBJ_DIR", os.path.join(HERE, "_build"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -47,11 +49,31 @@ def _compile(src: str, force: bool) -> str:
     return obj
 
 
+def _compile_pycall(force: bool) -> str:
+    """csrc/pycall.cpp against the installed PyTorch (paths only: nothing of it is initialised here)."""
+    src = os.path.join(CSRC, "pycall.cpp")
+    if not force and os.path.exists(PYCALL) and os.path.getmtime(PYCALL) > max(os.path.getmtime(src), _newest_header()):
+        return PYCALL
+    import torch
+    at = os.path.dirname(os.path.abspath(torch.__file__))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
+           "-I", os.path.join(at, "include"), "-I", os.path.join(at, "include", "torch", "csrc", "api", "include"),
+           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), src, "-o", PYCALL,
+           "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("g++ failed for %s:\n%s\n%s" % (src, r.stdout, r.stderr))
+    return PYCALL
+
+
 def build(force: bool = True, jobs: int = 8) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     srcs = sorted(glob.glob(os.path.join(CSRC, "*.hip")))
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        pycall = ex.submit(_compile_pycall, force)
         objs = list(ex.map(lambda s: _compile(s, force), srcs))
+        pycall.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-fno-gpu-rdc", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
