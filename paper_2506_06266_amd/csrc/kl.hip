@@ -143,6 +143,7 @@ template <bool LONG, typename T> __device__ __forceinline__ KlBuf kl_buf(const T
                                                    (LONG ? KL_DROP / 16 : r.nslot) * 16, 0x00027000)};
 }
 constexpr int KL_NT = 2;             // cache policy: non-temporal
+constexpr int KL_AHEAD = 4;          // turns ahead of its use that a vector which is not resident is requested
 template <int AUX> __device__ __forceinline__ u32x4 kl_ld(const KlBuf& b, int off) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b.r, off, 0, AUX));
 }
@@ -167,7 +168,7 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
 // other row twice, element by element (rows x vocabulary):
 //   16384 x 128256 bf16  1649 -> 1593 (5.28 TB/s)     4096 x 32000 bf16  153 -> 100
 //    1024 x  50257 bf16   146 ->   47                16384 x  1000 fp32   54 ->  47
-//    2048 x 128256 fp32   785 ->  412 (423 without the LDS part)
+//    2048 x 128256 fp32   785 ->  398 (10 more without the LDS part)
 // Some of the set-up's values live in scratch (up to 4 registers; 15 at 1024 threads, 26 with the LDS part): stored once,
 // loaded once a row between the sweeps.
 template <typename T, int THREADS, int NV, int NL, bool LONG = false>
@@ -282,8 +283,16 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         KL_FORGET(x);
         float sum = s0 + s1;
         const KlBuf src = kl_buf<LONG>(logits, R), dst = kl_buf<LONG>(dlogits, R);
-        for (int v = (NV + NL) * THREADS + tid; v < R.nslot; v += THREADS) {   // what is not resident
-            const u32x4 w = LONG ? reinterpret_cast<const u32x4*>(kl_slots(logits, R))[v] : kl_ld<0>(src, v * 16);
+        // What is not resident, each vector requested KL_AHEAD turns ahead of its use (past the row's end: zeros): one at a
+        // time, every turn was a round trip to memory with nothing else on the CU (us a call, 2048 rows of 128256 fp32 logits
+        // 418; 2 / 3 / 4 / 6 / 8 ahead 410 / 408 / 403 / 406 / 408; 1024 of 200000 bf16 165 -> 159).  A remainder of one turn
+        // has nothing to request ahead (1024 of 100003 fp32 147, with the loop 149).
+        constexpr int REST = (NV + NL) * THREADS;
+        auto rest = [&](int v) __attribute__((always_inline)) {
+            if constexpr (LONG) return reinterpret_cast<const u32x4*>(kl_slots(logits, R))[min(v, max(R.nslot - 1, 0))];
+            else return kl_ld<0>(src, v * 16);
+        };
+        auto rest_sum = [&](const u32x4& w) __attribute__((always_inline)) {
             const float m1 = kl_vec_max<T>(mx, w);
             if (m1 > mx) {
                 const float c1 = -m1 * CART_LOG2E;
@@ -294,6 +303,24 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             s0 = s1 = 0.f;
             kl_vec_sum<T>(s0, s1, w, c0);
             sum += s0 + s1;
+        };
+        if (REST < R.nslot && R.nslot <= REST + THREADS) {
+            if (REST + tid < R.nslot) rest_sum(rest(REST + tid));
+        } else if (REST < R.nslot) {
+            u32x4 w[KL_AHEAD];
+#pragma unroll
+            for (int i = 0; i < KL_AHEAD; ++i) w[i] = rest(REST + i * THREADS + tid);
+            for (int v0 = REST; v0 < R.nslot; v0 += KL_AHEAD * THREADS) {
+#pragma unroll
+                for (int i = 0; i < KL_AHEAD; ++i) {
+                    if (i > 0 && v0 + i * THREADS >= R.nslot) break;
+                    const int v = v0 + i * THREADS + tid;
+                    u32x4 wi = w[i];
+                    w[i] = rest(v + KL_AHEAD * THREADS);
+                    if (v >= R.nslot) wi = kl_fill<T>();
+                    rest_sum(wi);
+                }
+            }
         }
         // the row's sum, relative to the largest reference
         const float wc = -wave_max(-c0);
@@ -327,12 +354,29 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             elem<T>::store(dlogits + R.row + logit_single<T>(R, tid), g.c * fast_exp2(fmaf(xs, CART_LOG2E, -lse2)));
         xs = -3.0e38f;
         if (more && tid < Rn.head + Rn.tail) xs = elem<T>::load(logits + Rn.row + logit_single<T>(Rn, tid));
-        for (int v = (NV + NL) * THREADS + tid; v < R.nslot; v += THREADS) {
-            if constexpr (LONG)
-                reinterpret_cast<u32x4*>(const_cast<T*>(kl_slots(dlogits, R)))[v] =
-                    kl_vec_grad<T>(reinterpret_cast<const u32x4*>(kl_slots(logits, R))[v], g);
-            else
-                kl_st(dst, kl_vec_grad<T>(kl_ld<KL_NT>(src, v * 16), g), v * 16);
+        auto rest_grad = [&](int v, const u32x4& w) __attribute__((always_inline)) {
+            if constexpr (LONG) {
+                if (v < R.nslot) reinterpret_cast<u32x4*>(const_cast<T*>(kl_slots(dlogits, R)))[v] = kl_vec_grad<T>(w, g);
+            } else {
+                kl_st(dst, kl_vec_grad<T>(w, g), v * 16);
+            }
+        };
+        if (REST < R.nslot && R.nslot <= REST + THREADS) {
+            rest_grad(REST + tid, rest(REST + tid));
+        } else if (REST < R.nslot) {
+            u32x4 w[KL_AHEAD];
+#pragma unroll
+            for (int i = 0; i < KL_AHEAD; ++i) w[i] = rest(REST + i * THREADS + tid);
+            for (int v0 = REST; v0 < R.nslot; v0 += KL_AHEAD * THREADS) {
+#pragma unroll
+                for (int i = 0; i < KL_AHEAD; ++i) {
+                    if (i > 0 && v0 + i * THREADS >= R.nslot) break;
+                    const int v = v0 + i * THREADS + tid;
+                    const u32x4 wi = w[i];
+                    w[i] = rest(v + KL_AHEAD * THREADS);
+                    rest_grad(v, wi);
+                }
+            }
         }
         const KlBuf src_next = kl_buf<LONG>(logits, Rn);
 #pragma unroll
