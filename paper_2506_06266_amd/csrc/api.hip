@@ -109,7 +109,7 @@ size_t cart_attn_fwd_workspace(const cart_attn_desc* d) {
 size_t cart_attn_bwd_workspace(const cart_attn_desc* d) {
     if (check_attn(d) != CART_OK) return 0;
     size_t delta = round256(static_cast<size_t>(d->B) * d->Hq * d->S * sizeof(float));
-    return delta + (use_mfma_bwd(*d) ? cart::attn_mfma_bwd_workspace(*d) : 0);
+    return delta + (use_mfma_bwd(*d) ? cart::attn_mfma_bwd_workspace(*d) : cart::attn_vector_bwd_workspace(*d));
 }
 
 size_t cart_attn_varlen_fwd_workspace(const cart_attn_varlen_desc* d) {

@@ -16,8 +16,8 @@
 // small problem is bound by latency -- its launches, one round trip for the operands, one for the
 // sums -- and a large one by the matrix cores.  Against one wavefront per row or key, a serial chain of
 // shuffles and exponentials per key, us for forward and backward: 2 sequences of 64 tokens, 2 / 1
-// heads of 64, 32 slots: 175 -> 26 (launches); 4 of 256, 8 / 2 heads, 256 slots: head_dim 64 2268 -> 156,
-// head_dim 128 2855 -> 327.
+// heads of 64, 32 slots: 175 -> 20 (launches); 4 of 256, 8 / 2 heads, 256 slots: head_dim 64 2268 -> 93,
+// head_dim 128 2855 -> 175.
 #include "cart_common.h"
 
 namespace cart {
@@ -261,6 +261,8 @@ struct VecBwd {
     int B, S, Hq, Hkv, D, P;
     float scale;
     int n_frozen, accumulate;
+    int splits;                         // of a prefix block's token rows; more than one: sums into part [splits][2][Hkv,P,D]
+    float* part;
 };
 template <int NB> constexpr int VEC_TURN = 16 * (16 * NB + 4);      // floats of one wavefront's sums in LDS
 
@@ -360,10 +362,10 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
     const int lane = threadIdx.x & 63, c = lane & 15, g = lane >> 4;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nPt = (P + 15) / 16, nSt = (S + 15) / 16, G = Hq / Hkv;
-    const bool prefix = id < nPt * Hkv;
-    if (!prefix) id -= nPt * Hkv;
+    const bool prefix = id < nPt * Hkv * a.splits;
+    if (!prefix) id -= nPt * Hkv * a.splits;
     const int hk = id % Hkv; id /= Hkv;
-    const int key0 = 16 * (prefix ? id : id % nSt), b_own = prefix ? 0 : id / nSt;
+    const int key0 = 16 * (id % (prefix ? nPt : nSt)), split = prefix ? id / nPt : 0, b_own = prefix ? 0 : id / nSt;
     if (b_own >= B) return;
     const int nkeys = prefix ? P : S;
     auto key_row = [&](int j) { return prefix ? (static_cast<size_t>(hk) * P + j) * D
@@ -375,7 +377,9 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
     clear(ak);
     clear(av);
     // blocks of 16 token rows: (sequence, head of the group, block), from the block's own diagonal on
-    const int it0 = prefix ? 0 : key0 / 16, nIt = nSt - it0, n = (prefix ? B : 1) * G * nIt;
+    const int it0 = prefix ? 0 : key0 / 16, nIt = nSt - it0, all = (prefix ? B : 1) * G * nIt;
+    const int first = prefix ? static_cast<int>(static_cast<long>(all) * split / a.splits) : 0;
+    const int n = prefix ? static_cast<int>(static_cast<long>(all) * (split + 1) / a.splits) : all;      // blocks [first, n)
     // Of a block: its rows for the scores, lse, delta; then the same rows as columns for the sums
     struct Block { int i0, h, b; };
     auto block = [&](int t) __attribute__((always_inline)) {
@@ -406,13 +410,13 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
         for (int r = 0; r < 4; ++r) pr[r] = src + tok(x, x.i0 + 4 * g + r);
         f = col_frag<T, NB>(pr, D, c);
     };
-    Block cur = block(min(wv, n - 1));
+    Block cur = block(min(first + wv, n - 1));
     if constexpr (VEC_AHEAD<NB>) {
         load_rows(cur);
         load_cols(cur, gc, a.d_o);
         load_cols(cur, qc, a.q);
     }
-    for (int t = wv; t < n; t += NW) {
+    for (int t = first + wv; t < n; t += NW) {
         // (The block after the last is the last again: loads under a condition are all waited for at its end.  The columns
         // not requested ahead come behind the scores: head_dim above 128 has no registers for all four operands of a block --
         // 52 registers of fp32 problems, 128 of bf16 ones, spill as it is -- and two wavefronts on a SIMD are faster so:
@@ -465,7 +469,11 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
                 gk += sm_k[u][(t >> 4) * PITCH + d];
                 gv += sm_v[u][(t >> 4) * PITCH + d];
             }
-            if (prefix) {
+            if (prefix && a.splits > 1) {
+                const size_t all_z = static_cast<size_t>(Hkv) * P * D;
+                a.part[2 * split * all_z + r + d] = gk;
+                a.part[(2 * split + 1) * all_z + r + d] = gv;
+            } else if (prefix) {
                 gk = j < a.n_frozen ? 0.f : gk * a.scale;
                 gv = j < a.n_frozen ? 0.f : gv;
                 if (a.accumulate) { gk += a.dzk[r + d]; gv += a.dzv[r + d]; }
@@ -488,6 +496,24 @@ template <typename T, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(VecBwd<T> a) {
     __shared__ float sm[2][NW][VEC_TURN<NB>];
     dkv_block<T, NB, NW, false>(a, workgroup_id(), sm[0], sm[1]);
+}
+// dZ from the sums of split prefix blocks, in the splits' order
+__global__ __launch_bounds__(256) void attn_bwd_dz_vector(const float* __restrict__ part, float* __restrict__ dzk, float* __restrict__ dzv,
+                                                          int n, int P, int D, int splits, float scale, int n_frozen, int accumulate) {
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    float gk = 0.f, gv = 0.f;
+#pragma unroll 4
+    for (int s = 0; s < splits; ++s) {
+        gk += part[static_cast<size_t>(2 * s) * n + i];
+        gv += part[static_cast<size_t>(2 * s + 1) * n + i];
+    }
+    const bool frozen = i / D % P < n_frozen;
+    gk = frozen ? 0.f : gk * scale;
+    gv = frozen ? 0.f : gv;
+    if (accumulate) { gk += dzk[i]; gv += dzv[i]; }
+    dzk[i] = gk;
+    dzv[i] = gv;
 }
 // Both in one launch, the dK / dV blocks (the longer ones) first
 template <typename T, int NB, int NW>
@@ -589,21 +615,54 @@ int launch_attn_fwd_vector(const cart_attn_desc& d, float scale, const void* q, 
     return static_cast<int>(hipGetLastError());
 }
 
+// Into how many parts the token rows of a prefix block are split: it streams those of every sequence, an own-key block one
+// sequence's, and a problem of this path's size leaves most CUs idle meanwhile.  Blocks of 16 rows one after the other
+// cost a wavefront about VEC_TURN_US each, the sums their launch; no more prefix blocks than CUs.  us a backward call, whole ->
+// split: 4 x 128 tokens, 8 / 2 heads of 128, 128 slots 148 -> 47; 4 x 256, 256 slots 291 -> 138, of 64 134 -> 72; 2 x 64, 4 / 2
+// heads of 200, 64 slots 71 -> 53; 2 x 64, 8 / 2 heads of 64, 64 slots 22.7 -> 17.5.
+constexpr int VEC_MAX_SPLITS = 8;
+constexpr float VEC_TURN_US = 3.5f, VEC_SUM_US = 5.f;
+static int dz_splits(const cart_attn_desc& d, int NW) {
+    const long nSt = (d.S + 15) / 16, nPt = (d.P + 15) / 16, G = d.Hq / d.Hkv;
+    if (d.P == 0) return 1;
+    const long all = d.B * G * nSt, own = (G * nSt + NW - 1) / NW;
+    int best = 1;
+    float best_us = 0.f;
+    for (int s = 1; s <= VEC_MAX_SPLITS && s <= all; ++s) {
+        if (s > 1 && nPt * d.Hkv * s > device_cus()) break;
+        const long turns = ((all + s - 1) / s + NW - 1) / NW;
+        const float us = VEC_TURN_US * static_cast<float>(turns > own ? turns : own) + (s > 1 ? VEC_SUM_US : 0.f);
+        if (s == 1 || us < best_us) {
+            best_us = us;
+            best = s;
+        }
+    }
+    return best;
+}
+// what the sums of split prefix blocks take at most, for this problem or any smaller one
+size_t attn_vector_bwd_workspace(const cart_attn_desc& d) {
+    if (d.P == 0) return 0;
+    const size_t one = 2 * static_cast<size_t>(d.Hkv) * d.P * d.D * sizeof(float), most = 2 * static_cast<size_t>(device_cus()) * 16 * d.D * sizeof(float);
+    return VEC_MAX_SPLITS * one < most ? VEC_MAX_SPLITS * one : most;
+}
+
 template <typename T>
 static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const void* k, const void* v,
                   const void* zk, const void* zv, const void* o, const float* lse, const void* d_o,
                   void* dq, void* dk, void* dv, float* dzk, float* dzv, void* ws, hipStream_t st) {
     const long nSt = (d.S + 15) / 16, nPt = (d.P + 15) / 16;
-    const long n_q = nSt * d.Hq * d.B, n_kv = (nPt + nSt * d.B) * d.Hkv;
+    const int splits = dz_splits(d, d.D <= 64 ? 8 : 4);
+    const long n_q = nSt * d.Hq * d.B, n_kv = (nPt * splits + nSt * d.B) * d.Hkv;
+    float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + ((static_cast<size_t>(d.B) * d.Hq * d.S * sizeof(float) + 255) & ~static_cast<size_t>(255)));
     const VecBwd<T> a = {(const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (const T*)o, (const T*)d_o, lse,
                          static_cast<float*>(ws), (T*)dq, (T*)dk, (T*)dv, dzk, dzv, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale,
-                         d.n_frozen, d.dz_accumulate};
+                         d.n_frozen, d.dz_accumulate, splits, part};
     trace_begin(st);   // kernel order: dq (+ delta), dk/dv/dz; or both in one (nothing between the second's events)
     CART_DISPATCH_NB(d.D, {
         if constexpr (NB <= 8) {
             // One launch, each dK / dV block forming the delta of its rows itself: it does not wait for the dQ blocks, and a
             // launch fewer.  Against two (us, fp32): 2 x 64 tokens, 2 / 1 heads of 64, 32 slots 21.0 -> 17.0; 4 x 256, 8 / 2, 256
-            // slots 162 -> 134; of 128 375 -> 339; 16 x 512, 1000 slots 3968 -> 3251.  (Above 128: no registers for O's rows.)
+            // slots 162 -> 134; of 128 375 -> 339; 16 x 512, 1000 slots 3968 -> 3251 (prefix blocks whole).  (Above 128: no registers for O's rows.)
             hipLaunchKernelGGL((attn_bwd_vector<T, NB, NW>), grid_of(n_q + n_kv), dim3(64 * NW), 0, st, a, static_cast<int>(n_kv));
             trace_mark(st);
         } else {
@@ -613,6 +672,12 @@ static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const voi
         }
         trace_mark(st);
     });
+    if (splits > 1) {
+        const int n = d.Hkv * d.P * d.D;
+        hipLaunchKernelGGL(attn_bwd_dz_vector, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st, part, dzk, dzv, n, d.P, d.D, splits,
+                           scale, d.n_frozen, d.dz_accumulate);
+        trace_mark(st);
+    }
 }
 
 int launch_attn_bwd_vector(const cart_attn_desc& d, float scale, const void* q, const void* k,

@@ -191,12 +191,27 @@ VECTOR_CASES = [(torch.float32, 2, 17, 2, 1, 5, 33), (torch.float32, 1, 16, 4, 2
                 (torch.float32, 1, 33, 2, 1, 132, 20), (torch.float32, 1, 20, 2, 1, 256, 17), (torch.bfloat16, 2, 40, 4, 2, 64, 50),
                 (torch.bfloat16, 1, 18, 2, 1, 37, 9), (torch.bfloat16, 1, 70, 2, 2, 128, 0),
                 # a wavefront's blocks of token rows in dK / dV: many and not all wavefronts the same, head_dim below its registers'
-                (torch.float32, 3, 50, 4, 1, 100, 33), (torch.float32, 3, 45, 4, 1, 40, 20), (torch.bfloat16, 5, 19, 3, 1, 72, 40)]
+                (torch.float32, 3, 50, 4, 1, 100, 33), (torch.float32, 3, 45, 4, 1, 40, 20), (torch.bfloat16, 5, 19, 3, 1, 72, 40),
+                # ... and the prefix blocks' split into parts, of different lengths
+                (torch.float32, 5, 40, 6, 2, 64, 35), (torch.float32, 3, 70, 4, 1, 128, 20), (torch.bfloat16, 7, 33, 4, 2, 200, 17),
+                (torch.float32, 9, 20, 8, 1, 33, 3)]
 
 
 @pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D,P", VECTOR_CASES, ids=lambda v: str(v).replace("torch.", ""))
 def test_attention_vector(dtype, B, S, Hq, Hkv, D, P):
     check_attn(*attn_case((B, S), Hq, Hkv, D, P, dtype, S + D), impl=cb.IMPL_VECTOR, n_frozen=min(P, 2))
+
+
+def test_attention_vector_split_prefix_accumulates():
+    t = attn_case((4, 40), 8, 2, 64, 20, torch.float32, 1)
+    ref = orc.attn_bwd(*[f64(x) for x in t])[3:]
+    q, k, v, zk, zv, do = (x.to(DEV) for x in t)
+    o, lse = cb.cart_attn_fwd(q, k, v, zk, zv)
+    gk, gv = (torch.ones(2, 20, 64, device=DEV) for _ in range(2))
+    cb.cart_attn_bwd(q, k, v, zk, zv, o, lse, do, d_z_k=gk, d_z_v=gv, dz_accumulate=True, n_frozen=3)
+    torch.cuda.synchronize()
+    for g, r in zip((gk, gv), ref):
+        assert (g[:, :3] == 1).all() and rel_err(g[:, 3:] - 1, r[:, 3:]) <= 5 * TOL[torch.float32]    # (and the sum with 1: 2^-24 of it)
 
 
 # A NaN or an infinity reaches exactly the results whose sums hold it: tokens 11 .. leave the rows before
