@@ -312,22 +312,10 @@ def cart_decode_composed(q, shared, pool_k, pool_v, cart_id, k_own, v_own, cu_le
     """q [B,Hq,D]; shared: list of (z_k, z_v) tensors [Hkv,p_s,D] every request attends over;
     pool_k, pool_v [n_pool,Hkv,p_c,D] and cart_id [B] int32 (device; < 0 = none), or None;
     k_own, v_own [T,Hkv,D]; cu_lens [B+1] int32 (device) -> (o [B,Hq,D], lse [B,Hq])."""
-    lib = load()
-    B, Hq, D = q.shape
-    segs = (Segment * max(len(shared), 1))()
-    for i, (zk, zv) in enumerate(shared):
-        segs[i] = Segment(_ptr(zk), _ptr(zv), zk.shape[1])
-    n_pool, pool_p = (0, 0) if pool_k is None else (pool_k.shape[0], pool_k.shape[2])
-    d = DecodeComposedDesc(B, Hq, k_own.shape[1], D, len(shared), n_pool, pool_p, k_own.shape[0], max_own_len,
-                           _dtype_code(q), scale)
-    o = torch.empty_like(q) if o is None else o
-    lse = torch.empty(B, Hq, dtype=torch.float32, device=q.device) if lse is None else lse
-    need = lib.cart_decode_composed_workspace(C.byref(d), segs)
-    ws, ws_ptr, ws_bytes = _workspace(need, workspace, q.device)
-    st = lib.cart_decode_composed(C.byref(d), _ptr(q), segs, _ptr(pool_k), _ptr(pool_v), _ptr(cart_id),
-                                  _ptr(k_own), _ptr(v_own), _ptr(cu_lens), _ptr(o), _ptr(lse), ws_ptr, ws_bytes, _stream(stream))
-    _check(st, "cart_decode_composed")
-    return o, lse
+    load()
+    segs = [(zk, zv) for zk, zv in shared] if len(shared) else []
+    return _outputs(_native.decode_composed(q, segs, pool_k, pool_v, cart_id, k_own, v_own, cu_lens, max_own_len, scale, o, lse,
+                                            workspace, stream), "cart_decode_composed")
 
 
 # ------------------------------------------------------------------------------------------------

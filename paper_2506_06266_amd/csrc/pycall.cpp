@@ -1,13 +1,17 @@
 // The per-call host work of the Python binding's smallest entry points in native code: descriptor, output tensors,
 // workspace, the checks on the tensors handed over, the library call.  In Python with ctypes it is a third of a call whose
 // kernels take ten microseconds (decode of four requests, us of host time a call: 14.2, of which the two launches are 6.5, now 10.0;
-// a forward and backward call of fp32 attention over 2 x 64 tokens 23.8 -> 19.2).  The library is reached through the handle the binding opened (no link dependency on it).
+// a forward and backward call of fp32 attention over 2 x 64 tokens 23.8 -> 19.2; decode of one request over three shared
+// cartridges 16.7 -> 10.5).  The library is reached through the handle the binding
+// opened (no link dependency on it).
 //
 // Every function takes the arguments of its namesake in binding.py by position and returns the outputs, or the status of
 // a call that failed (an int, which the binding turns into its exception).
 #include <dlfcn.h>
 
+#include <algorithm>
 #include <string>
+#include <vector>
 
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -30,6 +34,8 @@ struct Api {
     decltype(&cart_teacher_topk) topk;
     decltype(&cart_decode_workspace) decode_workspace;
     decltype(&cart_decode) decode;
+    decltype(&cart_decode_composed_workspace) composed_workspace;
+    decltype(&cart_decode_composed) composed;
 } api;
 
 // a tensor argument (null: None)
@@ -249,6 +255,43 @@ PyObject* decode(PyObject*, PyObject* const* a, Py_ssize_t n) {
     END_HANDLE_TH_ERRORS
 }
 
+// q, shared (a list of pairs), pool_k, pool_v, cart_id, k_own, v_own, cu_lens, max_own_len, scale, o, lse, workspace, stream
+PyObject* decode_composed(PyObject*, PyObject* const* a, Py_ssize_t n) {
+    HANDLE_TH_ERRORS
+    count(n, 14);
+    const at::Tensor &q = tensor(a[0]), &k = tensor(a[5]), &v = tensor(a[6]), &cu = tensor(a[7]);
+    const at::Tensor *pool_k = tensor_or_none(a[2]), *pool_v = tensor_or_none(a[3]), *cart_id = tensor_or_none(a[4]);
+    cart_decode_composed_desc d = {};
+    d.B = size(q, 3, 0); d.Hq = size(q, 3, 1); d.D = size(q, 3, 2);
+    if (!PyList_Check(a[1]) && !PyTuple_Check(a[1])) throw torch::TypeError("a list of (z_k, z_v) is expected");
+    std::vector<cart_segment> segs(static_cast<size_t>(std::max<Py_ssize_t>(PySequence_Fast_GET_SIZE(a[1]), 1)));
+    for (Py_ssize_t i = 0; i < PySequence_Fast_GET_SIZE(a[1]); ++i) {
+        PyObject* const pair = PySequence_Fast_GET_ITEM(a[1], i);
+        if ((!PyList_Check(pair) && !PyTuple_Check(pair)) || PySequence_Fast_GET_SIZE(pair) != 2) throw torch::TypeError("a pair (z_k, z_v) is expected");
+        const at::Tensor &zk = tensor(PySequence_Fast_GET_ITEM(pair, 0)), *zv = tensor_or_none(PySequence_Fast_GET_ITEM(pair, 1));
+        segs[i].z_k = address(&zk);
+        segs[i].z_v = address(zv);
+        segs[i].p = size(zk, 0, 1);
+    }
+    d.Hkv = size(k, 0, 1);
+    d.n_shared = static_cast<int32_t>(PySequence_Fast_GET_SIZE(a[1]));
+    if (pool_k) { d.n_pool = size(*pool_k, 0, 0); d.pool_p = size(*pool_k, 0, 2); }
+    d.total_own_tokens = size(k, 0, 0);
+    d.max_own_len = int32(a[8]);
+    d.dtype = static_cast<decltype(d.dtype)>(dtype_code(q));
+    d.softmax_scale = real(a[9]);
+    const at::Tensor o = like(a[10], q), lse = fresh(a[11], {d.B, d.Hq}, at::kFloat, q);
+    const Workspace ws(a[12], api.composed_workspace(&d, segs.data()), q);
+    void *pq = address(&q), *ppk = address(pool_k), *ppv = address(pool_v), *pid = address(cart_id), *pk = address(&k), *pv = address(&v),
+         *pc = address(&cu), *po = address(&o), *pl = address(&lse);
+    void* const st = stream(a[13]);
+    return outputs(without_gil([&] {
+        return api.composed(&d, pq, segs.data(), ppk, ppv, static_cast<int32_t*>(pid), pk, pv, static_cast<int32_t*>(pc), po,
+                            static_cast<float*>(pl), ws.p, ws.bytes, st);
+    }), {&o, &lse});
+    END_HANDLE_TH_ERRORS
+}
+
 // the handle of the opened library, the binding's _stream
 PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
     HANDLE_TH_ERRORS
@@ -270,12 +313,14 @@ PyObject* init(PyObject*, PyObject* const* a, Py_ssize_t n) {
     get(api.topk, "cart_teacher_topk");
     get(api.decode_workspace, "cart_decode_workspace");
     get(api.decode, "cart_decode");
+    get(api.composed_workspace, "cart_decode_composed_workspace");
+    get(api.composed, "cart_decode_composed");
     Py_RETURN_NONE;
     END_HANDLE_TH_ERRORS
 }
 
 #define FAST(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(name)), METH_FASTCALL, nullptr}
-PyMethodDef methods[] = {FAST(attn_fwd), FAST(attn_bwd), FAST(distill_kl), FAST(teacher_topk), FAST(decode),
+PyMethodDef methods[] = {FAST(attn_fwd), FAST(attn_bwd), FAST(distill_kl), FAST(teacher_topk), FAST(decode), FAST(decode_composed),
                          FAST(init), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_pycall", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

@@ -16,6 +16,7 @@ CALLS = {
     "kl": lambda q=X, **kw: cb.cart_distill_kl_fwd_bwd(q, IDX, None, 1.0, **kw),
     "topk": lambda q=X, **kw: cb.cart_teacher_topk(q, 2, **kw),
     "decode": lambda q=Q[0], **kw: cb.cart_decode(q, Z, Z, K[0], K[0], CU, 4, **kw),
+    "composed": lambda q=Q[0], **kw: cb.cart_decode_composed(q, [], None, None, None, K[0], K[0], CU, 4, **kw),
 }
 
 
@@ -42,6 +43,14 @@ def test_refused_numbers(kw):
             CALLS[name](**kw)
     with pytest.raises(TypeError):
         cb.cart_decode(Q[0], Z, Z, K[0], K[0], CU, 2.5)
+
+
+def test_refused_segments():
+    with pytest.raises(ValueError, match="contiguous device tensors"):
+        cb.cart_decode_composed(Q[0], [(Z, Z)], None, None, None, K[0], K[0], CU, 4)
+    for shared in (None, [Z], [(Z,)], [(None, Z)]):
+        with pytest.raises((TypeError, ValueError, AttributeError)):
+            cb.cart_decode_composed(Q[0], shared, None, None, None, K[0], K[0], CU, 4)
 
 
 def test_accumulating_needs_the_gradients():
