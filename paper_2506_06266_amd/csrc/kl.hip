@@ -144,6 +144,8 @@ template <bool LONG, typename T> __device__ __forceinline__ KlBuf kl_buf(const T
 }
 constexpr int KL_NT = 2;             // cache policy: non-temporal
 constexpr int KL_AHEAD = 4;          // turns ahead of its use that a vector which is not resident is requested
+constexpr int KL_FEW = 64;           // up to so many rows ...
+constexpr int KL_SHORT = 8;          // ... a remainder of up to so many turns is read one turn at a time
 template <int AUX> __device__ __forceinline__ u32x4 kl_ld(const KlBuf& b, int off) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b.r, off, 0, AUX));
 }
@@ -286,8 +288,14 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         // What is not resident, each vector requested KL_AHEAD turns ahead of its use (past the row's end: zeros): one at a
         // time, every turn was a round trip to memory with nothing else on the CU (us a call, 2048 rows of 128256 fp32 logits
         // 418; 2 / 3 / 4 / 6 / 8 ahead 410 / 408 / 403 / 406 / 408; 1024 of 200000 bf16 165 -> 159).  A remainder of one turn
-        // has nothing to request ahead (1024 of 100003 fp32 147, with the loop 149).
+        // has nothing to request ahead (1024 of 100003 fp32 147, with the loop 149), and with a row on few of the CUs memory
+        // answers sooner than the longer loop's code arrives (32 of 128256 fp32 23.5, one at a time 23.1; 150 of 100000 the
+        // same either way; 128 of 300000, 49 turns, 69 ahead and 81 one at a time).
         constexpr int REST = (NV + NL) * THREADS;
+        // (only the last of a type's row lengths has a remainder at all)
+        constexpr bool MORE = LONG || (THREADS * NV == 1024 * 16 && (NL > 0 || sizeof(T) == 2));
+        const bool one_turn = R.nslot <= REST + THREADS;
+        const bool one_by_one = NL > 0 && N <= KL_FEW && R.nslot <= REST + KL_SHORT * THREADS;
         auto rest = [&](int v) __attribute__((always_inline)) {
             if constexpr (LONG) return reinterpret_cast<const u32x4*>(kl_slots(logits, R))[min(v, max(R.nslot - 1, 0))];
             else return kl_ld<0>(src, v * 16);
@@ -304,9 +312,12 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             kl_vec_sum<T>(s0, s1, w, c0);
             sum += s0 + s1;
         };
-        if (REST < R.nslot && R.nslot <= REST + THREADS) {
+        if (MORE && REST < R.nslot && one_turn) {
             if (REST + tid < R.nslot) rest_sum(rest(REST + tid));
-        } else if (REST < R.nslot) {
+        } else if (MORE && REST < R.nslot && one_by_one) {
+#pragma unroll 1
+            for (int v = REST + tid; v < R.nslot; v += THREADS) rest_sum(rest(v));
+        } else if (MORE && REST < R.nslot) {
             u32x4 w[KL_AHEAD];
 #pragma unroll
             for (int i = 0; i < KL_AHEAD; ++i) w[i] = rest(REST + i * THREADS + tid);
@@ -361,9 +372,12 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
                 kl_st(dst, kl_vec_grad<T>(w, g), v * 16);
             }
         };
-        if (REST < R.nslot && R.nslot <= REST + THREADS) {
+        if (MORE && REST < R.nslot && one_turn) {
             rest_grad(REST + tid, rest(REST + tid));
-        } else if (REST < R.nslot) {
+        } else if (MORE && REST < R.nslot && one_by_one) {
+#pragma unroll 1
+            for (int v = REST + tid; v < R.nslot; v += THREADS) rest_grad(v, rest(v));
+        } else if (MORE && REST < R.nslot) {
             u32x4 w[KL_AHEAD];
 #pragma unroll
             for (int i = 0; i < KL_AHEAD; ++i) w[i] = rest(REST + i * THREADS + tid);

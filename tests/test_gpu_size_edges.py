@@ -257,8 +257,10 @@ LOSS_CASES = [
     # (slots counted from a 128-byte line, up to seven more than vectors: the fullest rows of each width)
     (torch.bfloat16, 9, 4047, 20), (torch.bfloat16, 9, 4049, 20), (torch.bfloat16, 9, 32719, 20), (torch.bfloat16, 9, 65487, 20),
     (torch.bfloat16, 9, 131023, 20), (torch.float32, 33, 2023, 20), (torch.float32, 33, 16359, 20), (torch.float32, 9, 98279, 20),
-    # what is not resident: one turn, just more, more turns than are requested ahead, several rows a workgroup
-    (torch.float32, 3, 102400, 20), (torch.float32, 3, 102407, 20), (torch.float32, 300, 114697, 5), (torch.float32, 2, 135165, 20),
+    # what is not resident: one turn, just more, more turns than are requested ahead, several rows a workgroup; few rows
+    # (fp32) up to eight turns, and more of either
+    (torch.float32, 3, 102400, 20), (torch.float32, 3, 102407, 20), (torch.float32, 65, 102407, 5), (torch.float32, 3, 131072, 20),
+    (torch.float32, 300, 114697, 5), (torch.float32, 2, 135165, 20),
     (torch.bfloat16, 3, 163851, 20), (torch.bfloat16, 270, 172032, 5),
 ]
 
