@@ -55,16 +55,29 @@ void* address(const at::Tensor* t) {
     TORCH_CHECK_VALUE(t->is_cuda() && t->is_contiguous(), "tensors handed to libcartridge must be contiguous device tensors");
     return t->mutable_data_ptr();
 }
-// integers as a ctypes field takes them: Python's own, cut to their width
+// Numbers as a ctypes field takes them, which the entry points left in Python hand theirs to: an integer is whatever has
+// __index__ (numpy's, a tensor of one), cut to its width, a float is none; a real is whatever has __float__ or __index__.
 int32_t int32(PyObject* o) {
-    if (!PyLong_Check(o)) throw torch::TypeError(std::string("an integer is required (got type ") + Py_TYPE(o)->tp_name + ")");
-    return static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(o));
+    if (PyLong_CheckExact(o)) return static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(o));
+    PyObject* const i = PyNumber_Index(o);
+    if (!i) throw python_error();
+    const int32_t r = static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(i));
+    Py_DECREF(i);
+    return r;
 }
 float real(PyObject* o) {
-    if (!PyFloat_Check(o) && !PyLong_Check(o)) throw torch::TypeError(std::string("a number is required (got type ") + Py_TYPE(o)->tp_name + ")");
     const double x = PyFloat_AsDouble(o);
     if (x == -1.0 && PyErr_Occurred()) throw python_error();
     return static_cast<float>(x);
+}
+// int(o)
+int32_t truncated(PyObject* o) {
+    if (PyBool_Check(o)) return o == Py_True;
+    PyObject* const i = PyNumber_Long(o);
+    if (!i) throw python_error();
+    const int32_t r = static_cast<int32_t>(PyLong_AsUnsignedLongLongMask(i));
+    Py_DECREF(i);
+    return r;
 }
 PyObject* stream_of = nullptr;      // the binding's _stream: a stream object or None -> its raw handle
 void* stream(PyObject* o) {
@@ -168,14 +181,14 @@ PyObject* attn_bwd(PyObject*, PyObject* const* a, Py_ssize_t n) {
     count(n, 19);
     const at::Tensor &q = tensor(a[0]), &k = tensor(a[1]), &v = tensor(a[2]), &o = tensor(a[5]), &lse = tensor(a[6]), &d_o = tensor(a[7]);
     const at::Tensor *zk = tensor_or_none(a[3]), *zv = tensor_or_none(a[4]);
-    const int accumulate = PyObject_IsTrue(a[12]);
-    if (accumulate < 0) throw python_error();
-    const cart_attn_desc d = attn_desc(q, k, slots(zk), real(a[8]), int32(a[9]), accumulate, int32(a[13]));
+    const cart_attn_desc d = attn_desc(q, k, slots(zk), real(a[8]), int32(a[9]), truncated(a[12]), int32(a[13]));
     const at::Tensor dq = like(a[14], q), dk = like(a[15], k), dv = like(a[16], v);
     at::Tensor dzk, dzv;
     if (a[10] != Py_None) dzk = tensor(a[10]);
     if (a[11] != Py_None) dzv = tensor(a[11]);
     if (d.P > 0 && !dzk.defined()) {
+        const int accumulate = PyObject_IsTrue(a[12]);
+        if (accumulate < 0) throw python_error();
         TORCH_CHECK_VALUE(!accumulate, "dz_accumulate needs d_z_k / d_z_v");
         dzk = at::empty(zk->sizes(), q.options().dtype(at::kFloat));
         dzv = at::empty((zv ? zv : zk)->sizes(), q.options().dtype(at::kFloat));

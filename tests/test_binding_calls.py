@@ -1,6 +1,8 @@
-"""What the binding refuses before anything reaches the library, and that a refused call keeps nothing (host only)."""
+"""What the binding takes and what it refuses before anything reaches the library, and that a refused call keeps nothing (host only)."""
 import sys
+from fractions import Fraction
 
+import numpy as np
 import pytest
 import torch
 
@@ -36,13 +38,41 @@ def test_refused_tensors(name):
         call(q.numpy())
 
 
-@pytest.mark.parametrize("kw", [dict(scale="1"), dict(scale=torch.ones(())), dict(impl=1.0)])
+@pytest.mark.parametrize("kw", [dict(scale="1"), dict(scale=1j), dict(scale=torch.ones(2)), dict(impl=1.0), dict(impl=torch.ones(()))])
 def test_refused_numbers(kw):
     for name in ("attn_fwd", "attn_bwd", "decode"):
-        with pytest.raises(TypeError):
+        with pytest.raises((TypeError, ValueError), match="^(?!tensors handed)"):
             CALLS[name](**kw)
     with pytest.raises(TypeError):
         cb.cart_decode(Q[0], Z, Z, K[0], K[0], CU, 2.5)
+    for accumulate in (None, [], "x"):
+        with pytest.raises((TypeError, ValueError), match="int"):
+            CALLS["attn_bwd"](dz_accumulate=accumulate)
+
+
+# A number of any kind that a ctypes field takes gets as far as the check of the tensors, here too
+INTEGERS = [4, True, np.int64(4), np.uint8(4), torch.tensor(4), torch.tensor([4]), np.array(4)]
+REALS = [1, 0.5, np.float32(0.5), np.float64(0.5), np.int64(1), torch.tensor(0.5), torch.tensor([0.5]), Fraction(1, 2)]
+
+
+@pytest.mark.parametrize("n", INTEGERS, ids=repr)
+def test_accepted_integers(n):
+    for call in (lambda: CALLS["attn_fwd"](impl=n), lambda: CALLS["attn_bwd"](n_frozen=n), lambda: CALLS["attn_bwd"](impl=n),
+                 lambda: CALLS["kl"](mode=n), lambda: cb.cart_teacher_topk(X, n, teacher_idx=IDX, teacher_logp=X),
+                 lambda: cb.cart_decode(Q[0], Z, Z, K[0], K[0], CU, n),
+                 lambda: cb.cart_decode_composed(Q[0], [], None, None, None, K[0], K[0], CU, n),
+                 lambda: cb.cart_decode_static(Q[0], Z, Z, K[0], K[0], CU, n)):
+        with pytest.raises(ValueError, match="contiguous device tensors"):
+            call()
+
+
+@pytest.mark.parametrize("x", REALS, ids=repr)
+def test_accepted_reals(x):
+    for name in ("attn_fwd", "attn_bwd", "decode", "composed"):
+        with pytest.raises(ValueError, match="contiguous device tensors"):
+            CALLS[name](scale=x)
+    with pytest.raises(ValueError, match="contiguous device tensors"):
+        cb.cart_distill_kl_fwd_bwd(X, IDX, None, x)
 
 
 def test_refused_segments():
