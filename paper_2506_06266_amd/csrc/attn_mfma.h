@@ -192,6 +192,7 @@ inline float run_next(float* free_at, int n, float t) {
 // (the sums run over them in turn), for each workgroup.
 enum QueryKernel { QUERY_FWD, QUERY_DQ };
 struct SplitCost { float block, tile, fix, part, wg; };
+constexpr SplitCost SPLIT_COST[2] = {{9.2f, 1.21f, 3.5f, 0.7f, 0.045f}, {11.f, 1.95f, 4.f, 0.f, 0.05f}};
 void plan_query_split(QuerySplit& sp, int B, int S, int G, int Hkv, int P, int own_cap, bool meet, const SplitCost& us);
 // The cut of the key-stationary launch: token rows per dZ partial, the partials, and into how many parts the
 // query heads that read an own key are split
@@ -500,9 +501,9 @@ __device__ __forceinline__ void tile_load_async(char* tile, const char* base, in
 // the split of the query blocks, the most parts it can take (attn_mfma_fwd.hip)
 void attn_query_split(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, mfma::QueryKernel kind);
 size_t attn_query_parts(const cart_attn_desc& d, int T);
-// key tiles of each workgroup of a KV head in the split launch's order; how many, -1: more than `most`
 // every block in `parts` parts (1: whole); false: more than `most` of them
 bool attn_query_split_all(mfma::QuerySplit& sp, const cart_attn_desc& d, int T, int parts, int most);
+// key tiles of each workgroup of a KV head in the split launch's order; how many, -1: more than `most`
 int attn_query_tiles(const cart_attn_desc& d, int T, const mfma::QuerySplit& sp, int* tiles, int most);
 // the fused dK + dV kernel, its cut, the most bytes its partials can take; dQ beside it in one launch (attn_mfma_bwd_kv.hip)
 struct KvArgs {

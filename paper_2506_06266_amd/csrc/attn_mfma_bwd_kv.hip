@@ -699,6 +699,11 @@ size_t bwd_kv_most(const cart_attn_desc& d, long tokens) {
     return kv_chunk_bytes(d) + (extra < KV_MOST_EXTRA ? extra : KV_MOST_EXTRA);
 }
 
+// the partials' way through memory
+static float kv_parts_us(const cart_attn_desc& d, long tokens, const KvPlan& p) {
+    return KV_US_PER_MB * 1e-6f * 2.f * HD * 4.f * static_cast<float>(d.Hkv) *
+           (static_cast<float>(p.n_part) * d.P + (p.head_parts > 1 ? static_cast<float>(p.head_parts) * tokens : 0.f));
+}
 // The cuts that are considered: f(plan, own-key workgroups per KV head, microseconds of the partials' way)
 template <typename F>
 static void each_cut(const cart_attn_desc& d, long tokens, int M, F&& f) {
@@ -716,13 +721,12 @@ static void each_cut(const cart_attn_desc& d, long tokens, int M, F&& f) {
             if (p.n_part == last || (n > 1 && p.chunk < KV_MIN_CHUNK)) break;
             last = p.n_part;
             if (static_cast<size_t>(p.n_part - 1) * kv_chunk_bytes(d) + kv_own_bytes(d, tokens, hp) > KV_MOST_EXTRA) break;
-            f(p, n_own, KV_US_PER_MB * 1e-6f * 2.f * HD * 4.f * static_cast<float>(d.Hkv) *
-                            (static_cast<float>(p.n_part) * d.P + (hp > 1 ? static_cast<float>(hp) * tokens : 0.f)));
+            f(p, n_own, kv_parts_us(d, tokens, p));
         }
     }
 }
 
-// The times (us) of the workgroups of one KV head of a cut; full: the other kinds' workgroups fill the chip beside them
+// The times (us) of the workgroups of one KV head of a cut
 struct KvTimes {
     long n_pre, n_own;
     float pre, own_tile;                // a prefix block; 64 query rows of an own-key block
@@ -734,27 +738,30 @@ struct KvTimes {
         return t;
     }
 };
-static KvTimes kv_times(const cart_attn_desc& d, const KvPlan& p, int M, bool full) {
-    const int G = d.Hq / d.Hkv;
+static KvTimes kv_times(const cart_attn_desc& d, const KvPlan& p) {
     KvTimes t;
     t.nT = (d.S + KV_TILE - 1) / KV_TILE;
     t.nOb = (d.S + KV_WG_KEYS - 1) / KV_WG_KEYS;
-    t.heads = G / p.head_parts;
+    t.heads = d.Hq / d.Hkv / p.head_parts;
     t.n_pre = static_cast<long>((d.P + KV_WG_KEYS - 1) / KV_WG_KEYS) * p.n_part;
     t.n_own = static_cast<long>(t.nOb) * d.B * p.head_parts;
-    const bool full_pre = full || 4 * t.n_pre >= 3L * M, full_own = full || 4 * t.n_own >= 3L * M;
-    const float bp = full_pre ? KV_FULL_US : (4 * (t.n_pre + t.n_own) >= 3L * M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);
-    t.own_tile = full_own ? KV_FULL_US : (t.n_pre % M ? 0.5f * (KV_FULL_US + KV_LIGHT_US) : KV_LIGHT_US);
-    t.pre = KV_BLOCK_US + bp * static_cast<float>(p.chunk / KV_TILE * G);
     return t;
 }
+static void set_tiles(KvTimes& t, const cart_attn_desc& d, const KvPlan& p, float pre_tile, float own_tile) {
+    t.own_tile = own_tile;
+    t.pre = KV_BLOCK_US + pre_tile * static_cast<float>(p.chunk / KV_TILE * (d.Hq / d.Hkv));
+}
 
-// the cut of a launch of its own, and when it ends with its partials summed
-static KvPlan search_plan(const cart_attn_desc& d, long tokens, int M, float* us) {
+// the cut of a launch of its own
+static KvPlan search_plan(const cart_attn_desc& d, long tokens, int M) {
     KvPlan best = {};
     float best_t = 0.f;
     each_cut(d, tokens, M, [&](const KvPlan& p, long n_own, float parts_us) {
-        const KvTimes t = kv_times(d, p, M, false);
+        KvTimes t = kv_times(d, p);
+        const bool full_pre = 4 * t.n_pre >= 3L * M, full_own = 4 * t.n_own >= 3L * M;
+        const float half = 0.5f * (KV_FULL_US + KV_LIGHT_US);
+        set_tiles(t, d, p, full_pre ? KV_FULL_US : 4 * (t.n_pre + t.n_own) >= 3L * M ? half : KV_LIGHT_US,
+                  full_own ? KV_FULL_US : t.n_pre % M ? half : KV_LIGHT_US);
         const long q = t.n_pre / M, r = t.n_pre % M;
         float end = t.pre * static_cast<float>(q + (r ? 1 : 0));
         const float even = t.sum(d.B * p.head_parts) / static_cast<float>(M);
@@ -777,34 +784,77 @@ static KvPlan search_plan(const cart_attn_desc& d, long tokens, int M, float* us
             best = p;
         }
     });
-    *us = best_t;
     return best;
 }
 
-// dQ, dK and dV in one launch, or dQ and then dK and dV: whichever ends first by playing both through, the one launch for
-// the two cuts of each split of dQ that look best by their work spread evenly.  Launches of many rounds are not looked at:
-// their ends leave less idle than the statistics' own launch costs (32 x 1024 tokens, 24 / 8 heads, 2048 slots: 2943 us in
-// two, 2970 in one).  Measured, a backward call (us, two launches -> one):
-//   1 x 128, 32 / 8 heads, 1024 slots  52 -> 37     2 x 333, 32 / 8, 4096  191 -> 171     1 x 2048, 8 / 2, 256   88 -> 66
-//   1 x 700, 32 / 8, 1000              86 -> 82     3 x 1659, 32 / 8, 723  429 -> 393     1 x 2048, 32 / 8, 8192  863 -> 830
-//   packed: 4 of up to 272, 8 / 2, 1000  61 -> 41;  8 of up to 638, 32 / 8, 1501  307 -> 263
+// One KV head's workgroups played through in launch order.  Workgroup numbers go to the XCDs in turn, whatever these have
+// left to do: with fewer KV heads than XCDs, every n-th of a head's workgroups runs on the same 1/n of the head's CUs.
+// spare: one in 16 of these CUs left out.
+struct Played {
+    float cu[KV_MAX_CUS];
+    int n, per, at;
+    float end;
+    Played(int Hkv, int M, bool spare) : at(0), end(0.f) {
+        int g = Hkv;
+        for (int x = 8, y; x; x = y) { y = g % x; g = x; }             // gcd with the 8 XCDs
+        n = M >= 8 / g ? 8 / g : 1;
+        per = M / n;
+        if (spare && per > 2) per -= per >= 16 ? per / 16 : 1;
+        for (int i = 0; i < n * per; ++i) cu[i] = 0.f;
+    }
+    void run(float t) {
+        t = run_next(cu + at * per, per, t);
+        end = t > end ? t : end;
+        at = at + 1 == n ? 0 : at + 1;
+    }
+};
+
+// dQ, dK and dV in one launch, or dQ and then dK and dV: by playing both through, the one launch for the two cuts of each
+// split of dQ that look best by their work spread evenly.  A block's time varies by 8 %: where the blocks of the one launch
+// just fill whole rounds, the last of them start a round later than played, and little evens that out where the long
+// prefix blocks are much of the work.  Unless all but the short blocks start at once, the one launch is therefore played on
+// 15/16 of its CUs, which also picks the cuts that leave room; and its time is weighed by the prefix blocks' share.
+// Measured over 2400 random batched and packed problems of 35 to 3000 us: 1639 go to one launch, 11 of them are slower so than
+// in two by more than 1.5 %, and all 2400 are 1.124 times as fast as in two in the geometric mean (all in one launch 1.133, 137 slower;
+// the faster form of each 1.136).  The two estimates compared as they are, on all CUs: 21 of 1092 (of 1370 problems) slower.
+// Launches of many rounds are not looked at: their ends leave less idle than the statistics' own launch costs (32 x 1024
+// tokens, 24 / 8 heads, 2048 slots: 2943 us in two, 2970 in one).  Measured, a backward call (us, two launches -> one):
+//   1 x 128, 32 / 8 heads, 1024 slots  52 -> 37     2 x 333, 32 / 8, 4096  198 -> 176     1 x 2048, 8 / 2, 256   88 -> 66
+//   1 x 700, 32 / 8, 1000              87 -> 75     3 x 1659, 32 / 8, 723  448 -> 411     18 x 558, 8 / 2, 2942  418 -> 398
+//   packed: 4 of up to 272, 8 / 2, 1000  64 -> 43;  8 of up to 638, 32 / 8, 1501  321 -> 295
 // (own-key blocks as the two launches number them, a sequence's one after the other and all behind dQ's: 1 x 700 92, 3 x 1659 451)
-constexpr float DQ_BLOCK_US = 11.f, DQ_TILE_US = 1.95f, DQ_SPLIT_US = 4.f, DQ_PART_US = 0.05f;       // (SPLIT_COST of the dQ launch)
 constexpr int BOTH_ITEMS = 1024;        // most workgroups of a KV head that are played through
-static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, float kv_us, BwdPlan& best) {
+constexpr float ONE_SHORT = 0.4f;       // of the longest block: a block that long or shorter starts where it finds room
+// the one launch's weight, by the prefix blocks' share of its work (2400 problems, all in one launch: slower than in two by more
+// than 1.5 % where the share is up to 0.35 9 of 720, to 0.45 17 of 568, to 0.55 38 of 558, above 73 of 554)
+static float one_weight(float share) { return 0.88f + 0.17f * fminf(fmaxf((share - 0.25f) / 0.25f, 0.f), 1.f); }
+static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, BwdPlan& best) {
+    constexpr SplitCost us = SPLIT_COST[QUERY_DQ];
     const int most_parts = static_cast<int>(attn_query_parts(d, T));
     int tiles[BOTH_ITEMS];
     auto dq_items = [&](const QuerySplit& sp) { return attn_query_tiles(d, T, sp, tiles, BOTH_ITEMS); };
-    auto dq_extra = [&](const QuerySplit& sp) { return sp.n_blocks > 0 ? DQ_SPLIT_US + DQ_PART_US * static_cast<float>(sp.n_parts * d.Hkv) : 0.f; };
+    auto dq_extra = [&](const QuerySplit& sp) { return sp.n_blocks > 0 ? us.fix + us.wg * static_cast<float>(sp.n_parts * d.Hkv) : 0.f; };
+    auto dq_us = [&](int i) { return us.block + us.tile * static_cast<float>(tiles[i]); };
     int n_dq = dq_items(best.split);
     if (n_dq < 0 || best.split.e_full > 4 * M) return false;
-    float cu[KV_MAX_CUS];
-    float end = 0.f;
-    auto start = [&]() { for (int m = 0; m < M; ++m) cu[m] = 0.f; end = 0.f; };
-    auto run = [&](float t) { t = run_next(cu, M, t); end = t > end ? t : end; };
-    start();
-    for (int i = 0; i < n_dq; ++i) run(DQ_BLOCK_US + DQ_TILE_US * static_cast<float>(tiles[i]));
-    float best_t = end + dq_extra(best.split) + kv_us;
+    const long key_blocks = (d.P + KV_WG_KEYS - 1) / KV_WG_KEYS + static_cast<long>((d.S + KV_WG_KEYS - 1) / KV_WG_KEYS) * d.B;
+    if (key_blocks > BOTH_ITEMS) return false;
+    float best_t;                       // when the cheapest form so far ends
+    {
+        // (a tile's time, of its time when the chip is full)
+        auto light = [&](long blocks) {
+            return KV_LIGHT_US / KV_FULL_US + (1.f - KV_LIGHT_US / KV_FULL_US) * fminf(static_cast<float>(blocks) / static_cast<float>(M), 1.f);
+        };
+        Played dq(d.Hkv, M, false), kv(d.Hkv, M, false);
+        const float dq_tile = us.tile * light(n_dq);
+        for (int i = 0; i < n_dq; ++i) dq.run(us.block + dq_tile * static_cast<float>(tiles[i]));
+        KvTimes t = kv_times(d, best.kv);
+        const float kv_tile = KV_FULL_US * light(t.n_pre + t.n_own);
+        set_tiles(t, d, best.kv, kv_tile, kv_tile);
+        for (long j = 0; j < t.n_pre; ++j) kv.run(t.pre);
+        for (long j = 0; j < t.n_own; ++j) kv.run(t.own(static_cast<int>(j % t.nOb)));
+        best_t = dq.end + dq_extra(best.split) + kv.end + kv_parts_us(d, tokens, best.kv);
+    }
     bool one = false;
     const float stats_us = 4.f + static_cast<float>(tokens) * d.Hq * (2 * ROW_B) / 4.0e6f;
     for (int parts = 1; parts <= 6; ++parts) {
@@ -814,42 +864,49 @@ static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, 
         if (n_dq < 0) break;
         float dq_sum = 0.f, dq_most = 0.f;
         for (int i = 0; i < n_dq; ++i) {
-            const float t = DQ_BLOCK_US + DQ_TILE_US * static_cast<float>(tiles[i]);
-            dq_sum += t;
-            dq_most = t > dq_most ? t : dq_most;
+            dq_sum += dq_us(i);
+            dq_most = fmaxf(dq_most, dq_us(i));
         }
+        auto longest = [&](const KvTimes& t) { return fmaxf(dq_most, fmaxf(t.n_pre > 0 ? t.pre : 0.f, t.own(0))); };
         // of this split, the two cuts with the least bound
-        struct { KvPlan p; float bound, extra; } c[2] = {};
+        struct { KvPlan p; float bound, extra, weight; } c[2] = {};
         int n = 0;
         each_cut(d, tokens, M, [&](const KvPlan& p, long n_own, float parts_us) {
-            const KvTimes t = kv_times(d, p, M, true);
+            KvTimes t = kv_times(d, p);
+            set_tiles(t, d, p, KV_FULL_US, KV_FULL_US);
             if (t.n_pre + n_own > BOTH_ITEMS) return;
-            const float longest = fmaxf(dq_most, fmaxf(t.n_pre > 0 ? t.pre : 0.f, t.own(0)));
             const float extra = parts_us + dq_extra(sp) + stats_us;
-            const float bound = fmaxf(longest, (dq_sum + t.sum(d.B * p.head_parts)) / static_cast<float>(M)) + extra;
+            const float sum = dq_sum + t.sum(d.B * p.head_parts);
+            const float weight = one_weight(t.pre * static_cast<float>(t.n_pre) / sum);
+            const float bound = weight * (fmaxf(longest(t), sum / static_cast<float>(M)) + extra);
             if (bound >= best_t) return;
             const int at = n == 0 || bound < c[0].bound ? 0 : n == 1 || bound < c[1].bound ? 1 : 2;
             if (at == 0) c[1] = c[0];
-            if (at < 2) { c[at].p = p; c[at].bound = bound; c[at].extra = extra; }
+            if (at < 2) { c[at].p = p; c[at].bound = bound; c[at].extra = extra; c[at].weight = weight; }
             if (n < 2) ++n;
         });
         for (int i = 0; i < n; ++i) {
             if (c[i].bound >= best_t) continue;
-            const KvTimes t = kv_times(d, c[i].p, M, true);
+            KvTimes t = kv_times(d, c[i].p);
+            set_tiles(t, d, c[i].p, KV_FULL_US, KV_FULL_US);
             const long cols = static_cast<long>(d.B) * c[i].p.head_parts;
             int kb1 = 0;                                // own-key blocks 0 .. kb1 - 1 of each column go ahead of dQ
             while (kb1 < t.nOb && t.own(kb1) > dq_most) ++kb1;
-            start();
-            for (long j = 0; j < t.n_pre; ++j) run(t.pre);
-            for (int kb = 0; kb < t.nOb; ++kb) {
+            const float short_us = ONE_SHORT * longest(t);
+            long n_long = t.pre > short_us ? t.n_pre : 0;
+            for (int j = 0; j < n_dq; ++j) n_long += dq_us(j) > short_us;
+            for (int kb = 0; kb < t.nOb; ++kb) n_long += t.own(kb) > short_us ? cols : 0;
+            Played w(d.Hkv, M, n_long > M || d.Hkv % 8 != 0);
+            for (long j = 0; j < t.n_pre; ++j) w.run(t.pre);
+            for (int kb = 0; kb <= t.nOb; ++kb) {
                 if (kb == kb1)
-                    for (int j = 0; j < n_dq; ++j) run(DQ_BLOCK_US + DQ_TILE_US * static_cast<float>(tiles[j]));
-                for (long j = 0; j < cols; ++j) run(t.own(kb));
+                    for (int j = 0; j < n_dq; ++j) w.run(dq_us(j));
+                if (kb < t.nOb)
+                    for (long j = 0; j < cols; ++j) w.run(t.own(kb));
             }
-            if (kb1 == t.nOb)
-                for (int j = 0; j < n_dq; ++j) run(DQ_BLOCK_US + DQ_TILE_US * static_cast<float>(tiles[j]));
-            if (end + c[i].extra < best_t) {
-                best_t = end + c[i].extra;
+            const float one_t = c[i].weight * (w.end + c[i].extra);
+            if (one_t < best_t) {
+                best_t = one_t;
                 best.kv = c[i].p;
                 best.split = sp;
                 best.kv_front = static_cast<int>(t.n_pre + kb1 * cols);
@@ -870,10 +927,9 @@ const BwdPlan& plan_bwd(const cart_attn_desc& d, int T) {
         const long tokens = T > 0 ? T : static_cast<long>(d.B) * d.S;
         int M = k.cus / d.Hkv;
         M = M < 1 ? 1 : (M > KV_MAX_CUS ? KV_MAX_CUS : M);
-        float kv_us;
         attn_query_split(plan.split, d, T, QUERY_DQ);
-        plan.kv = search_plan(d, tokens, M, &kv_us);
-        plan.one_launch = plan_one_launch(d, T, tokens, M, kv_us, plan);
+        plan.kv = search_plan(d, tokens, M);
+        plan.one_launch = plan_one_launch(d, T, tokens, M, plan);
         key = k;
     }
     return plan;

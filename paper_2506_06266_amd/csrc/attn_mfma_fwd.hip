@@ -593,7 +593,6 @@ int launch_row_lo(const int32_t* cu, int B, int T, int32_t* row_lo, hipStream_t 
 // Only unmasked tiles are divided (see key_tiles): a part that ends in ten masked ones is no shorter for it (three packed
 // sequences of 700, 1 and 90 tokens, 32 / 8 heads, 300 slots: whole 40.6, 2 parts 49.7).
 constexpr int SPLIT_MIN_TILES = 4;      // (dQ: 1.95 (n - 1) > 4 + 2 x 0.05; the forward: 6)
-constexpr SplitCost SPLIT_COST[2] = {{9.2f, 1.21f, 3.5f, 0.7f, 0.045f}, {11.f, 1.95f, 4.f, 0.f, 0.05f}};
 
 // blocks per KV head the chip runs at one time
 static int query_slots(int Hkv) {

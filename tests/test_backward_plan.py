@@ -37,6 +37,13 @@ def test_two_launches_of_many_rounds(B, S, Hq, Hkv, P, T):
     assert not plan(B, S, Hq, Hkv, P, T).one_launch
 
 
+# blocks that just fill whole rounds, long prefix blocks much of the work: the last ones start a round late.  us a call in two
+# launches, in one: 185 -> 205, 402 -> 418, 420 -> 460, packed 378 -> 421
+@pytest.mark.parametrize("B,S,Hq,Hkv,P,T", [(13, 267, 8, 2, 2990, 0), (6, 639, 8, 2, 7952, 0), (7, 270, 32, 8, 3785, 0), (33, 261, 8, 2, 5179, 5547)])
+def test_two_launches_where_one_only_just_fits(B, S, Hq, Hkv, P, T):
+    assert not plan(B, S, Hq, Hkv, P, T).one_launch
+
+
 @pytest.mark.parametrize("seed", range(3))
 def test_cuts_of_one_launch(seed):
     rng = random.Random(seed)
