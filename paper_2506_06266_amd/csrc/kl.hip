@@ -144,8 +144,8 @@ template <bool LONG, typename T> __device__ __forceinline__ KlBuf kl_buf(const T
 }
 constexpr int KL_NT = 2;             // cache policy: non-temporal
 constexpr int KL_AHEAD = 4;          // turns ahead of its use that a vector which is not resident is requested
-constexpr int KL_FEW = 64;           // up to so many rows ...
-constexpr int KL_SHORT = 8;          // ... a remainder of up to so many turns is read one turn at a time
+// what of a row is not resident: nothing; read a turn at a time; KL_AHEAD turns ahead (see launch_rows)
+enum KlRemainder { KL_NONE, KL_BY_TURN, KL_TURNS_AHEAD };
 template <int AUX> __device__ __forceinline__ u32x4 kl_ld(const KlBuf& b, int off) {
     return __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(b.r, off, 0, AUX));
 }
@@ -170,10 +170,10 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
 // other row twice, element by element (rows x vocabulary):
 //   16384 x 128256 bf16  1649 -> 1593 (5.28 TB/s)     4096 x 32000 bf16  153 -> 100
 //    1024 x  50257 bf16   146 ->   47                16384 x  1000 fp32   54 ->  47
-//    2048 x 128256 fp32   785 ->  398 (10 more without the LDS part)
+//    2048 x 128256 fp32   785 ->  397 (10 more without the LDS part)
 // Some of the set-up's values live in scratch (up to 4 registers; 15 at 1024 threads, 26 with the LDS part): stored once,
 // loaded once a row between the sweeps.
-template <typename T, int THREADS, int NV, int NL, bool LONG = false>
+template <typename T, int THREADS, int NV, int NL, KlRemainder REM, bool LONG = false>
 __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const T* logits, const int32_t* idx,
                                                               const float* logp, T* dlogits, float* row_kl,
                                                               int N, int V, int K, float scale, int mode /* rest bucket | lead mask << 1 */) {
@@ -285,17 +285,10 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         KL_FORGET(x);
         float sum = s0 + s1;
         const KlBuf src = kl_buf<LONG>(logits, R), dst = kl_buf<LONG>(dlogits, R);
-        // What is not resident, each vector requested KL_AHEAD turns ahead of its use (past the row's end: zeros): one at a
-        // time, every turn was a round trip to memory with nothing else on the CU (us a call, 2048 rows of 128256 fp32 logits
-        // 418; 2 / 3 / 4 / 6 / 8 ahead 410 / 408 / 403 / 406 / 408; 1024 of 200000 bf16 165 -> 159).  A remainder of one turn
-        // has nothing to request ahead (1024 of 100003 fp32 147, with the loop 149), and with a row on few of the CUs memory
-        // answers sooner than the longer loop's code arrives (32 of 128256 fp32 23.5, one at a time 23.1; 150 of 100000 the
-        // same either way; 128 of 300000, 49 turns, 69 ahead and 81 one at a time).
+        // What is not resident; KL_TURNS_AHEAD: each vector requested KL_AHEAD turns ahead of its use (past the row's end:
+        // zeros).  One at a time, every turn is a round trip to memory with nothing else on the CU (us a call, 2048 rows of 128256
+        // fp32 logits 421, 2 / 3 / 4 / 6 / 8 ahead 410 / 408 / 403 / 406 / 408; 1024 of 200000 bf16 174, 4 ahead 167).
         constexpr int REST = (NV + NL) * THREADS;
-        // (only the last of a type's row lengths has a remainder at all)
-        constexpr bool MORE = LONG || (THREADS * NV == 1024 * 16 && (NL > 0 || sizeof(T) == 2));
-        const bool one_turn = R.nslot <= REST + THREADS;
-        const bool one_by_one = NL > 0 && N <= KL_FEW && R.nslot <= REST + KL_SHORT * THREADS;
         auto rest = [&](int v) __attribute__((always_inline)) {
             if constexpr (LONG) return reinterpret_cast<const u32x4*>(kl_slots(logits, R))[min(v, max(R.nslot - 1, 0))];
             else return kl_ld<0>(src, v * 16);
@@ -312,12 +305,9 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             kl_vec_sum<T>(s0, s1, w, c0);
             sum += s0 + s1;
         };
-        if (MORE && REST < R.nslot && one_turn) {
-            if (REST + tid < R.nslot) rest_sum(rest(REST + tid));
-        } else if (MORE && REST < R.nslot && one_by_one) {
-#pragma unroll 1
+        if constexpr (REM == KL_BY_TURN) {
             for (int v = REST + tid; v < R.nslot; v += THREADS) rest_sum(rest(v));
-        } else if (MORE && REST < R.nslot) {
+        } else if constexpr (REM == KL_TURNS_AHEAD) {
             u32x4 w[KL_AHEAD];
 #pragma unroll
             for (int i = 0; i < KL_AHEAD; ++i) w[i] = rest(REST + i * THREADS + tid);
@@ -365,6 +355,11 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
             elem<T>::store(dlogits + R.row + logit_single<T>(R, tid), g.c * fast_exp2(fmaf(xs, CART_LOG2E, -lse2)));
         xs = -3.0e38f;
         if (more && tid < Rn.head + Rn.tail) xs = elem<T>::load(logits + Rn.row + logit_single<T>(Rn, tid));
+        // (the last read of these vectors, as the stores next to it: 512 rows of 300000 fp32 288 -> 265, 1024 of 200000 347 -> 328)
+        auto rest_nt = [&](int v) __attribute__((always_inline)) {
+            if constexpr (LONG) return rest(v);
+            else return kl_ld<KL_NT>(src, v * 16);
+        };
         auto rest_grad = [&](int v, const u32x4& w) __attribute__((always_inline)) {
             if constexpr (LONG) {
                 if (v < R.nslot) reinterpret_cast<u32x4*>(const_cast<T*>(kl_slots(dlogits, R)))[v] = kl_vec_grad<T>(w, g);
@@ -372,22 +367,19 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
                 kl_st(dst, kl_vec_grad<T>(w, g), v * 16);
             }
         };
-        if (MORE && REST < R.nslot && one_turn) {
-            rest_grad(REST + tid, rest(REST + tid));
-        } else if (MORE && REST < R.nslot && one_by_one) {
-#pragma unroll 1
-            for (int v = REST + tid; v < R.nslot; v += THREADS) rest_grad(v, rest(v));
-        } else if (MORE && REST < R.nslot) {
+        if constexpr (REM == KL_BY_TURN) {
+            for (int v = REST + tid; v < R.nslot; v += THREADS) rest_grad(v, kl_ld<KL_NT>(src, v * 16));
+        } else if constexpr (REM == KL_TURNS_AHEAD) {
             u32x4 w[KL_AHEAD];
 #pragma unroll
-            for (int i = 0; i < KL_AHEAD; ++i) w[i] = rest(REST + i * THREADS + tid);
+            for (int i = 0; i < KL_AHEAD; ++i) w[i] = rest_nt(REST + i * THREADS + tid);
             for (int v0 = REST; v0 < R.nslot; v0 += KL_AHEAD * THREADS) {
 #pragma unroll
                 for (int i = 0; i < KL_AHEAD; ++i) {
                     if (i > 0 && v0 + i * THREADS >= R.nslot) break;
                     const int v = v0 + i * THREADS + tid;
                     const u32x4 wi = w[i];
-                    w[i] = rest(v + KL_AHEAD * THREADS);
+                    w[i] = rest_nt(v + KL_AHEAD * THREADS);
                     rest_grad(v, wi);
                 }
             }
@@ -466,15 +458,27 @@ __global__ __launch_bounds__(1024) void kl_reduce_rows(const float* row_kl, int 
     }
 }
 
-template <typename T, int THREADS, int NV, int NL, bool LONG = false>
+template <typename T, int THREADS, int NV, int NL, KlRemainder REM = KL_NONE, bool LONG = false>
 static void resident(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
                      float* rows, hipStream_t st) {
     const int slots = device_cus() * ((NV > 4 ? 1024 : 2048) / THREADS);      // workgroups the chip keeps resident
     const int spare = (NV + NL) * THREADS - d.V / LogitVec<T>::N;
     const int lead_mask = spare < 0 || spare >= 7 ? 7 : spare >= 3 ? 3 : spare >= 1 ? 1 : 0;
-    hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL, LONG>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
+    hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL, REM, LONG>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
                        dim3(THREADS), kl_record_bytes(d.K), st, static_cast<const T*>(logits), idx, logp,
                        static_cast<T*>(d_logits), rows, d.N, d.V, d.K, d.scale, (d.mode == CART_KL_REST ? 1 : 0) | lead_mask << 1);
+}
+// Whether a remainder of `rest` vectors is requested ahead.  Up to two turns there is nothing to request ahead; and with rows on
+// less than half of the CUs memory answers a turn sooner than the longer loop's code arrives, until the turns are many.
+// fp32, us a call one at a time / ahead:  rows        32             65             128            256            1024
+//   103122, 2 turns                              23.4 / 24.0    25.7 / 26.2    31.6 / 32.1    48.0 / 48.4    156.6 / 156.8
+//   110000, 3                                    24.5 / 24.7    26.7 / 26.8    33.3 / 32.6    52.3 / 50.6    171.0 / 168.4
+//   128256, 8                                    26.9 / 27.4    29.2 / 29.6    36.9 / 36.2    56.0 / 56.3    206.4 / 196.7
+//   200000, 25 (64 rows)                                        43.1 / 40.9    55.1 / 51.8    86.7 / 85.8    370.2 / 349.6
+// (bf16 alike: 145000, 2 turns, 1024 rows 128.1 / 128.5; 160000, 4 turns 140.4 / 138.5; 64 rows 28.2 / 27.8)
+static bool kl_ahead(long rest, int rows) {
+    const long turns = (rest + 1023) / 1024;
+    return turns > 2 && (2L * rows >= device_cus() || turns > 12);
 }
 template <typename T, int NL>
 static void launch_rows(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
@@ -485,8 +489,9 @@ static void launch_rows(const cart_kl_desc& d, const void* logits, const int32_t
     else if (nvec <= 256 * 16) resident<T, 256, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec <= 512 * 16) resident<T, 512, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec <= 1024 * 16) resident<T, 1024, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
-    else if (nvec < 1L << 26) resident<T, 1024, 16, NL>(d, logits, idx, logp, d_logits, rows, st);
-    else resident<T, 1024, 16, NL, true>(d, logits, idx, logp, d_logits, rows, st);
+    else if (nvec >= 1L << 26) resident<T, 1024, 16, NL, KL_TURNS_AHEAD, true>(d, logits, idx, logp, d_logits, rows, st);
+    else if (kl_ahead(nvec - 1024 * (16 + NL), d.N)) resident<T, 1024, 16, NL, KL_TURNS_AHEAD>(d, logits, idx, logp, d_logits, rows, st);
+    else resident<T, 1024, 16, NL, KL_BY_TURN>(d, logits, idx, logp, d_logits, rows, st);
 }
 
 int launch_kl(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp,

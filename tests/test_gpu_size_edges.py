@@ -257,11 +257,13 @@ LOSS_CASES = [
     # (slots counted from a 128-byte line, up to seven more than vectors: the fullest rows of each width)
     (torch.bfloat16, 9, 4047, 20), (torch.bfloat16, 9, 4049, 20), (torch.bfloat16, 9, 32719, 20), (torch.bfloat16, 9, 65487, 20),
     (torch.bfloat16, 9, 131023, 20), (torch.float32, 33, 2023, 20), (torch.float32, 33, 16359, 20), (torch.float32, 9, 98279, 20),
-    # what is not resident: one turn, just more, more turns than are requested ahead, several rows a workgroup; few rows
-    # (fp32) up to eight turns, and more of either
+    # what is not resident: one turn, just more, more turns than are requested ahead, several rows a workgroup
     (torch.float32, 3, 102400, 20), (torch.float32, 3, 102407, 20), (torch.float32, 65, 102407, 5), (torch.float32, 3, 131072, 20),
     (torch.float32, 300, 114697, 5), (torch.float32, 2, 135165, 20),
     (torch.bfloat16, 3, 163851, 20), (torch.bfloat16, 270, 172032, 5),
+    # a turn at a time or ahead: rows on half of the CUs from three turns on, on fewer from thirteen
+    (torch.float32, 128, 106496, 5), (torch.float32, 128, 106499, 5), (torch.float32, 127, 106499, 5), (torch.float32, 3, 147459, 20),
+    (torch.bfloat16, 128, 147463, 5), (torch.bfloat16, 2, 229376, 20), (torch.bfloat16, 2, 229385, 20),
 ]
 
 
