@@ -321,6 +321,8 @@ def main() -> int:
     # recomputing S, then dP, dV, dQ, dK), whatever they recompute between them, so `achieved`
     # prices the call: algorithmic flops of the backward / time of its kernels.  What the dominant
     # kernel itself executes per second is reported beside it.
+    # (this shape runs many rounds of workgroups, which the library launches as dQ, then dK + dV: tests/test_backward_plan.py
+    # holds it to that; a small one runs the row statistics, then all three gradients, and would need other labels)
     units = {"dq": 3, "dkv": 4}                  # contractions each kernel performs per pair
     dom = max(units, key=lambda n: k_ms[n])
     bwd_kernel_ms = sum(k_ms.values())

@@ -298,11 +298,16 @@ cart_status cart_attn_varlen_bwd(const cart_attn_varlen_desc *desc, const void *
  * cart_trace_events -- optional per-kernel timing hook for benchmarks (not part of the paper).
  * `events` is a host array of `count` hipEvent_t handles (passed as void*), or NULL to switch
  * the hook off.  While set, every later cart_attn_fwd / cart_attn_bwd (also the packed
- * variants) / cart_distill_kl_fwd_bwd / cart_decode call records events[0] on its stream before
+ * variants) / cart_distill_kl_fwd_bwd / cart_teacher_topk / cart_decode call records events[0] on its stream before
  * its first kernel and events[i] after its i-th kernel (as many as `count` allows).  Kernel
  * order, bf16 / head_dim 128: attention forward = forward, finish (combines the
- * parts of split blocks; no kernel, only its event, when none is split); backward = dQ (which also forms the row statistics),
- * dK + dV (one kernel), the sums of the partials; loss = row kernel, scalar reduction; decode = prefix + own-KV (one launch), merge.  The array must stay valid while the
+ * parts of split blocks; no kernel, only its event, when none is split); backward, by the problem's size
+ * (nothing tells the caller which) = dQ (which also forms the row statistics), dK + dV (one kernel) -- problems
+ * of many rounds of workgroups --, or the row statistics, then dQ, dK and dV (one kernel); then, either way,
+ * the sums of the partials.  Other types and head_dims: forward = one kernel; backward = dQ, dK + dV, or from
+ * head_dim 128 down all three in one kernel and an event without a kernel; then the sums of split prefix
+ * gradients, where there are any.  Loss = row kernel, scalar reduction; top-k = one kernel; decode = prefix + own-KV
+ * (one launch), merge.  The array must stay valid while the
  * hook is set.  Process-global, not thread-safe; the caller owns the events and reads them after
  * synchronising the stream.
  */

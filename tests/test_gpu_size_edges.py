@@ -6,6 +6,7 @@ import torch
 
 from oracle import cartridge_oracle as orc
 from paper_2506_06266_amd import binding as cb
+from paper_2506_06266_amd import synth
 
 pytestmark = pytest.mark.gpu
 
@@ -477,3 +478,25 @@ def test_attention_vector_of_millions_of_workgroups():
         ref = [*orc.attn_fwd(*n[:5]), *orc.attn_bwd(*n)[:3]]
         for x, r in zip([outs[0][b:b + 1], lse[b:b + 1]] + [t[b:b + 1] for t in outs[1:]], ref):
             assert rel_err(x, r) <= TOL[torch.float32]
+
+
+# Events of a backward call, in either form the planner takes and of the fp32 kernels: what stands in front of the
+# gradients' sums is dQ, dK + dV, or the row statistics, all three gradients, or all three and nothing.
+@pytest.mark.parametrize("cfg,first_share", [((1, 128, 32, 8, 128, 1024, "bf16"), (0.0, 0.6)), ((7, 270, 32, 8, 128, 3785, "bf16"), (0.15, 0.8)),
+                                             ((2, 128, 8, 2, 64, 256, "f32"), (0.5, 1.0))], ids=["one", "two", "f32"])
+def test_events_of_a_backward_call(cfg, first_share):
+    B, S, Hq, Hkv, D, P, dt = cfg
+    t = synth.attn_inputs(synth.AttnConfig("", 5, B, S, Hq, Hkv, D, P, dt, 1.0, 1.0, 0.1), DEV)
+    a = (t["q"], t["k_own"], t["v_own"], t["z_k"], t["z_v"])
+    o, lse = cb.cart_attn_fwd(*a)
+    tr = cb.KernelTrace(4)
+    shares = []
+    for _ in range(6):
+        with tr:
+            cb.cart_attn_bwd(*a, o, lse, t["d_o"])
+        torch.cuda.synchronize()
+        x, y, z = tr.intervals_ms()
+        assert min(x, y, z) >= 0.0
+        shares.append(x / (x + y))
+    tr.close()
+    assert first_share[0] <= sorted(shares)[3] <= first_share[1], shares
