@@ -1,7 +1,8 @@
 """Builds libcartridge.so (hand-written HIP for gfx950) in-tree with hipcc, and the binding's native half with g++.
 
 `python -m paper_2506_06266_amd.build` compiles every csrc/*.hip to an object file and links
-them, and csrc/pycall.cpp; they are rebuilt only when a source or header is newer unless force=True.
+them, and csrc/pycall.cpp; they are rebuilt only when a source or header is newer unless force=True, the native half also
+when another interpreter, PyTorch or command would build it.
 """
 from __future__ import annotations
 
@@ -16,7 +17,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 ROOT = os.path.dirname(HERE)
 LIB = os.environ.get("CART_LIB_OUT", os.path.join(HERE, "libcartridge.so"))
-PYCALL = os.path.join(HERE, "_pycall.so")
+PYCALL = os.path.join(os.path.dirname(os.path.abspath(LIB)), "_pycall.so")
 OBJ_DIR = os.environ.get("CART_OBJ_DIR", os.path.join(HERE, "_build"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -51,19 +52,26 @@ def _compile(src: str, force: bool) -> str:
 
 def _compile_pycall(force: bool) -> str:
     """csrc/pycall.cpp against the installed PyTorch (paths only: nothing of it is initialised here)."""
-    src = os.path.join(CSRC, "pycall.cpp")
-    if not force and os.path.exists(PYCALL) and os.path.getmtime(PYCALL) > max(os.path.getmtime(src), _newest_header()):
-        return PYCALL
     import torch
+    src = os.path.join(CSRC, "pycall.cpp")
     at = os.path.dirname(os.path.abspath(torch.__file__))
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-w",
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
            "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI),
-           "-I", os.path.join(at, "include"), "-I", os.path.join(at, "include", "torch", "csrc", "api", "include"),
-           "-I", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), src, "-o", PYCALL,
+           "-isystem", os.path.join(at, "include"), "-isystem", os.path.join(at, "include", "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-I", os.path.join(ROOT, "include"), src, "-o", PYCALL,
            "-L", os.path.join(at, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    # what the module's ABI hangs on, beside the objects: the module is loaded whatever it was built for
+    stamp, built_for = os.path.join(OBJ_DIR, "_pycall.stamp"), " ".join([torch.__version__, sysconfig.get_config_var("SOABI") or "", *cmd])
+    if (not force and os.path.exists(PYCALL) and os.path.exists(stamp) and open(stamp).read() == built_for
+            and os.path.getmtime(PYCALL) > max(os.path.getmtime(src), _newest_header())):
+        return PYCALL
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
         raise RuntimeError("g++ failed for %s:\n%s\n%s" % (src, r.stdout, r.stderr))
+    if r.stderr.strip():
+        sys.stderr.write(r.stderr)
+    with open(stamp, "w") as f:
+        f.write(built_for)
     return PYCALL
 
 
