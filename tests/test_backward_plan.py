@@ -57,7 +57,7 @@ def test_cuts_of_one_launch(seed):
         blocks = -(-(-(-(T if T and P else S) // 64) * G) // 4) * (1 if T and P else B)
         assert p.e_full + p.n_blocks == blocks
         assert p.n_parts <= max(1, CUS // Hkv) and G % p.head_parts == 0
-        assert p.n_part == (-(-tokens // p.chunk) if P else p.n_part) and p.chunk % 64 == 0
+        assert p.n_part == -(-tokens // p.chunk) and p.chunk % 64 == 0 and (P or p.n_part == 1)
         # every part of every split block once, in order
         seen = [(w & 255, (w >> 8) & 255, w >> 16) for w in p.part[:p.n_parts]]
         assert seen == [(b, i, n) for b, n in sorted({(b, n) for b, _, n in seen}) for i in range(n)]
@@ -65,3 +65,33 @@ def test_cuts_of_one_launch(seed):
         if p.one_launch:
             pre, per_kb = -(-P // 128) * p.n_part if P else 0, B * p.head_parts
             assert (p.kv_front - pre) % per_kb == 0 and 0 <= (p.kv_front - pre) // per_kb <= -(-S // 128)
+
+
+def _up(n):
+    return (n + 255) // 256 * 256
+
+
+# What a call lays out one behind the other -- the row statistics, the partials of dZ, of split query blocks, of own keys,
+# the packed rows' first rows -- ends inside what the query returns: an overrun would be a write no check sees.
+@pytest.mark.parametrize("seed", range(4))
+def test_every_plan_fits_the_workspace(seed):
+    lib, rng = cb.load(), random.Random(100 + seed)
+    log = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    forms = [0, 0]
+    for _ in range(600):
+        Hq, Hkv = rng.choice([(32, 8), (24, 8), (8, 2), (4, 1), (16, 16), (7, 1), (64, 8), (48, 4), (6, 3)])
+        B, S, P = log(1, 64), log(1, 4096), rng.choice([0, log(1, 16384)])
+        T = rng.choice([0, rng.randint(S, B * S)])
+        p = plan(B, S, Hq, Hkv, P, T)
+        forms[p.one_launch] += 1
+        tokens = T or B * S
+        laid = (2 * _up(4 * tokens * Hq) + 2 * _up(p.n_part * Hkv * P * 128 * 4) + p.n_parts * Hkv * 256 * 128 * 4 +
+                (2 * _up(p.head_parts * tokens * Hkv * 128 * 4) if p.head_parts > 1 else 0) + (_up(4 * T) if T and P else 0))
+        if T:
+            d = cb.AttnVarlenDesc(T, B, S, Hq, Hkv, 128, P, cb.CART_BF16, 0.0, 0, 0)
+            most = lib.cart_attn_varlen_bwd_workspace(C.byref(d))
+        else:
+            d = cb.AttnDesc(B, S, Hq, Hkv, 128, P, cb.CART_BF16, 0.0, 0, 0, cb.IMPL_AUTO)
+            most = lib.cart_attn_bwd_workspace(C.byref(d))
+        assert laid <= most, (B, S, Hq, Hkv, P, T, laid, most)
+    assert min(forms) > 50          # (both forms were looked at)

@@ -59,6 +59,33 @@ def test_attention_workspace_never_grows_towards_smaller_problems(lib, seed):
             _covers(_packed(lib, T, B, S, Hq, Hkv, P), _packed(lib, T2, B2, S2, Hq, Hkv, P2), (T, B, S, Hq, Hkv, P, T2, B2, S2, P2))
 
 
+# (fp32, and bf16 at other head_dims: delta, and the sums of prefix blocks split over the token rows)
+@pytest.mark.parametrize("dtype", [cb.CART_F32, cb.CART_BF16])
+def test_vector_workspace_never_grows_towards_smaller_problems(lib, dtype):
+    rng = random.Random(11 + dtype)
+
+    def need(B, S, Hq, Hkv, D, P):
+        d = cb.AttnDesc(B, S, Hq, Hkv, D, P, dtype, 0.0, 0, 0, cb.IMPL_VECTOR)
+        return lib.cart_attn_fwd_workspace(C.byref(d)), lib.cart_attn_bwd_workspace(C.byref(d))
+
+    for _ in range(1500):
+        Hq, Hkv = rng.choice(HEADS + [(2, 1), (28, 4)])
+        big = (_log(rng, 1, 64), _log(rng, 1, 2048), Hq, Hkv, _log(rng, 1, 256), rng.choice([0, _log(rng, 1, 8192)]))
+        small = [rng.choice([x, rng.randint(min(x, 1), x)]) for x in big]
+        small[2:4] = Hq, Hkv
+        _covers(need(*big), need(*small), (big, small))
+
+
+# (every split the rule may take: 2 sums of one part, at most eight parts and as many prefix blocks as CUs)
+@pytest.mark.parametrize("B,S,Hq,Hkv,D,P", [(4, 128, 8, 2, 128, 128), (2, 64, 4, 2, 200, 64), (1, 32, 2, 1, 64, 16), (4, 256, 8, 2, 64, 4096)])
+def test_vector_workspace_holds_the_split_sums(lib, B, S, Hq, Hkv, D, P):
+    d = cb.AttnDesc(B, S, Hq, Hkv, D, P, cb.CART_F32, 0.0, 0, 0, cb.IMPL_AUTO)
+    delta = (4 * B * Hq * S + 255) // 256 * 256
+    blocks = -(-P // 16) * Hkv
+    parts = max(s for s in range(1, 9) if s == 1 or blocks * s <= 256)        # (256 CUs are assumed where there is no GPU)
+    assert lib.cart_attn_bwd_workspace(C.byref(d)) >= delta + (parts * 2 * Hkv * P * D * 4 if parts > 1 else 0)
+
+
 # (the partials of a problem and those of a smaller one: as long as neither exceeds the static array)
 @pytest.mark.parametrize("seed", range(4))
 def test_decode_workspace_never_grows_towards_smaller_problems(lib, seed):
