@@ -148,11 +148,12 @@ template <int NB> __device__ __forceinline__ void to_lds(float* dst, const f32x4
     for (int db = 0; db < NB; ++db) *reinterpret_cast<f32x4*>(dst + c * (16 * NB + 4) + 16 * db + 4 * g) = acc[db];
 }
 
-// Head_dim 65 to 128: one wavefront per SIMD, which requests each operand's next block as soon as its products are out
-// (us, 4 x 256 tokens, 8 / 2 heads of 128, 256 slots: forward 37.6 -> 34.6, backward 319 -> 290).  Two wavefronts on a
-// SIMD cover each other (head_dim up to 64: backward 22.7 -> 25.3 at 2 x 64 tokens, 64 slots), and above 128 there are
-// no registers for it (forward 14.0 -> 14.6, 2 x 64 tokens, 4 / 2 heads of 200).
-template <int NB> constexpr bool VEC_AHEAD = NB == 8;
+// Head_dim 128: one wavefront per SIMD, which requests each operand's next block as soon as its products are out (AHEAD; us, 4 x 256
+// tokens, 8 / 2 heads, 256 slots: forward 37.6 -> 34.6, backward 319 -> 290).  Two wavefronts on a SIMD cover each
+// other (head_dim up to 64: backward 22.7 -> 25.3 at 2 x 64 tokens, 64 slots); below 128 the loads are under conditions and each
+// request is waited for at its end (forward, head_dim 96: 7 x 36 tokens, 32 / 8 heads 11.0 -> 12.1, 120 problems of 256 blocks or more
+// 1.5 % slower on average); above 128 there are no registers for it (forward 14.0 -> 14.6, 2 x 64 tokens, 4 / 2 heads of 200).
+template <int NB> constexpr bool VEC_AHEAD = NB == 8;       // .. in which register layout
 
 // key / value row j of the concatenated cache [prefix ; own] for (sequence b, KV head hk)
 template <typename T>
@@ -162,7 +163,7 @@ __device__ __forceinline__ const T* cache_row(const T* z, const T* own, int j, i
                  : own + ((static_cast<size_t>(b) * S + (j - P)) * Hkv + hk) * D;
 }
 
-template <typename T, int NB, int NW>
+template <typename T, int NB, int NW, bool AHEAD>
 __global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, const T* __restrict__ zk,
     const T* __restrict__ zv, T* __restrict__ o, float* __restrict__ lse, int B, int S, int Hq, int Hkv, int D, int P, float scale) {
@@ -193,10 +194,10 @@ __global__ __launch_bounds__(64 * NW) void attn_fwd_vector(
     };
     RowFrag<NB> kf;
     ColFrag<NB> vc;
-    if (VEC_AHEAD<NB>) { kf = load_k(16 * wv); vc = load_v(16 * wv); }
+    if (AHEAD) { kf = load_k(16 * wv); vc = load_v(16 * wv); }
     for (int j0 = 16 * wv; j0 < nk; j0 += 16 * NW) {
-        const bool more = VEC_AHEAD<NB> && j0 + 16 * NW < nk;
-        if (!VEC_AHEAD<NB>) { kf = load_k(j0); vc = load_v(j0); }
+        const bool more = AHEAD && j0 + 16 * NW < nk;
+        if (!AHEAD) { kf = load_k(j0); vc = load_v(j0); }
         f32x4 s = contract(kf, qf);
         if (more) kf = load_k(j0 + 16 * NW);
         float tm = VEC_HIDDEN;
@@ -277,8 +278,8 @@ __device__ __forceinline__ float row_delta(const RowFrag<NB>& of, const RowFrag<
     return col_sum(dl);
 }
 
-// dQ of 16 queries of one head; with WRITE_DELTA also delta[b,h,i] for the dK / dV launch that follows
-template <typename T, int NB, int NW, bool WRITE_DELTA>
+// dQ of 16 queries of one head.  ONE: in one launch with dK and dV; else also delta[b,h,i], for the dK / dV launch that follows.
+template <typename T, int NB, int NW, bool ONE, bool AHEAD>
 __device__ __forceinline__ void dq_block(const VecBwd<T>& a, int id, float (*sm_o)[VEC_TURN<NB>]) {
     constexpr int PITCH = 16 * NB + 4;
     const int B = a.B, S = a.S, Hq = a.Hq, Hkv = a.Hkv, D = a.D, P = a.P;
@@ -307,23 +308,23 @@ __device__ __forceinline__ void dq_block(const VecBwd<T>& a, int id, float (*sm_
     };
     const RowFrag<NB> qf = row_frag<T, NB>(a.q + row, D, g), gf = row_frag<T, NB>(a.d_o + row, D, g);
     const float c2 = a.scale * CART_LOG2E, l2 = a.lse[st] * CART_LOG2E;
-    // (the first keys are requested ahead of delta's wait for O and dO; head_dim above 128 has no registers for it)
+    // (the one launch's first keys are requested ahead of delta's wait for O and dO)
     float dl;
     {
         const RowFrag<NB> of = row_frag<T, NB>(a.o + row, D, g);
-        if constexpr (NB <= 8) {
+        if constexpr (ONE) {
             load_rows(16 * wv);
             load_cols(16 * wv);
             __builtin_amdgcn_sched_barrier(0);
         }
         dl = row_delta(of, gf);
     }
-    if (WRITE_DELTA && wv == 0 && g == 0 && i0 + c < S) a.delta[st] = dl;
+    if (!ONE && wv == 0 && g == 0 && i0 + c < S) a.delta[st] = dl;
     f32x4 acc[NB];
     clear(acc);
     for (int j0 = 16 * wv; j0 < nk; j0 += 16 * NW) {
-        const bool more = VEC_AHEAD<NB> && j0 + 16 * NW < nk;
-        if (NB > 8 || (!VEC_AHEAD<NB> && j0 != 16 * wv)) { load_rows(j0); load_cols(j0); }
+        const bool more = AHEAD && j0 + 16 * NW < nk;
+        if (!ONE || (!AHEAD && j0 != 16 * wv)) { load_rows(j0); load_cols(j0); }
         const f32x4 s = contract(kf, qf), dp = contract(vf, gf);
         if (more) load_rows(j0 + 16 * NW);
         f32x4 ds;
@@ -354,8 +355,8 @@ __device__ __forceinline__ void dq_block(const VecBwd<T>& a, int id, float (*sm_
 
 // dK, dV of 16 keys: prefix slots (summed over every sequence, every query head of the group, every
 // token) or own keys of one sequence (the group's heads, tokens from the block's first key on).
-// OWN_DELTA: the rows' delta is formed here from O and dO (the same sum in the same order), not read.
-template <typename T, int NB, int NW, bool OWN_DELTA>
+// ONE: in one launch with dQ, the rows' delta is formed here from O and dO (the same sum in the same order), not read.
+template <typename T, int NB, int NW, bool ONE, bool AHEAD>
 __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm_k)[VEC_TURN<NB>], float (*sm_v)[VEC_TURN<NB>]) {
     constexpr int PITCH = 16 * NB + 4;
     const int B = a.B, S = a.S, Hq = a.Hq, Hkv = a.Hkv, D = a.D, P = a.P;
@@ -396,12 +397,12 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
         const size_t rc = tok(x, x.i0 + c);
         qf = row_frag<T, NB>(a.q + rc, D, g);
         gf = row_frag<T, NB>(a.d_o + rc, D, g);
-        if constexpr (OWN_DELTA) of = row_frag<T, NB>(a.o + rc, D, g);
+        if constexpr (ONE) of = row_frag<T, NB>(a.o + rc, D, g);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const size_t st = (static_cast<size_t>(x.b) * Hq + x.h) * S + min(x.i0 + 4 * g + r, S - 1);
             l2[r] = a.lse[st] * CART_LOG2E;
-            if (!OWN_DELTA) dl[r] = a.delta[st];
+            if (!ONE) dl[r] = a.delta[st];
         }
     };
     auto load_cols = [&](const Block& x, ColFrag<NB>& f, const T* src) __attribute__((always_inline)) {
@@ -410,8 +411,9 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
         for (int r = 0; r < 4; ++r) pr[r] = src + tok(x, x.i0 + 4 * g + r);
         f = col_frag<T, NB>(pr, D, c);
     };
+    constexpr bool COLS_FIRST = !ONE && NB <= 8;
     Block cur = block(min(first + wv, n - 1));
-    if constexpr (VEC_AHEAD<NB>) {
+    if constexpr (AHEAD) {
         load_rows(cur);
         load_cols(cur, gc, a.d_o);
         load_cols(cur, qc, a.q);
@@ -421,9 +423,10 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
         // not requested ahead come behind the scores: head_dim above 128 has no registers for all four operands of a block --
         // 52 registers of fp32 problems, 128 of bf16 ones, spill as it is -- and two wavefronts on a SIMD are faster so:
         // backward 148 -> 135 us at 4 x 256 tokens, 8 / 2 heads of 64, 256 slots)
-        const Block nx = block(VEC_AHEAD<NB> ? min(t + NW, n - 1) : t);
-        if constexpr (!VEC_AHEAD<NB>) { cur = nx; load_rows(cur); }
-        if constexpr (OWN_DELTA) {
+        const Block nx = block(AHEAD ? min(t + NW, n - 1) : t);
+        if constexpr (!AHEAD) { cur = nx; load_rows(cur); }
+        if constexpr (COLS_FIRST) { load_cols(cur, gc, a.d_o); load_cols(cur, qc, a.q); }
+        if constexpr (ONE) {
             const float rd = row_delta(of, gf);      // of row i0 + c
 #pragma unroll
             for (int r = 0; r < 4; ++r) dl[r] = __shfl(rd, 4 * g + r, CART_WAVE);
@@ -439,20 +442,20 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
             p[r] = seen ? fast_exp2(fmaf(s[r], c2, -l2[r])) : 0.f;
             ds[r] = seen ? p[r] * (dp[r] - dl[r]) : 0.f;
         }
-        if constexpr (VEC_AHEAD<NB>) load_rows(nx);
+        if constexpr (AHEAD) load_rows(nx);
         const bool hidden = cur.i0 + 16 > S || (!prefix && cur.i0 == key0);
-        if constexpr (!VEC_AHEAD<NB>) {
+        if constexpr (!AHEAD && !COLS_FIRST) {
             asm volatile("" ::: "memory");
             load_cols(cur, gc, a.d_o);
         }
         accumulate_visible(av, gc, p, vis, hidden, c, g);
-        if constexpr (VEC_AHEAD<NB>) load_cols(nx, gc, a.d_o);
-        if constexpr (!VEC_AHEAD<NB>) {
+        if constexpr (AHEAD) load_cols(nx, gc, a.d_o);
+        if constexpr (!AHEAD && !COLS_FIRST) {
             asm volatile("" ::: "memory");
             load_cols(cur, qc, a.q);
         }
         accumulate_visible(ak, qc, ds, vis, hidden, c, g);
-        if constexpr (VEC_AHEAD<NB>) load_cols(nx, qc, a.q);
+        if constexpr (AHEAD) load_cols(nx, qc, a.q);
         cur = nx;
     }
     to_lds(sm_k[wv], ak, c, g);
@@ -490,12 +493,12 @@ __device__ __forceinline__ void dkv_block(const VecBwd<T>& a, int id, float (*sm
 template <typename T, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dq_vector(VecBwd<T> a) {
     __shared__ float sm[NW][VEC_TURN<NB>];
-    dq_block<T, NB, NW, true>(a, workgroup_id(), sm);
+    dq_block<T, NB, NW, false, false>(a, workgroup_id(), sm);
 }
 template <typename T, int NB, int NW>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_dkv_vector(VecBwd<T> a) {
     __shared__ float sm[2][NW][VEC_TURN<NB>];
-    dkv_block<T, NB, NW, false>(a, workgroup_id(), sm[0], sm[1]);
+    dkv_block<T, NB, NW, false, false>(a, workgroup_id(), sm[0], sm[1]);
 }
 // dZ from the sums of split prefix blocks, in the splits' order
 __global__ __launch_bounds__(256) void attn_bwd_dz_vector(const float* __restrict__ part, float* __restrict__ dzk, float* __restrict__ dzv,
@@ -516,12 +519,12 @@ __global__ __launch_bounds__(256) void attn_bwd_dz_vector(const float* __restric
     dzv[i] = gv;
 }
 // Both in one launch, the dK / dV blocks (the longer ones) first
-template <typename T, int NB, int NW>
+template <typename T, int NB, int NW, bool AHEAD>
 __global__ __launch_bounds__(64 * NW) void attn_bwd_vector(VecBwd<T> a, int n_kv) {
     __shared__ float sm[2][NW][VEC_TURN<NB>];
     const int id = workgroup_id();
-    if (id < n_kv) dkv_block<T, NB, NW, true>(a, id, sm[0], sm[1]);
-    else           dq_block<T, NB, NW, false>(a, id - n_kv, sm[0]);
+    if (id < n_kv) dkv_block<T, NB, NW, true, AHEAD>(a, id, sm[0], sm[1]);
+    else           dq_block<T, NB, NW, true, AHEAD>(a, id - n_kv, sm[0]);
 }
 
 // ---- decode: one wavefront per output row; lane l owns head elements l, l+64, ... ---------------
@@ -601,7 +604,8 @@ template <typename T>
 static void fwd_t(const cart_attn_desc& d, float scale, const void* q, const void* k, const void* v,
                   const void* zk, const void* zv, void* o, float* lse, hipStream_t st) {
     const long wgs = static_cast<long>((d.S + 15) / 16) * d.Hq * d.B;
-    CART_DISPATCH_NB(d.D, hipLaunchKernelGGL((attn_fwd_vector<T, NB, NW>), grid_of(wgs), dim3(64 * NW), 0, st, (const T*)q,
+    const bool ahead = d.D == 128;
+    CART_DISPATCH_NB(d.D, hipLaunchKernelGGL((ahead ? attn_fwd_vector<T, NB, NW, VEC_AHEAD<NB>> : attn_fwd_vector<T, NB, NW, false>), grid_of(wgs), dim3(64 * NW), 0, st, (const T*)q,
         (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (T*)o, lse, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale));
 }
 
@@ -653,6 +657,7 @@ static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const voi
     const long nSt = (d.S + 15) / 16, nPt = (d.P + 15) / 16;
     const int splits = dz_splits(d, d.D <= 64 ? 8 : 4);
     const long n_q = nSt * d.Hq * d.B, n_kv = (nPt * splits + nSt * d.B) * d.Hkv;
+    const bool ahead = d.D == 128;
     float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + ((static_cast<size_t>(d.B) * d.Hq * d.S * sizeof(float) + 255) & ~static_cast<size_t>(255)));
     const VecBwd<T> a = {(const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (const T*)o, (const T*)d_o, lse,
                          static_cast<float*>(ws), (T*)dq, (T*)dk, (T*)dv, dzk, dzv, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale,
@@ -663,7 +668,7 @@ static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const voi
             // One launch, each dK / dV block forming the delta of its rows itself: it does not wait for the dQ blocks, and a
             // launch fewer.  Against two (us, fp32): 2 x 64 tokens, 2 / 1 heads of 64, 32 slots 21.0 -> 17.0; 4 x 256, 8 / 2, 256
             // slots 162 -> 134; of 128 375 -> 339; 16 x 512, 1000 slots 3968 -> 3251 (prefix blocks whole).  (Above 128: no registers for O's rows.)
-            hipLaunchKernelGGL((attn_bwd_vector<T, NB, NW>), grid_of(n_q + n_kv), dim3(64 * NW), 0, st, a, static_cast<int>(n_kv));
+            hipLaunchKernelGGL((ahead ? attn_bwd_vector<T, NB, NW, VEC_AHEAD<NB>> : attn_bwd_vector<T, NB, NW, false>), grid_of(n_q + n_kv), dim3(64 * NW), 0, st, a, static_cast<int>(n_kv));
             trace_mark(st);
         } else {
             hipLaunchKernelGGL((attn_bwd_dq_vector<T, NB, NW>), grid_of(n_q), dim3(64 * NW), 0, st, a);
