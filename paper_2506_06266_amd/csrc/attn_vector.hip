@@ -629,7 +629,10 @@ constexpr float VEC_TURN_US = 3.5f, VEC_SUM_US = 5.f;
 static int dz_splits(const cart_attn_desc& d, int NW) {
     const long nSt = (d.S + 15) / 16, nPt = (d.P + 15) / 16, G = d.Hq / d.Hkv;
     if (d.P == 0) return 1;
-    const long all = d.B * G * nSt, own = (G * nSt + NW - 1) / NW;
+    // (nor where the blocks keep the CUs busy for as long as a whole prefix block takes: 7 x 208 tokens, 16 / 16 heads of 96, 37
+    // slots in five parts 221, whole 211)
+    const long all = d.B * G * nSt, even = d.Hkv * (nPt * all + d.B * nSt * G * (nSt + 1) / 2) / (NW * device_cus());
+    const long longest_own = (G * nSt + NW - 1) / NW, own = longest_own > even ? longest_own : even;
     int best = 1;
     float best_us = 0.f;
     for (int s = 1; s <= VEC_MAX_SPLITS && s <= all; ++s) {
@@ -650,6 +653,25 @@ size_t attn_vector_bwd_workspace(const cart_attn_desc& d) {
     return VEC_MAX_SPLITS * one < most ? VEC_MAX_SPLITS * one : most;
 }
 
+// One launch, each dK / dV block forming the delta of its rows itself: it does not wait for the dQ blocks, and a launch fewer
+// (us, fp32, two launches -> one: 2 x 64 tokens, 2 / 1 heads of 64, 32 slots 21.0 -> 17.0; 4 x 256, 8 / 2, 256 slots 162 -> 134; of
+// 128 375 -> 339).  The blocks read O's rows besides, and at head_dim up to 64 the dQ blocks share the kernel's 150 registers,
+// a workgroup a CU where 125 allow two: with many blocks two launches are ahead.  500 random problems, blocks of dQ + 4 x of
+// dK / dV per CU, two launches' time over one's: up to 4 1.47, 4 - 8 1.23, 8 - 12 1.11, 12 - 16 0.99, beyond 0.92 (3 x 560,
+// 16 / 16 heads of 32: two 142, one 173); head_dim up to 128, blocks per CU: up to 16 1.18 with several query
+// heads a KV head, beyond 0.95 (6 x 434, 24 / 8 of 96: two 637, one 668) and at 128, where the one launch requests ahead, 1.1.  One head, whose dK / dV blocks are as many as dQ's: a workgroup fills a CU in either form, so the one launch has to
+// save a round (3 x 119, 16 / 16 of 96, 384 blocks of each kind: one 43.7, two 49.7; 5 x 94, 480: 52.1, 49.8); to 1.5 blocks per CU
+// the launch and the wait saved outweigh that (1 x 164 28.9, 36.2), beyond 4 O's rows any round (7 x 208 two 211, one 242).
+// (Head_dim above 128: no registers for O's rows.)
+static bool vec_one_launch(const cart_attn_desc& d, long n_q, long n_kv) {
+    const long cus = device_cus();
+    if (d.D <= 64) return n_q + 4 * n_kv <= 12 * cus;
+    const long n = n_q + n_kv;
+    auto rounds = [&](long blocks) { return (blocks + cus - 1) / cus; };
+    if (d.Hq > d.Hkv) return d.D == 128 || (d.D < 128 && n <= 16 * cus);
+    return d.D <= 128 && (2 * n <= 3 * cus || (n <= 4 * cus && rounds(n) < rounds(n_q) + rounds(n_kv)));
+}
+
 template <typename T>
 static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const void* k, const void* v,
                   const void* zk, const void* zv, const void* o, const float* lse, const void* d_o,
@@ -657,7 +679,7 @@ static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const voi
     const long nSt = (d.S + 15) / 16, nPt = (d.P + 15) / 16;
     const int splits = dz_splits(d, d.D <= 64 ? 8 : 4);
     const long n_q = nSt * d.Hq * d.B, n_kv = (nPt * splits + nSt * d.B) * d.Hkv;
-    const bool ahead = d.D == 128;
+    const bool one = vec_one_launch(d, n_q, n_kv), ahead = d.D == 128;
     float* const part = reinterpret_cast<float*>(static_cast<char*>(ws) + ((static_cast<size_t>(d.B) * d.Hq * d.S * sizeof(float) + 255) & ~static_cast<size_t>(255)));
     const VecBwd<T> a = {(const T*)q, (const T*)k, (const T*)v, (const T*)zk, (const T*)zv, (const T*)o, (const T*)d_o, lse,
                          static_cast<float*>(ws), (T*)dq, (T*)dk, (T*)dv, dzk, dzv, d.B, d.S, d.Hq, d.Hkv, d.D, d.P, scale,
@@ -665,12 +687,12 @@ static void bwd_t(const cart_attn_desc& d, float scale, const void* q, const voi
     trace_begin(st);   // kernel order: dq (+ delta), dk/dv/dz; or both in one (nothing between the second's events)
     CART_DISPATCH_NB(d.D, {
         if constexpr (NB <= 8) {
-            // One launch, each dK / dV block forming the delta of its rows itself: it does not wait for the dQ blocks, and a
-            // launch fewer.  Against two (us, fp32): 2 x 64 tokens, 2 / 1 heads of 64, 32 slots 21.0 -> 17.0; 4 x 256, 8 / 2, 256
-            // slots 162 -> 134; of 128 375 -> 339; 16 x 512, 1000 slots 3968 -> 3251 (prefix blocks whole).  (Above 128: no registers for O's rows.)
-            hipLaunchKernelGGL((ahead ? attn_bwd_vector<T, NB, NW, VEC_AHEAD<NB>> : attn_bwd_vector<T, NB, NW, false>), grid_of(n_q + n_kv), dim3(64 * NW), 0, st, a, static_cast<int>(n_kv));
-            trace_mark(st);
-        } else {
+            if (one) {
+                hipLaunchKernelGGL((ahead ? attn_bwd_vector<T, NB, NW, VEC_AHEAD<NB>> : attn_bwd_vector<T, NB, NW, false>), grid_of(n_q + n_kv), dim3(64 * NW), 0, st, a, static_cast<int>(n_kv));
+                trace_mark(st);
+            }
+        }
+        if (!one) {
             hipLaunchKernelGGL((attn_bwd_dq_vector<T, NB, NW>), grid_of(n_q), dim3(64 * NW), 0, st, a);
             trace_mark(st);
             hipLaunchKernelGGL((attn_bwd_dkv_vector<T, NB, NW>), grid_of(n_kv), dim3(64 * NW), 0, st, a);

@@ -195,7 +195,10 @@ VECTOR_CASES = [(torch.float32, 2, 17, 2, 1, 5, 33), (torch.float32, 1, 16, 4, 2
                 (torch.float32, 3, 50, 4, 1, 100, 33), (torch.float32, 3, 45, 4, 1, 40, 20), (torch.bfloat16, 5, 19, 3, 1, 72, 40),
                 # ... and the prefix blocks' split into parts, of different lengths
                 (torch.float32, 5, 40, 6, 2, 64, 35), (torch.float32, 3, 70, 4, 1, 128, 20), (torch.bfloat16, 7, 33, 4, 2, 200, 17),
-                (torch.float32, 9, 20, 8, 1, 33, 3)]
+                (torch.float32, 9, 20, 8, 1, 33, 3),
+                # (two launches below head_dim 129: many blocks; one query head a KV head.  The last two just below each line)
+                (torch.float32, 5, 130, 16, 16, 33, 0), (torch.bfloat16, 6, 121, 16, 16, 64, 9), (torch.float32, 4, 61, 16, 16, 128, 0),
+                (torch.float32, 3, 76, 16, 16, 65, 0), (torch.float32, 4, 140, 16, 16, 64, 0), (torch.float32, 2, 81, 16, 16, 128, 0)]
 
 
 @pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D,P", VECTOR_CASES, ids=lambda v: str(v).replace("torch.", ""))
