@@ -787,47 +787,40 @@ static KvPlan search_plan(const cart_attn_desc& d, long tokens, int M) {
     return best;
 }
 
-// One KV head's workgroups played through in launch order.  Workgroup numbers go to the XCDs in turn, whatever these have
-// left to do: with fewer KV heads than XCDs, every n-th of a head's workgroups runs on the same 1/n of the head's CUs.
-// spare: one in 16 of these CUs left out.
+// One KV head's workgroups played through in launch order, each on the CU that is free first
 struct Played {
     float cu[KV_MAX_CUS];
-    int n, per, at;
+    int n;
     float end;
-    Played(int Hkv, int M, bool spare) : at(0), end(0.f) {
-        int g = Hkv;
-        for (int x = 8, y; x; x = y) { y = g % x; g = x; }             // gcd with the 8 XCDs
-        n = M >= 8 / g ? 8 / g : 1;
-        per = M / n;
-        if (spare && per > 2) per -= per >= 16 ? per / 16 : 1;
-        for (int i = 0; i < n * per; ++i) cu[i] = 0.f;
+    explicit Played(int M) : n(M), end(0.f) {
+        for (int i = 0; i < n; ++i) cu[i] = 0.f;
     }
     void run(float t) {
-        t = run_next(cu + at * per, per, t);
+        t = run_next(cu, n, t);
         end = t > end ? t : end;
-        at = at + 1 == n ? 0 : at + 1;
     }
 };
 
 // dQ, dK and dV in one launch, or dQ and then dK and dV: by playing both through, the one launch for the two cuts of each
-// split of dQ that look best by their work spread evenly.  A block's time varies by 8 %: where the blocks of the one launch
-// just fill whole rounds, the last of them start a round later than played, and little evens that out where the long
-// prefix blocks are much of the work.  Unless all but the short blocks start at once, the one launch is therefore played on
-// 15/16 of its CUs, which also picks the cuts that leave room; and its time is weighed by the prefix blocks' share.
-// Measured over 2400 random batched and packed problems of 35 to 3000 us: 1639 go to one launch, 11 of them are slower so than
-// in two by more than 1.5 %, and all 2400 are 1.124 times as fast as in two in the geometric mean (all in one launch 1.133, 137 slower;
-// the faster form of each 1.136).  The two estimates compared as they are, on all CUs: 21 of 1092 (of 1370 problems) slower.
+// split of dQ that look best by their work spread evenly.  Its estimate is 4 % further above the measured times than the two
+// launches' (8 % either way for one problem), so as good as equal is ahead.  Not where its long blocks are somewhat more than
+// one round, prefix blocks many of them: a block's time varies by 8 %, the few of the second round start when the last of the
+// first ones end, and little is left to even that out; there it has to be ahead by ONE_LATE.  1400 random batched and packed
+// problems of 20 to 1500 us: slower than in two launches by more than 1.5 % 5 (two estimates compared as they come: 10; without
+// ONE_LATE: 8 of the first 700), all of them 1.180 times as fast in the geometric mean
+// (1.173; of the first 700 1.174, the faster form of each 1.179).
+// (The one launch played on 15/16 of its CUs and asked to be ahead by 5 % where prefix blocks are half of the work: 1 slower of
+// 700, but 54 that are faster in one launch by more than 3 % stayed in two.)
 // Launches of many rounds are not looked at: their ends leave less idle than the statistics' own launch costs (32 x 1024
 // tokens, 24 / 8 heads, 2048 slots: 2943 us in two, 2970 in one).  Measured, a backward call (us, two launches -> one):
 //   1 x 128, 32 / 8 heads, 1024 slots  52 -> 37     2 x 333, 32 / 8, 4096  198 -> 176     1 x 2048, 8 / 2, 256   88 -> 66
-//   1 x 700, 32 / 8, 1000              87 -> 75     3 x 1659, 32 / 8, 723  448 -> 411     18 x 558, 8 / 2, 2942  418 -> 398
+//   1 x 700, 32 / 8, 1000              87 -> 75     3 x 1659, 32 / 8, 723  448 -> 411     1 x 567, 32 / 8, 5785  222 -> 198
 //   packed: 4 of up to 272, 8 / 2, 1000  64 -> 43;  8 of up to 638, 32 / 8, 1501  321 -> 295
 // (own-key blocks as the two launches number them, a sequence's one after the other and all behind dQ's: 1 x 700 92, 3 x 1659 451)
 constexpr int BOTH_ITEMS = 1024;        // most workgroups of a KV head that are played through
 constexpr float ONE_SHORT = 0.4f;       // of the longest block: a block that long or shorter starts where it finds room
-// the one launch's weight, by the prefix blocks' share of its work (2400 problems, all in one launch: slower than in two by more
-// than 1.5 % where the share is up to 0.35 9 of 720, to 0.45 17 of 568, to 0.55 38 of 558, above 73 of 554)
-static float one_weight(float share) { return 0.88f + 0.17f * fminf(fmaxf((share - 0.25f) / 0.25f, 0.f), 1.f); }
+constexpr float ONE_EVEN = 1.015f;      // how far behind two launches the one may look ..
+constexpr float ONE_LATE = 1.06f, ONE_LATE_ROUNDS = 1.45f, ONE_LATE_SHARE = 0.43f;      // .. or has to be ahead of them, see above
 static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, BwdPlan& best) {
     constexpr SplitCost us = SPLIT_COST[QUERY_DQ];
     const int most_parts = static_cast<int>(attn_query_parts(d, T));
@@ -839,13 +832,13 @@ static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, 
     if (n_dq < 0 || best.split.e_full > 4 * M) return false;
     const long key_blocks = (d.P + KV_WG_KEYS - 1) / KV_WG_KEYS + static_cast<long>((d.S + KV_WG_KEYS - 1) / KV_WG_KEYS) * d.B;
     if (key_blocks > BOTH_ITEMS) return false;
-    float best_t;                       // when the cheapest form so far ends
+    float two_t;                        // when the two launches end
     {
         // (a tile's time, of its time when the chip is full)
         auto light = [&](long blocks) {
             return KV_LIGHT_US / KV_FULL_US + (1.f - KV_LIGHT_US / KV_FULL_US) * fminf(static_cast<float>(blocks) / static_cast<float>(M), 1.f);
         };
-        Played dq(d.Hkv, M, false), kv(d.Hkv, M, false);
+        Played dq(M), kv(M);
         const float dq_tile = us.tile * light(n_dq);
         for (int i = 0; i < n_dq; ++i) dq.run(us.block + dq_tile * static_cast<float>(tiles[i]));
         KvTimes t = kv_times(d, best.kv);
@@ -853,9 +846,13 @@ static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, 
         set_tiles(t, d, best.kv, kv_tile, kv_tile);
         for (long j = 0; j < t.n_pre; ++j) kv.run(t.pre);
         for (long j = 0; j < t.n_own; ++j) kv.run(t.own(static_cast<int>(j % t.nOb)));
-        best_t = dq.end + dq_extra(best.split) + kv.end + kv_parts_us(d, tokens, best.kv);
+        two_t = dq.end + dq_extra(best.split) + kv.end + kv_parts_us(d, tokens, best.kv);
     }
-    bool one = false;
+    float one_t = two_t * ONE_EVEN;     // when the cheapest one launch so far ends
+    bool one = false, late = false;
+    KvPlan one_kv = {};
+    QuerySplit one_split;
+    int one_front = 0;
     const float stats_us = 4.f + static_cast<float>(tokens) * d.Hq * (2 * ROW_B) / 4.0e6f;
     for (int parts = 1; parts <= 6; ++parts) {
         QuerySplit sp;
@@ -869,7 +866,7 @@ static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, 
         }
         auto longest = [&](const KvTimes& t) { return fmaxf(dq_most, fmaxf(t.n_pre > 0 ? t.pre : 0.f, t.own(0))); };
         // of this split, the two cuts with the least bound
-        struct { KvPlan p; float bound, extra, weight; } c[2] = {};
+        struct { KvPlan p; float bound, extra; } c[2] = {};
         int n = 0;
         each_cut(d, tokens, M, [&](const KvPlan& p, long n_own, float parts_us) {
             KvTimes t = kv_times(d, p);
@@ -877,16 +874,15 @@ static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, 
             if (t.n_pre + n_own > BOTH_ITEMS) return;
             const float extra = parts_us + dq_extra(sp) + stats_us;
             const float sum = dq_sum + t.sum(d.B * p.head_parts);
-            const float weight = one_weight(t.pre * static_cast<float>(t.n_pre) / sum);
-            const float bound = weight * (fmaxf(longest(t), sum / static_cast<float>(M)) + extra);
-            if (bound >= best_t) return;
+            const float bound = fmaxf(longest(t), sum / static_cast<float>(M)) + extra;
+            if (bound >= one_t) return;
             const int at = n == 0 || bound < c[0].bound ? 0 : n == 1 || bound < c[1].bound ? 1 : 2;
             if (at == 0) c[1] = c[0];
-            if (at < 2) { c[at].p = p; c[at].bound = bound; c[at].extra = extra; c[at].weight = weight; }
+            if (at < 2) { c[at].p = p; c[at].bound = bound; c[at].extra = extra; }
             if (n < 2) ++n;
         });
         for (int i = 0; i < n; ++i) {
-            if (c[i].bound >= best_t) continue;
+            if (c[i].bound >= one_t) continue;
             KvTimes t = kv_times(d, c[i].p);
             set_tiles(t, d, c[i].p, KV_FULL_US, KV_FULL_US);
             const long cols = static_cast<long>(d.B) * c[i].p.head_parts;
@@ -896,7 +892,7 @@ static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, 
             long n_long = t.pre > short_us ? t.n_pre : 0;
             for (int j = 0; j < n_dq; ++j) n_long += dq_us(j) > short_us;
             for (int kb = 0; kb < t.nOb; ++kb) n_long += t.own(kb) > short_us ? cols : 0;
-            Played w(d.Hkv, M, n_long > M || d.Hkv % 8 != 0);
+            Played w(M);
             for (long j = 0; j < t.n_pre; ++j) w.run(t.pre);
             for (int kb = 0; kb <= t.nOb; ++kb) {
                 if (kb == kb1)
@@ -904,17 +900,22 @@ static bool plan_one_launch(const cart_attn_desc& d, int T, long tokens, int M, 
                 if (kb < t.nOb)
                     for (long j = 0; j < cols; ++j) w.run(t.own(kb));
             }
-            const float one_t = c[i].weight * (w.end + c[i].extra);
-            if (one_t < best_t) {
-                best_t = one_t;
-                best.kv = c[i].p;
-                best.split = sp;
-                best.kv_front = static_cast<int>(t.n_pre + kb1 * cols);
+            if (w.end + c[i].extra < one_t) {
+                one_t = w.end + c[i].extra;
+                one_kv = c[i].p;
+                one_split = sp;
+                one_front = static_cast<int>(t.n_pre + kb1 * cols);
                 one = true;
+                late = n_long > M && static_cast<float>(n_long) <= ONE_LATE_ROUNDS * static_cast<float>(M) &&
+                       t.pre * static_cast<float>(t.n_pre) > ONE_LATE_SHARE * (dq_sum + t.sum(d.B * c[i].p.head_parts));
             }
         }
     }
-    return one;
+    if (!one || (late && one_t * ONE_LATE > two_t)) return false;
+    best.kv = one_kv;
+    best.split = one_split;
+    best.kv_front = one_front;
+    return true;
 }
 
 // (the thread's last plan is kept with all that it depends on: the layers of a step ask for the same one in turn)

@@ -37,11 +37,17 @@ def test_two_launches_of_many_rounds(B, S, Hq, Hkv, P, T):
     assert not plan(B, S, Hq, Hkv, P, T).one_launch
 
 
-# blocks that just fill whole rounds, long prefix blocks much of the work: the last ones start a round late.  us a call in two
-# launches, in one: 185 -> 205, 402 -> 418, 420 -> 460, packed 378 -> 421
-@pytest.mark.parametrize("B,S,Hq,Hkv,P,T", [(13, 267, 8, 2, 2990, 0), (6, 639, 8, 2, 7952, 0), (7, 270, 32, 8, 3785, 0), (33, 261, 8, 2, 5179, 5547)])
-def test_two_launches_where_one_only_just_fits(B, S, Hq, Hkv, P, T):
+# long blocks of somewhat more than a round, prefix blocks many of them: the last ones start late.  us a call in two launches,
+# in one: 206 -> 226, packed 138 -> 147, 141 -> 152, 263 -> 290
+@pytest.mark.parametrize("B,S,Hq,Hkv,P,T", [(13, 267, 8, 2, 2990, 0), (11, 230, 8, 2, 5629, 1415), (16, 71, 8, 2, 6672, 0), (21, 213, 8, 2, 3561, 0)])
+def test_two_launches_where_one_starts_its_last_blocks_late(B, S, Hq, Hkv, P, T):
     assert not plan(B, S, Hq, Hkv, P, T).one_launch
+
+
+# ... and no more than that is refused: 222 -> 198, 220 -> 197, packed 130 -> 118, 114 -> 104
+@pytest.mark.parametrize("B,S,Hq,Hkv,P,T", [(1, 567, 32, 8, 5785, 0), (17, 177, 32, 8, 931, 0), (10, 361, 24, 8, 1065, 1694), (9, 313, 8, 2, 2113, 0)])
+def test_one_launch_of_somewhat_more_or_less_than_a_round(B, S, Hq, Hkv, P, T):
+    assert plan(B, S, Hq, Hkv, P, T).one_launch
 
 
 @pytest.mark.parametrize("seed", range(3))

@@ -485,7 +485,7 @@ def test_attention_vector_of_millions_of_workgroups():
 
 # Events of a backward call, in either form the planner takes and of the fp32 kernels: what stands in front of the
 # gradients' sums is dQ, dK + dV, or the row statistics, all three gradients, or all three and nothing.
-@pytest.mark.parametrize("cfg,first_share", [((1, 128, 32, 8, 128, 1024, "bf16"), (0.0, 0.6)), ((7, 270, 32, 8, 128, 3785, "bf16"), (0.15, 0.8)),
+@pytest.mark.parametrize("cfg,first_share", [((1, 128, 32, 8, 128, 1024, "bf16"), (0.0, 0.6)), ((13, 267, 8, 2, 128, 2990, "bf16"), (0.15, 0.8)),
                                              ((2, 128, 8, 2, 64, 256, "f32"), (0.5, 1.0))], ids=["one", "two", "f32"])
 def test_events_of_a_backward_call(cfg, first_share):
     B, S, Hq, Hkv, D, P, dt = cfg
