@@ -659,17 +659,20 @@ size_t attn_vector_bwd_workspace(const cart_attn_desc& d) {
 // a workgroup a CU where 125 allow two: with many blocks two launches are ahead.  500 random problems, blocks of dQ + 4 x of
 // dK / dV per CU, two launches' time over one's: up to 4 1.47, 4 - 8 1.23, 8 - 12 1.11, 12 - 16 0.99, beyond 0.92 (3 x 560,
 // 16 / 16 heads of 32: two 142, one 173); head_dim up to 128, blocks per CU: up to 16 1.18 with several query
-// heads a KV head, beyond 0.95 (6 x 434, 24 / 8 of 96: two 637, one 668) and at 128, where the one launch requests ahead, 1.1.  One head, whose dK / dV blocks are as many as dQ's: a workgroup fills a CU in either form, so the one launch has to
-// save a round (3 x 119, 16 / 16 of 96, 384 blocks of each kind: one 43.7, two 49.7; 5 x 94, 480: 52.1, 49.8); to 1.5 blocks per CU
-// the launch and the wait saved outweigh that (1 x 164 28.9, 36.2), beyond 4 O's rows any round (7 x 208 two 211, one 242).
+// heads a KV head, beyond 0.95 (6 x 434, 24 / 8 of 96: two 637, one 668).  One query head a KV head, whose dK / dV blocks are as many as dQ's: a
+// workgroup fills a CU in either form, so the one launch has to save a round (3 x 119, 16 / 16 of 96, 384 blocks of each kind: one
+// 43.7, two 49.7; 5 x 94, 480: 52.1, 49.8); to 1.5 blocks per CU the launch and the wait saved outweigh that (1 x 164 28.9, 36.2),
+// beyond 4 O's rows any round (7 x 208 two 211, one 242).  At 128 the one launch alone requests ahead: 1.1 with several heads a KV
+// head, and with one (6 x 389, 8 / 8, 380 slots: two 472, one 430; 2 x 304, 16 / 16, 67: 134, 128; 6 x 349, 31: 204, 194).
 // (Head_dim above 128: no registers for O's rows.)
 static bool vec_one_launch(const cart_attn_desc& d, long n_q, long n_kv) {
     const long cus = device_cus();
     if (d.D <= 64) return n_q + 4 * n_kv <= 12 * cus;
+    if (d.D >= 128) return d.D == 128;
     const long n = n_q + n_kv;
     auto rounds = [&](long blocks) { return (blocks + cus - 1) / cus; };
-    if (d.Hq > d.Hkv) return d.D == 128 || (d.D < 128 && n <= 16 * cus);
-    return d.D <= 128 && (2 * n <= 3 * cus || (n <= 4 * cus && rounds(n) < rounds(n_q) + rounds(n_kv)));
+    if (d.Hq > d.Hkv) return n <= 16 * cus;
+    return 2 * n <= 3 * cus || (n <= 4 * cus && rounds(n) < rounds(n_q) + rounds(n_kv));
 }
 
 template <typename T>

@@ -198,7 +198,7 @@ VECTOR_CASES = [(torch.float32, 2, 17, 2, 1, 5, 33), (torch.float32, 1, 16, 4, 2
                 (torch.float32, 9, 20, 8, 1, 33, 3),
                 # (two launches below head_dim 129: many blocks; one query head a KV head.  The last two just below each line)
                 (torch.float32, 5, 130, 16, 16, 33, 0), (torch.bfloat16, 6, 121, 16, 16, 64, 9), (torch.float32, 4, 61, 16, 16, 128, 0),
-                (torch.float32, 3, 76, 16, 16, 65, 0), (torch.float32, 4, 140, 16, 16, 64, 0), (torch.float32, 2, 81, 16, 16, 128, 0)]
+                (torch.float32, 3, 76, 16, 16, 65, 0), (torch.float32, 4, 140, 16, 16, 64, 0), (torch.float32, 2, 81, 16, 16, 112, 0)]
 
 
 @pytest.mark.parametrize("dtype,B,S,Hq,Hkv,D,P", VECTOR_CASES, ids=lambda v: str(v).replace("torch.", ""))
@@ -486,7 +486,8 @@ def test_attention_vector_of_millions_of_workgroups():
 # Events of a backward call, in either form the planner takes and of the fp32 kernels: what stands in front of the
 # gradients' sums is dQ, dK + dV, or the row statistics, all three gradients, or all three and nothing.
 @pytest.mark.parametrize("cfg,first_share", [((1, 128, 32, 8, 128, 1024, "bf16"), (0.0, 0.6)), ((13, 267, 8, 2, 128, 2990, "bf16"), (0.15, 0.8)),
-                                             ((2, 128, 8, 2, 64, 256, "f32"), (0.5, 1.0))], ids=["one", "two", "f32"])
+                                             ((2, 128, 8, 2, 64, 256, "f32"), (0.5, 1.0)), ((2, 304, 16, 16, 128, 67, "f32"), (0.9, 1.0)),
+                                             ((2, 304, 16, 16, 96, 67, "f32"), (0.1, 0.8))], ids=["one", "two", "f32", "f32_128", "f32_two"])
 def test_events_of_a_backward_call(cfg, first_share):
     B, S, Hq, Hkv, D, P, dt = cfg
     t = synth.attn_inputs(synth.AttnConfig("", 5, B, S, Hq, Hkv, D, P, dt, 1.0, 1.0, 0.1), DEV)
