@@ -814,7 +814,7 @@ struct Played {
 // Launches of many rounds are not looked at: their ends leave less idle than the statistics' own launch costs (32 x 1024
 // tokens, 24 / 8 heads, 2048 slots: 2943 us in two, 2970 in one).  Measured, a backward call (us, two launches -> one):
 //   1 x 128, 32 / 8 heads, 1024 slots  52 -> 37     2 x 333, 32 / 8, 4096  198 -> 176     1 x 2048, 8 / 2, 256   88 -> 66
-//   1 x 700, 32 / 8, 1000              87 -> 75     3 x 1659, 32 / 8, 723  448 -> 411     1 x 567, 32 / 8, 5785  222 -> 198
+//   1 x 700, 32 / 8, 1000              87 -> 83     3 x 1659, 32 / 8, 723  448 -> 411     1 x 567, 32 / 8, 5785  222 -> 198
 //   packed: 4 of up to 272, 8 / 2, 1000  64 -> 43;  8 of up to 638, 32 / 8, 1501  321 -> 295
 // (own-key blocks as the two launches number them, a sequence's one after the other and all behind dQ's: 1 x 700 92, 3 x 1659 451)
 constexpr int BOTH_ITEMS = 1024;        // most workgroups of a KV head that are played through
