@@ -807,15 +807,14 @@ struct Played {
 // one round, prefix blocks many of them: a block's time varies by 8 %, the few of the second round start when the last of the
 // first ones end, and little is left to even that out; there it has to be ahead by ONE_LATE.  1400 random batched and packed
 // problems of 20 to 1500 us: slower than in two launches by more than 1.5 % 5 (two estimates compared as they come: 10; without
-// ONE_LATE: 8 of the first 700), all of them 1.180 times as fast in the geometric mean
-// (1.173; of the first 700 1.174, the faster form of each 1.179).
-// (The one launch played on 15/16 of its CUs and asked to be ahead by 5 % where prefix blocks are half of the work: 1 slower of
-// 700, but 54 that are faster in one launch by more than 3 % stayed in two.)
+// ONE_LATE: 8 of the first 700), all of them 1.180 times as fast in the geometric mean (1.173; of
+// the first 700 1.174, the faster form of each 1.179).  (The one launch played on 15/16 of its CUs and asked to be ahead by 5 % where prefix blocks
+// are half of the work: 1 slower of 700, but 54 that are faster in one launch by more than 3 % stayed in two.)
 // Launches of many rounds are not looked at: their ends leave less idle than the statistics' own launch costs (32 x 1024
 // tokens, 24 / 8 heads, 2048 slots: 2943 us in two, 2970 in one).  Measured, a backward call (us, two launches -> one):
-//   1 x 128, 32 / 8 heads, 1024 slots  52 -> 37     2 x 333, 32 / 8, 4096  198 -> 176     1 x 2048, 8 / 2, 256   88 -> 66
-//   1 x 700, 32 / 8, 1000              87 -> 83     3 x 1659, 32 / 8, 723  448 -> 411     1 x 567, 32 / 8, 5785  222 -> 198
-//   packed: 4 of up to 272, 8 / 2, 1000  64 -> 43;  8 of up to 638, 32 / 8, 1501  321 -> 295
+//   1 x 128, 32 / 8 heads, 1024 slots  53 -> 38     2 x 333, 32 / 8, 4096  204 -> 184     1 x 2048, 8 / 2, 256   91 -> 68
+//   1 x 700, 32 / 8, 1000              92 -> 86     3 x 1659, 32 / 8, 723  463 -> 429     1 x 567, 32 / 8, 5785  235 -> 211
+//   packed: 4 of up to 272, 8 / 2, 1000  60 -> 41;  8 of up to 638, 32 / 8, 1501  343 -> 312
 // (own-key blocks as the two launches number them, a sequence's one after the other and all behind dQ's: 1 x 700 92, 3 x 1659 451)
 constexpr int BOTH_ITEMS = 1024;        // most workgroups of a KV head that are played through
 constexpr float ONE_SHORT = 0.4f;       // of the longest block: a block that long or shorter starts where it finds room
