@@ -461,6 +461,11 @@ __device__ __forceinline__ void dma16(const char* base, uint32_t voff, uint32_t 
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
 }
+// (of rows that are read once: not kept in the caches)
+__device__ __forceinline__ void dma16_nt(const char* base, uint32_t voff, uint32_t lds) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
+                 :: "v"(voff), "s"(base), "s"(lds) : "memory", "m0");
+}
 __device__ __forceinline__ void dma4(const char* base, uint32_t voff, uint32_t lds) {
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
                  :: "v"(voff), "s"(base), "s"(lds) : "memory", "m0");

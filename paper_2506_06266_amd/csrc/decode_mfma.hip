@@ -511,14 +511,20 @@ __device__ __forceinline__ void own_store(const OwnState& st, float* __restrict_
 }
 // 32 rows x 256 B from row `row0` of a [rows][pitch] tensor (rows past `lim` repeat row lim) into
 // the wavefront's slot: 8 direct-to-LDS loads of 4 rows each, per tensor
+template <bool ONCE>
 __device__ __forceinline__ void own_issue(const char* k_row0, const char* v_row0, uint32_t pitch, int lim, char* kt,
                                           char* vt, int lane) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const int r = 4 * i + (lane >> 4);
         const uint32_t off = static_cast<uint32_t>(min(r, lim)) * pitch + (((lane & 15) ^ swz(r)) << 4);
-        dma16(k_row0, off, lds_addr(kt) + 4 * i * ROW_B);
-        dma16(v_row0, off, lds_addr(vt) + 4 * i * ROW_B);
+        if constexpr (ONCE) {
+            dma16_nt(k_row0, off, lds_addr(kt) + 4 * i * ROW_B);
+            dma16_nt(v_row0, off, lds_addr(vt) + 4 * i * ROW_B);
+        } else {
+            dma16(k_row0, off, lds_addr(kt) + 4 * i * ROW_B);
+            dma16(v_row0, off, lds_addr(vt) + 4 * i * ROW_B);
+        }
     }
 }
 __device__ __forceinline__ void own_frags(const char* kt, const char* vt, bf16x8 (&ka)[8], bf16x8 (&va)[2][4], int lane) {
@@ -549,6 +555,7 @@ __device__ __forceinline__ void own_load_q(const bf16_t* __restrict__ q, int b, 
 // hardware hands out workgroups.  (One workgroup per four (request, head, chunk) items, left
 // to the dispatcher, measured 20 us slower on the serving shape: by the middle of the kernel 50
 // to 90 CUs sat empty with hundreds of workgroups still to start.)
+template <bool ONCE>
 __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                   const bf16_t* __restrict__ v, const int32_t* __restrict__ cu,
                                                   float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq,
@@ -582,7 +589,7 @@ __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __rest
     OwnState st;
     own_reset(st);
     int t = t_lo;
-    own_issue(k_h + static_cast<size_t>(t) * pitch, v_h + static_cast<size_t>(t) * pitch, pitch, run_end - 1 - t, kt, vt,
+    own_issue<ONCE>(k_h + static_cast<size_t>(t) * pitch, v_h + static_cast<size_t>(t) * pitch, pitch, run_end - 1 - t, kt, vt,
               lane);
     for (;;) {
         const int nkeys = min(DEC_SUB, run_end - t);
@@ -594,7 +601,7 @@ __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __rest
         dma_wait();                      // this step's rows have landed
         own_frags(kt, vt, ka, va, lane); // into registers; the slot then takes the next step's rows
         if (more)
-            own_issue(k_h + static_cast<size_t>(t_next) * pitch, v_h + static_cast<size_t>(t_next) * pitch, pitch,
+            own_issue<ONCE>(k_h + static_cast<size_t>(t_next) * pitch, v_h + static_cast<size_t>(t_next) * pitch, pitch,
                       next_end - 1 - t_next, kt, vt, lane);
         own_step(st, ka, va, qf, nkeys, c, lg);
         if (run_last) {
@@ -621,6 +628,7 @@ __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __rest
 // cartridge to the next, and every (request, range) pair leaves one partial.  (Chunks of a cartridge dealt out round-robin left
 // wavefronts with two chunks beside others with one: 128 cartridges of 2048 slots beside 2048
 // shared ones took 371 us a call against 273, and 252 with the prefix in one part.)
+template <bool ONCE>
 __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __restrict__ q,
                                                    const bf16_t* __restrict__ pool_k, const bf16_t* __restrict__ pool_v,
                                                    const int32_t* __restrict__ cart_id, int pool_p,
@@ -656,7 +664,7 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
     if (cur.b < 0) return;
     bf16x8 qf[8];
     OwnState st;
-    own_issue(cur.k + static_cast<size_t>(cur.s) * ROW_B, cur.v + static_cast<size_t>(cur.s) * ROW_B, ROW_B, cur.end - 1 - cur.s, kt, vt,
+    own_issue<ONCE>(cur.k + static_cast<size_t>(cur.s) * ROW_B, cur.v + static_cast<size_t>(cur.s) * ROW_B, ROW_B, cur.end - 1 - cur.s, kt, vt,
               lane);
     while (cur.b >= 0) {
         own_load_q(q, cur.b, Hq, hk, G, lc, lg, qf);
@@ -670,7 +678,7 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
             const char* kn = last ? nxt.k : cur.k;
             const char* vn = last ? nxt.v : cur.v;
             const int sn = last ? nxt.s : s + DEC_SUB, en = last ? nxt.end : cur.end;
-            if (kn) own_issue(kn + static_cast<size_t>(sn) * ROW_B, vn + static_cast<size_t>(sn) * ROW_B, ROW_B, en - 1 - sn, kt, vt, lane);
+            if (kn) own_issue<ONCE>(kn + static_cast<size_t>(sn) * ROW_B, vn + static_cast<size_t>(sn) * ROW_B, ROW_B, en - 1 - sn, kt, vt, lane);
             own_step(st, ka, va, qf, min(DEC_SUB, cur.end - s), c, lg);
         }
         const int j = r - static_cast<int>(static_cast<long>(cur.b) * pool_p / share);
@@ -683,6 +691,8 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
 // on data that sits in L2) and own-KV workgroups (HBM streaming) alternate in the grid while
 // both kinds remain, so that the two run side by side instead of one after the other.  The
 // launch holds no more workgroups than the chip keeps resident.
+// ONCE: the streamed rows are not kept in the caches (see DEC_ONCE_BYTES)
+template <bool ONCE>
 __global__ __launch_bounds__(256, 2) void decode_fused_kernel(
     const bf16_t* __restrict__ q, const PrefixTable tab, const bf16_t* __restrict__ k,
     const bf16_t* __restrict__ v, const int32_t* __restrict__ cu, const bf16_t* __restrict__ pool_k,
@@ -711,9 +721,9 @@ __global__ __launch_bounds__(256, 2) void decode_fused_kernel(
     const int wid = __builtin_amdgcn_readfirstlane(idx * 4 + static_cast<int>(threadIdx.x >> 6));
     const int r = wid / Hkv, hk = wid - r * Hkv;
     if (n_cc > 0 && r >= pool_r0)
-        decode_pool_stream(sm, q, pool_k, pool_v, cart_id, pool_p, part_o, part_l, B, Hq, Hkv, c, n_ps, pool_share, r - pool_r0, hk);
+        decode_pool_stream<ONCE>(sm, q, pool_k, pool_v, cart_id, pool_p, part_o, part_l, B, Hq, Hkv, c, n_ps, pool_share, r - pool_r0, hk);
     else
-        decode_own_stream(sm, q, k, v, cu, part_o, part_l, B, Hq, Hkv, c, n_ps + n_cc, n_oc, share, r, hk);
+        decode_own_stream<ONCE>(sm, q, k, v, cu, part_o, part_l, B, Hq, Hkv, c, n_ps + n_cc, n_oc, share, r, hk);
 }
 
 // o[b,h,:] = sum_i w_i part_o[i] / sum_i w_i, w_i = exp(lse_i - max lse), over the partial slots
@@ -831,8 +841,20 @@ size_t decode_composed_workspace(const cart_decode_composed_desc& d, const cart_
     return workspace_bytes(composed_plan(d, shared), d.B, d.Hq, d.max_own_len, seg_p, d.n_shared, d.n_pool > 0 ? d.pool_p : 0);
 }
 
+// Streamed rows are read once a step.  Kept in the caches all the same, they drive out what a later call or kernel could
+// still find there, and past a size each other: us a call, kept / not, 32 requests, 32 / 8 heads, 1024 shared slots, by the
+// MB of their own rows (columns: two or four such calls on rows of their own in turn; one behind 512 MB of other traffic):
+//     64   23.3 / 25.4   25.4 / 26.0   29.1 / 28.2        160   41.6 / 37.8   42.6 / 38.2   44.6 / 40.6
+//     96   26.5 / 29.2   31.8 / 29.7   33.8 / 32.0        192   48.1 / 41.7   48.2 / 42.4   49.8 / 45.0
+//    128   32.7 / 33.8   37.7 / 34.6   39.6 / 36.9        384   82.5 / 71.6   82.6 / 72.3   82.7 / 74.0
+// (private cartridges alike).  Two calls' rows fit in the 256 MB that the memory side caches up to about the line.  With fewer
+// cartridges in the pool than requests some are read more than once: kept.
+constexpr size_t DEC_ONCE_BYTES = static_cast<size_t>(144) << 20;
+static bool streamed_once(long own_rows, long pool_rows, int Hkv) {
+    return static_cast<size_t>(own_rows + pool_rows) * Hkv * 2 * ROW_B > DEC_ONCE_BYTES;
+}
 // prefix parts + private-cartridge chunks + own ranges (one launch), then the merge
-static int run_decode(const DecodePlan& p, int B, int Hq, int Hkv, float scale, const void* q, const void* pool_k,
+static int run_decode(const DecodePlan& p, bool once, int B, int Hq, int Hkv, float scale, const void* q, const void* pool_k,
                       const void* pool_v, const int32_t* cart_id, int pool_p, const void* k, const void* v,
                       const int32_t* cu, void* o, float* lse, void* ws, hipStream_t st) {
     float* part_o = static_cast<float*>(ws);
@@ -842,9 +864,13 @@ static int run_decode(const DecodePlan& p, int B, int Hq, int Hkv, float scale, 
                  *PK = static_cast<const bf16_t*>(pool_k), *PV = static_cast<const bf16_t*>(pool_v);
     trace_begin(st);   // kernel order: prefix + own (one launch), merge
     const int n_pre_wg = p.n_ps > 0 ? p.tab.blk0[p.tab.n_seg] : 0;
-    hipLaunchKernelGGL(decode_fused_kernel, dim3(static_cast<unsigned>(n_pre_wg + p.n_own_wg)), dim3(256), 0, st, Q,
-                       p.tab, K, V, cu, PK, PV, cart_id, pool_p, p.pool_r0, p.pool_share, part_o, part_l, B, Hq, Hkv, c, p.n_rb, p.n_cc, p.n_oc,
-                       p.share, p.n_ps, n_pre_wg, p.n_own_wg);
+    auto fused = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_pre_wg + p.n_own_wg)), dim3(256), 0, st, Q,
+                           p.tab, K, V, cu, PK, PV, cart_id, pool_p, p.pool_r0, p.pool_share, part_o, part_l, B, Hq, Hkv, c, p.n_rb, p.n_cc,
+                           p.n_oc, p.share, p.n_ps, n_pre_wg, p.n_own_wg);
+    };
+    if (once) fused(decode_fused_kernel<true>);
+    else      fused(decode_fused_kernel<false>);
     trace_mark(st);
     const long rows = static_cast<long>(B) * Hq;
     auto merge = [&](auto kernel, int rows_per_wg) {
@@ -866,7 +892,8 @@ int launch_decode_mfma(const cart_decode_desc& d, float scale, const void* q, co
         p.tab.zk[0] = static_cast<const bf16_t*>(zk);
         p.tab.zv[0] = static_cast<const bf16_t*>(zv);
     }
-    return run_decode(p, d.B, d.Hq, d.Hkv, scale, q, nullptr, nullptr, nullptr, 0, k, v, cu, o, lse, ws, st);
+    return run_decode(p, streamed_once(d.total_own_tokens, 0, d.Hkv), d.B, d.Hq, d.Hkv, scale, q, nullptr, nullptr, nullptr, 0, k, v, cu, o,
+                      lse, ws, st);
 }
 
 // ---- the decode step for callers that cannot allocate ---------------------------------------------
@@ -904,8 +931,9 @@ int launch_decode_composed(const cart_decode_composed_desc& d, float scale, cons
         ++kseg;
     }
     const bool pool = d.n_pool > 0 && d.pool_p > 0;
-    return run_decode(p, d.B, d.Hq, d.Hkv, scale, q, pool ? pool_k : nullptr, pool ? pool_v : nullptr,
-                      pool ? cart_id : nullptr, pool ? d.pool_p : 0, k, v, cu, o, lse, ws, st);
+    const bool once = (!pool || d.n_pool >= d.B) && streamed_once(d.total_own_tokens, pool ? static_cast<long>(d.B) * d.pool_p : 0, d.Hkv);
+    return run_decode(p, once, d.B, d.Hq, d.Hkv, scale, q, pool ? pool_k : nullptr, pool ? pool_v : nullptr, pool ? cart_id : nullptr,
+                      pool ? d.pool_p : 0, k, v, cu, o, lse, ws, st);
 }
 
 }  // namespace cart

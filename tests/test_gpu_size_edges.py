@@ -451,6 +451,25 @@ def test_decode_ranges(B, Hq, Hkv, P, pool_p, most):
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
 
 
+# Streamed rows of 144 MiB at most, one row more, and as private cartridges (one each; two requests on one: kept)
+@pytest.mark.parametrize("lens,pool_p,n_pool", [((20000, 1, 16863), 0, 0), ((20000, 1, 16864), 0, 0), ((5,) * 20, 2048, 20), ((5,) * 20, 2048, 19)])
+def test_decode_rows_that_are_not_kept_in_caches(lens, pool_p, n_pool):
+    Hq, Hkv, B = 16, 8, len(lens)
+    g = torch.Generator(device=DEV).manual_seed(sum(lens) + n_pool)
+    rn = lambda *sz: (0.6 * torch.randn(*sz, generator=g, device=DEV)).to(torch.bfloat16)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device=DEV)
+    q, k, v, shared = rn(B, Hq, 128), rn(sum(lens), Hkv, 128), rn(sum(lens), Hkv, 128), [(rn(Hkv, 70, 128), rn(Hkv, 70, 128))]
+    pk = pv = cid = None
+    if pool_p:
+        pk, pv, cid = rn(n_pool, Hkv, pool_p, 128), rn(n_pool, Hkv, pool_p, 128), torch.arange(B, device=DEV, dtype=torch.int32) % n_pool
+    o, lse = cb.cart_decode_composed(q, shared, pk, pv, cid, k, v, cu, max(lens))
+    torch.cuda.synchronize()
+    z = lambda t: None if t is None else f64(t)
+    o_ref, lse_ref = orc.decode_composed(f64(q), [(f64(a), f64(b)) for a, b in shared], z(pk), z(pv),
+                                         None if cid is None else cid.cpu().numpy(), f64(k), f64(v), cu.cpu().numpy())
+    assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
+
+
 # Launches of more than 2^32 threads (8.4 million rows in workgroups of 512): every row is computed.
 def test_topk_of_millions_of_rows():
     N, V, K = 8_400_000, 136, 130
