@@ -563,21 +563,37 @@ __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __rest
     const int G = Hq / Hkv;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int T = cu[B];
     const long t_lo_l = static_cast<long>(r) * share;
-    if (t_lo_l >= T) return;
-    const int t_lo = static_cast<int>(t_lo_l);
-    const int t_hi = min(t_lo + share, T);
-    // the request the range starts in: cu[b] <= t_lo < cu[b+1]
-    int cnt = 0;
-    for (int i = lane + 1; i <= B; i += 64) cnt += cu[i] <= t_lo ? 1 : 0;
+    // The request b the range starts in (cu[b] <= t_lo < cu[b+1]), its rows, the end of the next one and of all.  Up to 128
+    // requests' offsets are two loads, a lane each, and the last one: a single trip to memory ahead of the first rows, not three.
+    const int T = cu[B];
+    int b, req_lo, req_hi, next_hi;
+    if (B <= 128) {
+        const int c0 = cu[min(lane, B)], c1 = cu[min(lane + 64, B)];
+        if (t_lo_l >= T) return;
+        const int t = static_cast<int>(t_lo_l);
+        b = static_cast<int>(__popcll(__ballot(lane > 0 && lane <= B && c0 <= t)) + __popcll(__ballot(lane + 64 <= B && c1 <= t)));
+        if (b >= B) return;                       // (cu not increasing: nothing sensible to do)
+        auto at = [&](int i) __attribute__((always_inline)) {
+            return i >= B ? T : i < 64 ? __builtin_amdgcn_readlane(c0, i) : __builtin_amdgcn_readlane(c1, i - 64);
+        };
+        req_lo = at(b);
+        req_hi = at(b + 1);
+        next_hi = at(b + 2);
+    } else {
+        if (t_lo_l >= T) return;
+        int cnt = 0;
+        for (int i = lane + 1; i <= B; i += 64) cnt += cu[i] <= static_cast<int>(t_lo_l) ? 1 : 0;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, CART_WAVE);
-    int b = __builtin_amdgcn_readfirstlane(cnt);
-    if (b >= B) return;                       // (cu not increasing: nothing sensible to do)
-    int req_lo = cu[b], req_hi = cu[b + 1];
+        for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, CART_WAVE);
+        b = __builtin_amdgcn_readfirstlane(cnt);
+        if (b >= B) return;
+        req_lo = cu[b];
+        req_hi = cu[b + 1];
+        next_hi = b + 2 <= B ? cu[b + 2] : T;
+    }
+    const int t_lo = static_cast<int>(t_lo_l), t_hi = min(t_lo + share, T);
     int run_end = min(req_hi, t_hi);          // rows [t, run_end) belong to request b
-    int next_hi = b + 2 <= B ? cu[b + 2] : T; // end of request b+1
     const uint32_t pitch = static_cast<uint32_t>(Hkv) * ROW_B;
     const char* k_h = reinterpret_cast<const char*>(k) + static_cast<size_t>(hk) * ROW_B;
     const char* v_h = reinterpret_cast<const char*>(v) + static_cast<size_t>(hk) * ROW_B;

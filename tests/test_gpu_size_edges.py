@@ -451,6 +451,21 @@ def test_decode_ranges(B, Hq, Hkv, P, pool_p, most):
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
 
 
+# The offsets of up to 128 requests are held a lane each, those of more looked up in memory (requests of one row among them)
+@pytest.mark.parametrize("B", [1, 2, 62, 63, 64, 65, 126, 127, 128, 129])
+def test_decode_finds_the_request_of_a_range(B):
+    g = torch.Generator().manual_seed(B)
+    rn = lambda *sz, std=0.6: (std * torch.randn(*sz, generator=g)).to(torch.bfloat16)
+    lens = torch.randint(1, 90, (B,), generator=g)
+    lens[::3] = 1
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens.numpy())]), dtype=torch.int32)
+    q, k, v, zk, zv = rn(B, 8, 128), rn(int(cu[-1]), 2, 128), rn(int(cu[-1]), 2, 128), rn(2, 50, 128), rn(2, 50, 128)
+    o, lse = cb.cart_decode(*(t.to(DEV) for t in (q, zk, zv, k, v, cu)), int(lens.max()))
+    torch.cuda.synchronize()
+    o_ref, lse_ref = orc.decode(*(f64(t) for t in (q, zk, zv, k, v)), cu.numpy())
+    assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
+
+
 # Streamed rows of 144 MiB at most, one row more, and as private cartridges (one each; two requests on one: kept)
 @pytest.mark.parametrize("lens,pool_p,n_pool", [((20000, 1, 16863), 0, 0), ((20000, 1, 16864), 0, 0), ((5,) * 20, 2048, 20), ((5,) * 20, 2048, 19)])
 def test_decode_rows_that_are_not_kept_in_caches(lens, pool_p, n_pool):
