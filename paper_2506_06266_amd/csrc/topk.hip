@@ -138,8 +138,11 @@ __device__ __forceinline__ int list_best(const T* row, const LogitRow& R, int V,
 // on the maxima).  Keeping the two best LOGITS of a thread instead took seven per logit in 87 % of
 // the vectors: 16384 rows of 128256 bf16 logits 801 -> 693 us (6.07 TB/s).  Rows that are not whole
 // vectors and fp32 rows used to take the selection rounds: 1024 x 50257 bf16 1422 -> 26 us, 2048 x
-// 128256 fp32 6320 -> 178 us (5.9 TB/s).
-template <typename T, int THREADS, int CAP>
+// 128256 fp32 6320 -> 178 us (5.9 TB/s).  The last vectors of a row used to be one round trip
+// after the other (with the rule of TOPK_ONCE_BYTES; us): 16384 rows of 128256 bf16 703 -> 662 (6.4 TB/s), 2264 114 -> 97, 3000 of 8000
+// 18.7 -> 16.0; fp32 1500 of 128256 138 -> 124, 3000 of 8000 24.9 -> 21.8.
+// ONCE: the rows are not kept in the caches (see TOPK_ONCE_BYTES).
+template <typename T, int THREADS, int CAP, bool ONCE>
 __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t* idx_out, float* logp_out, int N, int V, int K) {
     constexpr int NW = THREADS / CART_WAVE, VE = LogitVec<T>::N, PER_LANE = THREADS / CART_WAVE;
     constexpr int LOW_BIT = sizeof(T) == 2 ? 16 : 0;      // (the keys of bf16 values differ in their upper halves)
@@ -193,15 +196,32 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
         note(max3_raw(ninf, __float_as_uint(x), __float_as_uint(x)), -1);
         sum += fast_exp2(fmaf(x, CART_LOG2E, -ref));
     }
-    int v = tid;
-    for (; v + 3 * THREADS < R.nvec; v += 4 * THREADS) {        // four vectors in flight
-        const u32x4 q0 = src[v], q1 = src[v + THREADS], q2 = src[v + 2 * THREADS], q3 = src[v + 3 * THREADS];
-        take(q0, v);
-        take(q1, v + THREADS);
-        take(q2, v + 2 * THREADS);
-        take(q3, v + 3 * THREADS);
+    // Four vectors in flight.  A thread's last turn may hold fewer: loaded together all the same (past the row's end its last
+    // vector, not taken).  Rows that are not kept take every turn through that form, whose loop is shorter (us, one form for the whole
+    // turns / this for all: 4000 rows of 50257 bf16 75.8 / 73.5, 900 of 100001 42.2 / 40.1); others do not gain where a launch is few
+    // rounds of rows (300 of 128256 bf16 23.9 / 25.5, 715 of 50257 17.4 / 18.0).
+    int v0 = 0;
+    if constexpr (!ONCE) {
+        for (; v0 + 4 * THREADS <= R.nvec; v0 += 4 * THREADS) {
+            u32x4 w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = src[v0 + tid + i * THREADS];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) take(w[i], v0 + tid + i * THREADS);
+        }
     }
-    for (; v < R.nvec; v += THREADS) take(src[v], v);
+    for (int v = v0 + tid; v < R.nvec; v += 4 * THREADS) {
+        u32x4 w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const u32x4* const from = src + min(v + i * THREADS, R.nvec - 1);
+            if constexpr (ONCE) w[i] = __builtin_nontemporal_load(from);
+            else if (i == 0 || v0 + i * THREADS < R.nvec) w[i] = *from;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (v + i * THREADS < R.nvec) take(w[i], v + i * THREADS);
+    }
 
     all_kmax[tid] = f32_key(t1);
     const float wref = wave_max(ref);
@@ -265,6 +285,12 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
     write_ranked<THREADS>(list, cnt, K, idx_out, logp_out, lse);
 }
 
+// Past a size the logits drive each other out of the memory-side cache on their way through, and what a later call or kernel
+// could still find there: not kept then.  us a call, kept / not (two tensors in turn; behind 512 MB of other traffic), bf16
+// 128256 a row: 98 MB 26.4 / 26.1, 29.8 / 29.9; 130 MB 35.4 / 35.4, 39.7 / 38.9; 200 MB 52.3 / 44.9, 54.4 / 48.8; 1 GB 184 / 174, 186 / 171.
+// (Two calls' logits fit in the 256 MB that the memory side caches up to about the line.)
+constexpr size_t TOPK_ONCE_BYTES = static_cast<size_t>(144) << 20;
+
 template <typename T>
 static void launch_rows(const cart_topk_desc& d, const void* logits, int32_t* idx, float* logp, hipStream_t st) {
     const T* x = static_cast<const T*>(logits);
@@ -279,12 +305,13 @@ static void launch_rows(const cart_topk_desc& d, const void* logits, int32_t* id
     // of little more than K logits were listed whole).
     const long nvec = d.V / LogitVec<T>::N;
     const int few = d.K > nvec ? (d.K <= 256 ? 256 : d.N <= device_cus() ? 1024 : d.K <= 512 ? 256 : 512) : 0;
-    auto launch = [&](auto kernel, int threads) {
-        hipLaunchKernelGGL(kernel, grid_of(d.N), dim3(threads), 0, st, x, idx, logp, d.N, d.V, d.K);
+    const bool once = static_cast<size_t>(d.N) * d.V * sizeof(T) > TOPK_ONCE_BYTES;
+    auto launch = [&](auto kept, auto not_kept, int threads) {
+        hipLaunchKernelGGL(once ? not_kept : kept, grid_of(d.N), dim3(threads), 0, st, x, idx, logp, d.N, d.V, d.K);
     };
-    if (few == 256 || (few == 0 && nvec <= 4096 && d.K <= 128))       launch(topk_row<T, 256, 1024>, 256);
-    else if (few == 512 || (few == 0 && nvec <= 12288 && d.K <= 256)) launch(topk_row<T, 512, 2048>, 512);
-    else                                                              launch(topk_row<T, 1024, 4096>, 1024);
+    if (few == 256 || (few == 0 && nvec <= 4096 && d.K <= 128))       launch(topk_row<T, 256, 1024, false>, topk_row<T, 256, 1024, true>, 256);
+    else if (few == 512 || (few == 0 && nvec <= 12288 && d.K <= 256)) launch(topk_row<T, 512, 2048, false>, topk_row<T, 512, 2048, true>, 512);
+    else                                                              launch(topk_row<T, 1024, 4096, false>, topk_row<T, 1024, 4096, true>, 1024);
 }
 
 int launch_topk(const cart_topk_desc& d, const void* logits, int32_t* idx, float* logp, hipStream_t st) {

@@ -485,6 +485,23 @@ def test_decode_rows_that_are_not_kept_in_caches(lens, pool_p, n_pool):
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
 
 
+# The last turn of a row has one to four vectors a thread, for some of the threads; rows that are not kept in caches (more than 144 MiB)
+@pytest.mark.parametrize("dtype,N,V", [(torch.bfloat16, 3, 8 * n + r) for n, r in ((1, 0), (255, 7), (256, 1), (257, 0), (1023, 0), (1024, 0), (1025, 3), (1792, 0))] +
+                         [(torch.float32, 3, 4 * n + r) for n, r in ((1, 0), (511, 3), (1025, 1), (4097, 0), (6145, 2), (12289, 0))] +
+                         [(torch.bfloat16, 599, 128256), (torch.float32, 1181, 32003)])
+def test_topk_last_turns(dtype, N, V):
+    K = min(20, V)
+    g = torch.Generator(device=DEV).manual_seed(V)
+    x = (3.0 * torch.randn(N, V, generator=g, device=DEV)).to(dtype)
+    x[0, -3:] = 40.0                                           # winners among the last elements
+    idx, lp = cb.cart_teacher_topk(x, K)
+    v, ref = (t[:, :K] for t in torch.sort(x.float(), dim=1, descending=True, stable=True))
+    assert torch.equal(idx.long(), ref)
+    want = v.double() - torch.logsumexp(x.double(), 1, keepdim=True)
+    # (the log-sum-exp's rounding, 2^-23 of at most 64, and its sum's, a few 2^-24)
+    assert (lp.double() - want).abs().max().item() <= 1e-5
+
+
 # Launches of more than 2^32 threads (8.4 million rows in workgroups of 512): every row is computed.
 def test_topk_of_millions_of_rows():
     N, V, K = 8_400_000, 136, 130
