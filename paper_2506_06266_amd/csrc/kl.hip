@@ -34,12 +34,12 @@ __device__ __forceinline__ KlTeacher kl_teacher(int K) {
 }
 
 // KL_n = sum_j t_j (logp_j - x_j + lse) (+ extra, the rest-bucket term), by the first wavefront
-__device__ __forceinline__ void kl_row_value(const KlTeacher& tc, int K, float lse, float extra, float* out) {
-    if (threadIdx.x < CART_WAVE) {
+__device__ __forceinline__ void kl_row_value(int tid, const KlTeacher& tc, int K, float lse, float extra, float* out) {
+    if (tid < CART_WAVE) {
         float a = 0.f;
-        for (int j = threadIdx.x; j < K; j += CART_WAVE) a += tc.t[j] * (tc.lp[j] - tc.x[j] + lse);
+        for (int j = tid; j < K; j += CART_WAVE) a += tc.t[j] * (tc.lp[j] - tc.x[j] + lse);
         a = wave_sum(a);
-        if (threadIdx.x == 0) *out = a + extra;
+        if (tid == 0) *out = a + extra;
     }
 }
 
@@ -48,13 +48,13 @@ __device__ __forceinline__ void kl_row_value(const KlTeacher& tc, int K, float l
 // of the off-support gradient, (M - S) / (1 - S), and the row's extra term
 // (1 - M)(log(1 - M) - log(1 - S)); the caller synchronises before reading them.  1 - M is
 // floored at 0 and 1 - S at 2^-24, below which fp32 cannot resolve them.
-__device__ __forceinline__ void kl_rest_terms(const KlTeacher& tc, int K, float lse2, float M, float* out2) {
-    if (threadIdx.x < CART_WAVE) {
+__device__ __forceinline__ void kl_rest_terms(int tid, const KlTeacher& tc, int K, float lse2, float M, float* out2) {
+    if (tid < CART_WAVE) {
         float a = 0.f;
-        for (int j = threadIdx.x; j < K; j += CART_WAVE)
+        for (int j = tid; j < K; j += CART_WAVE)
             if (tc.idx[j] >= 0) a += fast_exp2(fmaf(tc.x[j], CART_LOG2E, -lse2));
         a = wave_sum(a);
-        if (threadIdx.x == 0) {
+        if (tid == 0) {
             const float rs = fmaxf(1.f - a, 5.9604645e-8f), rt = fmaxf(1.f - M, 0.f);
             out2[0] = (M - a) / rs;
             out2[1] = rt > 0.f ? rt * (__logf(rt) - __logf(rs)) : 0.f;
@@ -71,6 +71,42 @@ template <typename T> __device__ __forceinline__ float kl_vec_max(float mx, cons
     for (int e = 0; e < LogitVec<T>::N; e += 2) mx = max3_raw(mx, LogitVec<T>::bits(w, e), LogitVec<T>::bits(w, e + 1));
     return mx;
 }
+// The largest of a thread's logits.  bf16: two at a time by their bits, which order as 16-bit integers do while one of them is
+// positive (or a zero); where none is, the smallest as unsigned integers is the largest.  A third of the instructions of widening each.
+template <typename T, int NV> __device__ __forceinline__ float kl_max(float mx, const u32x4 (&x)[NV]) {
+    if constexpr (sizeof(T) == 2) {
+        typedef short s16x2 __attribute__((ext_vector_type(2)));
+        typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+        s16x2 m[4];                          // (a dependent packed instruction waits a slot)
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t w = x[i][e];
+                m[e] = i == 0 ? __builtin_bit_cast(s16x2, w) : __builtin_elementwise_max(m[e], __builtin_bit_cast(s16x2, w));
+            }
+        m[0] = __builtin_elementwise_max(__builtin_elementwise_max(m[0], m[1]), __builtin_elementwise_max(m[2], m[3]));
+        int top = max(static_cast<int>(m[0][0]), static_cast<int>(m[0][1]));
+        if (__any(top < 0)) {
+            u16x2 l[4];
+#pragma unroll
+            for (int i = 0; i < NV; ++i)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t w = x[i][e];
+                    l[e] = i == 0 ? __builtin_bit_cast(u16x2, w) : __builtin_elementwise_min(l[e], __builtin_bit_cast(u16x2, w));
+                }
+            l[0] = __builtin_elementwise_min(__builtin_elementwise_min(l[0], l[1]), __builtin_elementwise_min(l[2], l[3]));
+            if (top < 0) top = min(static_cast<int>(l[0][0]), static_cast<int>(l[0][1]));
+        }
+        const uint32_t b = static_cast<uint32_t>(top) << 16;
+        return max3_raw(mx, b, b);
+    } else {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) mx = kl_vec_max<T>(mx, x[i]);
+        return mx;
+    }
+}
 // s0 + s1 += sum of 2^(x log2e + c0)
 template <typename T> __device__ __forceinline__ void kl_vec_sum(float& s0, float& s1, const u32x4& w, float c0) {
 #pragma unroll
@@ -86,7 +122,7 @@ struct KlGrad {
     uint32_t sgn;
 };
 template <typename T> __device__ __forceinline__ KlGrad kl_grad_coef(float c, float lse2) {
-    if (sizeof(T) == 2) return KlGrad{c, -(lse2 - fast_log2(fabsf(c))), c < 0.f ? 0x80008000u : 0u};
+    if (sizeof(T) == 2) return KlGrad{c, -(lse2 - fast_log2(fabsf(c))), static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(c < 0.f ? 0x80008000u : 0u))};
     return KlGrad{c, -lse2, 0u};
 }
 template <typename T> __device__ __forceinline__ u32x4 kl_vec_grad(const u32x4& w, const KlGrad& g) {
@@ -96,7 +132,11 @@ template <typename T> __device__ __forceinline__ u32x4 kl_vec_grad(const u32x4& 
         for (int e = 0; e < 4; ++e) {
             const float lo = fast_exp2(fmaf(__uint_as_float(w[e] << 16), CART_LOG2E, g.off));
             const float hi = fast_exp2(fmaf(__uint_as_float(w[e] & 0xffff0000u), CART_LOG2E, g.off));
-            r[e] = pack_bf16x2(lo, hi) ^ g.sgn;
+            r[e] = pack_bf16x2(lo, hi);
+        }
+        if (g.sgn) {
+            asm volatile("");            // (a branch, seldom taken)
+            r ^= g.sgn;
         }
     } else {
 #pragma unroll
@@ -171,18 +211,22 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
 //   16384 x 128256 bf16  1649 -> 1593 (5.28 TB/s)     4096 x 32000 bf16  153 -> 100
 //    1024 x  50257 bf16   146 ->   47                16384 x  1000 fp32   54 ->  47
 //    2048 x 128256 fp32   785 ->  397 (10 more without the LDS part)
-// Some of the set-up's values live in scratch (up to 4 registers; 15 at 1024 threads, 26 with the LDS part): stored once,
-// loaded once a row between the sweeps.
+// Rows of whole vectors leave the arithmetic little to hide behind, so it is kept short: the maxima two at a time, what is past the
+// row's end and a negative coefficient behind branches.  And nothing lives in scratch: the thread's number is opaque each row, or what
+// follows from it (LDS and record addresses) is kept across the sweeps at the price of up to 26 registers' reloads, each of which waits
+// for every store and load ahead of it.  Both, and the groups of the last sweep (us a call): 16384 x 128256 bf16 1557 -> 1530, 4000 402 ->
+// 391, 200 26.0 -> 22.2; 1024 x 50257 bf16 44.4 -> 41.5; 16000 x 32000 bf16 387 -> 384; 2048 x 128256 fp32 400 -> 386 (8192 x 32000 371 -> 374,
+// 25001 296 -> 291).
 template <typename T, int THREADS, int NV, int NL, KlRemainder REM, bool LONG = false>
 __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const T* logits, const int32_t* idx,
                                                               const float* logp, T* dlogits, float* row_kl,
                                                               int N, int V, int K, float scale, int mode /* rest bucket | lead mask << 1 */) {
-    constexpr int GRP = NV < 8 ? NV : 8;
+    constexpr int GRP = NV < 8 ? NV : THREADS == 1024 || (THREADS == 512 && sizeof(T) == 2) ? 16 : 8;
     constexpr int NW = THREADS / CART_WAVE, VE = LogitVec<T>::N;
     const KlTeacher tc = kl_teacher(K);
     __shared__ float red_c[NW], red_m[NW], red_sum[NW], rest_terms[2];
     __shared__ __attribute__((aligned(16))) u32x4 lds_x[NL > 0 ? NL * THREADS : 1];
-    const int tid = threadIdx.x, lane = tid & 63;
+    int tid = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     int n = blockIdx.x;
     if (n >= N) return;
@@ -195,7 +239,6 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
                     mfma::lds_addr(lds_x + i * THREADS + wv * CART_WAVE));
     };
     u32x4 x[NV];
-    const int voff = tid * 16;
     constexpr int STEP = THREADS * 16;
     float xs = -3.0e38f;          // the thread's single element
     int my_id = -1;               // the thread's teacher record (record tid; more of them by a loop)
@@ -216,7 +259,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         const KlBuf src = kl_buf<LONG>(logits, R);
         fetch_record(n);          // (ahead of the row: what depends on it need not wait for the row)
 #pragma unroll
-        for (int i = 0; i < NV; ++i) x[i] = kl_ld<KL_NT>(src, voff + i * STEP);
+        for (int i = 0; i < NV; ++i) x[i] = kl_ld<KL_NT>(src, tid * 16 + i * STEP);
         if constexpr (NL > 0) {
 #pragma unroll
             for (int i = 0; i < NL; ++i) lds_fetch(logits, R, i);
@@ -225,6 +268,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         fetch_logit(R);
     }
     for (;;) {
+        asm volatile("" : "+v"(tid));
         // teacher records into LDS
         float m_part = 0.f;
         for (int j = tid; j < K; j += THREADS) {
@@ -253,11 +297,13 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         // barrier between the sweeps); kept above -2e38 so that c0 stays finite.
         float mx = fmaxf(xs, -2.0e38f);
 #pragma unroll
-        for (int i = 0; i < NV; ++i) {
-            if ((i + 1) * THREADS > R.nslot && i * THREADS + tid >= R.nslot) x[i] = kl_fill<T>();
-            if (i == 0 && tid < R.lead) x[0] = kl_fill<T>();
-            mx = kl_vec_max<T>(mx, x[i]);
-        }
+        for (int i = 0; i < NV; ++i)
+            if ((i + 1) * THREADS > R.nslot) {
+                asm volatile("");        // (a branch, seldom taken: selects for every vector else)
+                if (i * THREADS + tid >= R.nslot) x[i] = kl_fill<T>();
+            }
+        if (tid < R.lead) x[0] = kl_fill<T>();
+        mx = kl_max<T>(mx, x);
         if constexpr (NL > 0) {
             mfma::dma_wait();            // the LDS part (each thread reads only what its own lane fetched)
 #pragma unroll
@@ -327,7 +373,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         const float wc = -wave_max(-c0);
         sum = wave_sum(sum * fast_exp2(wc - c0));
         m_part = wave_sum(m_part);
-        if (lane == 0) { red_c[wv] = wc; red_sum[wv] = sum; red_m[wv] = m_part; }
+        if ((tid & 63) == 0) { red_c[wv] = wc; red_sum[wv] = sum; red_m[wv] = m_part; }
         __syncthreads();
         float M = 0.f, gc = red_c[0];
 #pragma unroll
@@ -337,13 +383,15 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         for (int w = 0; w < NW; ++w) sum += red_sum[w] * fast_exp2(gc - red_c[w]);
         const float lse2 = fast_log2(sum) - gc;          // log2 of the softmax denominator
 
-        // sweep 3: the gradient, eight vectors at a time: their stores, then the loads of the same
+        // sweep 3: the gradient, a group of vectors at a time: their stores, then the loads of the same
         // vectors of the next row into their registers.  One store and one load in turn turns the
         // memory bus around too often (16384 rows of 128256 bf16 logits, us: groups of 1 / 2 / 4 / 8 /
-        // 16 vectors -> 1674 / 1672 / 1627 / 1605 / 1603; 2048 fp32 rows: 434 / 433 / 426 / 419 / 415).
+        // 16 vectors -> 1674 / 1672 / 1627 / 1605 / 1603; 2048 fp32 rows: 434 / 433 / 426 / 419 / 415).  Where more than one
+        // workgroup shares a CU groups of 8 do as well or better, but for bf16 in two of them (8 / 16: 8192 x 50257 bf16 308 / 304;
+        // 8192 x 32000 fp32 374 / 379; 16000 x 32000 bf16 384 / 389; 4000 x 100000 bf16, alone on the CU 325 / 315).
         float coef = M, extra = 0.f;
         if (mode & 1) {
-            kl_rest_terms(tc, K, lse2, M, rest_terms);
+            kl_rest_terms(tid, tc, K, lse2, M, rest_terms);
             __syncthreads();
             coef = rest_terms[0];
             extra = rest_terms[1];
@@ -389,19 +437,19 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         for (int i0 = 0; i0 < NV; i0 += GRP) {
 #pragma unroll
             for (int i = i0; i < i0 + GRP; ++i) {
-                if (i * THREADS < R.nslot) kl_st(dst, kl_vec_grad<T>(x[i], g), i == 0 && tid < R.lead ? KL_DROP : voff + i * STEP);
+                if (i * THREADS < R.nslot) kl_st(dst, kl_vec_grad<T>(x[i], g), i == 0 && tid < R.lead ? KL_DROP : tid * 16 + i * STEP);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (more) {
 #pragma unroll
-                for (int i = i0; i < i0 + GRP; ++i) x[i] = kl_ld<KL_NT>(src_next, voff + i * STEP);
+                for (int i = i0; i < i0 + GRP; ++i) x[i] = kl_ld<KL_NT>(src_next, tid * 16 + i * STEP);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
         if constexpr (NL > 0) {
 #pragma unroll
             for (int i = 0; i < NL; ++i) {
-                kl_st(dst, kl_vec_grad<T>(lds_x[i * THREADS + tid], g), voff + (NV + i) * STEP);
+                kl_st(dst, kl_vec_grad<T>(lds_x[i * THREADS + tid], g), tid * 16 + (NV + i) * STEP);
                 __builtin_amdgcn_sched_barrier(0);
             }
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the slots have been read
@@ -430,7 +478,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
                 elem<T>::store(dlogits + R.row + tc.idx[j], scale * ((mode & 1 ? 1.f : M) * s - tc.t[j]));
             }
         }
-        kl_row_value(tc, K, lse2 * CART_LN2, extra, row_kl + n);
+        kl_row_value(tid, tc, K, lse2 * CART_LN2, extra, row_kl + n);
         if (!more) break;
         n = n_next;
         R = Rn;

@@ -451,6 +451,32 @@ def test_decode_ranges(B, Hq, Hkv, P, pool_p, most):
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
 
 
+# The row maximum of bf16 logits comes from their bits: rows without a positive logit, of zeros of both signs, with one positive at either end,
+# masked ones; full, short and odd rows of every width of the workgroup
+@pytest.mark.parametrize("V", [5, 64, 1000, 4104, 9001, 20000, 32768, 50257, 65537, 131073])
+def test_loss_row_maxima(V):
+    g = torch.Generator().manual_seed(V)
+    x = -4.0 - 3.0 * torch.rand(8, V, generator=g)
+    x[1] = torch.where(torch.rand(V, generator=g) < 0.5, 0.0, -0.0)
+    x[2, 0], x[3, -1] = 2.5, 2.5
+    x[4, V // 2] = -0.0
+    x[5, : V // 2] = float("-inf")
+    x[6] = -300.0                        # (at 30000 the log-sum-exp's rounding in 32 bits, 2^-10, is more than the bound below)
+    x[7] = 3.0 * torch.randn(V, generator=g)
+    x = x.to(torch.bfloat16)
+    K = min(3, V)
+    idx = torch.stack([torch.randperm(V, generator=g)[:K] for _ in range(8)]).to(torch.int32)
+    idx[5] = V - 1 - torch.arange(K, dtype=torch.int32)        # (a recorded token of probability 0 has no finite divergence)
+    logp = torch.log_softmax(torch.randn(8, K, generator=g), 1) + float(np.log(0.9))
+    row = torch.empty(8, dtype=torch.float32, device=DEV)
+    loss, dl = cb.cart_distill_kl_fwd_bwd(x.to(DEV), idx.to(DEV), logp.to(DEV), 1.0 / 8, row_kl=row)
+    torch.cuda.synchronize()
+    l_ref, dl_ref, row_ref = orc.distill_kl(f64(x), idx.numpy(), f64(logp), 1.0 / 8)
+    assert np.abs(f64(row) - row_ref).max() <= 1e-4 * np.abs(row_ref).max() and abs(loss.item() - l_ref) <= 1e-4 * abs(l_ref)
+    for n in range(8):
+        assert rel_err(dl[n], dl_ref[n]) <= TOL[torch.bfloat16], n
+
+
 # The offsets of up to 128 requests are held a lane each, those of more looked up in memory (requests of one row among them)
 @pytest.mark.parametrize("B", [1, 2, 62, 63, 64, 65, 126, 127, 128, 129])
 def test_decode_finds_the_request_of_a_range(B):
