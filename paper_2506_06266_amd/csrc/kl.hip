@@ -217,15 +217,19 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
 // for every store and load ahead of it.  Both, and the groups of the last sweep (us a call): 16384 x 128256 bf16 1557 -> 1530, 4000 402 ->
 // 391, 200 26.0 -> 22.2; 1024 x 50257 bf16 44.4 -> 41.5; 16000 x 32000 bf16 387 -> 384; 2048 x 128256 fp32 400 -> 386 (8192 x 32000 371 -> 374,
 // 25001 296 -> 291).
-template <typename T, int THREADS, int NV, int NL, KlRemainder REM, bool LONG = false>
+// PF: at 1024 threads the CU has nothing to send for while its one workgroup forms maxima and sums.  The first PF vectors of the next row
+// are requested into LDS ahead of them, the others by the last sweep as ever (us a call, bf16: 16384 x 128256 1529 -> 1502, 600 71.0 ->
+// 67.7, 4000 x 100000 318 -> 301, x 66000 232 -> 229; four of the sixteen 1581; requested as early as the last sweep 1544.  fp32 rows,
+// whose sums are half as long, 380 -> 385; workgroups of 512, two a CU, 277 -> 282).
+template <typename T, int THREADS, int NV, int NL, KlRemainder REM, bool LONG = false, int PF = 0>
 __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const T* logits, const int32_t* idx,
                                                               const float* logp, T* dlogits, float* row_kl,
                                                               int N, int V, int K, float scale, int mode /* rest bucket | lead mask << 1 */) {
-    constexpr int GRP = NV < 8 ? NV : THREADS == 1024 || (THREADS == 512 && sizeof(T) == 2) ? 16 : 8;
+    constexpr int GRP = PF > 0 ? PF : NV < 8 ? NV : THREADS == 1024 || (THREADS == 512 && sizeof(T) == 2) ? 16 : 8;
     constexpr int NW = THREADS / CART_WAVE, VE = LogitVec<T>::N;
     const KlTeacher tc = kl_teacher(K);
     __shared__ float red_c[NW], red_m[NW], red_sum[NW], rest_terms[2];
-    __shared__ __attribute__((aligned(16))) u32x4 lds_x[NL > 0 ? NL * THREADS : 1];
+    __shared__ __attribute__((aligned(16))) u32x4 lds_x[NL + PF > 0 ? (NL + PF) * THREADS : 1];
     int tid = threadIdx.x;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
     int n = blockIdx.x;
@@ -237,6 +241,16 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         const int v = min((NV + i) * THREADS + tid, max(r.nslot - 1, 0));
         mfma::dma16(reinterpret_cast<const char*>(kl_slots(base, r)), static_cast<uint32_t>(v) * 16u,
                     mfma::lds_addr(lds_x + i * THREADS + wv * CART_WAVE));
+    };
+    // the first PF vectors of a row to come, likewise
+    auto fetch_ahead = [&](int m) __attribute__((always_inline)) {
+        const KlRow r = kl_row<T>(m, V, mode >> 1);
+        const char* const base = reinterpret_cast<const char*>(kl_slots(logits, r));
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");      // the slots have been read
+#pragma unroll
+        for (int i = 0; i < PF; ++i)
+            mfma::dma16_nt(base, static_cast<uint32_t>(min(i * THREADS + tid, max(r.nslot - 1, 0))) * 16u,
+                           mfma::lds_addr(lds_x + i * THREADS + wv * CART_WAVE));
     };
     u32x4 x[NV];
     constexpr int STEP = THREADS * 16;
@@ -266,6 +280,9 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         }
         if (tid < R.head + R.tail) xs = elem<T>::load(logits + R.row + logit_single<T>(R, tid));
         fetch_logit(R);
+        if constexpr (PF > 0) {
+            if (n + static_cast<int>(gridDim.x) < N) fetch_ahead(n + static_cast<int>(gridDim.x));
+        }
     }
     for (;;) {
         asm volatile("" : "+v"(tid));
@@ -440,7 +457,7 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
                 if (i * THREADS < R.nslot) kl_st(dst, kl_vec_grad<T>(x[i], g), i == 0 && tid < R.lead ? KL_DROP : tid * 16 + i * STEP);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (more) {
+            if (more && i0 >= PF) {
 #pragma unroll
                 for (int i = i0; i < i0 + GRP; ++i) x[i] = kl_ld<KL_NT>(src_next, tid * 16 + i * STEP);
             }
@@ -483,6 +500,12 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         n = n_next;
         R = Rn;
         __syncthreads();    // the teacher staging area and the reduction arrays are reused
+        if constexpr (PF > 0) {                 // (they have landed long since; the rest of the row was requested behind them)
+            mfma::dma_wait();
+#pragma unroll
+            for (int i = 0; i < PF; ++i) x[i] = lds_x[i * THREADS + tid];
+            if (n + static_cast<int>(gridDim.x) < N) fetch_ahead(n + static_cast<int>(gridDim.x));
+        }
     }
 }
 
@@ -506,13 +529,13 @@ __global__ __launch_bounds__(1024) void kl_reduce_rows(const float* row_kl, int 
     }
 }
 
-template <typename T, int THREADS, int NV, int NL, KlRemainder REM = KL_NONE, bool LONG = false>
+template <typename T, int THREADS, int NV, int NL, KlRemainder REM = KL_NONE, bool LONG = false, int PF = 0>
 static void resident(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
                      float* rows, hipStream_t st) {
     const int slots = device_cus() * ((NV > 4 ? 1024 : 2048) / THREADS);      // workgroups the chip keeps resident
     const int spare = (NV + NL) * THREADS - d.V / LogitVec<T>::N;
     const int lead_mask = spare < 0 || spare >= 7 ? 7 : spare >= 3 ? 3 : spare >= 1 ? 1 : 0;
-    hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL, REM, LONG>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
+    hipLaunchKernelGGL((kl_row_resident<T, THREADS, NV, NL, REM, LONG, PF>), dim3(static_cast<unsigned>(d.N < slots ? d.N : slots)),
                        dim3(THREADS), kl_record_bytes(d.K), st, static_cast<const T*>(logits), idx, logp,
                        static_cast<T*>(d_logits), rows, d.N, d.V, d.K, d.scale, (d.mode == CART_KL_REST ? 1 : 0) | lead_mask << 1);
 }
@@ -536,7 +559,7 @@ static void launch_rows(const cart_kl_desc& d, const void* logits, const int32_t
     else if (nvec <= 256 * 4) resident<T, 256, 4, 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec <= 256 * 16) resident<T, 256, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec <= 512 * 16) resident<T, 512, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
-    else if (nvec <= 1024 * 16) resident<T, 1024, 16, 0>(d, logits, idx, logp, d_logits, rows, st);
+    else if (nvec <= 1024 * 16) resident<T, 1024, 16, 0, KL_NONE, false, sizeof(T) == 2 ? 8 : 0>(d, logits, idx, logp, d_logits, rows, st);
     else if (nvec >= 1L << 26) resident<T, 1024, 16, NL, KL_TURNS_AHEAD, true>(d, logits, idx, logp, d_logits, rows, st);
     else if (kl_ahead(nvec - 1024 * (16 + NL), d.N)) resident<T, 1024, 16, NL, KL_TURNS_AHEAD>(d, logits, idx, logp, d_logits, rows, st);
     else resident<T, 1024, 16, NL, KL_BY_TURN>(d, logits, idx, logp, d_logits, rows, st);

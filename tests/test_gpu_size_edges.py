@@ -477,6 +477,31 @@ def test_loss_row_maxima(V):
         assert rel_err(dl[n], dl_ref[n]) <= TOL[torch.bfloat16], n
 
 
+# More rows than workgroups of 1024 threads: the first half of a workgroup's next row is requested ahead (rows that begin anywhere in a
+# line; one, two and three rows a workgroup; in place)
+@pytest.mark.parametrize("N,V", [(257, 65543), (515, 66000), (520, 131066)])
+def test_loss_rows_requested_ahead(N, V):
+    K = 7
+    g = torch.Generator(device=DEV).manual_seed(V)
+    x = (3.0 * torch.randn(N, V, generator=g, device=DEV)).to(torch.bfloat16)
+    idx = torch.randint(0, V // K, (N, K), generator=g, device=DEV) + torch.arange(K, device=DEV) * (V // K)
+    logp = torch.log_softmax(torch.randn(N, K, generator=g, device=DEV), 1) + float(np.log(0.9))
+    idx = idx.to(torch.int32)
+    row = torch.empty(N, dtype=torch.float32, device=DEV)
+    loss, dl = cb.cart_distill_kl_fwd_bwd(x, idx, logp, 1.0 / N, row_kl=row)
+    for c in torch.arange(N, device=DEV).split(64):
+        lp = torch.log_softmax(x[c].double(), 1)
+        t = logp[c].double().exp()
+        want = (t * (logp[c].double() - lp.gather(1, idx[c].long()))).sum(1)
+        assert ((row[c].double() - want).abs() <= 1e-4 * want.abs().max()).all()
+        d = t.sum(1, keepdim=True) * lp.exp()
+        d.scatter_add_(1, idx[c].long(), -t)
+        e = (dl[c].double() - d / N).abs().amax(1) / (d / N).abs().amax(1)
+        assert e.max().item() <= TOL[torch.bfloat16]
+    loss2, dl2 = cb.cart_distill_kl_fwd_bwd(x, idx, logp, 1.0 / N, d_logits=x)
+    assert torch.equal(dl2, dl) and loss2.item() == loss.item()
+
+
 # The offsets of up to 128 requests are held a lane each, those of more looked up in memory (requests of one row among them)
 @pytest.mark.parametrize("B", [1, 2, 62, 63, 64, 65, 126, 127, 128, 129])
 def test_decode_finds_the_request_of_a_range(B):
