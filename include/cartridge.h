@@ -304,7 +304,7 @@ cart_status cart_attn_varlen_bwd(const cart_attn_varlen_desc *desc, const void *
  * parts of split blocks; no kernel, only its event, when none is split); backward, by the problem's size
  * (nothing tells the caller which) = dQ (which also forms the row statistics), dK + dV (one kernel) -- problems
  * of many rounds of workgroups --, or the row statistics, then dQ, dK and dV (one kernel); then, either way,
- * the sums of the partials.  Other types and head_dims: forward = one kernel; backward = dQ, dK + dV, or, of a
+ * the sums of the partials (no kernel, only its event, when nothing is left to sum).  Other types and head_dims: forward = one kernel; backward = dQ, dK + dV, or, of a
  * small problem, all three in one kernel and an event without a kernel; then the sums of split prefix
  * gradients, where there are any.  Loss = row kernel, scalar reduction; top-k = one kernel; decode = prefix + own-KV
  * (one launch), merge.  The array must stay valid while the

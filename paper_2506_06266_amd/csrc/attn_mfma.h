@@ -515,12 +515,13 @@ struct KvArgs {
     const bf16_t *q, *k, *v, *zk, *zv, *d_o;
     const float *nlse2, *ndelta;
     bf16_t *dk_own, *dv_own;
-    float *part_k, *part_v;             // dZ partials, one per chunk of token rows
+    float *part_k, *part_v;             // dZ partials, one per chunk of token rows; or dZ itself (one chunk)
     float *own_k, *own_v;               // partials of own keys, one per part of the heads (head_parts > 1)
     const int32_t* cu;
     int n_tok, chunk, head_parts, Smax, Hq, Hkv, P;
     int own_cols;                       // own-key blocks: 0: a (sequence, part of the heads)'s one after the other; else the first of all own_cols of these, then the second ..
     float c, scale;
+    int n_frozen;                       // prefix rows stored as zeros (only where dZ itself is stored)
 };
 struct DqArgs;
 // one_launch: dQ beside dK and dV, behind the first kv_front blocks of the key side (per KV head)

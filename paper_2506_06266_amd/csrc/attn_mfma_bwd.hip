@@ -147,9 +147,13 @@ int launch_attn_bwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
     const bf16_t* O = static_cast<const bf16_t*>(o);
     const DqArgs qa = {Q, K, V, ZK, ZV, O, DO, lse, lse2, delta, static_cast<bf16_t*>(dq), q_cu, row_lo, part_q,
                        n_tok, q_S, d.Hq, d.Hkv, d.P, scale * CART_LOG2E, scale};
-    const KvArgs ka = {Q, K, V, ZK, ZV, DO, lse2, delta, static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), part_k, part_v, own_k, own_v,
-                       cu, n_tok, L.kv.chunk, L.kv.head_parts, d.S, d.Hq, d.Hkv, d.P, L.one_launch ? d.B * L.kv.head_parts : 0,
-                       scale * CART_LOG2E, scale};
+    // One chunk of token rows that is not added to what dZ holds has nothing to be summed with: its partial is dZ.  Without split heads
+    // and query blocks that is the call's last launch saved (us, forward and backward: 3 x 259 tokens, 24 / 8 heads, 4087 slots 224 -> 215; 1 x
+    // 796, 5016 258 -> 247; 12 x 75, 32 / 8, 2600 240 -> 232; 32 x 1024, 24 / 8, 2048 3842 -> 3830).
+    const bool dz_whole = L.kv.n_part == 1 && !d.dz_accumulate;
+    const KvArgs ka = {Q, K, V, ZK, ZV, DO, lse2, delta, static_cast<bf16_t*>(dk), static_cast<bf16_t*>(dv), dz_whole ? dzk : part_k,
+                       dz_whole ? dzv : part_v, own_k, own_v, cu, n_tok, L.kv.chunk, L.kv.head_parts, d.S, d.Hq, d.Hkv, d.P,
+                       L.one_launch ? d.B * L.kv.head_parts : 0, scale * CART_LOG2E, scale, dz_whole ? d.n_frozen : 0};
     trace_begin(st);   // kernel order: dq (+ row statistics), dk + dv; or the statistics, all three gradients; then the partials' sums
     if (L.one_launch) {
         launch_attn_bwd_stats(O, DO, lse, lse2, delta, n_tok, T > 0 ? T : d.S, d.Hq, st);
@@ -169,17 +173,15 @@ int launch_attn_bwd_mfma(const cart_attn_desc& d, float scale, const void* q, co
     r.dz_n4 = static_cast<long>(d.Hkv) * d.P * HD / 4;
     r.own_n4 = static_cast<long>(n_tok) * d.Hkv * HD / 4;
     r.dz_parts = L.kv.n_part; r.own_parts = L.kv.head_parts;
-    r.dz_wgs = static_cast<int>((r.dz_n4 + 255) / 256) * 2;
+    r.dz_wgs = dz_whole ? 0 : static_cast<int>((r.dz_n4 + 255) / 256) * 2;
     r.dq_wgs = L.split.n_blocks * d.Hkv * 32;
     r.P = d.P; r.n_frozen = d.n_frozen; r.accumulate = d.dz_accumulate;
     r.cu = q_cu; r.n_tok = n_tok; r.Smax = q_S; r.Hq = d.Hq; r.Hkv = d.Hkv;
     const long own_wgs = L.kv.head_parts > 1 ? (r.own_n4 + 255) / 256 * 2 : 0;
     const long wgs = r.dz_wgs + r.dq_wgs + own_wgs;
     r.wgs = static_cast<int>(wgs);
-    if (wgs > 0) {
-        hipLaunchKernelGGL(attn_bwd_reduce_kernel, grid_of(wgs), dim3(256), 0, st, r, L.split);
-        trace_mark(st);
-    }
+    if (wgs > 0) hipLaunchKernelGGL(attn_bwd_reduce_kernel, grid_of(wgs), dim3(256), 0, st, r, L.split);
+    trace_mark(st);
     return static_cast<int>(hipGetLastError());
 }
 

@@ -230,6 +230,16 @@ template <bool roleB>
         float* const part = roleB ? part_k : part_v;
         float* const own_part = roleB ? a.own_k : a.own_v;
         bf16_t* const own = roleB ? dk_own : dv_own;
+        if (pre && wkey0 < a.n_frozen) {        // (zeros, whatever the gradient is)
+#pragma unroll
+            for (int kc = 0; kc < 2; ++kc)
+                if (wkey0 + 32 * kc + lc < a.n_frozen) {
+#pragma unroll
+                    for (int db = 0; db < 4; ++db)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[db][kc][r] = 0.f;
+                }
+        }
         if (pre)
             store_rows64(turn, acc, mul, mul, part + ((static_cast<size_t>(b) * Hkv + hk) * P + wkey0) * HD, HD, P - wkey0, lane);
         else if (a.head_parts > 1)

@@ -477,6 +477,21 @@ def test_loss_row_maxima(V):
         assert rel_err(dl[n], dl_ref[n]) <= TOL[torch.bfloat16], n
 
 
+# Token rows of one chunk: the key side stores dZ itself, frozen rows as zeros (up to 128 tokens are never cut)
+@pytest.mark.parametrize("P,n_frozen", [(200, 0), (200, 1), (200, 32), (200, 63), (200, 64), (200, 65), (200, 130), (200, 200), (1, 1), (128, 96)])
+def test_dz_of_one_chunk(P, n_frozen):
+    q, k, v, zk, zv, do = attn_case((1, 100), 8, 2, 128, P, torch.bfloat16, 3 * P + n_frozen)
+    check_attn(q, k, v, zk, zv, do, impl=cb.IMPL_MFMA, n_frozen=n_frozen)
+    a = [t.to(DEV) for t in (q, k, v, zk, zv)]
+    o, lse = cb.cart_attn_fwd(*a)
+    dz = [torch.full((2, P, 128), float("nan"), device=DEV) for _ in range(2)]
+    first = [t.clone() for t in cb.cart_attn_bwd(*a, o, lse, do.to(DEV), n_frozen=n_frozen, d_z_k=dz[0], d_z_v=dz[1])[3:]]
+    assert all((t[:, :n_frozen] == 0).all() and torch.isfinite(t).all() for t in first)
+    # added to what is there: the sums' own kernel
+    cb.cart_attn_bwd(*a, o, lse, do.to(DEV), n_frozen=n_frozen, d_z_k=dz[0], d_z_v=dz[1], dz_accumulate=True)
+    assert all(torch.equal(t, 2 * f) for t, f in zip(dz, first))
+
+
 # More rows than workgroups of 1024 threads: the first half of a workgroup's next row is requested ahead (rows that begin anywhere in a
 # line; one, two and three rows a workgroup; in place)
 @pytest.mark.parametrize("N,V", [(257, 65543), (515, 66000), (520, 131066)])
