@@ -492,6 +492,31 @@ def test_dz_of_one_chunk(P, n_frozen):
     assert all(torch.equal(t, 2 * f) for t, f in zip(dz, first))
 
 
+# fp32 rows: the bound of the candidates is settled before the last bits: rows whose values differ in those only, in steps of each
+# power of two, of either sign, with -inf
+@pytest.mark.parametrize("V,K", [(4096, 1), (4096, 7), (9001, 20), (50257, 19), (70001, 64)])
+def test_topk_bound_of_fp32_rows(V, K):
+    g = torch.Generator().manual_seed(V + K)
+    r = lambda: torch.randint(0, 4 * K + 40, (V,), generator=g, dtype=torch.int32)
+    one = torch.tensor([1.0]).view(torch.int32)
+    x = torch.empty(8, V)
+    x[0] = (one + r()).view(torch.float32)
+    x[1] = -(one + r()).view(torch.float32)
+    x[2] = 2.0 ** (r() % 200 - 100).float()
+    x[3] = -(2.0 ** (r() % 200 - 100).float())
+    x[4] = torch.where(r() > 2 * K, float("-inf"), 0.0) + torch.randn(V, generator=g)
+    x[5] = torch.where(torch.arange(V) % (V // (K + 1)) == 0, 5.0, -5.0)
+    x[6] = (r() * 2 ** 12 + one).view(torch.float32)
+    x[7] = torch.randn(V, generator=g).abs() * 1.0e-38
+    idx, lp = cb.cart_teacher_topk(x.to(DEV), K)
+    ref = torch.sort(x, dim=1, descending=True, stable=True)[1][:, :K]
+    assert torch.equal(idx.cpu().long(), ref)
+    want = x.double().gather(1, ref) - torch.logsumexp(x.double(), 1, keepdim=True)
+    # (values up to 2^99: relative to the row's largest)
+    scale = x.double().abs().where(torch.isfinite(x), torch.zeros(1, dtype=torch.float64)).amax(1, keepdim=True).clamp(min=24.0)
+    assert ((lp.cpu().double() - want).abs() <= 5e-7 * scale).all()
+
+
 # More rows than workgroups of 1024 threads: the first half of a workgroup's next row is requested ahead (rows that begin anywhere in a
 # line; one, two and three rows a workgroup; in place)
 @pytest.mark.parametrize("N,V", [(257, 65543), (515, 66000), (520, 131066)])
