@@ -349,8 +349,8 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         float sum = s0 + s1;
         const KlBuf src = kl_buf<LONG>(logits, R), dst = kl_buf<LONG>(dlogits, R);
         // What is not resident; KL_TURNS_AHEAD: each vector requested KL_AHEAD turns ahead of its use (past the row's end:
-        // zeros).  One at a time, every turn is a round trip to memory with nothing else on the CU (us a call, 2048 rows of 128256
-        // fp32 logits 421, 2 / 3 / 4 / 6 / 8 ahead 410 / 408 / 403 / 406 / 408; 1024 of 200000 bf16 174, 4 ahead 167).
+        // zeros).  One at a time, every turn is a round trip to memory with nothing else on the CU (us a call when it was chosen, 2048 rows
+        // of 128256 fp32 logits 421, 2 / 3 / 4 / 6 / 8 ahead 410 / 408 / 403 / 406 / 408; the two forms now: see kl_ahead).
         constexpr int REST = (NV + NL) * THREADS;
         auto rest = [&](int v) __attribute__((always_inline)) {
             if constexpr (LONG) return reinterpret_cast<const u32x4*>(kl_slots(logits, R))[min(v, max(R.nslot - 1, 0))];
@@ -539,17 +539,17 @@ static void resident(const cart_kl_desc& d, const void* logits, const int32_t* i
                        dim3(THREADS), kl_record_bytes(d.K), st, static_cast<const T*>(logits), idx, logp,
                        static_cast<T*>(d_logits), rows, d.N, d.V, d.K, d.scale, (d.mode == CART_KL_REST ? 1 : 0) | lead_mask << 1);
 }
-// Whether a remainder of `rest` vectors is requested ahead.  Up to two turns there is nothing to request ahead; and with rows on
-// less than half of the CUs memory answers a turn sooner than the longer loop's code arrives, until the turns are many.
+// Whether a remainder of `rest` vectors is requested ahead.  Up to two turns there is nothing to request ahead; and with few turns of rows
+// on few CUs memory answers a turn sooner than the longer loop's code arrives.
 // fp32, us a call one at a time / ahead:  rows        32             65             128            256            1024
-//   103122, 2 turns                              23.4 / 24.0    25.7 / 26.2    31.6 / 32.1    48.0 / 48.4    156.6 / 156.8
-//   110000, 3                                    24.5 / 24.7    26.7 / 26.8    33.3 / 32.6    52.3 / 50.6    171.0 / 168.4
-//   128256, 8                                    26.9 / 27.4    29.2 / 29.6    36.9 / 36.2    56.0 / 56.3    206.4 / 196.7
-//   200000, 25 (64 rows)                                        43.1 / 40.9    55.1 / 51.8    86.7 / 85.8    370.2 / 349.6
-// (bf16 alike: 145000, 2 turns, 1024 rows 128.1 / 128.5; 160000, 4 turns 140.4 / 138.5; 64 rows 28.2 / 27.8)
+//   103122, 2 turns                              17.5 / 18.1    18.7 / 19.3    24.4 / 24.8    39.8 / 40.3    156.0 / 157.7
+//   110000, 3                                    18.8 / 19.0    19.8 / 19.9    25.5 / 25.2    42.4 / 42.1    175.1 / 171.7
+//   128256, 8                                    21.1 / 21.4    23.1 / 22.5    29.3 / 28.6    48.2 / 47.9    205.6 / 196.7
+//   200000, 25                                   33.8 / 31.2    35.5 / 32.4    48.1 / 43.6    80.2 / 76.9    341.1 / 318.7
+// (bf16 alike: 145000, 2 turns, 1024 rows 116.8 / 117.7; 160000, 4 turns 128.0 / 127.6, 64 rows 20.9 / 21.2)
 static bool kl_ahead(long rest, int rows) {
     const long turns = (rest + 1023) / 1024;
-    return turns > 2 && (2L * rows >= device_cus() || turns > 12);
+    return turns > 2 && (2L * rows >= device_cus() || turns * rows >= 2L * device_cus() || turns > 12);
 }
 template <typename T, int NL>
 static void launch_rows(const cart_kl_desc& d, const void* logits, const int32_t* idx, const float* logp, void* d_logits,
