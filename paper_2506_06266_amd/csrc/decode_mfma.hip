@@ -126,8 +126,11 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         if (nPt == 0) continue;                                     // an empty segment adds nothing
         const int k = p.tab.n_seg++;
         p.tab.p[k] = seg_p[s];
-        p.tab.tiles_per_split[k] = tps;
-        p.tab.n_ps[k] = (nPt + tps - 1) / tps;
+        // One of several segments: in parts of one length, up to a quarter longer than the estimate's where that is a part fewer (by
+        // the estimate's length a segment of 64 tiles was 52 and 12: us a call, 128 requests, 8192 slots in 4 segments 77.2 -> 66.2; 5, 7104 in 3 16.5 -> 14.4).
+        const int parts = nPt == total_tiles ? (nPt + tps - 1) / tps : (4 * nPt + 5 * tps - 1) / (5 * tps);
+        p.tab.tiles_per_split[k] = nPt == total_tiles ? tps : (nPt + parts - 1) / parts;
+        p.tab.n_ps[k] = (nPt + p.tab.tiles_per_split[k] - 1) / p.tab.tiles_per_split[k];
         p.tab.slot0[k] = p.n_ps;
         p.n_ps += p.tab.n_ps[k];
         p.tab.blk0[k + 1] = p.tab.blk0[k] + Hkv * p.n_rb * p.tab.n_ps[k];

@@ -557,6 +557,23 @@ def test_decode_finds_the_request_of_a_range(B):
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
 
 
+# Several shared segments: each in parts of one length (segments of a part, of somewhat more, of one slot, beside much longer ones)
+@pytest.mark.parametrize("B,segs", [(40, (2048, 2048, 2048, 2048)), (7, (700, 1, 33)), (3, (4000, 32, 64, 5)), (90, (1700, 1300, 1)), (1, (31, 3000)),
+                                    (20, (1, 1, 1, 1, 1, 1, 1, 1)), (12, (0, 900, 0, 420))])
+def test_decode_segments_in_equal_parts(B, segs):
+    g = torch.Generator().manual_seed(B + sum(segs))
+    rn = lambda *sz, std=0.6: (std * torch.randn(*sz, generator=g)).to(torch.bfloat16)
+    lens = torch.randint(1, 60, (B,), generator=g)
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens.numpy())]), dtype=torch.int32)
+    q, k, v = rn(B, 8, 128), rn(int(cu[-1]), 2, 128), rn(int(cu[-1]), 2, 128)
+    shared = [(rn(2, p, 128), rn(2, p, 128)) for p in segs]
+    dv = lambda t: t.to(DEV)
+    o, lse = cb.cart_decode_composed(dv(q), [(dv(a), dv(b)) for a, b in shared], None, None, None, dv(k), dv(v), dv(cu), int(lens.max()))
+    torch.cuda.synchronize()
+    o_ref, lse_ref = orc.decode_composed(f64(q), [(f64(a), f64(b)) for a, b in shared], None, None, None, f64(k), f64(v), cu.numpy())
+    assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
+
+
 # Streamed rows of 144 MiB at most, one row more, and as private cartridges (one each; two requests on one: kept)
 @pytest.mark.parametrize("lens,pool_p,n_pool", [((20000, 1, 16863), 0, 0), ((20000, 1, 16864), 0, 0), ((5,) * 20, 2048, 20), ((5,) * 20, 2048, 19)])
 def test_decode_rows_that_are_not_kept_in_caches(lens, pool_p, n_pool):
