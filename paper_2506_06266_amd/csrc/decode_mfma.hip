@@ -64,6 +64,21 @@ struct DecodePlan {
     size_t part_o_bytes, part_l_bytes;
 };
 
+// Tiles per part of one of several segments, where the estimate says tps: parts of one length, one part fewer where they are at most a
+// quarter longer for it; where tps is at most 3, as few as a quarter takes, rounded up to whole tiles (one more than tps then).  By the
+// estimate's length a segment of 64 tiles was 52 and 12.  us a call, by the estimate's length / so: 128 requests, 8192 slots in 4 segments 79.8 /
+// 65.4; 4, 20116 in 4 26.9 / 21.4; 44, 18406 in 3 34.4 / 36.2; 206 drawn problems of 2 to 8 segments 1.05 times as fast, 0.95 at worst (as few parts as
+// a quarter takes of any tps 1.04, 0.93; parts levelled and no longer 1.01, 0.94; none longer than tps where that is at most 3: 1.05, 0.95, few requests
+// up to 0.09 slower: three requests, 995 slots in 3 11.0 / 12.0).
+static int segment_tiles(int tiles, int tps) {
+    if (tps <= 3) {
+        const int parts = (4 * tiles + 5 * tps - 1) / (5 * tps);
+        return (tiles + parts - 1) / parts;
+    }
+    const int parts = (tiles + tps - 1) / tps, fewer = parts > 1 ? (tiles + parts - 2) / (parts - 1) : tiles;
+    return 4 * fewer <= 5 * tps ? fewer : (tiles + parts - 1) / parts;
+}
+
 // seg_p[n_seg]: slots per shared segment; pool_p: slots of a private cartridge (0 = none);
 // T: rows of the packed own caches
 // lean > 0: prefix workgroups for the chip and no more, and long ranges; 1: in no more parts than
@@ -121,15 +136,14 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
     p.tab.n_seg = 0;
     p.tab.blk0[0] = 0;
     p.n_ps = 0;
+    int longest = tps;
     for (int s = 0; s < n_seg; ++s) {
         const int nPt = (seg_p[s] + DEC_BN - 1) / DEC_BN;
         if (nPt == 0) continue;                                     // an empty segment adds nothing
         const int k = p.tab.n_seg++;
         p.tab.p[k] = seg_p[s];
-        // One of several segments: in parts of one length, up to a quarter longer than the estimate's where that is a part fewer (by
-        // the estimate's length a segment of 64 tiles was 52 and 12: us a call, 128 requests, 8192 slots in 4 segments 77.2 -> 66.2; 5, 7104 in 3 16.5 -> 14.4).
-        const int parts = nPt == total_tiles ? (nPt + tps - 1) / tps : (4 * nPt + 5 * tps - 1) / (5 * tps);
-        p.tab.tiles_per_split[k] = nPt == total_tiles ? tps : (nPt + parts - 1) / parts;
+        p.tab.tiles_per_split[k] = nPt == total_tiles ? tps : segment_tiles(nPt, tps);
+        longest = longest > p.tab.tiles_per_split[k] ? longest : p.tab.tiles_per_split[k];
         p.tab.n_ps[k] = (nPt + p.tab.tiles_per_split[k] - 1) / p.tab.tiles_per_split[k];
         p.tab.slot0[k] = p.n_ps;
         p.n_ps += p.tab.n_ps[k];
@@ -181,10 +195,11 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
         // From the workgroup on that shares a CU the prefix role takes longer (the 0.55 and 0.8 us above): longer ranges
         // where they leave every workgroup its own CU and the launch ends sooner for it.  212 requests, 8 / 2 heads, 10891
         // slots, up to 184 own rows: ranges of 64 rows (360 workgroups) 38.5 us a call, of 192 (238) 31.6; 200 requests,
-        // 4096 slots, up to 300 rows 28.1, now 26.2.
+        // 4096 slots, up to 300 rows 28.1, now 26.2.  (By the longest part there is where that is longer than the estimate's: 22 such
+        // problems 0.86 to 1.34 times as fast, 1.09 in the mean; by a shorter one 38 others 0.82 to 1.20, 0.98 in the mean.)
         const long longer = n_pre_wg > 0 ? unshared(n_pre_wg) : 0;
         if (longer > share) {
-            const float tiles = static_cast<float>(tps);
+            const float tiles = static_cast<float>(longest);
             if (1.1f * fmaxf(8.f + 0.55f * tiles, 4.f + row_us * static_cast<float>(longer)) <=
                 fmaxf(8.f + 0.8f * tiles, 4.f + row_us * static_cast<float>(share))) {
                 share = longer;
@@ -223,7 +238,7 @@ static DecodePlan make_plan(int B, int Hq, int Hkv, int max_own_len, int T, cons
 // cartridges there is no such entry point.  The finer cut is no faster at those sizes (128 requests, 512 slots,
 // 9000 own rows at most: 400 us either way; 96, 1000 slots, 12000: 393; 256, 2048, 3000: 85), but 208 requests of
 // up to 40 own rows, 47 shared slots and cartridges of 786 lost 32 us of 262 to a lean plan.
-static DecodePlan decode_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p) {
+DecodePlan decode_plan(int B, int Hq, int Hkv, int max_own_len, int T, const int* seg_p, int n_seg, int pool_p) {
     const DecodePlan p = make_plan(B, Hq, Hkv, max_own_len, T, seg_p, n_seg, pool_p, 0);
     if (pool_p == 0 && p.part_o_bytes + p.part_l_bytes > DEC_STATIC_BYTES)
         for (int lean = 1; lean <= 2; ++lean) {
