@@ -229,8 +229,11 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
     if (lane == 0) { red_max[wv] = wref; red_sum[wv] = sum; }
     __syncthreads();
     // tau, bit by bit from the top, by the first wavefront.  Of the 32 bits of an fp32 key the lower ones only tell a few candidates more or
-    // less apart: any bound that K maxima reach will do (us, all bits -> until few enough reach it: 42 rows of 50257 14.2 -> 10.8, 130 of
-    // 128256 25.6 -> 22.5, 1500 of 32000 36.8 -> 36.1; the 16 of a bf16 cost less than a longer list: 524 of 32000, K = 5 11.6, 14.1 so).
+    // less apart: any bound that K maxima reach will do.  With K up to a quarter of the threads so will one that somewhat more reach; with
+    // more records every further maximum brings further logits of its thread, and the list, ranked at the square of its length, outgrows
+    // what the bits cost (us, all bits / a bound that up to K + K/4 + 8 reach / this: 42 rows of 50257, K = 20 14.3 / 10.8 / 10.8, 500 31.8 / 32.0 / 30.0,
+    // 800 75 / 127 / 73; 4096 of 8000, K = 128 44.6 / 51.5 / 41.5, 850 745 / 3877 / 725, its list past CAP; 500 of 32000, K = 256 31.6 / 39.7 / 30.8).
+    // The 16 bits of a bf16 cost less than a longer list: 524 of 32000, K = 5 11.6, 14.1 so.
     // (rows of up to 128 logits and fewer vectors than records are listed whole: us, 16884 rows of 3 fp32, K = 1 34, now 19.6;
     // 20000 of 120, K = 100 66, now 48)
     const bool whole = V <= 128 && K > V / VE;
@@ -239,6 +242,7 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
 #pragma unroll
         for (int j = 0; j < PER_LANE; ++j) mine[j] = all_kmax[64 * j + lane];
         uint32_t t = 0;
+        const int enough = K + (K <= THREADS / 4 ? min(K / 4 + 8, 32) : 0);
         for (int bit = 31; bit >= LOW_BIT; --bit) {
             const uint32_t cand = t | (1u << bit);
             int c = 0;
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
             for (int j = 0; j < PER_LANE; ++j) c += __popcll(__ballot(mine[j] >= cand));
             if (c >= K) {
                 t = cand;
-                if (LOW_BIT == 0 && c <= K + K / 4 + 8) break;
+                if (LOW_BIT == 0 && c <= enough) break;
             }
         }
         if (lane == 0) tau_s = t;

@@ -385,6 +385,13 @@ def test_topk_time_of_all_records():
     assert us[1] < 100.0 * us[0], us
 
 
+# fp32 rows of many records: a tenth more of them must not list the row's better half (47 and 68; 63 and 323 with a bound that K + K / 4 + 8 maxima reach)
+def test_topk_time_of_many_fp32_records():
+    x = torch.randn(128, 16384, device=DEV)
+    us = [best_us(lambda: cb.cart_teacher_topk(x, K)) for K in (700, 800)]
+    assert us[1] < 2.5 * us[0], us
+
+
 # Rows with fewer finite logits than records (the lowest indices of the rest follow), of one value, of two with the
 # border inside the records; signed zeros are one value.
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32], ids=["bf16", "f32"])
@@ -494,7 +501,9 @@ def test_dz_of_one_chunk(P, n_frozen):
 
 # fp32 rows: the bound of the candidates is settled before the last bits: rows whose values differ in those only, in steps of each
 # power of two, of either sign, with -inf
-@pytest.mark.parametrize("V,K", [(4096, 1), (4096, 7), (9001, 20), (50257, 19), (70001, 64)])
+# (records up to and from a quarter of the 256, 512 and 1024 threads on)
+@pytest.mark.parametrize("V,K", [(4096, 1), (4096, 7), (9001, 20), (50257, 19), (70001, 64), (16384, 64), (16384, 65), (30000, 128), (30000, 129),
+                                 (50257, 256), (50257, 257), (16384, 513), (50257, 815), (16384, 900), (70001, 1000)])
 def test_topk_bound_of_fp32_rows(V, K):
     g = torch.Generator().manual_seed(V + K)
     r = lambda: torch.randint(0, 4 * K + 40, (V,), generator=g, dtype=torch.int32)
