@@ -18,6 +18,7 @@
 // per-request cartridges of App. A.3's serving protocol use the same two kernels: the shared
 // prefix is a list of segments, each split and run like a single cartridge (a segment is never
 // copied next to another), and a request's private cartridge is streamed like its own KV.
+#include <limits.h>
 #include <math.h>
 
 #include "attn_mfma.h"
@@ -662,12 +663,11 @@ __device__ __forceinline__ void decode_own_stream(char* sm, const bf16_t* __rest
 // cartridge to the next, and every (request, range) pair leaves one partial.  (Chunks of a cartridge dealt out round-robin left
 // wavefronts with two chunks beside others with one: 128 cartridges of 2048 slots beside 2048
 // shared ones took 371 us a call against 273, and 252 with the prefix in one part.)
-template <bool ONCE>
 __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __restrict__ q,
                                                    const bf16_t* __restrict__ pool_k, const bf16_t* __restrict__ pool_v,
                                                    const int32_t* __restrict__ cart_id, int pool_p,
                                                    float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq,
-                                                   int Hkv, float c, int slot0, int share, int r, int hk) {
+                                                   int Hkv, float c, int slot0, int share, int once_from, int r, int hk) {
     const int G = Hq / Hkv;
     const int lane = threadIdx.x & 63, lg = lane >> 5, lc = lane & 31;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -677,9 +677,9 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
     char* kt = sm + (2 * wv) * DEC_SUB_B;
     char* vt = kt + DEC_SUB_B;
     // the rows of the first request from b on that has a cartridge: slots [s, end) of it
-    struct Run { int b, s, end; const char *k, *v; };
+    struct Run { int b, s, end; bool once; const char *k, *v; };
     auto run_from = [&](int b, int s) __attribute__((always_inline)) {
-        Run w = {-1, 0, 0, nullptr, nullptr};
+        Run w = {-1, 0, 0, false, nullptr, nullptr};
         for (; b < B && static_cast<long>(b) * pool_p + s < hi; ++b, s = 0) {
             const int cid = cart_id ? cart_id[b] : -1;
             if (cid < 0) continue;
@@ -693,26 +693,48 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
         }
         return w;
     };
+    // whether a cartridge is no other request's and its rows are not kept in the caches (see DEC_ONCE_BYTES)
+    auto read_once = [&](int b) __attribute__((always_inline)) {
+        const int cid = cart_id[b];
+        int same = 0, with = 0;
+        for (int i0 = 0; i0 < B; i0 += 4 * CART_WAVE) {
+            int id[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) id[j] = cart_id[min(i0 + j * CART_WAVE + lane, B - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const bool is = i0 + j * CART_WAVE + lane < B;
+                same += static_cast<int>(__popcll(__ballot(is && id[j] == cid)));
+                with += static_cast<int>(__popcll(__ballot(is && id[j] >= 0)));
+            }
+        }
+        return same == 1 && with >= once_from;
+    };
+    auto issue = [&](const Run& w, int s) __attribute__((always_inline)) {
+        const char *ks = w.k + static_cast<size_t>(s) * ROW_B, *vs = w.v + static_cast<size_t>(s) * ROW_B;
+        if (w.once) own_issue<true>(ks, vs, ROW_B, w.end - 1 - s, kt, vt, lane);
+        else        own_issue<false>(ks, vs, ROW_B, w.end - 1 - s, kt, vt, lane);
+    };
     const int b0 = static_cast<int>(lo / pool_p);
     Run cur = run_from(b0, static_cast<int>(lo - static_cast<long>(b0) * pool_p));
     if (cur.b < 0) return;
     bf16x8 qf[8];
     OwnState st;
-    own_issue<ONCE>(cur.k + static_cast<size_t>(cur.s) * ROW_B, cur.v + static_cast<size_t>(cur.s) * ROW_B, ROW_B, cur.end - 1 - cur.s, kt, vt,
-              lane);
+    issue(cur, cur.s);                  // (the range's first rows ahead of what says who else reads them)
+    const bool may = once_from <= B;    // (the other requests' numbers: on their way together with rows that have been requested)
+    if (may) cur.once = read_once(cur.b);
     while (cur.b >= 0) {
         own_load_q(q, cur.b, Hq, hk, G, lc, lg, qf);
         own_reset(st);
-        const Run nxt = run_from(cur.b + 1, 0);
+        Run nxt = run_from(cur.b + 1, 0);
+        if (may && nxt.b >= 0) nxt.once = read_once(nxt.b);
         for (int s = cur.s; s < cur.end; s += DEC_SUB) {
             bf16x8 ka[8], va[2][4];
             dma_wait();
             own_frags(kt, vt, ka, va, lane);
             const bool last = s + DEC_SUB >= cur.end;
-            const char* kn = last ? nxt.k : cur.k;
-            const char* vn = last ? nxt.v : cur.v;
-            const int sn = last ? nxt.s : s + DEC_SUB, en = last ? nxt.end : cur.end;
-            if (kn) own_issue<ONCE>(kn + static_cast<size_t>(sn) * ROW_B, vn + static_cast<size_t>(sn) * ROW_B, ROW_B, en - 1 - sn, kt, vt, lane);
+            if (!last) issue(cur, s + DEC_SUB);
+            else if (nxt.b >= 0) issue(nxt, nxt.s);
             own_step(st, ka, va, qf, min(DEC_SUB, cur.end - s), c, lg);
         }
         const int j = r - static_cast<int>(static_cast<long>(cur.b) * pool_p / share);
@@ -725,14 +747,15 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
 // on data that sits in L2) and own-KV workgroups (HBM streaming) alternate in the grid while
 // both kinds remain, so that the two run side by side instead of one after the other.  The
 // launch holds no more workgroups than the chip keeps resident.
-// ONCE: the streamed rows are not kept in the caches (see DEC_ONCE_BYTES)
+// ONCE: the own rows are not kept in the caches; pool_once: from how many requests with a cartridge on those are not that only one of them
+// has (see DEC_ONCE_BYTES)
 template <bool ONCE>
 __global__ __launch_bounds__(256, 2) void decode_fused_kernel(
     const bf16_t* __restrict__ q, const PrefixTable tab, const bf16_t* __restrict__ k,
     const bf16_t* __restrict__ v, const int32_t* __restrict__ cu, const bf16_t* __restrict__ pool_k,
     const bf16_t* __restrict__ pool_v, const int32_t* __restrict__ cart_id, int pool_p,
-    int pool_r0, int pool_share, float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq, int Hkv, float c, int n_rb,
-    int n_cc, int n_oc, int share, int n_ps, int n_pre_wg, int n_own_wg) {
+    int pool_r0, int pool_share, int pool_once, float* __restrict__ part_o, float* __restrict__ part_l, int B, int Hq, int Hkv, float c,
+    int n_rb, int n_cc, int n_oc, int share, int n_ps, int n_pre_wg, int n_own_wg) {
     constexpr int pre_b = 2 * DEC_NBUF * DEC_TILE_B, own_b = 4 * 2 * DEC_SUB_B;   // the two roles share one LDS block
     __shared__ __attribute__((aligned(16))) char sm[pre_b > own_b ? pre_b : own_b];
     const int i = blockIdx.x;
@@ -755,7 +778,7 @@ __global__ __launch_bounds__(256, 2) void decode_fused_kernel(
     const int wid = __builtin_amdgcn_readfirstlane(idx * 4 + static_cast<int>(threadIdx.x >> 6));
     const int r = wid / Hkv, hk = wid - r * Hkv;
     if (n_cc > 0 && r >= pool_r0)
-        decode_pool_stream<ONCE>(sm, q, pool_k, pool_v, cart_id, pool_p, part_o, part_l, B, Hq, Hkv, c, n_ps, pool_share, r - pool_r0, hk);
+        decode_pool_stream(sm, q, pool_k, pool_v, cart_id, pool_p, part_o, part_l, B, Hq, Hkv, c, n_ps, pool_share, pool_once, r - pool_r0, hk);
     else
         decode_own_stream<ONCE>(sm, q, k, v, cu, part_o, part_l, B, Hq, Hkv, c, n_ps + n_cc, n_oc, share, r, hk);
 }
@@ -897,14 +920,15 @@ size_t decode_composed_workspace(const cart_decode_composed_desc& d, const cart_
 //     64   23.3 / 25.4   25.4 / 26.0   29.1 / 28.2        160   41.6 / 37.8   42.6 / 38.2   44.6 / 40.6
 //     96   26.5 / 29.2   31.8 / 29.7   33.8 / 32.0        192   48.1 / 41.7   48.2 / 42.4   49.8 / 45.0
 //    128   32.7 / 33.8   37.7 / 34.6   39.6 / 36.9        384   82.5 / 71.6   82.6 / 72.3   82.7 / 74.0
-// (private cartridges alike).  Two calls' rows fit in the 256 MB that the memory side caches up to about the line.  With fewer
-// cartridges in the pool than requests some are read more than once: kept.
+// Two calls' rows fit in the 256 MB that the memory side caches up to about the line.  Own rows are judged by themselves, cartridges by
+// those that the requests name, beside own rows that are kept: only the device knows how many there are and which of them several requests read.
+// Those are kept (us a call, all kept / none / as here; 128 requests, 2048 shared slots, cartridges of 2048: 4 of 256 for all of them 97.9 / 146.2 / 89.0;
+// 32 161.7 / 183.8 / 161.1; 64 179.8 / 188.5 / 179.5; one each 210.1 / 190.5 / 187.6, beside own rows of 242 MB 249.2 / 225.9 / 226.2;
+// for one request in twenty, beside them 130.4 / 122.7 / 113.0).
 constexpr size_t DEC_ONCE_BYTES = static_cast<size_t>(144) << 20;
-static bool streamed_once(long own_rows, long pool_rows, int Hkv) {
-    return static_cast<size_t>(own_rows + pool_rows) * Hkv * 2 * ROW_B > DEC_ONCE_BYTES;
-}
+static long once_rows(int Hkv) { return static_cast<long>(DEC_ONCE_BYTES / (static_cast<size_t>(Hkv) * 2 * ROW_B)); }   // rows kept at most
 // prefix parts + private-cartridge chunks + own ranges (one launch), then the merge
-static int run_decode(const DecodePlan& p, bool once, int B, int Hq, int Hkv, float scale, const void* q, const void* pool_k,
+static int run_decode(const DecodePlan& p, bool once, int pool_once, int B, int Hq, int Hkv, float scale, const void* q, const void* pool_k,
                       const void* pool_v, const int32_t* cart_id, int pool_p, const void* k, const void* v,
                       const int32_t* cu, void* o, float* lse, void* ws, hipStream_t st) {
     float* part_o = static_cast<float*>(ws);
@@ -916,8 +940,8 @@ static int run_decode(const DecodePlan& p, bool once, int B, int Hq, int Hkv, fl
     const int n_pre_wg = p.n_ps > 0 ? p.tab.blk0[p.tab.n_seg] : 0;
     auto fused = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(n_pre_wg + p.n_own_wg)), dim3(256), 0, st, Q,
-                           p.tab, K, V, cu, PK, PV, cart_id, pool_p, p.pool_r0, p.pool_share, part_o, part_l, B, Hq, Hkv, c, p.n_rb, p.n_cc,
-                           p.n_oc, p.share, p.n_ps, n_pre_wg, p.n_own_wg);
+                           p.tab, K, V, cu, PK, PV, cart_id, pool_p, p.pool_r0, p.pool_share, pool_once, part_o, part_l, B, Hq, Hkv, c, p.n_rb,
+                           p.n_cc, p.n_oc, p.share, p.n_ps, n_pre_wg, p.n_own_wg);
     };
     if (once) fused(decode_fused_kernel<true>);
     else      fused(decode_fused_kernel<false>);
@@ -942,7 +966,7 @@ int launch_decode_mfma(const cart_decode_desc& d, float scale, const void* q, co
         p.tab.zk[0] = static_cast<const bf16_t*>(zk);
         p.tab.zv[0] = static_cast<const bf16_t*>(zv);
     }
-    return run_decode(p, streamed_once(d.total_own_tokens, 0, d.Hkv), d.B, d.Hq, d.Hkv, scale, q, nullptr, nullptr, nullptr, 0, k, v, cu, o,
+    return run_decode(p, d.total_own_tokens > once_rows(d.Hkv), INT_MAX, d.B, d.Hq, d.Hkv, scale, q, nullptr, nullptr, nullptr, 0, k, v, cu, o,
                       lse, ws, st);
 }
 
@@ -981,8 +1005,13 @@ int launch_decode_composed(const cart_decode_composed_desc& d, float scale, cons
         ++kseg;
     }
     const bool pool = d.n_pool > 0 && d.pool_p > 0;
-    const bool once = (!pool || d.n_pool >= d.B) && streamed_once(d.total_own_tokens, pool ? static_cast<long>(d.B) * d.pool_p : 0, d.Hkv);
-    return run_decode(p, once, d.B, d.Hq, d.Hkv, scale, q, pool ? pool_k : nullptr, pool ? pool_v : nullptr, pool ? cart_id : nullptr,
+    const long kept = once_rows(d.Hkv);
+    const bool once = d.total_own_tokens > kept;
+    // (a wavefront looks at 256 requests' numbers at a time, hidden behind two steps of a cartridge: us a call, kept / looked at, 1000 requests, cartridges
+    // of 256 slots 342 / 317, 300 of 130 67.9 / 60.2, but 2000 of 64 586 / 780, of 32 419 / 833)
+    const bool look = pool && d.pool_p >= (d.B + 4 * CART_WAVE - 1) / (4 * CART_WAVE) * 2 * DEC_SUB;
+    const int pool_once = look ? static_cast<int>((kept - (once ? 0 : d.total_own_tokens)) / d.pool_p + 1) : INT_MAX;
+    return run_decode(p, once, pool_once, d.B, d.Hq, d.Hkv, scale, q, pool ? pool_k : nullptr, pool ? pool_v : nullptr, pool ? cart_id : nullptr,
                       pool ? d.pool_p : 0, k, v, cu, o, lse, ws, st);
 }
 

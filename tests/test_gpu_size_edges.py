@@ -583,23 +583,42 @@ def test_decode_segments_in_equal_parts(B, segs):
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
 
 
-# Streamed rows of 144 MiB at most, one row more, and as private cartridges (one each; two requests on one: kept)
-@pytest.mark.parametrize("lens,pool_p,n_pool", [((20000, 1, 16863), 0, 0), ((20000, 1, 16864), 0, 0), ((5,) * 20, 2048, 20), ((5,) * 20, 2048, 19)])
-def test_decode_rows_that_are_not_kept_in_caches(lens, pool_p, n_pool):
+# Own rows of 144 MiB at most, one row more; private cartridges: one each, two requests on one, up to 144 MiB with the own rows and past
+# them, half of the requests without, several on one beside others of their own, more requests than one look at the others' numbers takes
+@pytest.mark.parametrize("lens,pool_p,ids", [((20000, 1, 16863), 0, ()), ((20000, 1, 16864), 0, ()), ((20000, 1, 16864), 90, (1, -1, 0)), ((5,) * 20, 2048, range(20)),
+                                             ((5,) * 20, 2048, (*range(19), 0)), ((5,) * 36, 1019, range(36)), ((4,) * 36, 1020, range(36)), ((5,) * 36, 1020, range(36)),
+                                             ((30,) * 40, 2048, [i // 2 if i % 2 else -1 for i in range(40)]), ((7,) * 64, 1100, [i if i % 3 else i % 4 for i in range(64)]),
+                                             ((1, 3, 2) * 100, 160, [i if i % 5 else 299 - i // 9 for i in range(300)])])
+def test_decode_rows_that_are_not_kept_in_caches(lens, pool_p, ids):
     Hq, Hkv, B = 16, 8, len(lens)
+    n_pool = max(ids, default=-1) + 1
     g = torch.Generator(device=DEV).manual_seed(sum(lens) + n_pool)
     rn = lambda *sz: (0.6 * torch.randn(*sz, generator=g, device=DEV)).to(torch.bfloat16)
     cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device=DEV)
     q, k, v, shared = rn(B, Hq, 128), rn(sum(lens), Hkv, 128), rn(sum(lens), Hkv, 128), [(rn(Hkv, 70, 128), rn(Hkv, 70, 128))]
     pk = pv = cid = None
     if pool_p:
-        pk, pv, cid = rn(n_pool, Hkv, pool_p, 128), rn(n_pool, Hkv, pool_p, 128), torch.arange(B, device=DEV, dtype=torch.int32) % n_pool
+        pk, pv, cid = rn(n_pool, Hkv, pool_p, 128), rn(n_pool, Hkv, pool_p, 128), torch.tensor(list(ids), device=DEV, dtype=torch.int32)
     o, lse = cb.cart_decode_composed(q, shared, pk, pv, cid, k, v, cu, max(lens))
     torch.cuda.synchronize()
     z = lambda t: None if t is None else f64(t)
     o_ref, lse_ref = orc.decode_composed(f64(q), [(f64(a), f64(b)) for a, b in shared], z(pk), z(pv),
                                          None if cid is None else cid.cpu().numpy(), f64(k), f64(v), cu.cpu().numpy())
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
+
+
+# Cartridges that many requests read are kept in caches however many others the pool holds (us, a pool of 4 / of 132: 97 / 97; 97 / 147 when the size of
+# the pool decided)
+def test_decode_time_of_a_few_cartridges_of_many():
+    B, Hq, Hkv, pool_p = 128, 32, 8, 2048
+    g = torch.Generator(device=DEV).manual_seed(1)
+    rn = lambda *sz: (0.1 * torch.randn(*sz, generator=g, device=DEV)).to(torch.bfloat16)
+    lens = torch.randint(1, 101, (B,), generator=torch.Generator().manual_seed(2))
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens.numpy())]), dtype=torch.int32, device=DEV)
+    T, cid = int(cu[-1]), torch.arange(B, device=DEV, dtype=torch.int32) % 4
+    q, k, v, shared, pk, pv = rn(B, Hq, 128), rn(T, Hkv, 128), rn(T, Hkv, 128), [(rn(Hkv, 2048, 128), rn(Hkv, 2048, 128))], rn(132, Hkv, pool_p, 128), rn(132, Hkv, pool_p, 128)
+    us = [best_us(lambda: cb.cart_decode_composed(q, shared, pk[:n], pv[:n], cid, k, v, cu, int(lens.max()))) for n in (4, 132)]
+    assert us[1] < 1.2 * us[0], us
 
 
 # The last turn of a row has one to four vectors a thread, for some of the threads; rows that are not kept in caches (more than 144 MiB)
