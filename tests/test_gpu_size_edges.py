@@ -7,6 +7,7 @@ import torch
 from oracle import cartridge_oracle as orc
 from paper_2506_06266_amd import binding as cb
 from paper_2506_06266_amd import synth
+from test_backward_plan import plan
 
 pytestmark = pytest.mark.gpu
 
@@ -265,9 +266,11 @@ LOSS_CASES = [
     (torch.float32, 3, 102400, 20), (torch.float32, 3, 102407, 20), (torch.float32, 65, 102407, 5), (torch.float32, 3, 131072, 20),
     (torch.float32, 300, 114697, 5), (torch.float32, 2, 135165, 20),
     (torch.bfloat16, 3, 163851, 20), (torch.bfloat16, 270, 172032, 5),
-    # a turn at a time or ahead: rows on half of the CUs from three turns on, on fewer from thirteen
+    # a turn at a time or ahead: rows on half of the CUs from three turns on, on fewer from as many as make 512 with the rows, or thirteen
     (torch.float32, 128, 106496, 5), (torch.float32, 128, 106499, 5), (torch.float32, 127, 106499, 5), (torch.float32, 3, 147459, 20),
     (torch.bfloat16, 128, 147463, 5), (torch.bfloat16, 2, 229376, 20), (torch.bfloat16, 2, 229385, 20),
+    (torch.float32, 128, 106500, 5), (torch.float32, 127, 106500, 5), (torch.float32, 64, 128256, 5), (torch.float32, 63, 128256, 5),
+    (torch.float32, 3, 147460, 20), (torch.bfloat16, 128, 147464, 5), (torch.bfloat16, 43, 229376, 5), (torch.bfloat16, 42, 229376, 5),
 ]
 
 
@@ -484,6 +487,35 @@ def test_loss_row_maxima(V):
         assert rel_err(dl[n], dl_ref[n]) <= TOL[torch.bfloat16], n
 
 
+# A wrong maximum of a thread's logits shows only where one of them lies further above the rest than an exponential of 32 bits reaches: single
+# logits 250 above the others, at every element of a vector, in the first, the middle and the last ones, and in one of 32 vectors anywhere
+@pytest.mark.parametrize("base,top", [(-200.0, 50.0), (-300.0, -50.0)])
+@pytest.mark.parametrize("dtype,V", [(torch.bfloat16, v) for v in (64, 1000, 4104, 9001, 20000, 32768, 50257, 65537, 131073)] + [(torch.float32, v) for v in (1000, 50257, 100003)])
+def test_loss_maxima_far_above_the_rest(dtype, V, base, top):
+    e = 8 if dtype == torch.bfloat16 else 4
+    g = torch.Generator().manual_seed(V)
+    at = [[v * e + i] for v in (0, V // e // 2, V // e - 1) for i in range(e)] + [[V - 1]]
+    for _ in range(16):
+        v = torch.randperm(V // e, generator=g)[:max(1, V // e // 32)]
+        at.append((v * e + torch.randint(0, e, v.shape, generator=g)).tolist())
+    N, K = len(at), 3
+    x = base + 8.0 * torch.rand(N, V, generator=g)
+    for n, p in enumerate(at):
+        x[n, p] = top + torch.rand(len(p), generator=g)
+    x = x.to(dtype)
+    idx = torch.stack([torch.randperm(V, generator=g)[:K] for _ in range(N)]).to(torch.int32)
+    idx[::2, 0] = torch.tensor([p[0] for p in at[::2]], dtype=torch.int32)
+    idx[::2, 1:] = (idx[::2, :1] + torch.tensor([[V // 3, V // 2]], dtype=torch.int32)) % V
+    logp = torch.log_softmax(torch.randn(N, K, generator=g), 1) + float(np.log(0.9))
+    row = torch.empty(N, dtype=torch.float32, device=DEV)
+    loss, dl = cb.cart_distill_kl_fwd_bwd(x.to(DEV), idx.to(DEV), logp.to(DEV), 1.0 / N, row_kl=row)
+    torch.cuda.synchronize()
+    l_ref, dl_ref, row_ref = orc.distill_kl(f64(x), idx.numpy(), f64(logp), 1.0 / N)
+    assert rel_err(row, row_ref) <= 1e-4 and abs(loss.item() - l_ref) <= 1e-4 * abs(l_ref)
+    for n in range(N):
+        assert rel_err(dl[n], dl_ref[n]) <= TOL[dtype], n
+
+
 # Token rows of one chunk: the key side stores dZ itself, frozen rows as zeros (up to 128 tokens are never cut)
 @pytest.mark.parametrize("P,n_frozen", [(200, 0), (200, 1), (200, 32), (200, 63), (200, 64), (200, 65), (200, 130), (200, 200), (1, 1), (128, 96)])
 def test_dz_of_one_chunk(P, n_frozen):
@@ -497,6 +529,41 @@ def test_dz_of_one_chunk(P, n_frozen):
     # added to what is there: the sums' own kernel
     cb.cart_attn_bwd(*a, o, lse, do.to(DEV), n_frozen=n_frozen, d_z_k=dz[0], d_z_v=dz[1], dz_accumulate=True)
     assert all(torch.equal(t, 2 * f) for t, f in zip(dz, first))
+
+
+# ... of several sequences, batched and packed, by one launch of all gradients and by two, beside split query blocks (the last)
+@pytest.mark.parametrize("lens,packed,Hq,Hkv,P,one_launch", [([60] * 2, False, 8, 2, 200, True), ([40] * 3, False, 4, 1, 130, True), ([1] * 32, False, 8, 8, 130, False),
+                                                             ([24] * 32, False, 16, 8, 1500, False), ([5, 40, 1, 64], True, 8, 2, 200, True),
+                                                             ([10] * 148 + [9] * 147, True, 16, 16, 64, False), ([300, 299], True, 16, 16, 1500, False)])
+@pytest.mark.parametrize("n_frozen", [0, 1, 33])
+def test_dz_of_one_chunk_of_several_sequences(lens, packed, Hq, Hkv, P, one_launch, n_frozen):
+    p = plan(len(lens), max(lens), Hq, Hkv, P, sum(lens) if packed else 0)
+    assert p.n_part == 1 and p.one_launch == one_launch
+    rows = (sum(lens),) if packed else (len(lens), lens[0])
+    q, k, v, zk, zv, do = attn_case(rows, Hq, Hkv, 128, P, torch.bfloat16, P + Hq + n_frozen)
+    n = [f64(t) for t in (q, k, v, zk, zv, do)]
+    a = [t.to(DEV) for t in (q, k, v, zk, zv)]
+    dz = [torch.full((Hkv, P, 128), float("nan"), device=DEV) for _ in range(2)]
+    if packed:
+        cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32)
+        ref = [x.copy() for x in orc.attn_varlen_bwd(*n, cu.numpy())]
+        fwd = a + [cu.to(DEV), max(lens)]
+        bwd = lambda **kw: cb.cart_attn_varlen_bwd(*fwd, *cb.cart_attn_varlen_fwd(*fwd), do.to(DEV), n_frozen=n_frozen, d_z_k=dz[0], d_z_v=dz[1], **kw)
+    else:
+        ref = [x.copy() for x in orc.attn_bwd(*n)]
+        bwd = lambda **kw: cb.cart_attn_bwd(*a, *cb.cart_attn_fwd(*a), do.to(DEV), n_frozen=n_frozen, d_z_k=dz[0], d_z_v=dz[1], **kw)
+    for x in ref[3:]:
+        x[:, :n_frozen] = 0
+    out = [x.clone() for x in bwd()]
+    torch.cuda.synchronize()
+    for x, r in zip(out, ref):
+        if np.abs(r).max() < 1e-12:
+            assert np.abs(f64(x)).max() < 1e-2
+        else:
+            assert rel_err(x, r) <= TOL[torch.bfloat16]
+    assert all((t[:, :n_frozen] == 0).all() for t in out[3:])
+    bwd(dz_accumulate=True)
+    assert all(torch.equal(t, 2 * f) for t, f in zip(dz, out[3:]))
 
 
 # fp32 rows: the bound of the candidates is settled before the last bits: rows whose values differ in those only, in steps of each
@@ -583,6 +650,33 @@ def test_decode_segments_in_equal_parts(B, segs):
     assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
 
 
+# The merge reads slots that no part of the launch writes: what the workspace holds there does not matter (few output rows, four wavefronts a row, and many;
+# requests that reach into fewer ranges than the longest, with and without a cartridge)
+@pytest.mark.parametrize("B,Hq,Hkv,P,pool_p,most", [(4, 32, 8, 2048, 0, 150), (1, 8, 2, 0, 0, 9000), (9, 16, 8, 300, 700, 2500), (64, 32, 8, 100, 260, 700), (65, 32, 8, 100, 260, 700),
+                                                    (200, 16, 4, 4000, 0, 600)])
+def test_decode_in_a_workspace_of_nan(B, Hq, Hkv, P, pool_p, most):
+    g = torch.Generator().manual_seed(B + P)
+    rn = lambda *sz, std=0.6: (std * torch.randn(*sz, generator=g)).to(torch.bfloat16)
+    lens = torch.randint(1, max(2, most // 8), (B,), generator=g)
+    lens[0] = most
+    cu = torch.tensor(np.concatenate([[0], np.cumsum(lens.numpy())]), dtype=torch.int32)
+    T = int(cu[-1])
+    q, k, v, shared = rn(B, Hq, 128), rn(T, Hkv, 128), rn(T, Hkv, 128), [(rn(Hkv, P, 128), rn(Hkv, P, 128))] if P else []
+    pk = pv = cid = None
+    if pool_p:
+        pk, pv, cid = rn(3, Hkv, pool_p, 128), rn(3, Hkv, pool_p, 128), (torch.arange(B) % 4 - 1).to(torch.int32)
+    dv = lambda t: None if t is None else t.to(DEV)
+    a = (dv(q), [(dv(x), dv(y)) for x, y in shared], dv(pk), dv(pv), dv(cid), dv(k), dv(v), dv(cu), most)
+    ws = [torch.full((1 << 26,), b, dtype=torch.uint8, device=DEV) for b in (0xff, 0)]
+    o, lse = cb.cart_decode_composed(*a, workspace=ws[0])
+    o2, lse2 = cb.cart_decode_composed(*a, workspace=ws[1])
+    torch.cuda.synchronize()
+    assert torch.equal(o, o2) and torch.equal(lse, lse2)
+    z = lambda t: None if t is None else f64(t)
+    o_ref, lse_ref = orc.decode_composed(f64(q), [(f64(x), f64(y)) for x, y in shared], z(pk), z(pv), None if cid is None else cid.numpy(), f64(k), f64(v), cu.numpy())
+    assert rel_err(o, o_ref) <= TOL[torch.bfloat16] and rel_err(lse, lse_ref) <= TOL[torch.bfloat16]
+
+
 # Own rows of 144 MiB at most, one row more; private cartridges: one each, two requests on one, up to 144 MiB with the own rows and past
 # them, half of the requests without, several on one beside others of their own, more requests than one look at the others' numbers takes
 @pytest.mark.parametrize("lens,pool_p,ids", [((20000, 1, 16863), 0, ()), ((20000, 1, 16864), 0, ()), ((20000, 1, 16864), 90, (1, -1, 0)), ((5,) * 20, 2048, range(20)),
@@ -624,7 +718,8 @@ def test_decode_time_of_a_few_cartridges_of_many():
 # The last turn of a row has one to four vectors a thread, for some of the threads; rows that are not kept in caches (more than 144 MiB)
 @pytest.mark.parametrize("dtype,N,V", [(torch.bfloat16, 3, 8 * n + r) for n, r in ((1, 0), (255, 7), (256, 1), (257, 0), (1023, 0), (1024, 0), (1025, 3), (1792, 0))] +
                          [(torch.float32, 3, 4 * n + r) for n, r in ((1, 0), (511, 3), (1025, 1), (4097, 0), (6145, 2), (12289, 0))] +
-                         [(torch.bfloat16, 599, 128256), (torch.float32, 1181, 32003)])
+                         [(torch.bfloat16, 599, 128256), (torch.float32, 1181, 32003), (torch.bfloat16, 1901, 40001), (torch.bfloat16, 3803, 20003),
+                          (torch.float32, 2401, 16003), (torch.float32, 301, 128257)])
 def test_topk_last_turns(dtype, N, V):
     K = min(20, V)
     g = torch.Generator(device=DEV).manual_seed(V)
