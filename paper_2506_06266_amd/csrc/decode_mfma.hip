@@ -920,7 +920,8 @@ size_t decode_composed_workspace(const cart_decode_composed_desc& d, const cart_
 //     64   23.3 / 25.4   25.4 / 26.0   29.1 / 28.2        160   41.6 / 37.8   42.6 / 38.2   44.6 / 40.6
 //     96   26.5 / 29.2   31.8 / 29.7   33.8 / 32.0        192   48.1 / 41.7   48.2 / 42.4   49.8 / 45.0
 //    128   32.7 / 33.8   37.7 / 34.6   39.6 / 36.9        384   82.5 / 71.6   82.6 / 72.3   82.7 / 74.0
-// Two calls' rows fit in the 256 MB that the memory side caches up to about the line.  Own rows are judged by themselves, cartridges by
+// Two calls' rows fit in the 256 MB that the memory side caches up to about the line.  (It spares a program that loops over the same rows; one
+// whose layers each have their own, the last column, could do without them in the caches from 64 MB on: up to 7 %.)  Own rows are judged by themselves, cartridges by
 // those that the requests name, beside own rows that are kept: only the device knows how many there are and which of them several requests read.
 // Those are kept (us a call, all kept / none / as here; 128 requests, 2048 shared slots, cartridges of 2048: 4 of 256 for all of them 97.9 / 146.2 / 89.0;
 // 32 161.7 / 183.8 / 161.1; 64 179.8 / 188.5 / 179.5; one each 210.1 / 190.5 / 187.6, beside own rows of 242 MB 249.2 / 225.9 / 226.2;

@@ -212,7 +212,7 @@ __device__ __forceinline__ void kl_st(const KlBuf& b, u32x4 w, int off) {
 //    1024 x  50257 bf16   146 ->   47                16384 x  1000 fp32   54 ->  47
 //    2048 x 128256 fp32   785 ->  397 (10 more without the LDS part)
 // Rows of whole vectors leave the arithmetic little to hide behind, so it is kept short: the maxima two at a time, what is past the
-// row's end and a negative coefficient behind branches.  And nothing lives in scratch: the thread's number is opaque each row, or what
+// row's end and a negative coefficient behind branches.  And nothing lives in scratch (but three registers of bf16 rows past 1 GB): the thread's number is opaque each row, or what
 // follows from it (LDS and record addresses) is kept across the sweeps at the price of up to 26 registers' reloads, each of which waits
 // for every store and load ahead of it.  Both, and the groups of the last sweep (us a call): 16384 x 128256 bf16 1557 -> 1530, 4000 402 ->
 // 391, 200 26.0 -> 22.2; 1024 x 50257 bf16 44.4 -> 41.5; 16000 x 32000 bf16 387 -> 384; 2048 x 128256 fp32 400 -> 386 (8192 x 32000 371 -> 374,
@@ -500,7 +500,9 @@ __global__ __launch_bounds__(THREADS, NV > 4 ? 4 : 8) void kl_row_resident(const
         n = n_next;
         R = Rn;
         __syncthreads();    // the teacher staging area and the reduction arrays are reused
-        if constexpr (PF > 0) {                 // (they have landed long since; the rest of the row was requested behind them)
+        if constexpr (PF > 0) {
+            // The wait is for everything: the first half, requested a row ago, the gradient's stores, and the second half requested
+            // behind them, whose maxima are formed next in any case.  The row after it is requested once all that is there.
             mfma::dma_wait();
 #pragma unroll
             for (int i = 0; i < PF; ++i) x[i] = lds_x[i * THREADS + tid];

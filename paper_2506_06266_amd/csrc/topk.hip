@@ -139,7 +139,7 @@ __device__ __forceinline__ int list_best(const T* row, const LogitRow& R, int V,
 // the vectors: 16384 rows of 128256 bf16 logits 801 -> 693 us (6.07 TB/s).  Rows that are not whole
 // vectors and fp32 rows used to take the selection rounds: 1024 x 50257 bf16 1422 -> 26 us, 2048 x
 // 128256 fp32 6320 -> 178 us (5.9 TB/s).  The last vectors of a row used to be one round trip
-// after the other (with the rule of TOPK_ONCE_BYTES; us): 16384 rows of 128256 bf16 703 -> 662 (6.4 TB/s), 2264 114 -> 97, 3000 of 8000
+// after the other (with the rule of TOPK_ONCE_BYTES; us): 16384 rows of 128256 bf16 704 -> 665 (6.3 TB/s), 2264 114 -> 97, 3000 of 8000
 // 18.7 -> 16.0; fp32 1500 of 128256 138 -> 124, 3000 of 8000 24.9 -> 21.8.
 // ONCE: the rows are not kept in the caches (see TOPK_ONCE_BYTES).
 template <typename T, int THREADS, int CAP, bool ONCE>
@@ -297,7 +297,10 @@ __global__ __launch_bounds__(THREADS, 8) void topk_row(const T* logits, int32_t*
 // Past a size the logits drive each other out of the memory-side cache on their way through, and what a later call or kernel
 // could still find there: not kept then.  us a call, kept / not (two tensors in turn; behind 512 MB of other traffic), bf16
 // 128256 a row: 98 MB 26.4 / 26.1, 29.8 / 29.9; 130 MB 35.4 / 35.4, 39.7 / 38.9; 200 MB 52.3 / 44.9, 54.4 / 48.8; 1 GB 184 / 174, 186 / 171.
-// (Two calls' logits fit in the 256 MB that the memory side caches up to about the line.)
+// (Two calls' logits fit in the 256 MB that the memory side caches up to about the line.)  The price: what the candidates' threads read again
+// comes from memory too.  With records for more than an eighth of the threads that takes the gain back or up to 10 % more, but not at every size (us, kept /
+// not: 4096 x 20000 bf16, K = 20 37.1 / 34.7, 48 41.8 / 42.7, 64 45.6 / 47.3; 2048 x 20000 fp32, K = 20 36.6 / 32.0, 64 40.1 / 41.0, 128 51.0 / 54.3; 16384 x 32000
+// bf16, K = 20 190 / 177, 64 214 / 212, 128 276 / 303; 2000 x 50257, K = 20 44.6 / 38.3, 64 52.2 / 50.9, 192 76.3 / 66.4).
 constexpr size_t TOPK_ONCE_BYTES = static_cast<size_t>(144) << 20;
 
 template <typename T>
