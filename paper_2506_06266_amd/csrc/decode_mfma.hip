@@ -710,17 +710,13 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
         }
         return same == 1 && with >= once_from;
     };
-    auto issue = [&](const Run& w, int s) __attribute__((always_inline)) {
-        const char *ks = w.k + static_cast<size_t>(s) * ROW_B, *vs = w.v + static_cast<size_t>(s) * ROW_B;
-        if (w.once) own_issue<true>(ks, vs, ROW_B, w.end - 1 - s, kt, vt, lane);
-        else        own_issue<false>(ks, vs, ROW_B, w.end - 1 - s, kt, vt, lane);
-    };
     const int b0 = static_cast<int>(lo / pool_p);
     Run cur = run_from(b0, static_cast<int>(lo - static_cast<long>(b0) * pool_p));
     if (cur.b < 0) return;
     bf16x8 qf[8];
     OwnState st;
-    issue(cur, cur.s);                  // (the range's first rows ahead of what says who else reads them)
+    // (the range's first rows ahead of what says who else reads them)
+    own_issue<false>(cur.k + static_cast<size_t>(cur.s) * ROW_B, cur.v + static_cast<size_t>(cur.s) * ROW_B, ROW_B, cur.end - 1 - cur.s, kt, vt, lane);
     const bool may = once_from <= B;    // (the other requests' numbers: on their way together with rows that have been requested)
     if (may) cur.once = read_once(cur.b);
     while (cur.b >= 0) {
@@ -733,8 +729,16 @@ __device__ __forceinline__ void decode_pool_stream(char* sm, const bf16_t* __res
             dma_wait();
             own_frags(kt, vt, ka, va, lane);
             const bool last = s + DEC_SUB >= cur.end;
-            if (!last) issue(cur, s + DEC_SUB);
-            else if (nxt.b >= 0) issue(nxt, nxt.s);
+            const char* kn = last ? nxt.k : cur.k;
+            const char* vn = last ? nxt.v : cur.v;
+            const int sn = last ? nxt.s : s + DEC_SUB, en = last ? nxt.end : cur.end;
+            const bool once = last ? nxt.once : cur.once;
+            if (kn) {
+                kn += static_cast<size_t>(sn) * ROW_B;
+                vn += static_cast<size_t>(sn) * ROW_B;
+                if (once) own_issue<true>(kn, vn, ROW_B, en - 1 - sn, kt, vt, lane);
+                else      own_issue<false>(kn, vn, ROW_B, en - 1 - sn, kt, vt, lane);
+            }
             own_step(st, ka, va, qf, min(DEC_SUB, cur.end - s), c, lg);
         }
         const int j = r - static_cast<int>(static_cast<long>(cur.b) * pool_p / share);
@@ -921,11 +925,12 @@ size_t decode_composed_workspace(const cart_decode_composed_desc& d, const cart_
 //     96   26.5 / 29.2   31.8 / 29.7   33.8 / 32.0        192   48.1 / 41.7   48.2 / 42.4   49.8 / 45.0
 //    128   32.7 / 33.8   37.7 / 34.6   39.6 / 36.9        384   82.5 / 71.6   82.6 / 72.3   82.7 / 74.0
 // Two calls' rows fit in the 256 MB that the memory side caches up to about the line.  (It spares a program that loops over the same rows; one
-// whose layers each have their own, the last column, could do without them in the caches from 64 MB on: up to 7 %.)  Own rows are judged by themselves, cartridges by
-// those that the requests name, beside own rows that are kept: only the device knows how many there are and which of them several requests read.
-// Those are kept (us a call, all kept / none / as here; 128 requests, 2048 shared slots, cartridges of 2048: 4 of 256 for all of them 97.9 / 146.2 / 89.0;
-// 32 161.7 / 183.8 / 161.1; 64 179.8 / 188.5 / 179.5; one each 210.1 / 190.5 / 187.6, beside own rows of 242 MB 249.2 / 225.9 / 226.2;
-// for one request in twenty, beside them 130.4 / 122.7 / 113.0).
+// whose layers each have their own, the last column, could do without them in the caches from 64 MB on: up to 7 %.)  Own rows are judged by themselves
+// (together with cartridges, of which the host knows only how many there may be, 16 requests with 96 MB of own rows and two cartridges of 4 MB 28.0 /
+// 30.5; with one each, 65 MB, 36.1 / 34.7), cartridges by those that the requests name, beside own rows that are kept: only the device knows how many there
+// are and which of them several requests read.  Those are kept (us a call, all kept / none / as here; 128 requests, 2048 shared slots, cartridges of 2048: 4 of 256 for all of
+// them 97.9 / 146.2 / 89.0; 32 161.7 / 183.8 / 161.1; 64 179.8 / 188.5 / 179.5; one each 210.1 / 190.5 / 187.6, beside own rows of 242 MB
+// 249.2 / 225.9 / 226.2; for one request in twenty, beside them 130.4 / 122.7 / 113.0).
 constexpr size_t DEC_ONCE_BYTES = static_cast<size_t>(144) << 20;
 static long once_rows(int Hkv) { return static_cast<long>(DEC_ONCE_BYTES / (static_cast<size_t>(Hkv) * 2 * ROW_B)); }   // rows kept at most
 // prefix parts + private-cartridge chunks + own ranges (one launch), then the merge

@@ -680,7 +680,7 @@ def test_decode_in_a_workspace_of_nan(B, Hq, Hkv, P, pool_p, most):
 # Own rows of 144 MiB at most, one row more; private cartridges: one each, two requests on one, up to 144 MiB with the own rows and past
 # them, half of the requests without, several on one beside others of their own, more requests than one look at the others' numbers takes
 @pytest.mark.parametrize("lens,pool_p,ids", [((20000, 1, 16863), 0, ()), ((20000, 1, 16864), 0, ()), ((20000, 1, 16864), 90, (1, -1, 0)), ((5,) * 20, 2048, range(20)),
-                                             ((5,) * 20, 2048, (*range(19), 0)), ((5,) * 36, 1019, range(36)), ((4,) * 36, 1020, range(36)), ((5,) * 36, 1020, range(36)),
+                                             ((5,) * 20, 2048, (*range(19), 0)), ((600,) * 40, 321, range(40)), ((600,) * 40, 322, range(40)), ((5,) * 36, 1019, range(36)), ((4,) * 36, 1020, range(36)), ((5,) * 36, 1020, range(36)),
                                              ((30,) * 40, 2048, [i // 2 if i % 2 else -1 for i in range(40)]), ((7,) * 64, 1100, [i if i % 3 else i % 4 for i in range(64)]),
                                              ((1, 3, 2) * 100, 160, [i if i % 5 else 299 - i // 9 for i in range(300)])])
 def test_decode_rows_that_are_not_kept_in_caches(lens, pool_p, ids):
